@@ -309,8 +309,20 @@ hipError_t launch_decode(const CacheView& v, const __half* q, __half* out, float
   }
   *path = MIXKVQ_PATH_VECTOR;
   if (nt.k) {   // this path does not move the new token itself
-    e = launch_residual_copy(v, nt.k, nt.v, nt.st, 0, nt.row, 1, s);
-    if (e != hipSuccess) return e;
+    if (!sc.enabled) {
+      e = launch_residual_copy(v, nt.k, nt.v, nt.st, 0, n_fp16 - 1, 1, s);
+      if (e != hipSuccess) return e;
+    } else {
+      for (int b = 0; b < v.cfg.B; ++b) {
+        CacheView vb = v;
+        vb.cfg.B = 1;
+        vb.P = v.cfg.Hkv;
+        vb.res_k += (size_t)b * v.cfg.Hkv * v.RW * kD;
+        vb.res_v += (size_t)b * v.cfg.Hkv * v.RW * kD;
+        e = launch_residual_copy(vb, nt.k + (int64_t)b * nt.st.b, nt.v + (int64_t)b * nt.st.b, nt.st, 0, sc.n_fp16[b] - 1, 1, s);
+        if (e != hipSuccess) return e;
+      }
+    }
   }
   if (accumulate_q) {
     Strides3 qs{(int64_t)v.cfg.Hq * kD, (int64_t)kD, (int64_t)kD};

@@ -238,6 +238,7 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
     n_res = sc.n_fp16[b];
     skip_pair = n_blocks == 0 && n_res == 0;
   }
+  const int nt_dst = n_res - 1;      // fp16 row of this step's new token (if there is one): the last row in use
   // (the wavefront index is the same in all lanes: as a scalar it keeps record indices and addresses off the vector ALU)
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 15, kg = lane >> 4;
   // Two workgroups share a compute unit, and among wavefronts of equal priority a SIMD issues from the OLDER one
@@ -572,14 +573,14 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
 #pragma unroll
     for (int x = 0; x < 2; ++x) {
       const int row = sub_t0 + tokb + x;
-      const __half* src = (nt.k && row == nt.row) ? nt.k + nt_off : rk + (size_t)row * kD;
+      const __half* src = (nt.k && row == nt_dst) ? nt.k + nt_off : rk + (size_t)row * kD;
 #pragma unroll
       for (int st = 0; st < 4; ++st) kr[x][st] = *reinterpret_cast<const u32x4*>(src + 8 * kg + 32 * st);
     }
 #pragma unroll
     for (int it = 0; it < 8; ++it) {
       const int ci = it * 64 + lane, row = sub_t0 + (ci >> 4);
-      const __half* src = (nt.k && row == nt.row) ? nt.v + nt_off : rv + (size_t)row * kD;
+      const __half* src = (nt.k && row == nt_dst) ? nt.v + nt_off : rv + (size_t)row * kD;
       vr[it] = *reinterpret_cast<const u32x4*>(src + 8 * (ci & 15));
     }
   }
@@ -616,7 +617,7 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
   MIXKVQ_PHASE(1)
   if (bookkeeper) {   // the new token enters the window; |q| of this step joins the accumulator (one writer per pair)
     if (nt.k && lane < 32) {
-      const size_t dst = ((size_t)p * cv.RW + nt.row) * kD + (lane & 15) * 8;
+      const size_t dst = ((size_t)p * cv.RW + nt_dst) * kD + (lane & 15) * 8;
       *reinterpret_cast<uint4*>((lane < 16 ? cv.res_k : cv.res_v) + dst) = as_f16x8(nt_row, cv.cfg.in_dtype != 0);
     }
     if (accumulate_q) {
@@ -651,7 +652,7 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
     if (cv.cfg.in_dtype && nt.k) {     // the new token's rows came from the caller's bfloat16 tensors
 #pragma unroll
       for (int x = 0; x < 2; ++x)
-        if (sub_t0 + tokb + x == nt.row) {
+        if (sub_t0 + tokb + x == nt_dst) {
 #pragma unroll
           for (int st = 0; st < 4; ++st)
 #pragma unroll
@@ -659,7 +660,7 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
         }
 #pragma unroll
       for (int it = 0; it < 8; ++it)
-        if (sub_t0 + ((it * 64 + lane) >> 4) == nt.row) {
+        if (sub_t0 + ((it * 64 + lane) >> 4) == nt_dst) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) vr[it][e] = bf16x2_to_f16x2(vr[it][e]);
         }

@@ -21,9 +21,9 @@ struct Layout : mixkvq_block_layout_t {};
 
 struct Strides3 { int64_t b, h, t; };
 
-// One new token per sequence that the decode launch itself moves into fp16 row `row` of every pair
-// (k == nullptr: none).
-struct NewToken { const __half* k; const __half* v; Strides3 st; int row; };
+// One new token per sequence that the decode launch itself moves into the last fp16 row in use of every pair
+// (the counts of the launch include it; k == nullptr: none).
+struct NewToken { const __half* k; const __half* v; Strides3 st; };
 
 // Token counts per sequence for batches whose sequences differ in length, passed by value to the decode kernels
 // (enabled == 0: every sequence has the counts given as scalar arguments).
@@ -32,6 +32,14 @@ struct SeqCounts {
   int32_t enabled;
   int32_t n_blocks[kMaxRaggedB];      // quantized blocks of sequence b
   uint16_t n_fp16[kMaxRaggedB];       // its fp16 rows in use (sink + residual window)
+};
+
+// Sequences whose full window one launch of the pack kernel quantizes, passed by value (n == 0: every sequence of the
+// view, all starting at the same record).
+struct FlushList {
+  int32_t n;
+  uint16_t seq[kMaxRaggedB];
+  int32_t first_rec[kMaxRaggedB];     // first record of the block of that sequence
 };
 
 // Device-visible view of a cache: plain data passed by value to kernels.
@@ -76,6 +84,9 @@ hipError_t launch_select2(const CacheView& v, const __half* kA, int LA, Strides3
 uint8_t* select_scratch(const CacheView& v);   // room for one selection [P][k16 + k4] behind the range arrays in the workspace
 hipError_t launch_flush(const CacheView& v, const __half* k_new, const __half* v_new, Strides3 kvs,
                         int r0, int first_block, int n_flush, const uint8_t* sel, hipStream_t s);
+// The full windows of the listed sequences, each one record (a block of several records is flushed per sequence with
+// launch_flush): one launch whatever the number of sequences.
+hipError_t launch_flush_windows(const CacheView& v, const FlushList& list, hipStream_t s);
 // n tokens starting at new-token index src_first go to fp16 rows dst_row.. of every pair (row 0 = first sink row,
 // row S = first row of the residual window)
 hipError_t launch_residual_copy(const CacheView& v, const __half* k_new, const __half* v_new, Strides3 kvs,

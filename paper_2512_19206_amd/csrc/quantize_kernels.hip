@@ -67,9 +67,18 @@ __device__ __forceinline__ void load_tile(__half* sT, const __half* win, const _
   }
 }
 
+// Pair of this workgroup: blockIdx.x, or with a list of sequences the pair of the list's entry (which then also names
+// the first record).
+__device__ __forceinline__ int flush_pair(const FlushList& list, int Hkv, int* first_block) {
+  const int x = blockIdx.x;
+  if (list.n == 0) return x;
+  *first_block = list.first_rec[x / Hkv];
+  return (int)list.seq[x / Hkv] * Hkv + x % Hkv;
+}
+
 __global__ void __launch_bounds__(kFlushThreads)
 flush_block_kernel(CacheView cv, const __half* __restrict__ k_new, const __half* __restrict__ v_new, Strides3 st, int r0,
-                   int first_block, const uint8_t* __restrict__ sel_in) {
+                   int first_block, const uint8_t* __restrict__ sel_in, FlushList list) {
   __shared__ __align__(16) __half sT[kMaxR * kRowStride];   // K tile, then V tile
   __shared__ double sA[kD];
   __shared__ unsigned char sTier[kD];      // 0: 2 bit, 1: 4 bit, 2: fp16
@@ -83,7 +92,8 @@ flush_block_kernel(CacheView cv, const __half* __restrict__ k_new, const __half*
   const mixkvq_config& cfg = cv.cfg;
   const Layout& lay = cv.lay;
   const int R = cfg.R, Gk = cfg.Gk, Gv = cfg.Gv, k4 = cfg.k4, k16 = cfg.k16, ks = k4 + k16;
-  const int p = blockIdx.x, f = blockIdx.y, tid = threadIdx.x;
+  const int f = blockIdx.y, tid = threadIdx.x;
+  const int p = flush_pair(list, cfg.Hkv, &first_block);
   uint8_t* rec = cv.blocks + record_index(cv, p, first_block + f) * lay.rec_bytes;
 
   // zero the record's padding by clearing the small planes that may have holes
@@ -351,7 +361,7 @@ __device__ __forceinline__ uint4 load_chunk(const __half* res_p, const __half* f
 
 __global__ void __launch_bounds__(kFlushThreads, 3)   // three workgroups per CU (LDS) = three wavefronts per SIMD
 flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __half* __restrict__ v_new, Strides3 st,
-                        int r0, int first_block, const uint8_t* __restrict__ sel_in) {
+                        int r0, int first_block, const uint8_t* __restrict__ sel_in, FlushList list) {
   __shared__ __align__(16) __half sT[kMaxR * kFastStride];   // K tile, then V tile
   __shared__ double sA[kD];
   __shared__ unsigned char sTier[kD];      // 0: 2 bit, 1: 4 bit, 2: fp16
@@ -378,7 +388,8 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
             off_k4_z = cv.lay.off_k4_z, off_klo = cv.lay.off_klo, off_k4 = cv.lay.off_k4, off_k16 = cv.lay.off_k16,
             off_v = cv.lay.off_v, off_v_s = cv.lay.off_v_s, off_v_z = cv.lay.off_v_z, NLp = cv.lay.NLp,
             Wlo = cv.lay.Wlo, W4 = cv.lay.W4, NG = cv.lay.NG, NVG = cv.lay.NVG;
-  const int p = blockIdx.x, f = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int f = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int p = flush_pair(list, Hkv, &first_block);
   uint8_t* rec = cv.blocks + record_index(cv, p, first_block + f) * rec_bytes;
   const int n_chunks16 = R * 16;           // 16-byte pieces of a tile
   const int n_ch = R / 16;                 // chunks of 16 tokens
@@ -800,25 +811,41 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
   MIXKVQ_FPHASE(9)
 }
 
+static bool force_general_flush() {
+  static const bool force = getenv("MIXKVQ_FLUSH_GENERAL") != nullptr;
+  return force;
+}
+
 hipError_t launch_flush(const CacheView& v, const __half* k_new, const __half* v_new, Strides3 kvs, int r0,
                         int first_block, int n_flush, const uint8_t* sel, hipStream_t s) {
   // the throughput kernel needs 16-token chunks inside key groups, whole 16-byte pieces inside value groups and
   // 16-byte aligned rows; anything else takes the general kernel
   const bool aligned = ((reinterpret_cast<uintptr_t>(k_new) | reinterpret_cast<uintptr_t>(v_new)) & 15u) == 0 &&
                        kvs.b % 8 == 0 && kvs.h % 8 == 0 && kvs.t % 8 == 0;
-  static const bool force_general = getenv("MIXKVQ_FLUSH_GENERAL") != nullptr;
-  const bool fast = aligned && v.cfg.Gk % 16 == 0 && v.cfg.Gv % 16 == 0 && !force_general;
+  const bool fast = aligned && v.cfg.Gk % 16 == 0 && v.cfg.Gv % 16 == 0 && !force_general_flush();
+  FlushList none;
+  none.n = 0;
   // grid.y is limited to 65535 blocks per launch
   for (int f0 = 0; f0 < n_flush; f0 += 32768) {
     const int nf = n_flush - f0 < 32768 ? n_flush - f0 : 32768;
     // shift the stream origin so that block index 0 of this launch is block f0 of the call
     if (fast)
       flush_block_fast_kernel<<<dim3(v.P, nf), dim3(kFlushThreads), 0, s>>>(v, k_new, v_new, kvs, r0 - f0 * v.cfg.R,
-                                                                           first_block + f0, sel);
+                                                                           first_block + f0, sel, none);
     else
       flush_block_kernel<<<dim3(v.P, nf), dim3(kFlushThreads), 0, s>>>(v, k_new, v_new, kvs, r0 - f0 * v.cfg.R,
-                                                                      first_block + f0, sel);
+                                                                      first_block + f0, sel, none);
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_flush_windows(const CacheView& v, const FlushList& list, hipStream_t s) {
+  const Strides3 unused{0, 0, 0};      // every row comes from the windows
+  const dim3 grid(list.n * v.cfg.Hkv);
+  if (v.cfg.Gk % 16 == 0 && v.cfg.Gv % 16 == 0 && !force_general_flush())
+    flush_block_fast_kernel<<<grid, dim3(kFlushThreads), 0, s>>>(v, v.res_k, v.res_v, unused, v.cfg.R, 0, nullptr, list);
+  else
+    flush_block_kernel<<<grid, dim3(kFlushThreads), 0, s>>>(v, v.res_k, v.res_v, unused, v.cfg.R, 0, nullptr, list);
   return hipGetLastError();
 }
 
