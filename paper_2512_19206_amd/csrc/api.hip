@@ -121,7 +121,6 @@ static CacheView sub_view(const mixkvq_cache* c, int b0, int nb) {
   v.res_v += p0 * v.RW * kD;
   v.qacc += p0 * kD;
   v.qcnt += p0;
-  v.tickets += p0;
   return v;
 }
 
@@ -290,7 +289,7 @@ int mixkvq_cache_sizes(const mixkvq_config* cfg, mixkvq_sizes* out) {
   out->blocks = al256(P * (uint64_t)(cfg->T_max / rec_tokens(*cfg)) * (uint64_t)l.rec_bytes);
   out->res_k = al256(P * (uint64_t)(cfg->R + cfg->sink) * cfg->D * 2);
   out->res_v = out->res_k;
-  out->qacc = al256(P * (uint64_t)(cfg->D + 1) * 8 + P * 4);
+  out->qacc = al256(P * (uint64_t)(cfg->D + 1) * 8);
   uint64_t a = decode_workspace_bytes(*cfg), b = select_workspace_bytes(*cfg);
   out->workspace = al256(a > b ? a : b);
   return MIXKVQ_OK;
@@ -326,7 +325,6 @@ int mixkvq_cache_create(const mixkvq_config* cfg, const mixkvq_buffers* bufs, mi
   c->v.res_v = (__half*)bufs->res_v;
   c->v.qacc = (unsigned long long*)bufs->qacc;
   c->v.qcnt = c->v.qacc + (size_t)c->v.P * cfg->D;
-  c->v.tickets = (unsigned*)(c->v.qcnt + c->v.P);
   c->v.ws = (uint8_t*)bufs->workspace;
   for (int b = 0; b < cfg->B; ++b) c->seq[b] = SeqState{0, 0, 0};
   *out = c;

@@ -206,7 +206,8 @@ struct HalfSplit {
 // A thread owns four channels of one head, so g x 32 threads merge a pair without exchanging anything, and every load
 // of sixteen partials is in flight before the first wait.
 //
-// The last workgroup of a pair to finish merges it (a ticket per pair counts them).  The partials, the ticket and the
+// The last workgroup of a pair to finish merges it (the top byte of the pair's |q| count is the ticket that counts
+// them; a count of tokens never gets there, and at most kMaxSplits = 64 workgroups draw one).  The partials, the ticket and the
 // loads are agent-scope accesses, which go past the chip's eight L2 caches; no cache is flushed for them.  A launch of
 // its own for the merge costs what any dependent launch costs, whatever it does: 28.6 us per step instead of 24.1 at
 // 32 pairs of 32 805 tokens (16 partials each), 12.9 instead of 10.1 for one pair of 1 027 tokens (32 partials).
@@ -214,6 +215,7 @@ struct HalfSplit {
 // is the same.
 // ---------------------------------------------------------------------------
 typedef unsigned long long u64_t;
+constexpr u64_t kTicket = 1ull << 56;
 template <bool SHARED>
 __device__ __forceinline__ float2 load_part2(const float* p) {
   if constexpr (SHARED)
@@ -284,7 +286,7 @@ template <int K4, int K16, int NVG, int NKL, int RG, int THR, int G32, int PG, i
 __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __restrict__ q, float scale_log2e,
                                           int n_blocks, int n_res, int n_splits, float* __restrict__ part,
                                           int accumulate_q, const NewToken& nt, const SeqCounts& sc, unsigned char* smem,
-                                          unsigned* __restrict__ tickets, __half* __restrict__ out, float* __restrict__ lse) {
+                                          u64_t* __restrict__ tickets, __half* __restrict__ out, float* __restrict__ lse) {
   using T = Tiers<K4, K16, THR>;
   constexpr int NU = T::NU;
   // scalars of the by-value view (kept in SGPRs; no references into the kernel argument)
@@ -605,13 +607,12 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
   // residual sub-unit, the first record.
   int blk = blk_lo;
   // the pair's bookkeeping wavefront: old accumulator values and the new token's rows, first in the queue
-  unsigned long long qacc_old[2] = {0ull, 0ull}, qcnt_old = 0ull;
+  unsigned long long qacc_old[2] = {0ull, 0ull};
   uint4 nt_row = make_uint4(0u, 0u, 0u, 0u);
   if (bookkeeper) {
     if (accumulate_q) {
       qacc_old[0] = cv.qacc[(size_t)p * kD + lane];
       qacc_old[1] = cv.qacc[(size_t)p * kD + lane + 64];
-      if (lane == 0) qcnt_old = cv.qcnt[p];
     }
     if (nt.k && lane < 32) {
       const int64_t src = (int64_t)b * nt.st.b + (int64_t)jkv * nt.st.h + (lane & 15) * 8;
@@ -703,7 +704,8 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
         for (int h = 0; h < g; ++h) acc += fix24_abs(sQraw[h * kD + d]);
         cv.qacc[(size_t)p * kD + d] = acc;
       }
-      if (lane == 0) cv.qcnt[p] = qcnt_old + (unsigned long long)g;
+      // (an atomic: the pair's other workgroups may be drawing tickets from the same word)
+      if (lane == 0) __hip_atomic_fetch_add(cv.qcnt + p, (u64_t)g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
   // q in the slot order of the first record, while that record is still on its way (its value words are
@@ -1254,11 +1256,11 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
     // every store of this workgroup has reached the coherence point before its ticket is drawn
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (tid == 0) *sTicket = (int)__hip_atomic_fetch_add(tickets + p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) *sTicket = (int)(__hip_atomic_fetch_add(tickets + p, kTicket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) / kTicket);
     __syncthreads();
     if (*sTicket == n_splits - 1) {     // all partials of the pair are there; the ticket goes back to 0 for the next launch
       if (eh < g) merge_pair<true>(pair, n_splits, g, eh, c4, out, lse, bh, cv.cfg.in_dtype);
-      if (tid == 0) __hip_atomic_store(tickets + p, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (tid == 0) __hip_atomic_fetch_sub(tickets + p, (u64_t)n_splits * kTicket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
   MIXKVQ_PHASE(15)
@@ -1270,7 +1272,7 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
 template <int K4, int K16, int NVG, int NKL, int RG, int THR, int G32, int PG, int RH>
 __global__ void __launch_bounds__(kMfmaThreads, 2)
 decode_fused_kernel(CacheView cv, const __half* __restrict__ q, float scale, int n_blocks, int n_res, int n_splits,
-                    float* __restrict__ part, int accumulate_q, NewToken nt, SeqCounts sc, unsigned* __restrict__ tickets,
+                    float* __restrict__ part, int accumulate_q, NewToken nt, SeqCounts sc, u64_t* __restrict__ tickets,
                     __half* __restrict__ out, float* __restrict__ lse) {
   extern __shared__ __align__(16) unsigned char smem[];
   mfma_part<K4, K16, NVG, NKL, RG, THR, G32, PG, RH>(cv, q, scale * 1.4426950408889634f, n_blocks, n_res, n_splits, part,
@@ -1294,7 +1296,7 @@ static hipError_t launch_one(const CacheView& v, const __half* q, float scale, i
     attr_set.fetch_or(bit, std::memory_order_release);
   }
   // the partials in the cache's workspace come with tickets for the merge; any other buffer takes the merge launch
-  unsigned* tickets = part == reinterpret_cast<float*>(v.ws) ? v.tickets : nullptr;
+  u64_t* tickets = part == reinterpret_cast<float*>(v.ws) ? v.qcnt : nullptr;
   if (ev_start && ev_stop) {
     // profiling aid: the two events take the start and the end time of this kernel itself (not of the launch call)
     hipExtLaunchKernelGGL(kern, dim3(v.P, n_splits), dim3(kMfmaThreads), (uint32_t)lds, s, ev_start, ev_stop, 0u, v, q,

@@ -56,8 +56,7 @@ struct CacheView {
   __half* res_k;         // [P][RW][D]
   __half* res_v;
   unsigned long long* qacc;  // [P][D]
-  unsigned long long* qcnt;  // [P]
-  unsigned* tickets;     // [P] workgroups of the pair that have left their partial (0 between launches)
+  unsigned long long* qcnt;  // [P]; the top byte is the merge ticket of a running decode launch, 0 between launches
   uint8_t* ws;
 };
 
