@@ -82,8 +82,8 @@ typedef struct {
   uint64_t blocks;     /* [B*Hkv][T_max/Rr] block records (Rr tokens each, see R above), see mixkvq_block_layout */
   uint64_t res_k;      /* [B*Hkv][sink + R][D] fp16 keys: per pair the sink rows, then the residual window */
   uint64_t res_v;      /* [B*Hkv][sink + R][D] fp16 values likewise */
-  uint64_t qacc;       /* [B*Hkv][D] u64 sums of |q| in units of 2^-24, then [B*Hkv] u64 counts (a running decode launch
-                        * counts its workgroups in the top byte of a count and leaves it 0) */
+  uint64_t qacc;       /* [B*Hkv][D] u64 sums of |q| in units of 2^-24, then [B*Hkv] u64 counts (a running launch counts
+                        * its workgroups in the top 16 bits of a count and leaves them 0) */
   uint64_t workspace;  /* split-K partials and selection scratch */
 } mixkvq_sizes;
 

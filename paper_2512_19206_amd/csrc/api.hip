@@ -326,6 +326,8 @@ int mixkvq_cache_create(const mixkvq_config* cfg, const mixkvq_buffers* bufs, mi
   c->v.qacc = (unsigned long long*)bufs->qacc;
   c->v.qcnt = c->v.qacc + (size_t)c->v.P * cfg->D;
   c->v.ws = (uint8_t*)bufs->workspace;
+  const uint64_t wd = decode_workspace_bytes(*cfg), wsel = select_workspace_bytes(*cfg);
+  c->v.ws_bytes = (int64_t)(wd > wsel ? wd : wsel);
   for (int b = 0; b < cfg->B; ++b) c->seq[b] = SeqState{0, 0, 0};
   *out = c;
   return MIXKVQ_OK;
@@ -399,12 +401,9 @@ int mixkvq_select_channels(mixkvq_cache* c, const void* q, int32_t Lq, const int
   if (Lq > 0 && (!q || !q_strides)) return MIXKVQ_EINVAL;
   if (c->v.cfg.k4 + c->v.cfg.k16 == 0) return MIXKVQ_EINVAL;
   hipStream_t s = (hipStream_t)stream;
-  if (Lq > 0) {
-    Strides3 qs{q_strides[0], q_strides[1], q_strides[2]};
-    MIXKVQ_TRY_HIP(launch_qabs_accumulate(c->v, (const __half*)q, Lq, qs, s));
-  }
+  const Strides3 qs = Lq > 0 ? Strides3{q_strides[0], q_strides[1], q_strides[2]} : Strides3{0, 0, 0};
   Strides3 ks{k_strides[0], k_strides[1], k_strides[2]};
-  MIXKVQ_TRY_HIP(launch_select(c->v, (const __half*)k, L, ks, sel, s));
+  MIXKVQ_TRY_HIP(launch_select(c->v, (const __half*)q, Lq, qs, (const __half*)k, L, ks, sel, s));
   return MIXKVQ_OK;
 }
 
@@ -415,12 +414,9 @@ int mixkvq_select_channels_seq(mixkvq_cache* c, int32_t b, const void* q, int32_
   if (c->v.cfg.k4 + c->v.cfg.k16 == 0) return MIXKVQ_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   const CacheView v = sub_view(c, b, 1);
-  if (Lq > 0) {
-    Strides3 qs{0, q_strides[0], q_strides[1]};
-    MIXKVQ_TRY_HIP(launch_qabs_accumulate(v, (const __half*)q, Lq, qs, s));
-  }
+  const Strides3 qs = Lq > 0 ? Strides3{0, q_strides[0], q_strides[1]} : Strides3{0, 0, 0};
   Strides3 ks{0, k_strides[0], k_strides[1]};
-  MIXKVQ_TRY_HIP(launch_select(v, (const __half*)k, L, ks, sel, s));
+  MIXKVQ_TRY_HIP(launch_select(v, (const __half*)q, Lq, qs, (const __half*)k, L, ks, sel, s));
   return MIXKVQ_OK;
 }
 
@@ -483,12 +479,9 @@ int mixkvq_prefill(mixkvq_cache* c, const void* q, int32_t Lq, const int64_t q_s
     if (pl.F > (1 << 24)) return MIXKVQ_EINVAL;
   }
   hipStream_t s = (hipStream_t)stream;
-  if (Lq > 0) {
-    Strides3 qs{q_strides[0], q_strides[1], q_strides[2]};
-    MIXKVQ_TRY_HIP(launch_qabs_accumulate(c->v, (const __half*)q, Lq, qs, s));
-  }
+  const Strides3 qs = Lq > 0 ? Strides3{q_strides[0], q_strides[1], q_strides[2]} : Strides3{0, 0, 0};
   Strides3 ks{kv_strides[0], kv_strides[1], kv_strides[2]};
-  MIXKVQ_TRY_HIP(launch_select(c->v, (const __half*)k, L, ks, sel, s));
+  MIXKVQ_TRY_HIP(launch_select(c->v, (const __half*)q, Lq, qs, (const __half*)k, L, ks, sel, s));
   return mixkvq_quantize_append(c, k, v, L, kv_strides, sel, stream);
 }
 

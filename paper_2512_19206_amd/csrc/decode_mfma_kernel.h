@@ -206,8 +206,7 @@ struct HalfSplit {
 // A thread owns four channels of one head, so g x 32 threads merge a pair without exchanging anything, and every load
 // of sixteen partials is in flight before the first wait.
 //
-// The last workgroup of a pair to finish merges it (the top byte of the pair's |q| count is the ticket that counts
-// them; a count of tokens never gets there, and at most kMaxSplits = 64 workgroups draw one).  The partials, the ticket and the
+// The last workgroup of a pair to finish merges it (see kTicket).  The partials, the ticket and the
 // loads are agent-scope accesses, which go past the chip's eight L2 caches; no cache is flushed for them.  A launch of
 // its own for the merge costs what any dependent launch costs, whatever it does: 28.6 us per step instead of 24.1 at
 // 32 pairs of 32 805 tokens (16 partials each), 12.9 instead of 10.1 for one pair of 1 027 tokens (32 partials).
@@ -215,7 +214,6 @@ struct HalfSplit {
 // is the same.
 // ---------------------------------------------------------------------------
 typedef unsigned long long u64_t;
-constexpr u64_t kTicket = 1ull << 56;
 template <bool SHARED>
 __device__ __forceinline__ float2 load_part2(const float* p) {
   if constexpr (SHARED)

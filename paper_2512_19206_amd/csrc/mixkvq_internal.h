@@ -42,6 +42,10 @@ struct FlushList {
   int32_t first_rec[kMaxRaggedB];     // first record of the block of that sequence
 };
 
+// The last workgroup of a (batch, KV head) pair to finish is found by a ticket that the pair's workgroups draw from the
+// top 16 bits of its |q| count (a count of tokens never gets there; a launch gives a pair at most 65 535 workgroups).
+constexpr unsigned long long kTicket = 1ull << 48;
+
 // Device-visible view of a cache: plain data passed by value to kernels.
 struct CacheView {
   mixkvq_config cfg;
@@ -56,8 +60,9 @@ struct CacheView {
   __half* res_k;         // [P][RW][D]
   __half* res_v;
   unsigned long long* qacc;  // [P][D]
-  unsigned long long* qcnt;  // [P]; the top byte is the merge ticket of a running decode launch, 0 between launches
+  unsigned long long* qcnt;  // [P]; the top 16 bits are the ticket of a running launch (kTicket), 0 between launches
   uint8_t* ws;
+  int64_t ws_bytes;      // bytes of the workspace (of the whole cache, also in a view of some sequences)
 };
 
 // Index (in records) of block `blk` of pair p inside cv.blocks.
@@ -76,12 +81,14 @@ int max_splits_for(int P);                                 // split-K ceiling us
 // ---- kernel launchers (each returns a hipError_t from the launch) ----
 hipError_t launch_zero_qacc(const CacheView& v, hipStream_t s);
 hipError_t launch_qabs_accumulate(const CacheView& v, const __half* q, int Lq, Strides3 qs, hipStream_t s);
-hipError_t launch_select(const CacheView& v, const __half* k, int L, Strides3 ks, uint8_t* sel, hipStream_t s);
-// The same over two runs of tokens: LA rows of the residual windows (binary16, kA = first row of the view's first pair,
+// adds |q| of Lq tokens (0: none) to the accumulator, then scores and selects over the L tokens of k
+hipError_t launch_select(const CacheView& v, const __half* q, int Lq, Strides3 qs, const __half* k, int L, Strides3 ks,
+                         uint8_t* sel, hipStream_t s);
+// Selection from the accumulator as it is over two runs of tokens: LA rows of the residual windows (binary16, kA = first row of the view's first pair,
 // strides of the fp16-row buffers) followed by LB rows of the caller's tensor (kB, its strides and dtype).
 hipError_t launch_select2(const CacheView& v, const __half* kA, int LA, Strides3 sA, const __half* kB, int LB, Strides3 sB,
                           uint8_t* sel, hipStream_t s);
-uint8_t* select_scratch(const CacheView& v);   // room for one selection [P][k16 + k4] behind the range arrays in the workspace
+uint8_t* select_scratch(const CacheView& v);   // room for one selection [P][k16 + k4] in the workspace
 hipError_t launch_flush(const CacheView& v, const __half* k_new, const __half* v_new, Strides3 kvs,
                         int r0, int first_block, int n_flush, const uint8_t* sel, hipStream_t s);
 // The full windows of the listed sequences, each one record (a block of several records is flushed per sequence with
@@ -177,6 +184,42 @@ __device__ __forceinline__ void tier_sizes(const mixkvq_config& cfg, int c16, in
     *n16 = cfg.k16;
     *n4 = cfg.k4;
   }
+}
+
+// Tier (2: fp16, 1: 4 bit, 0: 2 bit) of channel tid in threads 0..127 of a workgroup of 256 (0 in the others), from the
+// 128 scores sA (16-byte aligned) and the pair's token count: the rank of a channel is the number of channels that beat it
+// (higher score, or equal score and lower index).  The two halves of the workgroup compare against 64 channels each, with
+// the loop unrolled so that the LDS reads run ahead of the compares (as a plain loop with the threshold counts in it, one
+// LDS latency per channel, this took 6.6 us of the 19 us of a pack workgroup).  sPart: 256 words.
+__device__ __forceinline__ int rank_channels(const mixkvq_config& cfg, unsigned long long count, const double* sA,
+                                             unsigned* sPart) {
+  const int tid = threadIdx.x, d = tid & (kD - 1), e0 = (tid >> 7) * (kD / 2);
+  const double Ad = sA[d];
+  int rank = 0;
+  const double2* row = reinterpret_cast<const double2*>(sA + e0);
+#pragma unroll 16
+  for (int i = 0; i < kD / 4; ++i) {
+    const double2 o = row[i];
+    const int e = e0 + 2 * i;
+    rank += (o.x > Ad) || (o.x == Ad && e < d);
+    rank += (o.y > Ad) || (o.y == Ad && e + 1 < d);
+  }
+  int c16 = 0, c_any = 0;      // channels above the thresholds among the 64 of this wavefront
+  if (cfg.policy == 1) {
+    const double thr16 = score_threshold(cfg.tau16, count, cfg.score_mode);
+    const double thr4 = score_threshold(cfg.tau4, count, cfg.score_mode);
+    c16 = __popcll(__ballot(Ad > thr16));
+    c_any = __popcll(__ballot(Ad > thr16 || Ad > thr4));
+  }
+  sPart[tid] = (unsigned)rank | ((unsigned)c16 << 8) | ((unsigned)c_any << 16);     // rank, c16, c_any <= 64 each
+  __syncthreads();
+  if (tid >= kD) return 0;
+  const unsigned mine = sPart[tid], other = sPart[tid ^ 64];                       // the two wavefronts with the channels
+  int n16, n4;
+  tier_sizes(cfg, (int)((mine >> 8) & 0xffu) + (int)((other >> 8) & 0xffu), (int)((mine >> 16) & 0xffu) + (int)((other >> 16) & 0xffu),
+             &n16, &n4);
+  rank = (int)(mine & 0xffu) + (int)(sPart[tid + kD] & 0xffu);
+  return rank < n16 ? 2 : (rank < n16 + n4 ? 1 : 0);
 }
 
 }  // namespace mixkvq

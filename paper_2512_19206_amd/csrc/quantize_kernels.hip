@@ -363,7 +363,7 @@ __global__ void __launch_bounds__(kFlushThreads, 3)   // three workgroups per CU
 flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __half* __restrict__ v_new, Strides3 st,
                         int r0, int first_block, const uint8_t* __restrict__ sel_in, FlushList list) {
   __shared__ __align__(16) __half sT[kMaxR * kFastStride];   // K tile, then V tile
-  __shared__ double sA[kD];
+  __shared__ __align__(16) double sA[kD];
   __shared__ unsigned char sTier[kD];      // 0: 2 bit, 1: 4 bit, 2: fp16
   __shared__ unsigned char sPos[kD];       // position of the channel inside its tier
   __shared__ unsigned char sLoList[kD];    // 2-bit channels, ascending
@@ -495,40 +495,9 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
       sA[tid] = A;
     }
     __syncthreads();
-    // rank of every channel (number of channels that beat it) and, under the threshold policy, how many channels
-    // pass each threshold: the two halves of the workgroup each compare against 64 of the channels
-    {
-      const int d = tid & (kD - 1), e0 = (tid >> 7) * (kD / 2);
-      const double Ad = sA[d];
-      int rank = 0, c16 = 0, c_any = 0;
-      if (policy == 1) {
-        const double thr16 = score_threshold(cv.cfg.tau16, cv.qcnt[p], score_mode);
-        const double thr4 = score_threshold(cv.cfg.tau4, cv.qcnt[p], score_mode);
-        for (int e = e0; e < e0 + kD / 2; ++e) {
-          const double o = sA[e];
-          rank += (o > Ad) || (o == Ad && e < d);
-          c16 += o > thr16;
-          c_any += (o > thr16) || (o > thr4);
-        }
-      } else {
-        for (int e = e0; e < e0 + kD / 2; ++e) {
-          const double o = sA[e];
-          rank += (o > Ad) || (o == Ad && e < d);
-        }
-      }
-      unsigned* sPart = reinterpret_cast<unsigned*>(sR);      // not yet in use: [2][kD] packed partial counts
-      sPart[tid] = (unsigned)rank | ((unsigned)c16 << 8) | ((unsigned)c_any << 16);     // each count <= 64
-      __syncthreads();
-      if (tid < kD) {
-        const unsigned both = sPart[tid] + sPart[tid + kD];                              // each count <= 128: no carry
-        rank = (int)(both & 0xffu);
-        c16 = (int)((both >> 8) & 0xffu);
-        c_any = (int)((both >> 16) & 0xffu);
-        int n16, n4;
-        tier_sizes(cv.cfg, c16, c_any, &n16, &n4);
-        sTier[tid] = rank < n16 ? 2 : (rank < n16 + n4 ? 1 : 0);
-      }
-    }
+    // (sR is not yet in use)
+    const int tier = rank_channels(cv.cfg, policy == 1 ? cv.qcnt[p] : 0ull, sA, reinterpret_cast<unsigned*>(sR));
+    if (tid < kD) sTier[tid] = (unsigned char)tier;
   } else {
     if (tid < kD) sTier[tid] = 0;
     __syncthreads();

@@ -24,26 +24,56 @@ hipError_t launch_zero_qacc(const CacheView& v, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------
-// Eq. 6: sum of |q| per KV head and channel, over tokens and the g query heads
-// of the group.  Streaming form: a workgroup takes `rows` rows of one query head;
-// 16 threads cover a row of 256 bytes with one 16-byte load each, 16 rows per pass,
-// eight passes in flight.  Per-thread 64-bit sums, one LDS reduction over the 16 row
-// lanes, one 64-bit atomic per channel and workgroup (integers: any order is exact).
+// Scoring and selection in one launch.  Workgroups (pair, y): the first nq of a pair add |q| (Eq. 6) over one piece of
+// one query head each, the others take the range (Eq. 7) of one piece of the keys; the last of a pair to finish scores
+// and selects (Eq. 8).  Memory-bound on large tensors: 16 threads cover a row of 256 bytes with one 16-byte load each,
+// 16 rows per pass, eight passes in flight.
+//   |q|     per-thread sums, one LDS reduction over the 16 row lanes, one 64-bit atomic per channel and workgroup
+//           (integers: any order is exact).
+//   range   running minima and maxima of packed 16-bit keys that order like the fp16 values; a workgroup leaves its
+//           result (128 channels, 512 bytes) in the workspace, so nothing has to be initialised.
+//   select  the workgroups of a pair draw tickets from the top bits of its |q| count, which the |q| workgroups advance
+//           with the same atomic.  Sums, partial ranges and tickets are agent-scope accesses (they pass the chip's eight
+//           L2 caches by), and a workgroup's own have been acknowledged before its ticket is drawn.
+// As launches of their own (|q|, initial ranges, ranges, selection) the four took 7.5 + 1.4 + 6.3 + 9.5 us and the gaps
+// between them on 8 pairs of 1 000 tokens, of which the work itself is a fraction.
 // ---------------------------------------------------------------------------
 constexpr int kStreamThreads = 256;
-constexpr int kMinRowsPerWG = 512, kMaxRowsPerWG = 2048;
+constexpr int kMinRowsPerWG = 256, kMaxRowsPerWG = 8192;
+constexpr int kMaxExactRows = 131072;      // rows of a |q| workgroup up to which its binary64 sums are exact
 constexpr int kInFlight = 8;      // 16-byte loads a thread has in flight
+constexpr int kRangePartBytes = kD * 4;    // partial range of one workgroup: 64 words of minima, 64 of maxima
 
-// Rows one workgroup takes: 512, or up to 2048 when that still leaves every compute unit tens of workgroups (fewer
-// reductions and atomics per byte streamed: +2 % on a 5 GB tensor).
+struct SelectArgs {
+  const __half *q, *kA, *kB;       // queries; keys: run A (binary16 window rows), then run B (the caller's tensor)
+  Strides3 qs, sA, sB;
+  int Lq, LA, LB;
+  int rows_q, rows_k;              // rows one workgroup takes
+  int nq, nA, nB;                  // workgroups per pair
+  unsigned* part;                  // [P][nA + nB][128]
+  uint8_t* sel;                    // [P][k16 + k4], or nullptr: |q| only
+};
+
+// Rows one workgroup takes.  Small calls are bound by latency: 256 rows are two passes of eight loads (128 and 512: 35.4
+// and 34.7 us for a prompt of 1 531 tokens in 4 pairs, 256: 33.2).  More rows as soon as that still leaves every compute
+// unit four workgroups, and above 512 rows eight of them: fewer reductions, atomics and tickets per byte streamed (16
+// prompts of 32 768 tokens, up to 2 048 / 4 096 / 8 192 rows: 1 810, 1 775, 1 742 us; 32 768 rows measure the same).
 static int rows_per_workgroup(int64_t pairs_times_heads, int L) {
   int rows = kMinRowsPerWG;
-  while (rows < kMaxRowsPerWG && pairs_times_heads * ((L + 2 * rows - 1) / (2 * rows)) >= 4096) rows *= 2;
+  while (rows < kMaxRowsPerWG &&
+         pairs_times_heads * (((int64_t)L + 2 * rows - 1) / (2 * rows)) >= (rows < 512 ? 1024 : 2048)) rows *= 2;
   return rows;
 }
 
+typedef short s16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ s16x2 order_key(unsigned w) {     // involution: also maps keys back to fp16 bits
+  const s16x2 v = __builtin_bit_cast(s16x2, w);
+  return v ^ ((v >> 15) & (short)0x7fff);
+}
+__device__ __forceinline__ s16x2 as_key(unsigned w) { return __builtin_bit_cast(s16x2, w); }
+
 // The per-thread sums run in binary64, which is exact here: every |fp16| is a multiple of 2^-24 below 2^16, so up to
-// 2^13 of them add without rounding in a 53-bit significand (a thread adds at most kMaxRowsPerWG / 16 = 128 per channel);
+// 2^13 of them add without rounding in a 53-bit significand (a thread adds rows / 16 per channel);
 // the sum times 2^24 is the exact integer.
 typedef _Float16 sh2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ void add8(double (&acc)[8], uint4 v) {
@@ -56,241 +86,249 @@ __device__ __forceinline__ void add8(double (&acc)[8], uint4 v) {
   }
 }
 
-template <bool BF>      // BF: the tensor holds bfloat16 (converted to binary16 on entry)
-__global__ void __launch_bounds__(kStreamThreads)
-qabs_accumulate_kernel(const __half* __restrict__ q, int Lq, Strides3 qs, int Hkv, int g, int rows,
-                       unsigned long long* __restrict__ qacc, unsigned long long* __restrict__ qcnt) {
-  __shared__ unsigned long long sAcc[16][kD];
-  const int p = blockIdx.x, b = p / Hkv, j = p % Hkv, tid = threadIdx.x;
-  const int hh = blockIdx.y % g, chunk = blockIdx.y / g;
-  const int c = tid & 15, r = tid >> 4;
-  const int t0 = chunk * rows, t1 = min(Lq, t0 + rows);
-  const __half* base = q + (int64_t)b * qs.b + (int64_t)(j * g + hh) * qs.h + 8 * c;
-  static_assert(kMaxRowsPerWG / 16 <= 8192, "per-thread binary64 sums must stay exact");
-  double acc[8];
+// eight elements of a row; rows of any alignment when AL is false
+template <bool AL>
+__device__ __forceinline__ uint4 load8(const __half* p) {
+  if (AL) return *reinterpret_cast<const uint4*>(p);
+  unsigned w[4];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) acc[i] = 0.0;
+  for (int i = 0; i < 4; ++i) w[i] = (unsigned)h2bits(p[2 * i]) | ((unsigned)h2bits(p[2 * i + 1]) << 16);
+  return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// f(16-byte piece) for rows t0 + r, t0 + r + 16, ... below t1; `base` is this thread's piece of row 0
+template <bool AL, class F>
+__device__ __forceinline__ void stream_rows(const __half* base, int64_t stride_t, int t0, int t1, int r, bool bf16, F f) {
   int t = t0 + r;
   constexpr int NF = kInFlight;
   for (; t + 16 * (NF - 1) < t1; t += 16 * NF) {
     uint4 v[NF];
 #pragma unroll
-    for (int u = 0; u < NF; ++u) v[u] = *reinterpret_cast<const uint4*>(base + (int64_t)(t + 16 * u) * qs.t);
+    for (int u = 0; u < NF; ++u) v[u] = load8<AL>(base + (int64_t)(t + 16 * u) * stride_t);
 #pragma unroll
-    for (int u = 0; u < NF; ++u) add8(acc, as_f16x8(v[u], BF));
+    for (int u = 0; u < NF; ++u) f(as_f16x8(v[u], bf16));
   }
-  for (; t < t1; t += 16) add8(acc, as_f16x8(*reinterpret_cast<const uint4*>(base + (int64_t)t * qs.t), BF));
+  if (t < t1) {      // up to seven rows more: asked for together as well (a row past the end repeats the last one)
+    uint4 v[NF - 1];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) sAcc[r][8 * c + i] = (unsigned long long)(acc[i] * 16777216.0);
-  __syncthreads();
-  if (tid < kD) {
-    unsigned long long sum = 0;
+    for (int u = 0; u < NF - 1; ++u) v[u] = load8<AL>(base + (int64_t)(t + 16 * u < t1 ? t + 16 * u : t) * stride_t);
 #pragma unroll
-    for (int rr = 0; rr < 16; ++rr) sum += sAcc[rr][tid];
-    atomicAdd(&qacc[(size_t)p * kD + tid], sum);
+    for (int u = 0; u < NF - 1; ++u)
+      if (t + 16 * u < t1) f(as_f16x8(v[u], bf16));
   }
-  if (tid == 0) atomicAdd(&qcnt[p], (unsigned long long)(t1 - t0));
 }
 
-// Fallback for tensors whose rows are not 16-byte aligned: one thread per channel.
-__global__ void __launch_bounds__(kD) qabs_accumulate_unaligned_kernel(const __half* __restrict__ q, int Lq, Strides3 qs,
-                                                                      int Hkv, int g, int rows, int bf16,
-                                                                      unsigned long long* __restrict__ qacc,
-                                                                      unsigned long long* __restrict__ qcnt) {
-  const int p = blockIdx.x, b = p / Hkv, j = p % Hkv, d = threadIdx.x;
-  const int hh = blockIdx.y % g, chunk = blockIdx.y / g;
-  const int t0 = chunk * rows, t1 = min(Lq, t0 + rows);
-  const __half* base = q + (int64_t)b * qs.b + (int64_t)(j * g + hh) * qs.h + d;
-  unsigned long long acc = 0;
-  for (int t = t0; t < t1; ++t) acc += fix24_abs(in_bits(base + (int64_t)t * qs.t, bf16));
-  atomicAdd(&qacc[(size_t)p * kD + d], acc);
-  if (d == 0) atomicAdd(&qcnt[p], (unsigned long long)(t1 - t0));
+template <class T>
+__device__ __forceinline__ T load_agent(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+template <bool BF, bool AL>      // BF: the caller's tensors hold bfloat16 (converted to binary16 on entry); AL: 16-byte aligned rows
+__global__ void __launch_bounds__(kStreamThreads) select_kernel(CacheView cv, SelectArgs a) {
+  __shared__ __align__(16) unsigned char smem[16 * kD * 8];
+  __shared__ unsigned long long sCount;
+  const int Hkv = cv.cfg.Hkv, g = cv.g;
+  const int p = blockIdx.x, b = p / Hkv, j = p % Hkv, tid = threadIdx.x, y = blockIdx.y;
+  const int c = tid & 15, r = tid >> 4;
+  const int nk = a.nA + a.nB;
+  int tokens = 0;      // |q| workgroups: what the pair's count grows by
+  if (y < a.nq) {
+    auto sAcc = reinterpret_cast<unsigned long long (*)[kD]>(smem);      // [16][kD]
+    const int hh = y % g, t0 = (y / g) * a.rows_q, t1 = min(a.Lq, t0 + a.rows_q);
+    double acc[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i] = 0.0;
+    stream_rows<AL>(a.q + (int64_t)b * a.qs.b + (int64_t)(j * g + hh) * a.qs.h + 8 * c, a.qs.t, t0, t1, r, BF,
+                    [&](uint4 v) { add8(acc, v); });
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sAcc[r][8 * c + i] = (unsigned long long)(acc[i] * 16777216.0);
+    __syncthreads();
+    if (tid < kD) {
+      unsigned long long sum = 0;
+#pragma unroll
+      for (int rr = 0; rr < 16; ++rr) sum += sAcc[rr][tid];
+      __hip_atomic_fetch_add(cv.qacc + (size_t)p * kD + tid, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    tokens = t1 - t0;
+  } else {
+    auto sLo = reinterpret_cast<unsigned (*)[kD / 2]>(smem);      // [16][kD / 2]
+    auto sHi = sLo + 16;
+    const int yk = y - a.nq;
+    const bool inA = yk < a.nA;
+    const Strides3 ks = inA ? a.sA : a.sB;
+    const int L = inA ? a.LA : a.LB, t0 = (inA ? yk : yk - a.nA) * a.rows_k, t1 = min(L, t0 + a.rows_k);
+    s16x2 lo[4], hi[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      lo[i] = s16x2{(short)0x7fff, (short)0x7fff};
+      hi[i] = s16x2{(short)-0x8000, (short)-0x8000};
+    }
+    stream_rows<AL>((inA ? a.kA : a.kB) + (int64_t)b * ks.b + (int64_t)j * ks.h + 8 * c, ks.t, t0, t1, r, BF && !inA,
+                    [&](uint4 v) {
+                      const unsigned w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                      for (int i = 0; i < 4; ++i) {
+                        const s16x2 key = order_key(w[i]);
+                        lo[i] = __builtin_elementwise_min(lo[i], key);
+                        hi[i] = __builtin_elementwise_max(hi[i], key);
+                      }
+                    });
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      sLo[r][4 * c + i] = __builtin_bit_cast(unsigned, lo[i]);
+      sHi[r][4 * c + i] = __builtin_bit_cast(unsigned, hi[i]);
+    }
+    __syncthreads();
+    if (tid < kD) {      // the first wavefront joins the minima, the second the maxima
+      const int d2 = tid & 63;
+      s16x2 m = as_key(tid < 64 ? sLo[0][d2] : sHi[0][d2]);
+#pragma unroll
+      for (int rr = 1; rr < 16; ++rr)
+        m = tid < 64 ? __builtin_elementwise_min(m, as_key(sLo[rr][d2])) : __builtin_elementwise_max(m, as_key(sHi[rr][d2]));
+      __hip_atomic_store(a.part + ((size_t)p * nk + yk) * kD + tid, __builtin_bit_cast(unsigned, m), __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+  if (!a.sel) {      // |q| alone: no ticket
+    if (tid == 0) __hip_atomic_fetch_add(cv.qcnt + p, (unsigned long long)tokens, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return;
+  }
+  // every store and atomic of this workgroup has reached the coherence point before its ticket is drawn
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 0)
+    sCount = __hip_atomic_fetch_add(cv.qcnt + p, kTicket + (unsigned long long)tokens, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  const int n_wgs = a.nq + nk;
+  const unsigned long long before = sCount;
+  if ((int)(before / kTicket) != n_wgs - 1) return;
+  // ---- the pair's last workgroup: all sums and partial ranges are there; the ticket goes back to 0 ----
+  if (tid == 0) __hip_atomic_fetch_sub(cv.qcnt + p, (unsigned long long)n_wgs * kTicket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const unsigned long long count = before % kTicket + (unsigned long long)tokens;
+  unsigned long long sum = 0ull;
+  if (tid < kD) sum = load_agent(cv.qacc + (size_t)p * kD + tid);
+  {
+    const unsigned* part = a.part + (size_t)p * nk * kD + (tid & 63);
+    s16x2 lo = s16x2{(short)0x7fff, (short)0x7fff}, hi = s16x2{(short)-0x8000, (short)-0x8000};
+    constexpr int NF = 8;
+    for (int i0 = tid >> 6; i0 < nk; i0 += 4 * NF) {
+      unsigned vl[NF], vh[NF];
+#pragma unroll
+      for (int u = 0; u < NF; ++u) {
+        const size_t at = (size_t)(i0 + 4 * u < nk ? i0 + 4 * u : i0) * kD;
+        vl[u] = load_agent(part + at);
+        vh[u] = load_agent(part + at + 64);
+      }
+#pragma unroll
+      for (int u = 0; u < NF; ++u) {
+        lo = __builtin_elementwise_min(lo, as_key(vl[u]));
+        hi = __builtin_elementwise_max(hi, as_key(vh[u]));
+      }
+    }
+    unsigned* sM = reinterpret_cast<unsigned*>(smem);      // [4][2][64]
+    sM[tid >> 6 << 7 | (tid & 63)] = __builtin_bit_cast(unsigned, order_key(__builtin_bit_cast(unsigned, lo)));
+    sM[tid >> 6 << 7 | 64 | (tid & 63)] = __builtin_bit_cast(unsigned, order_key(__builtin_bit_cast(unsigned, hi)));
+  }
+  __syncthreads();
+  double* sA = reinterpret_cast<double*>(smem + 2048);
+  unsigned* sPart = reinterpret_cast<unsigned*>(smem + 2048 + 1024);
+  if (tid < kD) {
+    const unsigned short* m = reinterpret_cast<const unsigned short*>(smem);      // [4][2][128] fp16 bits
+    long long lo = fix24(m[tid]), hi = fix24(m[kD + tid]);
+#pragma unroll
+    for (int w = 1; w < 4; ++w) {
+      const long long l = fix24(m[2 * kD * w + tid]), h = fix24(m[2 * kD * w + kD + tid]);
+      lo = l < lo ? l : lo;
+      hi = h > hi ? h : hi;
+    }
+    const long long rng = hi - lo;
+    sA[tid] = cv.cfg.score_mode ? (double)rng : (double)sum * (double)rng;
+  }
+  __syncthreads();
+  const int tier = rank_channels(cv.cfg, count, sA, sPart);      // (threads 0..127: of their channel)
+  // positions inside the tiers: ballots over the two wavefronts that hold the channels
+  const unsigned long long m1 = __ballot(tier == 1), m2 = __ballot(tier == 2);
+  unsigned long long* sMask = reinterpret_cast<unsigned long long*>(smem);      // the first wavefront's two ballots
+  if (tid == 0) sMask[0] = m1, sMask[1] = m2;
+  __syncthreads();
+  const int k16 = cv.cfg.k16, k4 = cv.cfg.k4, ks = k16 + k4;
+  uint8_t* out = a.sel + (size_t)p * ks;
+  const bool second = tid >= 64;
+  const int f1 = second ? __popcll(sMask[0]) : 0, f2 = second ? __popcll(sMask[1]) : 0;
+  if (tid < kD && tier) {
+    const unsigned long long mine = tier == 2 ? m2 : m1;
+    const int pos = __popcll(mine & ((1ull << (tid & 63)) - 1ull)) + (tier == 2 ? f2 : f1);
+    out[(tier == 2 ? 0 : k16) + pos] = (uint8_t)tid;
+  }
+  // entries no channel claims (threshold policy): the second wavefront knows both ballots
+  if (second && tid < kD) {
+    const int n2 = f2 + __popcll(m2), n1 = f1 + __popcll(m1);
+    for (int i = tid - 64; i < ks; i += 64)
+      if (i < k16 ? i >= n2 : i - k16 >= n1) out[i] = MIXKVQ_NO_CHANNEL;
+  }
 }
 
 static bool rows_aligned16(const void* ptr, Strides3 st) {
   return (reinterpret_cast<uintptr_t>(ptr) & 15u) == 0 && st.b % 8 == 0 && st.h % 8 == 0 && st.t % 8 == 0;
 }
 
-hipError_t launch_qabs_accumulate(const CacheView& v, const __half* q, int Lq, Strides3 qs, hipStream_t s) {
-  const int rows = rows_per_workgroup((int64_t)v.P * v.g, Lq);
-  dim3 grid(v.P, v.g * ((Lq + rows - 1) / rows));
-  if (!rows_aligned16(q, qs))
-    qabs_accumulate_unaligned_kernel<<<grid, dim3(kD), 0, s>>>(q, Lq, qs, v.cfg.Hkv, v.g, rows, v.cfg.in_dtype, v.qacc, v.qcnt);
-  else if (v.cfg.in_dtype)
-    qabs_accumulate_kernel<true><<<grid, dim3(kStreamThreads), 0, s>>>(q, Lq, qs, v.cfg.Hkv, v.g, rows, v.qacc, v.qcnt);
-  else
-    qabs_accumulate_kernel<false><<<grid, dim3(kStreamThreads), 0, s>>>(q, Lq, qs, v.cfg.Hkv, v.g, rows, v.qacc, v.qcnt);
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// Eq. 7: per-channel min and max of the keys over L tokens.  Same streaming form; the
-// running min/max are kept on packed 16-bit keys that order like the fp16 values
-// (sign-magnitude -> two's complement), two channels per instruction, and only the
-// workgroup's result is converted to the exact integers the atomics work on.
-// ---------------------------------------------------------------------------
-typedef short s16x2 __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ s16x2 order_key(unsigned w) {     // involution: also maps keys back to fp16 bits
-  const s16x2 v = __builtin_bit_cast(s16x2, w);
-  return v ^ ((v >> 15) & (short)0x7fff);
-}
-
-__global__ void range_init_kernel(long long* mn, long long* mx, int n) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) {
-    mn[i] = 0x7fffffffffffffffll;
-    mx[i] = -0x7fffffffffffffffll - 1;
-  }
-}
-
-template <bool BF>
-__global__ void __launch_bounds__(kStreamThreads)
-key_range_kernel(const __half* __restrict__ k, int L, Strides3 ks, int Hkv, int rows, long long* __restrict__ mn,
-                 long long* __restrict__ mx) {
-  __shared__ unsigned sLo[16][kD / 2], sHi[16][kD / 2];
-  const int p = blockIdx.x, b = p / Hkv, j = p % Hkv, tid = threadIdx.x;
-  const int c = tid & 15, r = tid >> 4;
-  const int t0 = blockIdx.y * rows, t1 = min(L, t0 + rows);
-  const __half* base = k + (int64_t)b * ks.b + (int64_t)j * ks.h + 8 * c;
-  s16x2 lo[4], hi[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    lo[i] = s16x2{(short)0x7fff, (short)0x7fff};
-    hi[i] = s16x2{(short)-0x8000, (short)-0x8000};
-  }
-  auto upd = [&](uint4 v) {
-    const unsigned w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const s16x2 key = order_key(w[i]);
-      lo[i] = __builtin_elementwise_min(lo[i], key);
-      hi[i] = __builtin_elementwise_max(hi[i], key);
-    }
-  };
-  int t = t0 + r;
-  constexpr int NF = kInFlight;
-  for (; t + 16 * (NF - 1) < t1; t += 16 * NF) {
-    uint4 v[NF];
-#pragma unroll
-    for (int u = 0; u < NF; ++u) v[u] = *reinterpret_cast<const uint4*>(base + (int64_t)(t + 16 * u) * ks.t);
-#pragma unroll
-    for (int u = 0; u < NF; ++u) upd(as_f16x8(v[u], BF));
-  }
-  for (; t < t1; t += 16) upd(as_f16x8(*reinterpret_cast<const uint4*>(base + (int64_t)t * ks.t), BF));
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    sLo[r][4 * c + i] = __builtin_bit_cast(unsigned, lo[i]);
-    sHi[r][4 * c + i] = __builtin_bit_cast(unsigned, hi[i]);
-  }
-  __syncthreads();
-  if (tid < kD / 2) {
-    s16x2 l = __builtin_bit_cast(s16x2, sLo[0][tid]), h = __builtin_bit_cast(s16x2, sHi[0][tid]);
-#pragma unroll
-    for (int rr = 1; rr < 16; ++rr) {
-      l = __builtin_elementwise_min(l, __builtin_bit_cast(s16x2, sLo[rr][tid]));
-      h = __builtin_elementwise_max(h, __builtin_bit_cast(s16x2, sHi[rr][tid]));
-    }
-    const unsigned lb = __builtin_bit_cast(unsigned, order_key(__builtin_bit_cast(unsigned, l)));
-    const unsigned hb = __builtin_bit_cast(unsigned, order_key(__builtin_bit_cast(unsigned, h)));
-    const size_t o = (size_t)p * kD + 2 * tid;
-    if (t1 > t0) {
-      atomicMin(&mn[o], fix24((unsigned short)(lb & 0xffffu)));
-      atomicMin(&mn[o + 1], fix24((unsigned short)(lb >> 16)));
-      atomicMax(&mx[o], fix24((unsigned short)(hb & 0xffffu)));
-      atomicMax(&mx[o + 1], fix24((unsigned short)(hb >> 16)));
-    }
-  }
-}
-
-__global__ void __launch_bounds__(kD) key_range_unaligned_kernel(const __half* __restrict__ k, int L, Strides3 ks,
-                                                                int Hkv, int rows, int bf16, long long* __restrict__ mn,
-                                                                long long* __restrict__ mx) {
-  const int p = blockIdx.x, b = p / Hkv, j = p % Hkv, d = threadIdx.x;
-  const int t0 = blockIdx.y * rows;
-  const int t1 = min(L, t0 + rows);
-  const __half* base = k + (int64_t)b * ks.b + (int64_t)j * ks.h + d;
-  long long lo = 0x7fffffffffffffffll, hi = -0x7fffffffffffffffll - 1;
-  for (int t = t0; t < t1; ++t) {
-    long long x = fix24(in_bits(base + (int64_t)t * ks.t, bf16));
-    lo = x < lo ? x : lo;
-    hi = x > hi ? x : hi;
-  }
-  atomicMin(&mn[(size_t)p * kD + d], lo);
-  atomicMax(&mx[(size_t)p * kD + d], hi);
-}
-
-// ---------------------------------------------------------------------------
-// Eq. 8 + top-k.  One workgroup per (batch, KV head) pair, one thread per channel.
-// rank_d = number of channels that beat d (higher score, or equal score and lower index).
-// ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(kD) select_topk_kernel(CacheView cv, const long long* __restrict__ mn,
-                                                        const long long* __restrict__ mx, uint8_t* __restrict__ sel) {
-  __shared__ double sA[kD];
-  __shared__ unsigned char sTier[kD];
-  const mixkvq_config& cfg = cv.cfg;
-  const int p = blockIdx.x, d = threadIdx.x, k16 = cfg.k16, ks = cfg.k16 + cfg.k4;
-  const long long rng = mx[(size_t)p * kD + d] - mn[(size_t)p * kD + d];
-  const double A = cfg.score_mode ? (double)rng : (double)cv.qacc[(size_t)p * kD + d] * (double)rng;
-  uint8_t* out = sel + (size_t)p * ks;
-  if (d < ks) out[d] = MIXKVQ_NO_CHANNEL;     // entries no channel claims (threshold policy)
-  sA[d] = A;
-  __syncthreads();
-  const double thr16 = cfg.policy == 1 ? score_threshold(cfg.tau16, cv.qcnt[p], cfg.score_mode) : 0.0;
-  const double thr4 = cfg.policy == 1 ? score_threshold(cfg.tau4, cv.qcnt[p], cfg.score_mode) : 0.0;
-  int rank = 0, c16 = 0, c_any = 0;
-  for (int e = 0; e < kD; ++e) {
-    const double o = sA[e];
-    rank += (o > A) || (o == A && e < d);
-    c16 += o > thr16;
-    c_any += (o > thr16) || (o > thr4);
-  }
-  int n16, n4;
-  tier_sizes(cfg, c16, c_any, &n16, &n4);
-  const unsigned char tier = rank < n16 ? 2 : (rank < n16 + n4 ? 1 : 0);
-  sTier[d] = tier;
-  __syncthreads();
-  if (tier) {
-    int pos = 0;
-    for (int e = 0; e < d; ++e) pos += sTier[e] == tier;
-    out[(tier == 2 ? 0 : k16) + pos] = (uint8_t)d;
-  }
-}
-
+// The workspace holds a selection per pair (select_scratch), then the partial ranges.
 size_t select_workspace_bytes(const mixkvq_config& c) {
-  // minima and maxima per (pair, channel), then one selection per pair
   return (size_t)c.B * c.Hkv * kD * 2 * sizeof(long long) + (size_t)c.B * c.Hkv * kD;
 }
 
-uint8_t* select_scratch(const CacheView& v) { return v.ws + (size_t)v.P * kD * 2 * sizeof(long long); }
+uint8_t* select_scratch(const CacheView& v) { return v.ws; }
 
-// One run of tokens into the range arrays.
-static void launch_key_range(const CacheView& v, const __half* k, int L, Strides3 ks, bool bf16, long long* mn, long long* mx,
-                             hipStream_t s) {
-  const int rows = rows_per_workgroup(v.P, L);
-  dim3 grid(v.P, (L + rows - 1) / rows);
-  if (!rows_aligned16(k, ks))
-    key_range_unaligned_kernel<<<grid, dim3(kD), 0, s>>>(k, L, ks, v.cfg.Hkv, rows, bf16 ? 1 : 0, mn, mx);
-  else if (bf16)
-    key_range_kernel<true><<<grid, dim3(kStreamThreads), 0, s>>>(k, L, ks, v.cfg.Hkv, rows, mn, mx);
-  else
-    key_range_kernel<false><<<grid, dim3(kStreamThreads), 0, s>>>(k, L, ks, v.cfg.Hkv, rows, mn, mx);
+static hipError_t launch_select_kernel(const CacheView& v, SelectArgs a, hipStream_t s) {
+  a.rows_q = rows_per_workgroup((int64_t)v.P * v.g, a.Lq);
+  auto pieces = [](int L, int rows) { return (int)(((int64_t)L + rows - 1) / rows); };
+  while ((int64_t)v.g * pieces(a.Lq, a.rows_q) > 32768 && a.rows_q < kMaxExactRows) a.rows_q *= 2;
+  a.nq = v.g * pieces(a.Lq, a.rows_q);
+  a.nA = a.nB = 0;
+  a.part = reinterpret_cast<unsigned*>(v.ws + (size_t)v.P * kD);
+  if (a.sel) {
+    // as many partial ranges as the workspace has room for (at least four per pair), and as a ticket can count
+    int64_t room = (v.ws_bytes - (int64_t)v.P * kD) / ((int64_t)v.P * kRangePartBytes);
+    room = room < 16384 ? room : 16384;
+    int64_t rows = rows_per_workgroup(v.P, a.LA + a.LB);
+    while (((int64_t)a.LA + rows - 1) / rows + ((int64_t)a.LB + rows - 1) / rows > room) rows *= 2;
+    a.rows_k = (int)(rows < (1ll << 30) ? rows : (1ll << 30));
+    a.nA = pieces(a.LA, a.rows_k);
+    a.nB = pieces(a.LB, a.rows_k);
+  }
+  if (a.nq + a.nA + a.nB > 65535) return hipErrorInvalidConfiguration;
+  const dim3 grid(v.P, a.nq + a.nA + a.nB), block(kStreamThreads);
+  const bool al = (a.nq == 0 || rows_aligned16(a.q, a.qs)) && (a.nB == 0 || rows_aligned16(a.kB, a.sB));
+  if (v.cfg.in_dtype) {
+    if (al) select_kernel<true, true><<<grid, block, 0, s>>>(v, a);
+    else select_kernel<true, false><<<grid, block, 0, s>>>(v, a);
+  } else {
+    if (al) select_kernel<false, true><<<grid, block, 0, s>>>(v, a);
+    else select_kernel<false, false><<<grid, block, 0, s>>>(v, a);
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_qabs_accumulate(const CacheView& v, const __half* q, int Lq, Strides3 qs, hipStream_t s) {
+  SelectArgs a{};
+  a.q = q, a.qs = qs, a.Lq = Lq;
+  return launch_select_kernel(v, a, s);
 }
 
 hipError_t launch_select2(const CacheView& v, const __half* kA, int LA, Strides3 sA, const __half* kB, int LB, Strides3 sB,
                           uint8_t* sel, hipStream_t s) {
-  long long* mn = (long long*)v.ws;
-  long long* mx = mn + (size_t)v.P * kD;
-  const int n = v.P * kD;
-  range_init_kernel<<<dim3((n + 255) / 256), dim3(256), 0, s>>>(mn, mx, n);
-  if (LA > 0) launch_key_range(v, kA, LA, sA, false, mn, mx, s);       // window rows are binary16 already
-  if (LB > 0) launch_key_range(v, kB, LB, sB, v.cfg.in_dtype != 0, mn, mx, s);
-  select_topk_kernel<<<dim3(v.P), dim3(kD), 0, s>>>(v, mn, mx, sel);
-  return hipGetLastError();
+  SelectArgs a{};
+  a.kA = kA, a.sA = sA, a.LA = LA;
+  a.kB = kB, a.sB = sB, a.LB = LB;
+  a.sel = sel;
+  return launch_select_kernel(v, a, s);
 }
 
-hipError_t launch_select(const CacheView& v, const __half* k, int L, Strides3 ks, uint8_t* sel, hipStream_t s) {
-  return launch_select2(v, nullptr, 0, Strides3{0, 0, 0}, k, L, ks, sel, s);
+hipError_t launch_select(const CacheView& v, const __half* q, int Lq, Strides3 qs, const __half* k, int L, Strides3 ks,
+                         uint8_t* sel, hipStream_t s) {
+  SelectArgs a{};
+  a.q = q, a.qs = qs, a.Lq = Lq;
+  a.kB = k, a.sB = ks, a.LB = L;
+  a.sel = sel;
+  return launch_select_kernel(v, a, s);
 }
 
 }  // namespace mixkvq
