@@ -163,7 +163,7 @@ static int append_range(mixkvq_cache* c, int b0, int nb, const __half* k_new, co
     const int first_rec = (int)(st.n_quant / Rr);
     if (pl.F > 0 && (sel || per == 1 || cfg.k4 + cfg.k16 == 0)) {
       // one selection for the call, blocks of one record each (the pack kernel scores those itself), or nothing to select
-      MIXKVQ_TRY_HIP(launch_flush(v, kw, vw, kvs, r0, first_rec, (int)pl.F * per, sel, s));
+      MIXKVQ_TRY_HIP(launch_flush(v, kw, vw, kvs, r0, first_rec, (int)pl.F * per, sel, pl.n_rest, s));
     } else if (pl.F > 0) {
       // blocks of several records without a given selection: every block is scored over all its R tokens first
       // (they may lie partly in the window, partly in the new tokens), then its records are packed with that choice
@@ -177,17 +177,11 @@ static int append_range(mixkvq_cache* c, int b0, int nb, const __half* k_new, co
         MIXKVQ_TRY_HIP(launch_select2(v, kA, nA, ws, kB, R - nA, kvs, sel_blk, s));
         // (stream origin shifted so that record 0 of this launch is record u * per of the call; r0 - u R <= 0 for u >= 1)
         MIXKVQ_TRY_HIP(launch_flush(v, kw + (u ? (u * R - r0) * kvs.t : 0), vw + (u ? (u * R - r0) * kvs.t : 0), kvs,
-                                    u ? 0 : r0, first_rec + (int)u * per, per, sel_blk, s));
+                                    u ? 0 : r0, first_rec + (int)u * per, per, sel_blk, u == pl.F - 1 ? pl.n_rest : 0, s));
       }
     }
-    // Tokens that stay in the window.  Stream position x of (old residual ++ new tokens) maps to
-    // new-token index x - r0; after F flushes positions [F*R, total) remain.
-    const int64_t rest_first = pl.F * R;
-    if (pl.F == 0) {
-      MIXKVQ_TRY_HIP(launch_residual_copy(v, kw, vw, kvs, 0, S + r0, pl.n_win, s));
-    } else if (pl.n_rest > 0) {
-      MIXKVQ_TRY_HIP(launch_residual_copy(v, kw, vw, kvs, (int)(rest_first - r0), S, pl.n_rest, s));
-    }
+    // (the tokens that stay in the window after a flush were copied by its launch)
+    if (pl.F == 0) MIXKVQ_TRY_HIP(launch_residual_copy(v, kw, vw, kvs, 0, S + r0, pl.n_win, s));
     if (pl.F > 0 && cfg.qacc_reset_on_flush) MIXKVQ_TRY_HIP(launch_zero_qacc(v, s));
     nx.n_quant += pl.F * R;
     nx.n_res = pl.n_rest;
@@ -252,7 +246,7 @@ static int flush_full_windows(mixkvq_cache* c, bool equal, hipStream_t s) {
         const CacheView v = sub_view(c, b0, b1 - b0);
         uint8_t* const sel = scored_apart ? select_scratch(v) : nullptr;
         if (sel) MIXKVQ_TRY_HIP(launch_select2(v, v.res_k + (size_t)cfg.sink * kD, R, ws, nullptr, 0, ws, sel, s));
-        MIXKVQ_TRY_HIP(launch_flush(v, v.res_k, v.res_v, ws, R, (int)(c->seq[b0].n_quant / Rr), per, sel, s));
+        MIXKVQ_TRY_HIP(launch_flush(v, v.res_k, v.res_v, ws, R, (int)(c->seq[b0].n_quant / Rr), per, sel, 0, s));
       }
       b0 = b1;
     }

@@ -89,8 +89,9 @@ hipError_t launch_select(const CacheView& v, const __half* q, int Lq, Strides3 q
 hipError_t launch_select2(const CacheView& v, const __half* kA, int LA, Strides3 sA, const __half* kB, int LB, Strides3 sB,
                           uint8_t* sel, hipStream_t s);
 uint8_t* select_scratch(const CacheView& v);   // room for one selection [P][k16 + k4] in the workspace
+// n_flush records of every pair, then n_rest tokens behind them into the window (rows S..)
 hipError_t launch_flush(const CacheView& v, const __half* k_new, const __half* v_new, Strides3 kvs,
-                        int r0, int first_block, int n_flush, const uint8_t* sel, hipStream_t s);
+                        int r0, int first_block, int n_flush, const uint8_t* sel, int n_rest, hipStream_t s);
 // The full windows of the listed sequences, each one record (a block of several records is flushed per sequence with
 // launch_flush): one launch whatever the number of sequences.
 hipError_t launch_flush_windows(const CacheView& v, const FlushList& list, hipStream_t s);

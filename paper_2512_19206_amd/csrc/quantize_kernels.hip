@@ -14,6 +14,7 @@
 namespace mixkvq {
 
 constexpr int kFlushThreads = 256;
+constexpr int64_t kSplitBlocks = 2048;     // up to this many blocks per launch the keys and the values of a block are two workgroups
 constexpr int kRowPad = 8;                 // halfs of padding per LDS row (keeps 16-byte alignment)
 constexpr int kRowStride = kD + kRowPad;   // 136 halfs = 272 bytes
 
@@ -64,6 +65,24 @@ __device__ __forceinline__ void load_tile(__half* sT, const __half* win, const _
     const __half* row = token_row(win, fresh, st, p, Hkv, r0, pos0 + t);
     uint4 v = as_f16x8(*reinterpret_cast<const uint4*>(row + c * 8), bf16 && pos0 + t >= r0);
     *reinterpret_cast<uint4*>(sT + t * kRowStride + c * 8) = v;
+  }
+}
+
+// The tokens of a call that stay behind in the window: n tokens starting at new-token index src_first go to fp16 rows
+// dst_row.. of every pair (row 0 = first sink row, row S = first row of the residual window).  n == 0: none.
+// wgs > 0: workgroups per pair that do nothing else; in_block: the pair's first block does it when it has read the window.
+struct WindowCopy { int n, src_first, dst_row, wgs, in_block; };
+// part `x` of `nx` of the copy for pair p
+__device__ __forceinline__ void copy_rows(const CacheView& cv, const __half* __restrict__ k_new, const __half* __restrict__ v_new,
+                                          Strides3 st, const WindowCopy& wc, int p, int x, int nx, bool do_k, bool do_v) {
+  const int b = p / cv.cfg.Hkv, j = p % cv.cfg.Hkv;
+  const bool bf16 = cv.cfg.in_dtype != 0;
+  for (int idx = x * blockDim.x + threadIdx.x; idx < wc.n * 16; idx += nx * blockDim.x) {
+    const int t = idx >> 4, c = idx & 15;
+    const int64_t src = (int64_t)b * st.b + (int64_t)j * st.h + (int64_t)(wc.src_first + t) * st.t + c * 8;
+    const size_t dst = ((size_t)p * cv.RW + wc.dst_row + t) * kD + c * 8;
+    if (do_k) *reinterpret_cast<uint4*>(cv.res_k + dst) = as_f16x8(*reinterpret_cast<const uint4*>(k_new + src), bf16);
+    if (do_v) *reinterpret_cast<uint4*>(cv.res_v + dst) = as_f16x8(*reinterpret_cast<const uint4*>(v_new + src), bf16);
   }
 }
 
@@ -359,9 +378,21 @@ __device__ __forceinline__ uint4 load_chunk(const __half* res_p, const __half* f
   return as_f16x8(*reinterpret_cast<const uint4*>(row + c * 8), bf16 && pos >= r0);   // window rows are binary16 already
 }
 
+// SPLIT: a block is two workgroups, blockIdx.z = 0 for its keys and 1 for its values.  The halves of a record share
+// nothing, and where the grid does not fill the chip the time is one workgroup's chain of phases.  Once it is full several
+// times over the fused form is the better one: it overlaps the keys' arithmetic with the values' loads.  Fused / split at
+// R = G = 128 and 12 fp16 channels: 32 to 256 blocks 13.1-13.9 / 8.8-9.2 us, 512: 16.9 / 16.8, 1 024: 31.3 / 28.1, 2 048:
+// 49.5 / 47.7, 3 072: 66.8 / 67.5, 4 096: 93.0 / 96.7.
+// Rows blockIdx.y >= gridDim.y - wc.wgs copy the tokens that stay behind in the window (WindowCopy).
+template <bool SPLIT>
 __global__ void __launch_bounds__(kFlushThreads, 3)   // three workgroups per CU (LDS) = three wavefronts per SIMD
 flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __half* __restrict__ v_new, Strides3 st,
-                        int r0, int first_block, const uint8_t* __restrict__ sel_in, FlushList list) {
+                        int r0, int first_block, const uint8_t* __restrict__ sel_in, FlushList list, WindowCopy wc) {
+  const bool do_k = !SPLIT || blockIdx.z == 0, do_v = !SPLIT || blockIdx.z == 1;
+  if ((int)blockIdx.y >= (int)gridDim.y - wc.wgs) {
+    copy_rows(cv, k_new, v_new, st, wc, blockIdx.x, (int)blockIdx.y - ((int)gridDim.y - wc.wgs), wc.wgs, do_k, do_v);
+    return;
+  }
   __shared__ __align__(16) __half sT[kMaxR * kFastStride];   // K tile, then V tile
   __shared__ __align__(16) double sA[kD];
   __shared__ unsigned char sTier[kD];      // 0: 2 bit, 1: 4 bit, 2: fp16
@@ -397,7 +428,7 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
   MIXKVQ_FPHASE(0)
   // ---- the key tile first; the value tile is requested once the keys are staged in LDS, so that the wait for the
   //      keys is a wait for 32 KiB and the values arrive while the keys are encoded ------------------------------
-  uint4 kreg[8], vreg[8];
+  uint4 vreg[8];
   const int64_t pair_off = (int64_t)(p / Hkv) * st.b + (int64_t)(p % Hkv) * st.h;
   const __half* res_kp = window_rows(cv, cv.res_k, p);
   const __half* res_vp = window_rows(cv, cv.res_v, p);
@@ -409,374 +440,389 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
   const int64_t row_stride = from_res ? (int64_t)kD : st.t;
   const int64_t first = (int64_t)(from_res ? pos0 : pos0 - r0) + (tid >> 4);
   const bool v_pending = one_place && bf16 && !from_res;     // the value tile in registers still holds bfloat16
-  if (one_place) {
-    const __half* kp = (from_res ? res_kp : k_new + pair_off) + first * row_stride + (tid & 15) * 8;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      kreg[i] = make_uint4(0u, 0u, 0u, 0u);
-      if (tid + kFlushThreads * i < n_chunks16) kreg[i] = *reinterpret_cast<const uint4*>(kp + 16 * i * row_stride);
-    }
-    if (bf16 && !from_res) {     // rows of the caller's bfloat16 tensors enter as binary16 (the values when they are staged)
-#pragma unroll
-      for (int i = 0; i < 8; ++i) kreg[i] = as_f16x8(kreg[i], true);
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int idx = tid + kFlushThreads * i;
-      kreg[i] = make_uint4(0u, 0u, 0u, 0u);
-      if (idx < n_chunks16) kreg[i] = load_chunk(res_kp, k_new + pair_off, st.t, r0, pos0, idx, bf16);
-    }
-  }
-  // zero the small planes of the record (index bytes, tails of the scale/zero planes)
-  // (under the threshold policy the channel lists start out as "no channel")
-  for (int i = tid; i < off_klo / 4; i += kFlushThreads)
-    reinterpret_cast<unsigned*>(rec)[i] = (policy == 1 && i < ks / 4) ? 0xffffffffu : 0u;
   if (tid < 9) sKmax[tid] = 0u;
+  if (do_k) {
+    uint4 kreg[8];
+    if (one_place) {
+      const __half* kp = (from_res ? res_kp : k_new + pair_off) + first * row_stride + (tid & 15) * 8;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int idx = tid + kFlushThreads * i;
-    if (idx < n_chunks16) {
-      unsigned* dst = reinterpret_cast<unsigned*>(sT + (idx >> 4) * kFastStride + (idx & 15) * 8);
-      dst[0] = kreg[i].x; dst[1] = kreg[i].y; dst[2] = kreg[i].z; dst[3] = kreg[i].w;
-    }
-  }
-  if (one_place) {
-    const __half* vp = (from_res ? res_vp : v_new + pair_off) + first * row_stride + (tid & 15) * 8;
+      for (int i = 0; i < 8; ++i) {
+        kreg[i] = make_uint4(0u, 0u, 0u, 0u);
+        if (tid + kFlushThreads * i < n_chunks16) kreg[i] = *reinterpret_cast<const uint4*>(kp + 16 * i * row_stride);
+      }
+      if (bf16 && !from_res) {     // rows of the caller's bfloat16 tensors enter as binary16 (the values when they are staged)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      vreg[i] = make_uint4(0u, 0u, 0u, 0u);
-      if (tid + kFlushThreads * i < n_chunks16) vreg[i] = *reinterpret_cast<const uint4*>(vp + 16 * i * row_stride);
+        for (int i = 0; i < 8; ++i) kreg[i] = as_f16x8(kreg[i], true);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int idx = tid + kFlushThreads * i;
+        kreg[i] = make_uint4(0u, 0u, 0u, 0u);
+        if (idx < n_chunks16) kreg[i] = load_chunk(res_kp, k_new + pair_off, st.t, r0, pos0, idx, bf16);
+      }
     }
-  } else {
+    // zero the small planes of the record (index bytes, tails of the scale/zero planes)
+    // (under the threshold policy the channel lists start out as "no channel")
+    // (the kmax plane is written whole further down: its entry [NG] belongs to the values)
+    for (int i = tid; i < off_klo / 4; i += kFlushThreads)
+      if (i < off_kmax / 4 || i >= off_klo_s / 4)
+        reinterpret_cast<unsigned*>(rec)[i] = (policy == 1 && i < ks / 4) ? 0xffffffffu : 0u;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int idx = tid + kFlushThreads * i;
-      vreg[i] = make_uint4(0u, 0u, 0u, 0u);
-      if (idx < n_chunks16) vreg[i] = load_chunk(res_vp, v_new + pair_off, st.t, r0, pos0, idx, bf16);
+      if (idx < n_chunks16) {
+        unsigned* dst = reinterpret_cast<unsigned*>(sT + (idx >> 4) * kFastStride + (idx & 15) * 8);
+        dst[0] = kreg[i].x; dst[1] = kreg[i].y; dst[2] = kreg[i].z; dst[3] = kreg[i].w;
+      }
     }
   }
-  __syncthreads();
-
-  MIXKVQ_FPHASE(1)
-  // ---- minimum / maximum per chunk of 16 tokens and channel pair -----------------------------
-  {
-    const int d2 = tid & 63;
-    const unsigned* sT32 = reinterpret_cast<const unsigned*>(sT);
-    for (int ch = tid >> 6; ch < n_ch; ch += 4) {
-      fh2 lo = as_h2(sT32[(16 * ch) * (kFastStride / 2) + d2]), hi = lo;
+  if (do_v) {
+    if (one_place) {
+      const __half* vp = (from_res ? res_vp : v_new + pair_off) + first * row_stride + (tid & 15) * 8;
 #pragma unroll
-      for (int t = 1; t < 16; ++t) {
-        const fh2 key = as_h2(sT32[(16 * ch + t) * (kFastStride / 2) + d2]);
-        lo = __builtin_elementwise_min(lo, key);
-        hi = __builtin_elementwise_max(hi, key);
+      for (int i = 0; i < 8; ++i) {
+        vreg[i] = make_uint4(0u, 0u, 0u, 0u);
+        if (tid + kFlushThreads * i < n_chunks16) vreg[i] = *reinterpret_cast<const uint4*>(vp + 16 * i * row_stride);
       }
-      sCLo[ch][d2] = __builtin_bit_cast(unsigned, lo);
-      sCHi[ch][d2] = __builtin_bit_cast(unsigned, hi);
-    }
-  }
-  __syncthreads();
-
-  MIXKVQ_FPHASE(2)
-  // ---- channel tiers ------------------------------------------------------------------------
-  if (sel_in == nullptr && ks > 0) {
-    double A = 0.0;
-    if (tid < kD) {
-      const _Float16* cl = reinterpret_cast<const _Float16*>(&sCLo[0][0]);
-      const _Float16* chh = reinterpret_cast<const _Float16*>(&sCHi[0][0]);
-      _Float16 lo = cl[tid], hi = chh[tid];
-      for (int ch = 1; ch < n_ch; ++ch) {
-        const _Float16 a = cl[ch * kD + tid], b2 = chh[ch * kD + tid];
-        lo = a < lo ? a : lo;
-        hi = b2 > hi ? b2 : hi;
-      }
-      const long long rng = fix24(h_bits(hi)) - fix24(h_bits(lo));
-      A = score_mode ? (double)rng : (double)cv.qacc[(size_t)p * kD + tid] * (double)rng;
-      sA[tid] = A;
-    }
-    __syncthreads();
-    // (sR is not yet in use)
-    const int tier = rank_channels(cv.cfg, policy == 1 ? cv.qcnt[p] : 0ull, sA, reinterpret_cast<unsigned*>(sR));
-    if (tid < kD) sTier[tid] = (unsigned char)tier;
-  } else {
-    if (tid < kD) sTier[tid] = 0;
-    __syncthreads();
-    if (tid < ks) {
-      const unsigned ch = sel_in[(size_t)p * ks + tid];
-      if (ch < (unsigned)kD) sTier[ch] = tid < k16 ? 2 : 1;     // MIXKVQ_NO_CHANNEL: an unused entry
-    }
-  }
-  __syncthreads();
-  // position of every channel inside its tier: ballots over the two wavefronts that hold the channels
-  {
-    const int tier = tid < kD ? sTier[tid] : 3;
-    const unsigned long long m0 = __ballot(tier == 0), m1 = __ballot(tier == 1), m2 = __ballot(tier == 2);
-    if (lane == 0 && wave < 2) {
-      sCnt[3 * wave] = __popcll(m0);
-      sCnt[3 * wave + 1] = __popcll(m1);
-      sCnt[3 * wave + 2] = __popcll(m2);
-    }
-    __syncthreads();
-    if (tid < kD) {
-      const unsigned long long mine = tier == 0 ? m0 : (tier == 1 ? m1 : m2);
-      const int pos = __popcll(mine & ((1ull << lane) - 1ull)) + (wave == 1 ? sCnt[tier] : 0);
-      sPos[tid] = (unsigned char)pos;
-      if (tier == 0) sLoList[pos] = (unsigned char)tid;
-      else {
-        const int slot = (tier == 2 ? 0 : k16) + pos;
-        sHiList[slot] = (unsigned char)tid;
-        rec[off_idx + slot] = (uint8_t)tid;
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int idx = tid + kFlushThreads * i;
+        vreg[i] = make_uint4(0u, 0u, 0u, 0u);
+        if (idx < n_chunks16) vreg[i] = load_chunk(res_vp, v_new + pair_off, st.t, r0, pos0, idx, bf16);
       }
     }
   }
   __syncthreads();
+  if (do_k) {
 
-  // sizes of the tiers of this block (the budgets, or what passed the thresholds)
-  // (the same for every thread: kept in scalar registers)
-  const int n_lo = __builtin_amdgcn_readfirstlane(sCnt[0] + sCnt[3]), n_4 = __builtin_amdgcn_readfirstlane(sCnt[1] + sCnt[4]),
-            n_16 = __builtin_amdgcn_readfirstlane(sCnt[2] + sCnt[5]);
+    MIXKVQ_FPHASE(1)
+    // ---- minimum / maximum per chunk of 16 tokens and channel pair -----------------------------
+    {
+      const int d2 = tid & 63;
+      const unsigned* sT32 = reinterpret_cast<const unsigned*>(sT);
+      for (int ch = tid >> 6; ch < n_ch; ch += 4) {
+        fh2 lo = as_h2(sT32[(16 * ch) * (kFastStride / 2) + d2]), hi = lo;
+#pragma unroll
+        for (int t = 1; t < 16; ++t) {
+          const fh2 key = as_h2(sT32[(16 * ch + t) * (kFastStride / 2) + d2]);
+          lo = __builtin_elementwise_min(lo, key);
+          hi = __builtin_elementwise_max(hi, key);
+        }
+        sCLo[ch][d2] = __builtin_bit_cast(unsigned, lo);
+        sCHi[ch][d2] = __builtin_bit_cast(unsigned, hi);
+      }
+    }
+    __syncthreads();
 
-  MIXKVQ_FPHASE(3)
-  // ---- key group parameters from the chunk extrema ------------------------------------------
-  {
-    const _Float16* cl = reinterpret_cast<const _Float16*>(&sCLo[0][0]);
-    const _Float16* chh = reinterpret_cast<const _Float16*>(&sCHi[0][0]);
-    const int cpg = Gk / 16;     // chunks per group
-    // (a wavefront's 64 items of one pass belong to one group: its largest scale is reduced over the wavefront first,
-    //  one LDS atomic per wavefront and pass)
-    for (int it = tid; it < NG * kD; it += kFlushThreads) {
-      const int grp = it / kD, d = it % kD;
-      const unsigned char tier = sTier[d];
-      unsigned s16v = 0u;
-      if (tier != 2) {
-        _Float16 lo = cl[(grp * cpg) * kD + d], hi = chh[(grp * cpg) * kD + d];
-        for (int c = 1; c < cpg; ++c) {
-          const _Float16 a = cl[(grp * cpg + c) * kD + d], b2 = chh[(grp * cpg + c) * kD + d];
+    MIXKVQ_FPHASE(2)
+    // ---- channel tiers ------------------------------------------------------------------------
+    if (sel_in == nullptr && ks > 0) {
+      double A = 0.0;
+      if (tid < kD) {
+        const _Float16* cl = reinterpret_cast<const _Float16*>(&sCLo[0][0]);
+        const _Float16* chh = reinterpret_cast<const _Float16*>(&sCHi[0][0]);
+        _Float16 lo = cl[tid], hi = chh[tid];
+        for (int ch = 1; ch < n_ch; ++ch) {
+          const _Float16 a = cl[ch * kD + tid], b2 = chh[ch * kD + tid];
           lo = a < lo ? a : lo;
           hi = b2 > hi ? b2 : hi;
         }
-        const GroupParams gp = group_params((float)lo, (float)hi, tier ? 15.f : 3.f);
-        sSZ[grp * kD + d] = (unsigned)gp.s16 | ((unsigned)gp.z16 << 16);
-        fast_params(gp.s, gp.z, &sR[grp * kD + d], &sNZ[grp * kD + d]);
-        const int pos = sPos[d];
-        s16v = gp.s16;
-        if (tier == 0) {
-          reinterpret_cast<unsigned short*>(rec + off_klo_s)[grp * NLp + pos] = gp.s16;
-          reinterpret_cast<unsigned short*>(rec + off_klo_z)[grp * NLp + pos] = gp.z16;
-        } else {
-          reinterpret_cast<unsigned short*>(rec + off_k4_s)[grp * k4 + pos] = gp.s16;
-          reinterpret_cast<unsigned short*>(rec + off_k4_z)[grp * k4 + pos] = gp.z16;
+        const long long rng = fix24(h_bits(hi)) - fix24(h_bits(lo));
+        A = score_mode ? (double)rng : (double)cv.qacc[(size_t)p * kD + tid] * (double)rng;
+        sA[tid] = A;
+      }
+      __syncthreads();
+      // (sR is not yet in use)
+      const int tier = rank_channels(cv.cfg, policy == 1 ? cv.qcnt[p] : 0ull, sA, reinterpret_cast<unsigned*>(sR));
+      if (tid < kD) sTier[tid] = (unsigned char)tier;
+    } else {
+      if (tid < kD) sTier[tid] = 0;
+      __syncthreads();
+      if (tid < ks) {
+        const unsigned ch = sel_in[(size_t)p * ks + tid];
+        if (ch < (unsigned)kD) sTier[ch] = tid < k16 ? 2 : 1;     // MIXKVQ_NO_CHANNEL: an unused entry
+      }
+    }
+    __syncthreads();
+    // position of every channel inside its tier: ballots over the two wavefronts that hold the channels
+    {
+      const int tier = tid < kD ? sTier[tid] : 3;
+      const unsigned long long m0 = __ballot(tier == 0), m1 = __ballot(tier == 1), m2 = __ballot(tier == 2);
+      if (lane == 0 && wave < 2) {
+        sCnt[3 * wave] = __popcll(m0);
+        sCnt[3 * wave + 1] = __popcll(m1);
+        sCnt[3 * wave + 2] = __popcll(m2);
+      }
+      __syncthreads();
+      if (tid < kD) {
+        const unsigned long long mine = tier == 0 ? m0 : (tier == 1 ? m1 : m2);
+        const int pos = __popcll(mine & ((1ull << lane) - 1ull)) + (wave == 1 ? sCnt[tier] : 0);
+        sPos[tid] = (unsigned char)pos;
+        if (tier == 0) sLoList[pos] = (unsigned char)tid;
+        else {
+          const int slot = (tier == 2 ? 0 : k16) + pos;
+          sHiList[slot] = (unsigned char)tid;
+          rec[off_idx + slot] = (uint8_t)tid;
         }
       }
-      const unsigned wmax = wave_max_u32(s16v);
-      if (lane == 0) atomicMax(&sKmax[grp], wmax);
     }
-  }
-  __syncthreads();
-  if (tid < NG) reinterpret_cast<unsigned short*>(rec + off_kmax)[tid] = (unsigned short)sKmax[tid];
+    __syncthreads();
 
-  MIXKVQ_FPHASE(4)
-  // ---- 2-bit key words [token][Wlo]: thread = (word column, token lane); the 16 channels of the column
-  //      and their parameters stay in registers ---------------------------------------------------------
-  {
-    const int wd = tid & 7, tl = tid >> 3;
-    if (wd < Wlo) {
-      int doff[16];
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int jj = 16 * wd + i;
-        doff[i] = jj < n_lo ? (int)sLoList[jj] : -1;
+    // sizes of the tiers of this block (the budgets, or what passed the thresholds)
+    // (the same for every thread: kept in scalar registers)
+    const int n_lo = __builtin_amdgcn_readfirstlane(sCnt[0] + sCnt[3]), n_4 = __builtin_amdgcn_readfirstlane(sCnt[1] + sCnt[4]),
+              n_16 = __builtin_amdgcn_readfirstlane(sCnt[2] + sCnt[5]);
+
+    MIXKVQ_FPHASE(3)
+    // ---- key group parameters from the chunk extrema ------------------------------------------
+    {
+      const _Float16* cl = reinterpret_cast<const _Float16*>(&sCLo[0][0]);
+      const _Float16* chh = reinterpret_cast<const _Float16*>(&sCHi[0][0]);
+      const int cpg = Gk / 16;     // chunks per group
+      // (a wavefront's 64 items of one pass belong to one group: its largest scale is reduced over the wavefront first,
+      //  one LDS atomic per wavefront and pass)
+      for (int it = tid; it < NG * kD; it += kFlushThreads) {
+        const int grp = it / kD, d = it % kD;
+        const unsigned char tier = sTier[d];
+        unsigned s16v = 0u;
+        if (tier != 2) {
+          _Float16 lo = cl[(grp * cpg) * kD + d], hi = chh[(grp * cpg) * kD + d];
+          for (int c = 1; c < cpg; ++c) {
+            const _Float16 a = cl[(grp * cpg + c) * kD + d], b2 = chh[(grp * cpg + c) * kD + d];
+            lo = a < lo ? a : lo;
+            hi = b2 > hi ? b2 : hi;
+          }
+          const GroupParams gp = group_params((float)lo, (float)hi, tier ? 15.f : 3.f);
+          sSZ[grp * kD + d] = (unsigned)gp.s16 | ((unsigned)gp.z16 << 16);
+          fast_params(gp.s, gp.z, &sR[grp * kD + d], &sNZ[grp * kD + d]);
+          const int pos = sPos[d];
+          s16v = gp.s16;
+          if (tier == 0) {
+            reinterpret_cast<unsigned short*>(rec + off_klo_s)[grp * NLp + pos] = gp.s16;
+            reinterpret_cast<unsigned short*>(rec + off_klo_z)[grp * NLp + pos] = gp.z16;
+          } else {
+            reinterpret_cast<unsigned short*>(rec + off_k4_s)[grp * k4 + pos] = gp.s16;
+            reinterpret_cast<unsigned short*>(rec + off_k4_z)[grp * k4 + pos] = gp.z16;
+          }
+        }
+        const unsigned wmax = wave_max_u32(s16v);
+        if (lane == 0) atomicMax(&sKmax[grp], wmax);
       }
-      for (int grp = 0; grp < NG; ++grp) {
-        float rc[16], nz[16];
+    }
+    __syncthreads();
+    if (tid < (off_klo_s - off_kmax) / 2 && tid != NG)
+      reinterpret_cast<unsigned short*>(rec + off_kmax)[tid] = tid < NG ? (unsigned short)sKmax[tid] : (unsigned short)0;
+
+    MIXKVQ_FPHASE(4)
+    // ---- 2-bit key words [token][Wlo]: thread = (word column, token lane); the 16 channels of the column
+    //      and their parameters stay in registers ---------------------------------------------------------
+    {
+      const int wd = tid & 7, tl = tid >> 3;
+      if (wd < Wlo) {
+        int doff[16];
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-          const int d = doff[i] < 0 ? 0 : doff[i];
-          rc[i] = doff[i] < 0 ? 0.f : sR[grp * kD + d];   // (0, 0) gives code 0: the padding of the last word
-          nz[i] = doff[i] < 0 ? 0.f : sNZ[grp * kD + d];
+          const int jj = 16 * wd + i;
+          doff[i] = jj < n_lo ? (int)sLoList[jj] : -1;
         }
-        // LDS address of each of the 16 elements in this thread's first token of the group; its other tokens are 32
-        // rows further each, a compile-time distance once the loop is unrolled (no address arithmetic per element)
-        const __half* col[16];
+        for (int grp = 0; grp < NG; ++grp) {
+          float rc[16], nz[16];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) col[i] = sT + (grp * Gk + tl) * kFastStride + (doff[i] < 0 ? 0 : doff[i]);
-        const int n_it = (Gk - tl + 31) / 32;      // tokens tl, tl + 32, ... below Gk: at most 4 (Gk <= 128)
+          for (int i = 0; i < 16; ++i) {
+            const int d = doff[i] < 0 ? 0 : doff[i];
+            rc[i] = doff[i] < 0 ? 0.f : sR[grp * kD + d];   // (0, 0) gives code 0: the padding of the last word
+            nz[i] = doff[i] < 0 ? 0.f : sNZ[grp * kD + d];
+          }
+          // LDS address of each of the 16 elements in this thread's first token of the group; its other tokens are 32
+          // rows further each, a compile-time distance once the loop is unrolled (no address arithmetic per element)
+          const __half* col[16];
 #pragma unroll
-        for (int k = 0; k < kMaxR / 32; ++k) {
-          if (k >= n_it) break;
-          const int t = grp * Gk + tl + 32 * k;
-          float hw[2] = {0.f, 0.f};
-          float dev[4] = {0.f, 0.f, 0.f, 0.f};     // per run of four codes: the search below stays short
+          for (int i = 0; i < 16; ++i) col[i] = sT + (grp * Gk + tl) * kFastStride + (doff[i] < 0 ? 0 : doff[i]);
+          const int n_it = (Gk - tl + 31) / 32;      // tokens tl, tl + 32, ... below Gk: at most 4 (Gk <= 128)
 #pragma unroll
-          for (int i = 0; i < 16; ++i)
-            add_code<2>(hw, i, code_fast(col[i][k * 32 * kFastStride], rc[i], nz[i], dev[i >> 2]));
-          // some quotient sits next to a rounding boundary (exact ties are common: about every other pass has one)
-          if (__any(fmaxf(fmaxf(dev[0], dev[1]), fmaxf(dev[2], dev[3])) > 0.5f - kEps2)) {
+          for (int k = 0; k < kMaxR / 32; ++k) {
+            if (k >= n_it) break;
+            const int t = grp * Gk + tl + 32 * k;
+            float hw[2] = {0.f, 0.f};
+            float dev[4] = {0.f, 0.f, 0.f, 0.f};     // per run of four codes: the search below stays short
 #pragma unroll
-            for (int i4 = 0; i4 < 4; ++i4) {
-              if (!__any(dev[i4] > 0.5f - kEps2)) continue;
+            for (int i = 0; i < 16; ++i)
+              add_code<2>(hw, i, code_fast(col[i][k * 32 * kFastStride], rc[i], nz[i], dev[i >> 2]));
+            // some quotient sits next to a rounding boundary (exact ties are common: about every other pass has one)
+            if (__any(fmaxf(fmaxf(dev[0], dev[1]), fmaxf(dev[2], dev[3])) > 0.5f - kEps2)) {
 #pragma unroll
-              for (int i = 4 * i4; i < 4 * i4 + 4; ++i) {     // find the codes concerned and correct them
-                const int d = doff[i] < 0 ? 0 : doff[i];
-                const __half x = col[i][k * 32 * kFastStride];
-                float dv = 0.f;
-                const float c = code_fast(x, rc[i], nz[i], dv);
-                if (__any(dv > 0.5f - kEps2))
-                  add_code<2>(hw, i, code_exact(x, doff[i] < 0 ? 0u : sSZ[grp * kD + d], 3.f) - c);
+              for (int i4 = 0; i4 < 4; ++i4) {
+                if (!__any(dev[i4] > 0.5f - kEps2)) continue;
+#pragma unroll
+                for (int i = 4 * i4; i < 4 * i4 + 4; ++i) {     // find the codes concerned and correct them
+                  const int d = doff[i] < 0 ? 0 : doff[i];
+                  const __half x = col[i][k * 32 * kFastStride];
+                  float dv = 0.f;
+                  const float c = code_fast(x, rc[i], nz[i], dv);
+                  if (__any(dv > 0.5f - kEps2))
+                    add_code<2>(hw, i, code_exact(x, doff[i] < 0 ? 0u : sSZ[grp * kD + d], 3.f) - c);
+                }
               }
             }
+            const unsigned w = join_halves(hw);
+            reinterpret_cast<unsigned*>(rec + off_klo)[t * Wlo + wd] = w;
           }
-          const unsigned w = join_halves(hw);
-          reinterpret_cast<unsigned*>(rec + off_klo)[t * Wlo + wd] = w;
         }
       }
     }
-  }
-  MIXKVQ_FPHASE(5)
-  // ---- 4-bit key words: [token][k4/8] -------------------------------------
-  // (a thread keeps its token; the two halves of the workgroup alternate over the words: no divisions by run-time values)
-  for (int wd = tid >> 7; wd < W4; wd += 2) {
-    const int t = tid & 127;
-    if (t >= R) break;
-    const int grp = t / Gk, it = t * W4 + wd;
-    float hw[2] = {0.f, 0.f};
-    float dev[2] = {0.f, 0.f};
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const bool used = wd * 8 + i < n_4;                    // an unused entry gets (0, 0), i.e. code 0
-      const int d = used ? sHiList[k16 + wd * 8 + i] : 0;
-      add_code<4>(hw, i, code_fast(sT[t * kFastStride + d], used ? sR[grp * kD + d] : 0.f,
-                                   used ? sNZ[grp * kD + d] : 0.f, dev[i >> 2]));
-    }
-    if (__any(fmaxf(dev[0], dev[1]) > 0.5f - kEps4)) {     // some quotient sits next to a rounding boundary
-#pragma unroll
-      for (int i4 = 0; i4 < 2; ++i4) {
-        if (!__any(dev[i4] > 0.5f - kEps4)) continue;
-#pragma unroll
-        for (int i = 4 * i4; i < 4 * i4 + 4; ++i) {
-          const bool used = wd * 8 + i < n_4;
-          const int d = used ? sHiList[k16 + wd * 8 + i] : 0;
-          float dv = 0.f;
-          const float c = code_fast(sT[t * kFastStride + d], used ? sR[grp * kD + d] : 0.f, used ? sNZ[grp * kD + d] : 0.f, dv);
-          if (__any(dv > 0.5f - kEps4))
-            add_code<4>(hw, i, code_exact(sT[t * kFastStride + d], used ? sSZ[grp * kD + d] : 0u, 15.f) - c);
-        }
-      }
-    }
-    const unsigned w = join_halves(hw);
-    reinterpret_cast<unsigned*>(rec + off_k4)[it] = w;
-  }
-  // ---- fp16 tier: [token][k16] ------------------------------------------
-  for (int i = tid >> 7; i < k16; i += 2) {
-    const int t = tid & 127;
-    if (t < R) reinterpret_cast<__half*>(rec + off_k16)[t * k16 + i] = i < n_16 ? sT[t * kFastStride + sHiList[i]] : __ushort_as_half(0);
-  }
-  __syncthreads();
-
-  MIXKVQ_FPHASE(6)
-  // ---- values ---------------------------------------------------------------------------------
-  // The tile goes to LDS; on the way every thread reduces its 16-byte pieces (still in registers) to the minimum
-  // and maximum per token and value group: 16 threads cover a row, a group is Gv/8 neighbouring threads, and the
-  // pair (min, -max) is reduced with packed fp16 minima over DPP lane exchanges inside the row of 16.
-  {
-    const int c = tid & 15, lpg = Gv / 8;                 // lpg = 2, 4, 8 or 16 (Gv divides 128)
-    const int lpg_shift = 31 - __builtin_clz(lpg);
-    unsigned* sRow = &sChunk[0][0][0];     // [token][value group] packed (min, -max); <= 128 * 8 entries
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int row = (tid >> 4) + 16 * i;
-      if (row < R) {
-        const uint4 v = as_f16x8(vreg[i], v_pending);
-        unsigned* dst = reinterpret_cast<unsigned*>(sT + row * kFastStride + c * 8);
-        dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
-        const fh2 k0 = as_h2(v.x), k1 = as_h2(v.y), k2 = as_h2(v.z), k3 = as_h2(v.w);
-        const fh2 lo2 = __builtin_elementwise_min(__builtin_elementwise_min(k0, k1), __builtin_elementwise_min(k2, k3));
-        const fh2 hi2 = __builtin_elementwise_max(__builtin_elementwise_max(k0, k1), __builtin_elementwise_max(k2, k3));
-        fh2 m;
-        m[0] = lo2[0] < lo2[1] ? lo2[0] : lo2[1];
-        m[1] = -(hi2[0] > hi2[1] ? hi2[0] : hi2[1]);
-        int mi = __builtin_bit_cast(int, m);
-#define MIXKVQ_DPP_MIN(CTRL)                                                                                   \
-  mi = __builtin_bit_cast(int, __builtin_elementwise_min(                                                      \
-      __builtin_bit_cast(fh2, mi), __builtin_bit_cast(fh2, __builtin_amdgcn_update_dpp(mi, mi, CTRL, 0xf, 0xf, false))));
-        if (lpg >= 2) MIXKVQ_DPP_MIN(0xB1)     // quad_perm [1,0,3,2]
-        if (lpg >= 4) MIXKVQ_DPP_MIN(0x4E)     // quad_perm [2,3,0,1]
-        if (lpg >= 8) MIXKVQ_DPP_MIN(0x141)    // row_half_mirror
-        if (lpg >= 16) MIXKVQ_DPP_MIN(0x140)   // row_mirror
-#undef MIXKVQ_DPP_MIN
-        if ((c & (lpg - 1)) == 0) sRow[row * NVG + (c >> lpg_shift)] = (unsigned)mi;
-      }
-    }
-    MIXKVQ_FPHASE(7)
-    __syncthreads();
-    unsigned vmax_t = 0u;
-    for (int it = tid; it < R * NVG; it += kFlushThreads) {
-      const fh2 mm = as_h2(sRow[it]);
-      const GroupParams gp = group_params((float)mm[0], -(float)mm[1], 3.f);
-      sSZ[it] = (unsigned)gp.s16 | ((unsigned)gp.z16 << 16);
-      fast_params(gp.s, gp.z, &sR[it], &sNZ[it]);
-      vmax_t = gp.s16 > vmax_t ? gp.s16 : vmax_t;
-      reinterpret_cast<unsigned short*>(rec + off_v_s)[it] = gp.s16;
-      reinterpret_cast<unsigned short*>(rec + off_v_z)[it] = gp.z16;
-    }
-    const unsigned wmax = wave_max_u32(vmax_t);       // every lane is here: the loop above has ended for all
-    if (lane == 0) atomicMax(&sKmax[8], wmax);
-  }
-  __syncthreads();
-  if (tid == 0) reinterpret_cast<unsigned short*>(rec + off_kmax)[NG] = (unsigned short)sKmax[8];
-  MIXKVQ_FPHASE(8)
-  // value words [token group][channel], 16 codes along tokens: the 16 tokens' parameters in registers
-  {
-    const int d = tid & (kD - 1), vg = d / Gv;
-    const int ilv = cv.lay.v_interleave;
-    for (int tg = tid >> 7; tg < n_ch; tg += 2) {
-      // tokens of the word: two runs of 8 (tok0 .. tok0+7 and tok1 .. tok1+7), consecutive unless interleaved; each run
-      // gets one base address, so that the elements sit at compile-time offsets from it
-      const int tok0 = value_word_token(tg, 0, ilv), tok1 = tok0 + (ilv ? 32 : 8);
-      const __half* const col0 = sT + tok0 * kFastStride + d;
-      const __half* const col1 = sT + tok1 * kFastStride + d;
-      float rc[16], nz[16];
-      if (NVG == 1) {
-#pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4) {
-          const int t4 = (i4 >> 1 ? tok1 : tok0) + 4 * (i4 & 1);
-          const float4 a = *reinterpret_cast<const float4*>(sR + t4);
-          const float4 b2 = *reinterpret_cast<const float4*>(sNZ + t4);
-          rc[4 * i4] = a.x; rc[4 * i4 + 1] = a.y; rc[4 * i4 + 2] = a.z; rc[4 * i4 + 3] = a.w;
-          nz[4 * i4] = b2.x; nz[4 * i4 + 1] = b2.y; nz[4 * i4 + 2] = b2.z; nz[4 * i4 + 3] = b2.w;
-        }
-      } else {
-        const float* const r0 = sR + tok0 * NVG + vg, * const r1 = sR + tok1 * NVG + vg;
-        const float* const z0 = sNZ + tok0 * NVG + vg, * const z1 = sNZ + tok1 * NVG + vg;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          rc[i] = (i < 8 ? r0 : r1)[(i & 7) * NVG];
-          nz[i] = (i < 8 ? z0 : z1)[(i & 7) * NVG];
-        }
-      }
+    MIXKVQ_FPHASE(5)
+    // ---- 4-bit key words: [token][k4/8] -------------------------------------
+    // (a thread keeps its token; the two halves of the workgroup alternate over the words: no divisions by run-time values)
+    for (int wd = tid >> 7; wd < W4; wd += 2) {
+      const int t = tid & 127;
+      if (t >= R) break;
+      const int grp = t / Gk, it = t * W4 + wd;
       float hw[2] = {0.f, 0.f};
-      float dev[4] = {0.f, 0.f, 0.f, 0.f};
+      float dev[2] = {0.f, 0.f};
 #pragma unroll
-      for (int i = 0; i < 16; ++i)
-        add_code<2>(hw, i, code_fast((i < 8 ? col0 : col1)[(i & 7) * kFastStride], rc[i], nz[i], dev[i >> 2]));
-      // some quotient sits next to a rounding boundary
-      if (__any(fmaxf(fmaxf(dev[0], dev[1]), fmaxf(dev[2], dev[3])) > 0.5f - kEps2)) {
+      for (int i = 0; i < 8; ++i) {
+        const bool used = wd * 8 + i < n_4;                    // an unused entry gets (0, 0), i.e. code 0
+        const int d = used ? sHiList[k16 + wd * 8 + i] : 0;
+        add_code<4>(hw, i, code_fast(sT[t * kFastStride + d], used ? sR[grp * kD + d] : 0.f,
+                                     used ? sNZ[grp * kD + d] : 0.f, dev[i >> 2]));
+      }
+      if (__any(fmaxf(dev[0], dev[1]) > 0.5f - kEps4)) {     // some quotient sits next to a rounding boundary
 #pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4) {
-          if (!__any(dev[i4] > 0.5f - kEps2)) continue;
+        for (int i4 = 0; i4 < 2; ++i4) {
+          if (!__any(dev[i4] > 0.5f - kEps4)) continue;
 #pragma unroll
           for (int i = 4 * i4; i < 4 * i4 + 4; ++i) {
-            const int t = (i < 8 ? tok0 : tok1) + (i & 7);
+            const bool used = wd * 8 + i < n_4;
+            const int d = used ? sHiList[k16 + wd * 8 + i] : 0;
             float dv = 0.f;
-            const float c = code_fast(sT[t * kFastStride + d], rc[i], nz[i], dv);
-            if (__any(dv > 0.5f - kEps2)) add_code<2>(hw, i, code_exact(sT[t * kFastStride + d], sSZ[t * NVG + vg], 3.f) - c);
+            const float c = code_fast(sT[t * kFastStride + d], used ? sR[grp * kD + d] : 0.f, used ? sNZ[grp * kD + d] : 0.f, dv);
+            if (__any(dv > 0.5f - kEps4))
+              add_code<4>(hw, i, code_exact(sT[t * kFastStride + d], used ? sSZ[grp * kD + d] : 0u, 15.f) - c);
           }
         }
       }
       const unsigned w = join_halves(hw);
-      reinterpret_cast<unsigned*>(rec + off_v)[tg * kD + d] = w;
+      reinterpret_cast<unsigned*>(rec + off_k4)[it] = w;
+    }
+    // ---- fp16 tier: [token][k16] ------------------------------------------
+    for (int i = tid >> 7; i < k16; i += 2) {
+      const int t = tid & 127;
+      if (t < R) reinterpret_cast<__half*>(rec + off_k16)[t * k16 + i] = i < n_16 ? sT[t * kFastStride + sHiList[i]] : __ushort_as_half(0);
     }
   }
+  if (!SPLIT) __syncthreads();     // the key tile makes room for the values
+
+  if (do_v) {
+    MIXKVQ_FPHASE(6)
+    // ---- values ---------------------------------------------------------------------------------
+    // The tile goes to LDS; on the way every thread reduces its 16-byte pieces (still in registers) to the minimum
+    // and maximum per token and value group: 16 threads cover a row, a group is Gv/8 neighbouring threads, and the
+    // pair (min, -max) is reduced with packed fp16 minima over DPP lane exchanges inside the row of 16.
+    {
+      const int c = tid & 15, lpg = Gv / 8;                 // lpg = 2, 4, 8 or 16 (Gv divides 128)
+      const int lpg_shift = 31 - __builtin_clz(lpg);
+      unsigned* sRow = &sChunk[0][0][0];     // [token][value group] packed (min, -max); <= 128 * 8 entries
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int row = (tid >> 4) + 16 * i;
+        if (row < R) {
+          const uint4 v = as_f16x8(vreg[i], v_pending);
+          unsigned* dst = reinterpret_cast<unsigned*>(sT + row * kFastStride + c * 8);
+          dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
+          const fh2 k0 = as_h2(v.x), k1 = as_h2(v.y), k2 = as_h2(v.z), k3 = as_h2(v.w);
+          const fh2 lo2 = __builtin_elementwise_min(__builtin_elementwise_min(k0, k1), __builtin_elementwise_min(k2, k3));
+          const fh2 hi2 = __builtin_elementwise_max(__builtin_elementwise_max(k0, k1), __builtin_elementwise_max(k2, k3));
+          fh2 m;
+          m[0] = lo2[0] < lo2[1] ? lo2[0] : lo2[1];
+          m[1] = -(hi2[0] > hi2[1] ? hi2[0] : hi2[1]);
+          int mi = __builtin_bit_cast(int, m);
+#define MIXKVQ_DPP_MIN(CTRL)                                                                                   \
+    mi = __builtin_bit_cast(int, __builtin_elementwise_min(                                                      \
+        __builtin_bit_cast(fh2, mi), __builtin_bit_cast(fh2, __builtin_amdgcn_update_dpp(mi, mi, CTRL, 0xf, 0xf, false))));
+          if (lpg >= 2) MIXKVQ_DPP_MIN(0xB1)     // quad_perm [1,0,3,2]
+          if (lpg >= 4) MIXKVQ_DPP_MIN(0x4E)     // quad_perm [2,3,0,1]
+          if (lpg >= 8) MIXKVQ_DPP_MIN(0x141)    // row_half_mirror
+          if (lpg >= 16) MIXKVQ_DPP_MIN(0x140)   // row_mirror
+#undef MIXKVQ_DPP_MIN
+          if ((c & (lpg - 1)) == 0) sRow[row * NVG + (c >> lpg_shift)] = (unsigned)mi;
+        }
+      }
+      MIXKVQ_FPHASE(7)
+      __syncthreads();
+      unsigned vmax_t = 0u;
+      for (int it = tid; it < R * NVG; it += kFlushThreads) {
+        const fh2 mm = as_h2(sRow[it]);
+        const GroupParams gp = group_params((float)mm[0], -(float)mm[1], 3.f);
+        sSZ[it] = (unsigned)gp.s16 | ((unsigned)gp.z16 << 16);
+        fast_params(gp.s, gp.z, &sR[it], &sNZ[it]);
+        vmax_t = gp.s16 > vmax_t ? gp.s16 : vmax_t;
+        reinterpret_cast<unsigned short*>(rec + off_v_s)[it] = gp.s16;
+        reinterpret_cast<unsigned short*>(rec + off_v_z)[it] = gp.z16;
+      }
+      const unsigned wmax = wave_max_u32(vmax_t);       // every lane is here: the loop above has ended for all
+      if (lane == 0) atomicMax(&sKmax[8], wmax);
+    }
+    __syncthreads();
+    if (tid == 0) reinterpret_cast<unsigned short*>(rec + off_kmax)[NG] = (unsigned short)sKmax[8];
+    MIXKVQ_FPHASE(8)
+    // value words [token group][channel], 16 codes along tokens: the 16 tokens' parameters in registers
+    {
+      const int d = tid & (kD - 1), vg = d / Gv;
+      const int ilv = cv.lay.v_interleave;
+      for (int tg = tid >> 7; tg < n_ch; tg += 2) {
+        // tokens of the word: two runs of 8 (tok0 .. tok0+7 and tok1 .. tok1+7), consecutive unless interleaved; each run
+        // gets one base address, so that the elements sit at compile-time offsets from it
+        const int tok0 = value_word_token(tg, 0, ilv), tok1 = tok0 + (ilv ? 32 : 8);
+        const __half* const col0 = sT + tok0 * kFastStride + d;
+        const __half* const col1 = sT + tok1 * kFastStride + d;
+        float rc[16], nz[16];
+        if (NVG == 1) {
+#pragma unroll
+          for (int i4 = 0; i4 < 4; ++i4) {
+            const int t4 = (i4 >> 1 ? tok1 : tok0) + 4 * (i4 & 1);
+            const float4 a = *reinterpret_cast<const float4*>(sR + t4);
+            const float4 b2 = *reinterpret_cast<const float4*>(sNZ + t4);
+            rc[4 * i4] = a.x; rc[4 * i4 + 1] = a.y; rc[4 * i4 + 2] = a.z; rc[4 * i4 + 3] = a.w;
+            nz[4 * i4] = b2.x; nz[4 * i4 + 1] = b2.y; nz[4 * i4 + 2] = b2.z; nz[4 * i4 + 3] = b2.w;
+          }
+        } else {
+          const float* const r0 = sR + tok0 * NVG + vg, * const r1 = sR + tok1 * NVG + vg;
+          const float* const z0 = sNZ + tok0 * NVG + vg, * const z1 = sNZ + tok1 * NVG + vg;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            rc[i] = (i < 8 ? r0 : r1)[(i & 7) * NVG];
+            nz[i] = (i < 8 ? z0 : z1)[(i & 7) * NVG];
+          }
+        }
+        float hw[2] = {0.f, 0.f};
+        float dev[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          add_code<2>(hw, i, code_fast((i < 8 ? col0 : col1)[(i & 7) * kFastStride], rc[i], nz[i], dev[i >> 2]));
+        // some quotient sits next to a rounding boundary
+        if (__any(fmaxf(fmaxf(dev[0], dev[1]), fmaxf(dev[2], dev[3])) > 0.5f - kEps2)) {
+#pragma unroll
+          for (int i4 = 0; i4 < 4; ++i4) {
+            if (!__any(dev[i4] > 0.5f - kEps2)) continue;
+#pragma unroll
+            for (int i = 4 * i4; i < 4 * i4 + 4; ++i) {
+              const int t = (i < 8 ? tok0 : tok1) + (i & 7);
+              float dv = 0.f;
+              const float c = code_fast(sT[t * kFastStride + d], rc[i], nz[i], dv);
+              if (__any(dv > 0.5f - kEps2)) add_code<2>(hw, i, code_exact(sT[t * kFastStride + d], sSZ[t * NVG + vg], 3.f) - c);
+            }
+          }
+        }
+        const unsigned w = join_halves(hw);
+        reinterpret_cast<unsigned*>(rec + off_v)[tg * kD + d] = w;
+      }
+    }
+  }
+  // The window's rows are read by the first block alone (wc.in_block says that the copy waits for it): by now all of
+  // them are in registers or LDS.
+  if (wc.in_block && f == 0) copy_rows(cv, k_new, v_new, st, wc, p, 0, 1, do_k, do_v);
   MIXKVQ_FPHASE(9)
 }
 
@@ -785,8 +831,22 @@ static bool force_general_flush() {
   return force;
 }
 
+// One launch of the pack kernel over nf blocks of every pair of the view (with a list: of the pairs of its sequences).
+static void launch_blocks(const CacheView& v, const __half* k_new, const __half* v_new, Strides3 kvs, int r0, int first_block,
+                          int n_pairs, int nf, const uint8_t* sel, const FlushList& list, const WindowCopy& wc, bool fast,
+                          hipStream_t s) {
+  if (!fast)
+    flush_block_kernel<<<dim3(n_pairs, nf), dim3(kFlushThreads), 0, s>>>(v, k_new, v_new, kvs, r0, first_block, sel, list);
+  else if ((int64_t)n_pairs * nf <= kSplitBlocks)
+    flush_block_fast_kernel<true><<<dim3(n_pairs, nf + wc.wgs, 2), dim3(kFlushThreads), 0, s>>>(v, k_new, v_new, kvs, r0,
+                                                                                               first_block, sel, list, wc);
+  else
+    flush_block_fast_kernel<false><<<dim3(n_pairs, nf + wc.wgs), dim3(kFlushThreads), 0, s>>>(v, k_new, v_new, kvs, r0,
+                                                                                             first_block, sel, list, wc);
+}
+
 hipError_t launch_flush(const CacheView& v, const __half* k_new, const __half* v_new, Strides3 kvs, int r0,
-                        int first_block, int n_flush, const uint8_t* sel, hipStream_t s) {
+                        int first_block, int n_flush, const uint8_t* sel, int n_rest, hipStream_t s) {
   // the throughput kernel needs 16-token chunks inside key groups, whole 16-byte pieces inside value groups and
   // 16-byte aligned rows; anything else takes the general kernel
   const bool aligned = ((reinterpret_cast<uintptr_t>(k_new) | reinterpret_cast<uintptr_t>(v_new)) & 15u) == 0 &&
@@ -794,45 +854,36 @@ hipError_t launch_flush(const CacheView& v, const __half* k_new, const __half* v
   const bool fast = aligned && v.cfg.Gk % 16 == 0 && v.cfg.Gv % 16 == 0 && !force_general_flush();
   FlushList none;
   none.n = 0;
+  // The tokens behind the last block go to the window in the same launch: in workgroups of their own when no block reads
+  // the window, by the first block when only that one does.
+  const int R = v.cfg.R, src_first = (int)((int64_t)n_flush * R - r0);
+  WindowCopy wc{0, 0, 0, 0, 0};
+  const bool fused = n_rest > 0 && fast && n_flush <= 32768 && r0 <= R;
+  if (fused) {
+    wc = WindowCopy{n_rest, src_first, v.S, 0, r0 > 0 ? 1 : 0};
+    if (r0 <= 0) wc.wgs = n_rest * 16 < 8 * kFlushThreads ? (n_rest * 16 + kFlushThreads - 1) / kFlushThreads : 8;
+  }
   // grid.y is limited to 65535 blocks per launch
   for (int f0 = 0; f0 < n_flush; f0 += 32768) {
     const int nf = n_flush - f0 < 32768 ? n_flush - f0 : 32768;
     // shift the stream origin so that block index 0 of this launch is block f0 of the call
-    if (fast)
-      flush_block_fast_kernel<<<dim3(v.P, nf), dim3(kFlushThreads), 0, s>>>(v, k_new, v_new, kvs, r0 - f0 * v.cfg.R,
-                                                                           first_block + f0, sel, none);
-    else
-      flush_block_kernel<<<dim3(v.P, nf), dim3(kFlushThreads), 0, s>>>(v, k_new, v_new, kvs, r0 - f0 * v.cfg.R,
-                                                                      first_block + f0, sel, none);
+    launch_blocks(v, k_new, v_new, kvs, r0 - f0 * R, first_block + f0, v.P, nf, sel, none, wc, fast, s);
   }
-  return hipGetLastError();
+  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  if (n_rest > 0 && !fused) return launch_residual_copy(v, k_new, v_new, kvs, src_first, v.S, n_rest, s);
+  return hipSuccess;
 }
 
 hipError_t launch_flush_windows(const CacheView& v, const FlushList& list, hipStream_t s) {
   const Strides3 unused{0, 0, 0};      // every row comes from the windows
-  const dim3 grid(list.n * v.cfg.Hkv);
-  if (v.cfg.Gk % 16 == 0 && v.cfg.Gv % 16 == 0 && !force_general_flush())
-    flush_block_fast_kernel<<<grid, dim3(kFlushThreads), 0, s>>>(v, v.res_k, v.res_v, unused, v.cfg.R, 0, nullptr, list);
-  else
-    flush_block_kernel<<<grid, dim3(kFlushThreads), 0, s>>>(v, v.res_k, v.res_v, unused, v.cfg.R, 0, nullptr, list);
+  const bool fast = v.cfg.Gk % 16 == 0 && v.cfg.Gv % 16 == 0 && !force_general_flush();
+  launch_blocks(v, v.res_k, v.res_v, unused, v.cfg.R, 0, list.n * v.cfg.Hkv, 1, nullptr, list, WindowCopy{0, 0, 0, 0, 0}, fast, s);
   return hipGetLastError();
 }
 
-// ---------------------------------------------------------------------------
-// copy into the fp16 rows: n tokens starting at new-token index src_first go to rows dst_row.. of every pair
-// (row 0 = first sink row, row S = first row of the residual window).
-// ---------------------------------------------------------------------------
 __global__ void residual_copy_kernel(CacheView cv, const __half* __restrict__ k_new, const __half* __restrict__ v_new,
-                                     Strides3 st, int src_first, int dst_row, int n) {
-  const int p = blockIdx.x, b = p / cv.cfg.Hkv, j = p % cv.cfg.Hkv;
-  for (int idx = blockIdx.y * blockDim.x + threadIdx.x; idx < n * 16; idx += gridDim.y * blockDim.x) {
-    const int t = idx >> 4, c = idx & 15;
-    const int64_t src = (int64_t)b * st.b + (int64_t)j * st.h + (int64_t)(src_first + t) * st.t + c * 8;
-    const size_t dst = ((size_t)p * cv.RW + dst_row + t) * kD + c * 8;
-    const bool bf16 = cv.cfg.in_dtype != 0;
-    *reinterpret_cast<uint4*>(cv.res_k + dst) = as_f16x8(*reinterpret_cast<const uint4*>(k_new + src), bf16);
-    *reinterpret_cast<uint4*>(cv.res_v + dst) = as_f16x8(*reinterpret_cast<const uint4*>(v_new + src), bf16);
-  }
+                                     Strides3 st, WindowCopy wc) {
+  copy_rows(cv, k_new, v_new, st, wc, blockIdx.x, blockIdx.y, gridDim.y, true, true);
 }
 
 hipError_t launch_residual_copy(const CacheView& v, const __half* k_new, const __half* v_new, Strides3 kvs,
@@ -840,7 +891,7 @@ hipError_t launch_residual_copy(const CacheView& v, const __half* k_new, const _
   const int threads = n * 16 < 256 ? 64 : 256;
   int gy = (n * 16 + threads - 1) / threads;
   if (gy > 8) gy = 8;
-  residual_copy_kernel<<<dim3(v.P, gy), dim3(threads), 0, s>>>(v, k_new, v_new, kvs, src_first, dst_row, n);
+  residual_copy_kernel<<<dim3(v.P, gy), dim3(threads), 0, s>>>(v, k_new, v_new, kvs, WindowCopy{n, src_first, dst_row, 0, 0});
   return hipGetLastError();
 }
 

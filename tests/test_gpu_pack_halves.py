@@ -1,0 +1,62 @@
+"""Small launches pack the keys and the values of a block in two workgroups and move the tokens that stay in the window in
+the same launch: in workgroups of their own when no block reads the window, by the first block when that one does.
+Records, window rows and counts are compared byte for byte with the oracle, on either side of both rules (blocks per
+launch, tokens waiting in the window, blocks of two records)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def H():
+    import gpu_common
+    return gpu_common
+
+
+@pytest.mark.parametrize("kw", [
+    dict(Gk=128, Gv=128, R=128, k4=16, k16=0),
+    dict(Gk=32, Gv=32, R=128, k4=8, k16=4, policy=1, tau16=1.5, tau4=0.3),
+    dict(Gk=128, Gv=64, R=256, k4=8, k16=0),          # two records per block
+    dict(Gk=32, Gv=32, R=32, k4=8, k16=0, in_dtype=0, sink=32),
+])
+@pytest.mark.parametrize("first", [0, 1, 100, 128, 200])      # tokens in the cache before
+@pytest.mark.parametrize("n", [29, 129, 385])                 # tokens of the call
+def test_append_onto_a_window(H, kw, first, n):
+    kw = dict(B=2, Hq=4, Hkv=2, D=128, T_max=1024, **kw)
+    oc, gc = H.make_pair(**kw)
+    rng = np.random.default_rng(first * 1000 + n)
+    K = (rng.standard_normal((2, 2, first + n, 128)) * rng.uniform(0.3, 9, 128)).astype(np.float16)
+    V = rng.standard_normal((2, 2, first + n, 128)).astype(np.float16)
+    Q = rng.standard_normal((2, 4, 3, 128)).astype(np.float16)
+    gc.select_channels(H.dev(Q), H.dev(K))
+    oc.select_channels(Q, K)
+    for a, b in ((0, first), (first, first + n)):
+        if b > a:
+            gc.quantize_append(H.dev(K[:, :, a:b]), H.dev(V[:, :, a:b]))
+            oc.append(K[:, :, a:b], V[:, :, a:b])
+    H.check_state(oc, gc)
+
+
+@pytest.mark.parametrize("blocks", [2047, 2048, 2049])
+def test_both_forms_give_the_same_records(H, blocks):
+    """One pair, more blocks than any oracle run is worth: records of a launch just above the line against records of
+    the same tokens appended in pieces far below it."""
+    import torch
+    import paper_2512_19206_amd as M
+    kw = dict(B=1, Hq=2, Hkv=1, D=128, T_max=(blocks + 1) * 32, Gk=32, Gv=128, R=32, k4=8, k16=0)
+    gen = torch.Generator(device="cuda").manual_seed(blocks)
+    n = blocks * 32 + 5
+    k = (torch.randn((1, 1, n, 128), generator=gen, device="cuda") * 3).half()
+    v = torch.randn((1, 1, n, 128), generator=gen, device="cuda").half()
+    caches = [M.Cache(M.make_config(**kw)) for _ in range(2)]
+    q = torch.cat((k[:, :, :300], v[:, :, :300]), dim=1)
+    sel = [c.select_channels(q, k) for c in caches]
+    assert torch.equal(sel[0], sel[1])
+    caches[0].quantize_append(k, v, sel=sel[0])
+    for t in range(0, n, 1000):
+        caches[1].quantize_append(k[:, :, t:t + 1000], v[:, :, t:t + 1000], sel=sel[1])
+    assert caches[0].state() == caches[1].state() == (blocks * 32, 5)
+    assert torch.equal(caches[0].block_records()[:, :blocks], caches[1].block_records()[:, :blocks])
+    for a, b in zip(caches[0].residual(), caches[1].residual()):
+        assert torch.equal(a[:, :5], b[:, :5])
