@@ -210,6 +210,7 @@ static bool decode_counts(const mixkvq_cache* c, int* n_blocks, int* n_fp16, Seq
   *n_blocks = mb;
   *n_fp16 = mf;
   sc->enabled = lock_step(c) ? 0 : 1;
+  sc->n_units = 0;
   if (sc->enabled) {
     if (cfg.B > kMaxRaggedB) return false;
     for (int b = 0; b < cfg.B; ++b) {

@@ -305,8 +305,19 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
             off_kmax = cv.lay.off_kmax, off_klo = cv.lay.off_klo, off_k4 = cv.lay.off_k4, off_k16 = cv.lay.off_k16, off_v = cv.lay.off_v,
             off_v_s = cv.lay.off_v_s;
   const unsigned char* const blocks = cv.blocks;
-  const int p = blockIdx.x, split = blockIdx.y, tid = threadIdx.x;
-  const int b = p / Hkv, jkv = p % Hkv;
+  const int tid = threadIdx.x;
+  int p = blockIdx.x, split = blockIdx.y, part0 = p * n_splits;     // part0: first partial of the pair
+  int b = p / Hkv;
+  if (sc.n_units) {      // grid (KV heads, units): the sequences have workgroups by their lengths
+    const int u = blockIdx.y;
+    b = (int)(sc.owner[u >> 2] >> (8 * (u & 3)) & 0xffu);
+    const unsigned span = sc.span[b];
+    n_splits = (int)(span >> 16);
+    split = u - (int)(span & 0xffffu);
+    part0 = (int)(span & 0xffffu) * Hkv + p * n_splits;
+    p += b * Hkv;
+  }
+  const int jkv = p - b * Hkv;
   bool skip_pair = false;
   if (sc.enabled) {      // sequences of different lengths: this pair's own counts; a sequence without tokens is skipped
     n_blocks = sc.n_blocks[b];
@@ -1223,7 +1234,7 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
   // one thread per (head, four channels)
   const int eh = tid >> 5, c4 = tid & 31;
   const size_t bh = (size_t)b * Hq + (size_t)jkv * g + eh;
-  float* const pair = part + (size_t)p * n_splits * g * kPartStrideM;
+  float* const pair = part + (size_t)part0 * g * kPartStrideM;
   if (eh < g) {
     const float* r0 = reinterpret_cast<const float*>(smem + kHdrLds);
     constexpr int kWaveF = kWaveLds / 4;
@@ -1293,14 +1304,15 @@ static hipError_t launch_one(const CacheView& v, const __half* q, float scale, i
     if (e != hipSuccess) return e;
     attr_set.fetch_or(bit, std::memory_order_release);
   }
+  const dim3 grid = sc.n_units ? dim3(v.cfg.Hkv, sc.n_units) : dim3(v.P, n_splits);
   // the partials in the cache's workspace come with tickets for the merge; any other buffer takes the merge launch
   u64_t* tickets = part == reinterpret_cast<float*>(v.ws) ? v.qcnt : nullptr;
   if (ev_start && ev_stop) {
     // profiling aid: the two events take the start and the end time of this kernel itself (not of the launch call)
-    hipExtLaunchKernelGGL(kern, dim3(v.P, n_splits), dim3(kMfmaThreads), (uint32_t)lds, s, ev_start, ev_stop, 0u, v, q,
+    hipExtLaunchKernelGGL(kern, grid, dim3(kMfmaThreads), (uint32_t)lds, s, ev_start, ev_stop, 0u, v, q,
                           scale, n_blocks, n_res, n_splits, part, accumulate_q, nt, sc, tickets, out, lse);
   } else {
-    kern<<<dim3(v.P, n_splits), dim3(kMfmaThreads), lds, s>>>(v, q, scale, n_blocks, n_res, n_splits, part, accumulate_q, nt, sc,
+    kern<<<grid, dim3(kMfmaThreads), lds, s>>>(v, q, scale, n_blocks, n_res, n_splits, part, accumulate_q, nt, sc,
                                                              tickets, out, lse);
   }
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;

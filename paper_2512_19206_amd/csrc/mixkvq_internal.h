@@ -28,10 +28,16 @@ struct NewToken { const __half* k; const __half* v; Strides3 st; };
 // Token counts per sequence for batches whose sequences differ in length, passed by value to the decode kernels
 // (enabled == 0: every sequence has the counts given as scalar arguments).
 constexpr int kMaxRaggedB = 256;
+constexpr int kMaxUnits = 512;
 struct SeqCounts {
   int32_t enabled;
   int32_t n_blocks[kMaxRaggedB];      // quantized blocks of sequence b
   uint16_t n_fp16[kMaxRaggedB];       // its fp16 rows in use (sink + residual window)
+  // How the matrix-core kernel's workgroups are dealt to the sequences (n_units == 0: every sequence takes the launch's
+  // n_splits).  A unit is one workgroup per KV head; the units of a sequence are consecutive.
+  int32_t n_units;
+  uint32_t span[kMaxRaggedB];         // first unit of the sequence | its units << 16
+  uint32_t owner[kMaxUnits / 4];      // sequence of unit u: byte u % 4 of word u / 4
 };
 
 // Sequences whose full window one launch of the pack kernel quantizes, passed by value (n == 0: every sequence of the
@@ -104,7 +110,7 @@ hipError_t launch_residual_copy(const CacheView& v, const __half* k_new, const _
 // With sc != nullptr (sequences of different lengths) n_blocks and n_fp16 are the largest counts of the batch, a
 // sequence without tokens is skipped (output 0, lse -inf), and a new token (nt) goes to the last fp16 row in use.
 hipError_t launch_decode(const CacheView& v, const __half* q, __half* out, float* lse, float scale,
-                         int n_blocks, int n_fp16, int accumulate_q, NewToken nt, const SeqCounts* sc, hipStream_t s,
+                         int n_blocks, int n_fp16, int accumulate_q, NewToken nt, SeqCounts* sc, hipStream_t s,
                          hipEvent_t ev_start, hipEvent_t ev_stop, int* path,   // *path: MIXKVQ_PATH_* of the launch
                          float* part = nullptr);   // split-K partials; nullptr: the cache's workspace
 // bytes of split-K partials that launch would write
