@@ -193,14 +193,14 @@ __device__ __forceinline__ void tier_sizes(const mixkvq_config& cfg, int c16, in
   }
 }
 
-// Tier (2: fp16, 1: 4 bit, 0: 2 bit) of channel tid in threads 0..127 of a workgroup of 256 (0 in the others), from the
+// Tier (2: fp16, 1: 4 bit, 0: 2 bit) of channel tid in threads 0..127 of a workgroup of 256 or more (0 in the others), from the
 // 128 scores sA (16-byte aligned) and the pair's token count: the rank of a channel is the number of channels that beat it
 // (higher score, or equal score and lower index).  The two halves of the workgroup compare against 64 channels each, with
 // the loop unrolled so that the LDS reads run ahead of the compares (as a plain loop with the threshold counts in it, one
 // LDS latency per channel, this took 6.6 us of the 19 us of a pack workgroup).  sPart: 256 words.
 __device__ __forceinline__ int rank_channels(const mixkvq_config& cfg, unsigned long long count, const double* sA,
                                              unsigned* sPart) {
-  const int tid = threadIdx.x, d = tid & (kD - 1), e0 = (tid >> 7) * (kD / 2);
+  const int tid = threadIdx.x, d = tid & (kD - 1), e0 = (tid >> 7 & 1) * (kD / 2);
   const double Ad = sA[d];
   int rank = 0;
   const double2* row = reinterpret_cast<const double2*>(sA + e0);
@@ -218,7 +218,7 @@ __device__ __forceinline__ int rank_channels(const mixkvq_config& cfg, unsigned 
     c16 = __popcll(__ballot(Ad > thr16));
     c_any = __popcll(__ballot(Ad > thr16 || Ad > thr4));
   }
-  sPart[tid] = (unsigned)rank | ((unsigned)c16 << 8) | ((unsigned)c_any << 16);     // rank, c16, c_any <= 64 each
+  if (tid < 2 * kD) sPart[tid] = (unsigned)rank | ((unsigned)c16 << 8) | ((unsigned)c_any << 16);     // rank, c16, c_any <= 64 each
   __syncthreads();
   if (tid >= kD) return 0;
   const unsigned mine = sPart[tid], other = sPart[tid ^ 64];                       // the two wavefronts with the channels

@@ -14,6 +14,7 @@
 namespace mixkvq {
 
 constexpr int kFlushThreads = 256;
+constexpr int64_t kWideBlocks = 128;       // up to this many records of 128 tokens per launch the workgroups have 512 threads
 constexpr int64_t kSplitBlocks = 2048;     // up to this many blocks per launch the keys and the values of a block are two workgroups
 constexpr int kRowPad = 8;                 // halfs of padding per LDS row (keeps 16-byte alignment)
 constexpr int kRowStride = kD + kRowPad;   // 136 halfs = 272 bytes
@@ -383,9 +384,13 @@ __device__ __forceinline__ uint4 load_chunk(const __half* res_p, const __half* f
 // times over the fused form is the better one: it overlaps the keys' arithmetic with the values' loads.  Fused / split at
 // R = G = 128 and 12 fp16 channels: 32 to 256 blocks 13.1-13.9 / 8.8-9.2 us, 512: 16.9 / 16.8, 1 024: 31.3 / 28.1, 2 048:
 // 49.5 / 47.7, 3 072: 66.8 / 67.5, 4 096: 93.0 / 96.7.
+// NT: 512 threads halve the serial work of a phase, but one such workgroup fills a compute unit (registers, LDS), so only
+// where the grid is at most one per unit: 256 / 512 threads at 128-token records with 16 4-bit channels 8.0 / 7.7 us at 32
+// blocks, 8.8 / 8.2 at 128, 8.7 / 10.6 at 160; scored under thresholds, groups of 32: 13.0 / 12.2, 13.3 / 12.4, 13.5 / 12.7
+// and 13.5 / 15.2 at 192.  Records of 64 or 32 tokens gain nothing (6.8 / 6.7, 6.6 / 6.9 at 64 blocks).
 // Rows blockIdx.y >= gridDim.y - wc.wgs copy the tokens that stay behind in the window (WindowCopy).
-template <bool SPLIT>
-__global__ void __launch_bounds__(kFlushThreads, 3)   // three workgroups per CU (LDS) = three wavefronts per SIMD
+template <bool SPLIT, int NT>
+__global__ void __launch_bounds__(NT, NT == 256 ? 3 : 2)   // 256: three workgroups per CU (LDS) = three wavefronts per SIMD; 512: one
 flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __half* __restrict__ v_new, Strides3 st,
                         int r0, int first_block, const uint8_t* __restrict__ sel_in, FlushList list, WindowCopy wc) {
   const bool do_k = !SPLIT || blockIdx.z == 0, do_v = !SPLIT || blockIdx.z == 1;
@@ -428,7 +433,8 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
   MIXKVQ_FPHASE(0)
   // ---- the key tile first; the value tile is requested once the keys are staged in LDS, so that the wait for the
   //      keys is a wait for 32 KiB and the values arrive while the keys are encoded ------------------------------
-  uint4 vreg[8];
+  constexpr int kPieces = kMaxR * 16 / NT, kRows = NT / 16;     // 16-byte pieces a thread stages, rows between them
+  uint4 vreg[kPieces];
   const int64_t pair_off = (int64_t)(p / Hkv) * st.b + (int64_t)(p % Hkv) * st.h;
   const __half* res_kp = window_rows(cv, cv.res_k, p);
   const __half* res_vp = window_rows(cv, cv.res_v, p);
@@ -441,23 +447,30 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
   const int64_t first = (int64_t)(from_res ? pos0 : pos0 - r0) + (tid >> 4);
   const bool v_pending = one_place && bf16 && !from_res;     // the value tile in registers still holds bfloat16
   if (tid < 9) sKmax[tid] = 0u;
+  // what decides the tiers is asked for ahead of the tile: the given channels, or the |q| sums and their count
+  const bool scored = do_k && sel_in == nullptr && ks > 0;
+  unsigned given = MIXKVQ_NO_CHANNEL;
+  unsigned long long qsum = 0ull, qcount = 0ull;
+  if (do_k && sel_in && tid < ks) given = sel_in[(size_t)p * ks + tid];
+  if (scored && !score_mode && tid < kD) qsum = cv.qacc[(size_t)p * kD + tid];
+  if (scored && policy == 1) qcount = cv.qcnt[p];
   if (do_k) {
-    uint4 kreg[8];
+    uint4 kreg[kPieces];
     if (one_place) {
       const __half* kp = (from_res ? res_kp : k_new + pair_off) + first * row_stride + (tid & 15) * 8;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
+      for (int i = 0; i < kPieces; ++i) {
         kreg[i] = make_uint4(0u, 0u, 0u, 0u);
-        if (tid + kFlushThreads * i < n_chunks16) kreg[i] = *reinterpret_cast<const uint4*>(kp + 16 * i * row_stride);
+        if (tid + NT * i < n_chunks16) kreg[i] = *reinterpret_cast<const uint4*>(kp + kRows * i * row_stride);
       }
       if (bf16 && !from_res) {     // rows of the caller's bfloat16 tensors enter as binary16 (the values when they are staged)
 #pragma unroll
-        for (int i = 0; i < 8; ++i) kreg[i] = as_f16x8(kreg[i], true);
+        for (int i = 0; i < kPieces; ++i) kreg[i] = as_f16x8(kreg[i], true);
       }
     } else {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int idx = tid + kFlushThreads * i;
+      for (int i = 0; i < kPieces; ++i) {
+        const int idx = tid + NT * i;
         kreg[i] = make_uint4(0u, 0u, 0u, 0u);
         if (idx < n_chunks16) kreg[i] = load_chunk(res_kp, k_new + pair_off, st.t, r0, pos0, idx, bf16);
       }
@@ -465,12 +478,12 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
     // zero the small planes of the record (index bytes, tails of the scale/zero planes)
     // (under the threshold policy the channel lists start out as "no channel")
     // (the kmax plane is written whole further down: its entry [NG] belongs to the values)
-    for (int i = tid; i < off_klo / 4; i += kFlushThreads)
+    for (int i = tid; i < off_klo / 4; i += NT)
       if (i < off_kmax / 4 || i >= off_klo_s / 4)
         reinterpret_cast<unsigned*>(rec)[i] = (policy == 1 && i < ks / 4) ? 0xffffffffu : 0u;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int idx = tid + kFlushThreads * i;
+    for (int i = 0; i < kPieces; ++i) {
+      const int idx = tid + NT * i;
       if (idx < n_chunks16) {
         unsigned* dst = reinterpret_cast<unsigned*>(sT + (idx >> 4) * kFastStride + (idx & 15) * 8);
         dst[0] = kreg[i].x; dst[1] = kreg[i].y; dst[2] = kreg[i].z; dst[3] = kreg[i].w;
@@ -481,14 +494,14 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
     if (one_place) {
       const __half* vp = (from_res ? res_vp : v_new + pair_off) + first * row_stride + (tid & 15) * 8;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
+      for (int i = 0; i < kPieces; ++i) {
         vreg[i] = make_uint4(0u, 0u, 0u, 0u);
-        if (tid + kFlushThreads * i < n_chunks16) vreg[i] = *reinterpret_cast<const uint4*>(vp + 16 * i * row_stride);
+        if (tid + NT * i < n_chunks16) vreg[i] = *reinterpret_cast<const uint4*>(vp + kRows * i * row_stride);
       }
     } else {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int idx = tid + kFlushThreads * i;
+      for (int i = 0; i < kPieces; ++i) {
+        const int idx = tid + NT * i;
         vreg[i] = make_uint4(0u, 0u, 0u, 0u);
         if (idx < n_chunks16) vreg[i] = load_chunk(res_vp, v_new + pair_off, st.t, r0, pos0, idx, bf16);
       }
@@ -502,7 +515,7 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
     {
       const int d2 = tid & 63;
       const unsigned* sT32 = reinterpret_cast<const unsigned*>(sT);
-      for (int ch = tid >> 6; ch < n_ch; ch += 4) {
+      for (int ch = tid >> 6; ch < n_ch; ch += NT / 64) {
         fh2 lo = as_h2(sT32[(16 * ch) * (kFastStride / 2) + d2]), hi = lo;
 #pragma unroll
         for (int t = 1; t < 16; ++t) {
@@ -518,7 +531,7 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
 
     MIXKVQ_FPHASE(2)
     // ---- channel tiers ------------------------------------------------------------------------
-    if (sel_in == nullptr && ks > 0) {
+    if (scored) {
       double A = 0.0;
       if (tid < kD) {
         const _Float16* cl = reinterpret_cast<const _Float16*>(&sCLo[0][0]);
@@ -530,20 +543,17 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
           hi = b2 > hi ? b2 : hi;
         }
         const long long rng = fix24(h_bits(hi)) - fix24(h_bits(lo));
-        A = score_mode ? (double)rng : (double)cv.qacc[(size_t)p * kD + tid] * (double)rng;
+        A = score_mode ? (double)rng : (double)qsum * (double)rng;
         sA[tid] = A;
       }
       __syncthreads();
       // (sR is not yet in use)
-      const int tier = rank_channels(cv.cfg, policy == 1 ? cv.qcnt[p] : 0ull, sA, reinterpret_cast<unsigned*>(sR));
+      const int tier = rank_channels(cv.cfg, qcount, sA, reinterpret_cast<unsigned*>(sR));
       if (tid < kD) sTier[tid] = (unsigned char)tier;
     } else {
       if (tid < kD) sTier[tid] = 0;
       __syncthreads();
-      if (tid < ks) {
-        const unsigned ch = sel_in[(size_t)p * ks + tid];
-        if (ch < (unsigned)kD) sTier[ch] = tid < k16 ? 2 : 1;     // MIXKVQ_NO_CHANNEL: an unused entry
-      }
+      if (given < (unsigned)kD) sTier[given] = tid < k16 ? 2 : 1;     // MIXKVQ_NO_CHANNEL: an unused entry
     }
     __syncthreads();
     // position of every channel inside its tier: ballots over the two wavefronts that hold the channels
@@ -583,7 +593,7 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
       const int cpg = Gk / 16;     // chunks per group
       // (a wavefront's 64 items of one pass belong to one group: its largest scale is reduced over the wavefront first,
       //  one LDS atomic per wavefront and pass)
-      for (int it = tid; it < NG * kD; it += kFlushThreads) {
+      for (int it = tid; it < NG * kD; it += NT) {
         const int grp = it / kD, d = it % kD;
         const unsigned char tier = sTier[d];
         unsigned s16v = 0u;
@@ -619,7 +629,11 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
     // ---- 2-bit key words [token][Wlo]: thread = (word column, token lane); the 16 channels of the column
     //      and their parameters stay in registers ---------------------------------------------------------
     {
-      const int wd = tid & 7, tl = tid >> 3;
+      // with 512 threads the two halves of the workgroup take alternate groups, or alternate runs of 32 tokens of the only one
+      const int wd = tid & 7, half = NT == 512 ? tid >> 8 : 0;
+      const bool by_group = NT == 512 && NG > 1;
+      const int tl = (tid >> 3 & 31) + (NT == 512 && !by_group ? 32 * half : 0);
+      const int t_step = NT == 512 && !by_group ? 64 : 32;
       if (wd < Wlo) {
         int doff[16];
 #pragma unroll
@@ -627,7 +641,7 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
           const int jj = 16 * wd + i;
           doff[i] = jj < n_lo ? (int)sLoList[jj] : -1;
         }
-        for (int grp = 0; grp < NG; ++grp) {
+        for (int grp = by_group ? half : 0; grp < NG; grp += by_group ? 2 : 1) {
           float rc[16], nz[16];
 #pragma unroll
           for (int i = 0; i < 16; ++i) {
@@ -635,21 +649,21 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
             rc[i] = doff[i] < 0 ? 0.f : sR[grp * kD + d];   // (0, 0) gives code 0: the padding of the last word
             nz[i] = doff[i] < 0 ? 0.f : sNZ[grp * kD + d];
           }
-          // LDS address of each of the 16 elements in this thread's first token of the group; its other tokens are 32
-          // rows further each, a compile-time distance once the loop is unrolled (no address arithmetic per element)
+          // LDS address of each of the 16 elements in this thread's first token of the group; its other tokens are t_step
+          // rows further each (256 threads: a compile-time distance once the loop is unrolled, no address arithmetic)
           const __half* col[16];
 #pragma unroll
           for (int i = 0; i < 16; ++i) col[i] = sT + (grp * Gk + tl) * kFastStride + (doff[i] < 0 ? 0 : doff[i]);
-          const int n_it = (Gk - tl + 31) / 32;      // tokens tl, tl + 32, ... below Gk: at most 4 (Gk <= 128)
+          const int n_it = tl < Gk ? (Gk - tl + t_step - 1) / t_step : 0;      // tokens tl, tl + t_step, ... below Gk (Gk <= 128)
 #pragma unroll
-          for (int k = 0; k < kMaxR / 32; ++k) {
+          for (int k = 0; k < (NT == 512 ? 2 : kMaxR / 32); ++k) {
             if (k >= n_it) break;
-            const int t = grp * Gk + tl + 32 * k;
+            const int t = grp * Gk + tl + t_step * k;
             float hw[2] = {0.f, 0.f};
             float dev[4] = {0.f, 0.f, 0.f, 0.f};     // per run of four codes: the search below stays short
 #pragma unroll
             for (int i = 0; i < 16; ++i)
-              add_code<2>(hw, i, code_fast(col[i][k * 32 * kFastStride], rc[i], nz[i], dev[i >> 2]));
+              add_code<2>(hw, i, code_fast(col[i][k * t_step * kFastStride], rc[i], nz[i], dev[i >> 2]));
             // some quotient sits next to a rounding boundary (exact ties are common: about every other pass has one)
             if (__any(fmaxf(fmaxf(dev[0], dev[1]), fmaxf(dev[2], dev[3])) > 0.5f - kEps2)) {
 #pragma unroll
@@ -658,7 +672,7 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
 #pragma unroll
                 for (int i = 4 * i4; i < 4 * i4 + 4; ++i) {     // find the codes concerned and correct them
                   const int d = doff[i] < 0 ? 0 : doff[i];
-                  const __half x = col[i][k * 32 * kFastStride];
+                  const __half x = col[i][k * t_step * kFastStride];
                   float dv = 0.f;
                   const float c = code_fast(x, rc[i], nz[i], dv);
                   if (__any(dv > 0.5f - kEps2))
@@ -674,8 +688,8 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
     }
     MIXKVQ_FPHASE(5)
     // ---- 4-bit key words: [token][k4/8] -------------------------------------
-    // (a thread keeps its token; the two halves of the workgroup alternate over the words: no divisions by run-time values)
-    for (int wd = tid >> 7; wd < W4; wd += 2) {
+    // (a thread keeps its token; the runs of 128 threads alternate over the words: no divisions by run-time values)
+    for (int wd = tid >> 7; wd < W4; wd += NT / 128) {
       const int t = tid & 127;
       if (t >= R) break;
       const int grp = t / Gk, it = t * W4 + wd;
@@ -707,7 +721,7 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
       reinterpret_cast<unsigned*>(rec + off_k4)[it] = w;
     }
     // ---- fp16 tier: [token][k16] ------------------------------------------
-    for (int i = tid >> 7; i < k16; i += 2) {
+    for (int i = tid >> 7; i < k16; i += NT / 128) {
       const int t = tid & 127;
       if (t < R) reinterpret_cast<__half*>(rec + off_k16)[t * k16 + i] = i < n_16 ? sT[t * kFastStride + sHiList[i]] : __ushort_as_half(0);
     }
@@ -725,8 +739,8 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
       const int lpg_shift = 31 - __builtin_clz(lpg);
       unsigned* sRow = &sChunk[0][0][0];     // [token][value group] packed (min, -max); <= 128 * 8 entries
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int row = (tid >> 4) + 16 * i;
+      for (int i = 0; i < kPieces; ++i) {
+        const int row = (tid >> 4) + kRows * i;
         if (row < R) {
           const uint4 v = as_f16x8(vreg[i], v_pending);
           unsigned* dst = reinterpret_cast<unsigned*>(sT + row * kFastStride + c * 8);
@@ -752,7 +766,7 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
       MIXKVQ_FPHASE(7)
       __syncthreads();
       unsigned vmax_t = 0u;
-      for (int it = tid; it < R * NVG; it += kFlushThreads) {
+      for (int it = tid; it < R * NVG; it += NT) {
         const fh2 mm = as_h2(sRow[it]);
         const GroupParams gp = group_params((float)mm[0], -(float)mm[1], 3.f);
         sSZ[it] = (unsigned)gp.s16 | ((unsigned)gp.z16 << 16);
@@ -771,7 +785,7 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
     {
       const int d = tid & (kD - 1), vg = d / Gv;
       const int ilv = cv.lay.v_interleave;
-      for (int tg = tid >> 7; tg < n_ch; tg += 2) {
+      for (int tg = tid >> 7; tg < n_ch; tg += NT / 128) {
         // tokens of the word: two runs of 8 (tok0 .. tok0+7 and tok1 .. tok1+7), consecutive unless interleaved; each run
         // gets one base address, so that the elements sit at compile-time offsets from it
         const int tok0 = value_word_token(tg, 0, ilv), tok1 = tok0 + (ilv ? 32 : 8);
@@ -837,11 +851,14 @@ static void launch_blocks(const CacheView& v, const __half* k_new, const __half*
                           hipStream_t s) {
   if (!fast)
     flush_block_kernel<<<dim3(n_pairs, nf), dim3(kFlushThreads), 0, s>>>(v, k_new, v_new, kvs, r0, first_block, sel, list);
+  else if (v.cfg.R == kMaxR && (int64_t)n_pairs * nf <= kWideBlocks)
+    flush_block_fast_kernel<true, 512><<<dim3(n_pairs, nf + wc.wgs, 2), dim3(512), 0, s>>>(v, k_new, v_new, kvs, r0, first_block,
+                                                                                          sel, list, wc);
   else if ((int64_t)n_pairs * nf <= kSplitBlocks)
-    flush_block_fast_kernel<true><<<dim3(n_pairs, nf + wc.wgs, 2), dim3(kFlushThreads), 0, s>>>(v, k_new, v_new, kvs, r0,
+    flush_block_fast_kernel<true, 256><<<dim3(n_pairs, nf + wc.wgs, 2), dim3(kFlushThreads), 0, s>>>(v, k_new, v_new, kvs, r0,
                                                                                                first_block, sel, list, wc);
   else
-    flush_block_fast_kernel<false><<<dim3(n_pairs, nf + wc.wgs), dim3(kFlushThreads), 0, s>>>(v, k_new, v_new, kvs, r0,
+    flush_block_fast_kernel<false, 256><<<dim3(n_pairs, nf + wc.wgs), dim3(kFlushThreads), 0, s>>>(v, k_new, v_new, kvs, r0,
                                                                                              first_block, sel, list, wc);
 }
 

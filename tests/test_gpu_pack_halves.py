@@ -60,3 +60,26 @@ def test_both_forms_give_the_same_records(H, blocks):
     assert torch.equal(caches[0].block_records()[:, :blocks], caches[1].block_records()[:, :blocks])
     for a, b in zip(caches[0].residual(), caches[1].residual()):
         assert torch.equal(a[:, :5], b[:, :5])
+
+
+@pytest.mark.parametrize("per_pair", [15, 16, 17])      # 120, 128 and 136 records in a launch of 8 pairs
+@pytest.mark.parametrize("kw", [
+    dict(Gk=128, Gv=128, R=128, k4=16, k16=0),
+    dict(Gk=64, Gv=64, R=128, k4=0, k16=12),
+    dict(Gk=16, Gv=16, R=128, k4=24, k16=4),
+    dict(Gk=32, Gv=32, R=128, k4=16, k16=8, policy=1, tau16=1.5, tau4=0.3),
+])
+def test_both_widths_give_the_same_records(H, kw, per_pair):
+    """Records of one launch around the line between workgroups of 512 and of 256 threads against the oracle's."""
+    kw = dict(B=2, Hq=8, Hkv=4, D=128, T_max=(per_pair + 1) * 128, **kw)
+    oc, gc = H.make_pair(**kw)
+    rng = np.random.default_rng(per_pair)
+    n = per_pair * 128 + 3
+    K = (rng.standard_normal((2, 4, n, 128)) * rng.uniform(0.3, 9, 128)).astype(np.float16)
+    V = rng.standard_normal((2, 4, n, 128)).astype(np.float16)
+    Q = rng.standard_normal((2, 8, 3, 128)).astype(np.float16)
+    sel, ref = gc.select_channels(H.dev(Q), H.dev(K)), oc.select_channels(Q, K)
+    scored = kw.get("policy", 0) == 1
+    gc.quantize_append(H.dev(K), H.dev(V), sel=None if scored else sel)
+    oc.append(K, V, None if scored else ref)
+    H.check_state(oc, gc)
