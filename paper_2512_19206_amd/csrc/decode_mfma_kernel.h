@@ -306,7 +306,7 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
             off_v_s = cv.lay.off_v_s;
   const unsigned char* const blocks = cv.blocks;
   const int tid = threadIdx.x;
-  int p = blockIdx.x, split = blockIdx.y;
+  int p = blockIdx.x, split = blockIdx.y, part0 = p * n_splits;     // part0: first partial of the pair
   int b = p / Hkv;
   if (sc.n_units) {      // grid (KV heads, units): the sequences have workgroups by their lengths
     const int u = blockIdx.y;
@@ -314,6 +314,7 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
     const unsigned span = sc.span[b];
     n_splits = (int)(span >> 16);
     split = u - (int)(span & 0xffffu);
+    part0 = (int)(span & 0xffffu) * Hkv + p * n_splits;
     p += b * Hkv;
   }
   const int jkv = p - b * Hkv;
@@ -1231,14 +1232,14 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
   }
   __syncthreads();
   // one thread per (head, four channels)
-  // (formed from a copy the compiler cannot see through: as common subexpressions with the q staging both would occupy
-  // registers across the record loop)
+  // (the variants without registers to spare form these, and the pair's first partial, from a copy the compiler cannot see
+  // through: as common subexpressions with the q staging they would live across the record loop, where one of these
+  // variants then spilled: 305 instead of 278 us per step at 64 x 16 390 tokens; the others are up to 1 % faster without)
   int tid_e = tid;
-  asm volatile("" : "+v"(tid_e));
+  if constexpr (kLeanConstants) asm volatile("" : "+v"(tid_e));
   const int eh = tid_e >> 5, c4 = tid_e & 31;
   const size_t bh = (size_t)b * Hq + (size_t)jkv * g + eh;
-  // first partial of the pair (formed only here: nothing more is kept across the record loop for it)
-  const int part0 = sc.n_units ? (int)(sc.span[b] & 0xffffu) * Hkv + jkv * n_splits : p * n_splits;
+  if constexpr (kLeanConstants) part0 = sc.n_units ? (int)(sc.span[b] & 0xffffu) * Hkv + jkv * n_splits : p * n_splits;
   float* const pair = part + (size_t)part0 * g * kPartStrideM;
   if (eh < g) {
     const float* r0 = reinterpret_cast<const float*>(smem + kHdrLds);
