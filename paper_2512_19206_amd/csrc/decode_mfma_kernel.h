@@ -43,7 +43,7 @@ constexpr int kVMetaMax = 2048;                 // value scales + zero-points of
 constexpr int kQsStride = 168;                  // halfs per head row of the slot-ordered q table (160 slots + padding)
 constexpr int kQsBytes = 8 * kQsStride * 2;
 constexpr int kWaveLds = kKPartMax + kVMetaMax + 256 + kQsBytes;   // + a spare 256 bytes + slot-ordered q
-constexpr int kHdrLds = 2048 + 256 + 2048 + 2048;   // normalised q [8][128], exponents and wave maxima, q transposed [128][8], raw q [8][128]
+constexpr int kHdrLds = 2048 + 256 + 2048;      // q as given [8][128], exponents and wave maxima, normalised q transposed [128][8]
 constexpr int kPartStrideM = kD + 2;
 constexpr int kPBoost = 8;                      // softmax weights go to the matrix cores as p * 2^kPBoost (see mfma_part)
 constexpr unsigned kBigScale = 0x5BF8u;         // fp16 255: the largest value scale for which p' * s cannot overflow
@@ -339,10 +339,9 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
   const int head = n & 7, role = n >> 3;     // role 0: head of q*s, role 1: tail
   const bool live = head < g;
 
-  __half* sQn = reinterpret_cast<__half*>(smem);                   // [8][128] normalised q
+  unsigned short* sQraw = reinterpret_cast<unsigned short*>(smem);   // [8][128] q as given, in binary16
   int* sEq = reinterpret_cast<int*>(smem + 2048);                   // [8] exponents
-  __half* sQt = reinterpret_cast<__half*>(smem + 2048 + 256);       // [128][8]: the 8 heads of a channel in 16 bytes
-  unsigned short* sQraw = reinterpret_cast<unsigned short*>(smem + 2048 + 256 + 2048);   // [8][128] q as given
+  __half* sQt = reinterpret_cast<__half*>(smem + 2048 + 256);       // normalised q [128][8]: the 8 heads of a channel in 16 bytes
   unsigned char* wbase = smem + kHdrLds + wave * kWaveLds;           // this wave's private region
   unsigned char* sK = wbase;                                        // record bytes [0, NKL KiB)
   unsigned char* sVm = wbase + kKPartMax;                           // v_s, v_z planes
@@ -688,8 +687,7 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
     uint2 qn;
     qn.x = cvt_pk(ldexpf(v[0], -eq), ldexpf(v[1], -eq));
     qn.y = cvt_pk(ldexpf(v[2], -eq), ldexpf(v[3], -eq));
-    *reinterpret_cast<uint2*>(sQn + h * kD + l32 * 4) = qn;
-    if (accumulate_q) *reinterpret_cast<uint2*>(sQraw + h * kD + l32 * 4) = qraw;
+    *reinterpret_cast<uint2*>(sQraw + h * kD + l32 * 4) = qraw;
     unsigned short* qt = reinterpret_cast<unsigned short*>(sQt) + (l32 * 4) * 8 + h;
     qt[0] = (unsigned short)(qn.x & 0xffffu);
     qt[8] = (unsigned short)(qn.x >> 16);
@@ -752,14 +750,15 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
         }
     }
     constexpr int kVStride = 264;     // bytes per staged value row (+8 against bank conflicts)
-    const float Cres = ldexpf(scale_log2e, Eq);
+    // Nothing here is narrower than binary32.  The queries go in as they are (binary16 already); both halves of a row
+    // of 16 lanes carry the heads' logits, and the weights p 2^kWBoost go to the value product as their binary16 head
+    // (columns 0..7) and the binary16 remainder (columns 8..15, added once at the end like the remainders of P*s): 22 bits
+    // and more of every weight above 2^-16 of the largest, and nothing is lost above 2^-39.
+    constexpr int kWBoost = 14;
     f32x4 S0 = {0.f, 0.f, 0.f, 0.f}, S1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int st = 0; st < 4; ++st) {
-      u32x4 bq;       // normalised q in natural channel order; columns 8..15 stay zero
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        bq[e] = (role == 0 && live) ? *reinterpret_cast<const unsigned*>(sQn + head * kD + 32 * st + 8 * kg + 2 * e) : 0u;
+      const u32x4 bq = *reinterpret_cast<const u32x4*>(sQraw + head * kD + 32 * st + 8 * kg);    // (0 past the last head)
       S0 = mfma(kr[0][st], bq, S0);
       S1 = mfma(kr[1][st], bq, S1);
     }
@@ -768,18 +767,20 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int tok = t0 + 8 * kg + 2 * i;      // token of xa; xb is the next one
-      xa[i] = (role == 0 && tok < n_res) ? S0[i] * Cres : -INFINITY;
-      xb[i] = (role == 0 && tok + 1 < n_res) ? S1[i] * Cres : -INFINITY;
+      xa[i] = tok < n_res ? S0[i] * scale_log2e : -INFINITY;
+      xb[i] = tok + 1 < n_res ? S1[i] * scale_log2e : -INFINITY;
       mx = fmaxf(mx, fmaxf(xa[i], xb[i]));
     }
-    mx = xkg_max(mx);
-    mx = fmaxf(mx, row_ror8(mx));       // finite: token t0 is valid
-    m_run = mx;                          // nothing has been accumulated yet
+    m_run = xkg_max(mx);                 // finite: token t0 is valid; nothing has been accumulated yet
     u32x4 Bp;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      Bp[i] = cvt_pk(__builtin_amdgcn_exp2f(xa[i] - m_run), __builtin_amdgcn_exp2f(xb[i] - m_run));
-      l_run = dot2(Bp[i], 0x3c003c00u, l_run);
+      float ea = __builtin_amdgcn_exp2f(xa[i] - m_run), eb = __builtin_amdgcn_exp2f(xb[i] - m_run);
+      l_run += role ? 0.f : ea + eb;     // (the halves of a row are added at the end)
+      ea *= (float)(1 << kWBoost);
+      eb *= (float)(1 << kWBoost);
+      const unsigned hd = cvt_pk(ea, eb);
+      Bp[i] = role ? cvt_pk(ea - half_lo(hd), eb - half_hi(hd)) : hd;
     }
     // values through LDS (rows beyond the window are zeroed), read back transposed: A row = channel,
     // slot pair = adjacent tokens
@@ -804,9 +805,13 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
                                      value_channel<NVG>(xp, qq, n);
           a[e] = (unsigned)cp[0] | ((unsigned)cp[kVStride / 2] << 16);
         }
+        f32x4 t = mfma(a, Bp, f32x4{0.f, 0.f, 0.f, 0.f});
+        if (role) {      // a value that is infinite must not meet a remainder of the other sign, or 0: the head alone decides
+#pragma unroll
+          for (int i = 0; i < 4; ++i) t[i] = fminf(fmaxf(t[i], -3e38f), 3e38f);
+        }
         // the block loop accumulates sum p' c 4^sc 2^-24 = 2^(kPBoost-24) sum p c and is scaled back at the end
-        const f32x4 t = mfma(a, Bp, f32x4{0.f, 0.f, 0.f, 0.f});
-        O[xp][qq] = t * (5.9604644775390625e-8f * (float)(1 << kPBoost));
+        O[xp][qq] = t * (5.9604644775390625e-8f * (float)(1 << kPBoost) / (float)(1 << kWBoost));
       }
     wave_lds_handoff();     // the staging area is the record buffer of the block loop
   }

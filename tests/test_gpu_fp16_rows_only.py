@@ -39,3 +39,63 @@ def test_fp16_rows_only(H, R, sink, n, g, bf16):
     assert np.all(np.abs(out.float().cpu().numpy() - ro) <= H.ATOL + rtol * np.abs(ro))
     assert np.all(np.abs(lse.cpu().numpy() - rl) <= H.LSE_ATOL + 1e-4 * np.abs(rl))
     H.check_state(oc, gc)
+
+
+@pytest.mark.parametrize("n,g,R,sink,far", [(2, 7, 128, 0, 0), (5, 1, 64, 32, 1), (33, 8, 128, 0, 1), (90, 7, 128, 0, 0), (290, 4, 256, 64, 1)])
+def test_fp16_rows_in_binary32(H, n, g, R, sink, far):
+    """The softmax weights and the queries of fp16 rows keep what binary32 gives them.  Bars: a logit is four matrix steps
+    of 32 products each, whose binary32 sums round at most a few times per step (16 in all, 2^-20 of the sum of
+    magnitudes); exp2, log2, the sum of the weights and their two binary16 parts (22 bits) add 2^-20 of the result; the
+    output is then rounded to binary16 once (2^-11).  Weights rounded to binary16 miss the log-sum-exp bar by up to 2^-13.
+    far: an element 2^15 above the others in the queries meets zeros in the keys, so the small ones decide."""
+    import paper_2512_19206_amd as M
+    rng = np.random.default_rng(7300 + n)
+    B, Hkv = 2, 2
+    kw = dict(B=B, Hq=Hkv * g, Hkv=Hkv, D=128, T_max=4 * R, Gk=64, Gv=64, R=R, k4=16, k16=0, sink=sink)
+    gc = M.Cache(M.make_config(**kw))
+    K = rng.standard_normal((B, Hkv, n, 128)).astype(np.float16)
+    V = rng.standard_normal((B, Hkv, n, 128)).astype(np.float16)
+    q = (0.5 * rng.standard_normal((B, Hkv * g, 128))).astype(np.float16)
+    if far:
+        q[..., 5] = np.float16(32768.0)
+        K[..., 5] = 0
+    d = lambda a: torch.from_numpy(a).cuda()
+    gc.quantize_append(d(K), d(V))
+    out, lse = gc.decode_attention(d(q))
+    torch.cuda.synchronize()
+    assert gc.decode_path() == M.PATH_MATRIX
+    k64, v64 = (np.repeat(x.astype(np.float64), g, axis=1) for x in (K, V))
+    prod = q.astype(np.float64)[:, :, None] * k64
+    s = prod.sum(-1) / np.sqrt(128.0)
+    ds = (np.abs(prod).sum(-1) / np.sqrt(128.0)).max(-1) * 2.0 ** -20      # error of a logit
+    m = s.max(-1, keepdims=True)
+    p = np.exp(s - m)
+    ref_lse = (m + np.log(p.sum(-1, keepdims=True)))[..., 0]
+    p /= p.sum(-1, keepdims=True)
+    ref = np.einsum("bht,bhtd->bhd", p, v64)
+    err_lse = np.abs(lse.cpu().numpy() - ref_lse)
+    assert np.all(err_lse <= ds + 2.0 ** -20 * (1.0 + np.abs(ref_lse))), f"lse off by {err_lse.max():.2e}"
+    err = np.abs(out.float().cpu().numpy() - ref)
+    mass = np.einsum("bht,bhtd->bhd", p, np.abs(v64))
+    bar = 2.0 ** -11 * np.abs(ref) * (1 + 2.0 ** -11) + (2.0 * ds[..., None] + 2.0 ** -19) * mass + 2.0 ** -25
+    assert np.all(err <= bar), f"out: excess {(err - bar).max():.2e} of {err.max():.2e}"
+
+
+def test_an_infinite_value_reaches_its_channel_only(H):
+    import paper_2512_19206_amd as M
+    rng = np.random.default_rng(7400)
+    n, g = 40, 4
+    kw = dict(B=1, Hq=g, Hkv=1, D=128, T_max=256, Gk=128, Gv=128, R=128, k4=16, k16=0)
+    K = rng.standard_normal((1, 1, n, 128)).astype(np.float16)
+    V = rng.standard_normal((1, 1, n, 128)).astype(np.float16)
+    q = rng.standard_normal((1, g, 128)).astype(np.float16)
+    outs = []
+    for x in (0.0, np.inf):
+        V[0, 0, 11, 77] = x
+        gc = M.Cache(M.make_config(**kw))
+        gc.quantize_append(torch.from_numpy(K).cuda(), torch.from_numpy(V).cuda())
+        outs.append(gc.decode_attention(torch.from_numpy(q).cuda())[0].float().cpu().numpy())
+    assert gc.decode_path() == M.PATH_MATRIX
+    assert np.all(np.isposinf(outs[1][..., 77]))
+    rest = np.arange(128) != 77
+    assert np.array_equal(outs[0][..., rest], outs[1][..., rest])
