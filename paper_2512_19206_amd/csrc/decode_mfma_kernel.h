@@ -1211,6 +1211,14 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
     for (int qq = 0; qq < 4; ++qq)
 #pragma unroll
       for (int i = 0; i < 4; ++i) Ot[xp][qq][i] = O[xp][qq][i] + row_ror8(O[xp][qq][i]);
+  // The variants without registers to spare form the thread's places in what follows, and the pair's first partial, from a
+  // copy the compiler cannot see through: as common subexpressions with the staging of q and of the fp16 rows they would live
+  // across the record loop, where one of these variants then spilled (305 instead of 278 us per step at 64 x 16 390 tokens;
+  // the others are up to 1 % faster without).
+  constexpr bool kLeanEnd = kLeanConstants || (NVG == 4 && NKL > 8);
+  int tid_e = tid;
+  if constexpr (kLeanEnd) asm volatile("" : "+v"(tid_e));
+  const int kg_e = (tid_e & 63) >> 4;
   float* wO = reinterpret_cast<float*>(wbase);        // [8][128] O, then [8] l
   float* sM = reinterpret_cast<float*>(smem + 2048 + 64);          // [waves][8]
   int* sTicket = reinterpret_cast<int*>(smem + 2048 + 64 + 128);
@@ -1224,27 +1232,22 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
         for (int qq = 0; qq < 4; ++qq)
           r[qq] = fmaf(Ot[xp][qq][i], 16777216.f / (float)(1 << kPBoost), zsum[value_group<NVG>(xp, qq)]);
         if (NVG == 4) {
-          *reinterpret_cast<float2*>(wO + head * kD + value_channel<NVG>(xp, 0, 4 * kg + i)) = make_float2(r[0], r[1]);
-          *reinterpret_cast<float2*>(wO + head * kD + value_channel<NVG>(xp, 2, 4 * kg + i)) = make_float2(r[2], r[3]);
+          *reinterpret_cast<float2*>(wO + head * kD + value_channel<NVG>(xp, 0, 4 * kg_e + i)) = make_float2(r[0], r[1]);
+          *reinterpret_cast<float2*>(wO + head * kD + value_channel<NVG>(xp, 2, 4 * kg_e + i)) = make_float2(r[2], r[3]);
         } else {
-          *reinterpret_cast<float4*>(wO + head * kD + value_channel<NVG>(xp, 0, 4 * kg + i)) = make_float4(r[0], r[1], r[2], r[3]);
+          *reinterpret_cast<float4*>(wO + head * kD + value_channel<NVG>(xp, 0, 4 * kg_e + i)) = make_float4(r[0], r[1], r[2], r[3]);
         }
       }
-    if (kg == 0) {
+    if (kg_e == 0) {
       wO[8 * kD + head] = l_run;
       sM[wave * 8 + head] = m_run;
     }
   }
   __syncthreads();
   // one thread per (head, four channels)
-  // (the variants without registers to spare form these, and the pair's first partial, from a copy the compiler cannot see
-  // through: as common subexpressions with the q staging they would live across the record loop, where one of these
-  // variants then spilled: 305 instead of 278 us per step at 64 x 16 390 tokens; the others are up to 1 % faster without)
-  int tid_e = tid;
-  if constexpr (kLeanConstants) asm volatile("" : "+v"(tid_e));
   const int eh = tid_e >> 5, c4 = tid_e & 31;
   const size_t bh = (size_t)b * Hq + (size_t)jkv * g + eh;
-  if constexpr (kLeanConstants) part0 = sc.n_units ? (int)(sc.span[b] & 0xffffu) * Hkv + jkv * n_splits : p * n_splits;
+  if constexpr (kLeanEnd) part0 = sc.n_units ? (int)(sc.span[b] & 0xffffu) * Hkv + jkv * n_splits : p * n_splits;
   float* const pair = part + (size_t)part0 * g * kPartStrideM;
   if (eh < g) {
     const float* r0 = reinterpret_cast<const float*>(smem + kHdrLds);
