@@ -205,6 +205,32 @@ decode_split_kernel(CacheView cv, const __half* __restrict__ q, float scale, int
   }
 }
 
+// What a step changes besides its outputs, one workgroup per pair: the new token's rows go to the last fp16 row in use, |q|
+// joins the accumulator (not of a sequence without tokens).  The matrix-core kernel does this itself.  (With a copy launch
+// and a |q| launch per sequence a step of 256 sequences of two lengths took 987 us, 29 this way.)
+__global__ void __launch_bounds__(kD) token_books_kernel(CacheView cv, const __half* __restrict__ q, int n_blocks, int n_fp16,
+                                                         int accumulate_q, NewToken nt, SeqCounts sc) {
+  const int Hkv = cv.cfg.Hkv, p = blockIdx.x, b = p / Hkv, j = p % Hkv, tid = threadIdx.x;
+  const bool bf16 = cv.cfg.in_dtype != 0;
+  if (sc.enabled) {
+    n_blocks = sc.n_blocks[b];
+    n_fp16 = sc.n_fp16[b];
+  }
+  if (nt.k && tid < 32) {      // 16 threads for the key row, 16 for the value row
+    const int64_t src = (int64_t)b * nt.st.b + (int64_t)j * nt.st.h + (tid & 15) * 8;
+    const size_t dst = ((size_t)p * cv.RW + n_fp16 - 1) * kD + (tid & 15) * 8;
+    *reinterpret_cast<uint4*>((tid < 16 ? cv.res_k : cv.res_v) + dst) =
+        as_f16x8(*reinterpret_cast<const uint4*>((tid < 16 ? nt.k : nt.v) + src), bf16);
+  }
+  if (accumulate_q && (n_blocks || n_fp16)) {
+    unsigned long long sum = 0ull;
+    for (int h = 0; h < cv.g; ++h)
+      sum += fix24_abs(in_bits(q + ((size_t)b * cv.cfg.Hq + (size_t)j * cv.g + h) * kD + tid, bf16));
+    cv.qacc[(size_t)p * kD + tid] += sum;
+    if (tid == 0) cv.qcnt[p] += (unsigned long long)cv.g;
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Merge of the splits: m* = max m_i, l* = sum l_i e^(m_i - m*), O = sum O_i e^(m_i - m*) / l*.
 // One workgroup per (batch, query head), one thread per channel.
@@ -362,39 +388,9 @@ hipError_t launch_decode(const CacheView& v, const __half* q, __half* out, float
     return e;
   }
   *path = MIXKVQ_PATH_VECTOR;
-  if (nt.k) {   // this path does not move the new token itself
-    if (!sc.enabled) {
-      e = launch_residual_copy(v, nt.k, nt.v, nt.st, 0, n_fp16 - 1, 1, s);
-      if (e != hipSuccess) return e;
-    } else {
-      for (int b = 0; b < v.cfg.B; ++b) {
-        CacheView vb = v;
-        vb.cfg.B = 1;
-        vb.P = v.cfg.Hkv;
-        vb.res_k += (size_t)b * v.cfg.Hkv * v.RW * kD;
-        vb.res_v += (size_t)b * v.cfg.Hkv * v.RW * kD;
-        e = launch_residual_copy(vb, nt.k + (int64_t)b * nt.st.b, nt.v + (int64_t)b * nt.st.b, nt.st, 0, sc.n_fp16[b] - 1, 1, s);
-        if (e != hipSuccess) return e;
-      }
-    }
-  }
-  if (accumulate_q) {
-    Strides3 qs{(int64_t)v.cfg.Hq * kD, (int64_t)kD, (int64_t)kD};
-    if (!sc.enabled) {
-      e = launch_qabs_accumulate(v, q, 1, qs, s);
-      if (e != hipSuccess) return e;
-    } else {      // sequences without tokens are skipped
-      for (int b = 0; b < v.cfg.B; ++b) {
-        if (sc.n_blocks[b] == 0 && sc.n_fp16[b] == 0) continue;
-        CacheView vb = v;
-        vb.cfg.B = 1;
-        vb.P = v.cfg.Hkv;
-        vb.qacc += (size_t)b * v.cfg.Hkv * kD;
-        vb.qcnt += (size_t)b * v.cfg.Hkv;
-        e = launch_qabs_accumulate(vb, q + (size_t)b * v.cfg.Hq * kD, 1, qs, s);
-        if (e != hipSuccess) return e;
-      }
-    }
+  if (nt.k || accumulate_q) {
+    token_books_kernel<<<dim3(v.P), dim3(kD), 0, s>>>(v, q, n_blocks, n_fp16, accumulate_q, nt, sc);
+    if (e = hipGetLastError(); e != hipSuccess) return e;
   }
   if (ev_start) (void)hipEventRecord(ev_start, s);
   decode_split_kernel<<<dim3(v.P, n_splits), dim3(kDecThreads), 0, s>>>(v, q, scale, n_blocks, n_fp16, n_splits, part, sc);

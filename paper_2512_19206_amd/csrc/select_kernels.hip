@@ -51,7 +51,7 @@ struct SelectArgs {
   int rows_q, rows_k;              // rows one workgroup takes
   int nq, nA, nB;                  // workgroups per pair
   unsigned* part;                  // [P][nA + nB][128]
-  uint8_t* sel;                    // [P][k16 + k4], or nullptr: |q| only
+  uint8_t* sel;                    // [P][k16 + k4]
 };
 
 // Rows one workgroup takes.  Small calls are bound by latency: 256 rows are two passes of eight loads (128 and 512: 35.4
@@ -187,10 +187,6 @@ __global__ void __launch_bounds__(kStreamThreads) select_kernel(CacheView cv, Se
                          __HIP_MEMORY_SCOPE_AGENT);
     }
   }
-  if (!a.sel) {      // |q| alone: no ticket
-    if (tid == 0) __hip_atomic_fetch_add(cv.qcnt + p, (unsigned long long)tokens, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return;
-  }
   // every store and atomic of this workgroup has reached the coherence point before its ticket is drawn
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
@@ -282,18 +278,15 @@ static hipError_t launch_select_kernel(const CacheView& v, SelectArgs a, hipStre
   auto pieces = [](int L, int rows) { return (int)(((int64_t)L + rows - 1) / rows); };
   while ((int64_t)v.g * pieces(a.Lq, a.rows_q) > 32768 && a.rows_q < kMaxExactRows) a.rows_q *= 2;
   a.nq = v.g * pieces(a.Lq, a.rows_q);
-  a.nA = a.nB = 0;
   a.part = reinterpret_cast<unsigned*>(v.ws + (size_t)v.P * kD);
-  if (a.sel) {
-    // as many partial ranges as the workspace has room for (at least four per pair), and as a ticket can count
-    int64_t room = (v.ws_bytes - (int64_t)v.P * kD) / ((int64_t)v.P * kRangePartBytes);
-    room = room < 16384 ? room : 16384;
-    int64_t rows = rows_per_workgroup(v.P, a.LA + a.LB);
-    while (((int64_t)a.LA + rows - 1) / rows + ((int64_t)a.LB + rows - 1) / rows > room) rows *= 2;
-    a.rows_k = (int)(rows < (1ll << 30) ? rows : (1ll << 30));
-    a.nA = pieces(a.LA, a.rows_k);
-    a.nB = pieces(a.LB, a.rows_k);
-  }
+  // as many partial ranges as the workspace has room for (at least four per pair), and as a ticket can count
+  int64_t room = (v.ws_bytes - (int64_t)v.P * kD) / ((int64_t)v.P * kRangePartBytes);
+  room = room < 16384 ? room : 16384;
+  int64_t rows = rows_per_workgroup(v.P, a.LA + a.LB);
+  while (((int64_t)a.LA + rows - 1) / rows + ((int64_t)a.LB + rows - 1) / rows > room) rows *= 2;
+  a.rows_k = (int)(rows < (1ll << 30) ? rows : (1ll << 30));
+  a.nA = pieces(a.LA, a.rows_k);
+  a.nB = pieces(a.LB, a.rows_k);
   if (a.nq + a.nA + a.nB > 65535) return hipErrorInvalidConfiguration;
   const dim3 grid(v.P, a.nq + a.nA + a.nB), block(kStreamThreads);
   const bool al = (a.nq == 0 || rows_aligned16(a.q, a.qs)) && (a.nB == 0 || rows_aligned16(a.kB, a.sB));
@@ -305,12 +298,6 @@ static hipError_t launch_select_kernel(const CacheView& v, SelectArgs a, hipStre
     else select_kernel<false, false><<<grid, block, 0, s>>>(v, a);
   }
   return hipGetLastError();
-}
-
-hipError_t launch_qabs_accumulate(const CacheView& v, const __half* q, int Lq, Strides3 qs, hipStream_t s) {
-  SelectArgs a{};
-  a.q = q, a.qs = qs, a.Lq = Lq;
-  return launch_select_kernel(v, a, s);
 }
 
 hipError_t launch_select2(const CacheView& v, const __half* kA, int LA, Strides3 sA, const __half* kB, int LB, Strides3 sB,
