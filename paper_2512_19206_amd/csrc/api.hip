@@ -230,14 +230,15 @@ static int flush_full_windows(mixkvq_cache* c, bool equal, hipStream_t s) {
   const int R = c->Rw, Rr = cfg.R, per = R / Rr;
   const Strides3 ws{(int64_t)cfg.Hkv * c->v.RW * kD, (int64_t)c->v.RW * kD, (int64_t)kD};
   const bool scored_apart = per > 1 && cfg.k4 + cfg.k16 > 0;
-  if (!equal && per == 1) {
-    FlushList list;
-    list.n = 0;
+  FlushList list;      // (a batch of more than kMaxRaggedB sequences is in equal state)
+  list.n = 0;
+  if (!equal)
     for (int b = 0; b < cfg.B; ++b)
       if (c->seq[b].n_res == R) {
         list.seq[list.n] = (uint16_t)b;
         list.first_rec[list.n++] = (int)(c->seq[b].n_quant / Rr);
       }
+  if (!equal && per == 1) {
     MIXKVQ_TRY_HIP(launch_flush_windows(c->v, list, s));
   } else {
     for (int b0 = 0; b0 < cfg.B;) {
@@ -252,13 +253,12 @@ static int flush_full_windows(mixkvq_cache* c, bool equal, hipStream_t s) {
       b0 = b1;
     }
   }
+  if (cfg.qacc_reset_on_flush) MIXKVQ_TRY_HIP(equal ? launch_zero_qacc(c->v, s) : launch_zero_qacc_listed(c->v, list, s));
   for (int b = 0; b < cfg.B; ++b)
     if (c->seq[b].n_res == R) {
-      if (cfg.qacc_reset_on_flush && !equal) MIXKVQ_TRY_HIP(launch_zero_qacc(sub_view(c, b, 1), s));
       c->seq[b].n_quant += R;
       c->seq[b].n_res = 0;
     }
-  if (cfg.qacc_reset_on_flush && equal) MIXKVQ_TRY_HIP(launch_zero_qacc(c->v, s));
   return MIXKVQ_OK;
 }
 

@@ -86,6 +86,7 @@ int max_splits_for(int P);                                 // split-K ceiling us
 
 // ---- kernel launchers (each returns a hipError_t from the launch) ----
 hipError_t launch_zero_qacc(const CacheView& v, hipStream_t s);
+hipError_t launch_zero_qacc_listed(const CacheView& v, const FlushList& list, hipStream_t s);     // of the listed sequences
 // adds |q| of Lq tokens (0: none) to the accumulator, then scores and selects over the L tokens of k
 hipError_t launch_select(const CacheView& v, const __half* q, int Lq, Strides3 qs, const __half* k, int L, Strides3 ks,
                          uint8_t* sel, hipStream_t s);

@@ -23,6 +23,19 @@ hipError_t launch_zero_qacc(const CacheView& v, hipStream_t s) {
   return hipGetLastError();
 }
 
+// One workgroup per pair of the listed sequences.  (A launch per sequence: 411 us for a step in which 255 of 256 sequences
+// pack a block, 24 this way.)
+__global__ void __launch_bounds__(kD) zero_listed_kernel(CacheView cv, FlushList list) {
+  const int Hkv = cv.cfg.Hkv, p = (int)list.seq[blockIdx.x / Hkv] * Hkv + blockIdx.x % Hkv;
+  cv.qacc[(size_t)p * kD + threadIdx.x] = 0ull;
+  if (threadIdx.x == 0) cv.qcnt[p] = 0ull;
+}
+
+hipError_t launch_zero_qacc_listed(const CacheView& v, const FlushList& list, hipStream_t s) {
+  zero_listed_kernel<<<dim3(list.n * v.cfg.Hkv), dim3(kD), 0, s>>>(v, list);
+  return hipGetLastError();
+}
+
 // ---------------------------------------------------------------------------
 // Scoring and selection in one launch.  Workgroups (pair, y): the first nq of a pair add |q| (Eq. 6) over one piece of
 // one query head each, the others take the range (Eq. 7) of one piece of the keys; the last of a pair to finish scores

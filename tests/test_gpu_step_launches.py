@@ -81,3 +81,20 @@ def test_vector_path_keeps_the_books_of_all_sequences_in_one_launch(H, lens):
     gc, ocs = _filled(H, rng, lens, dict(Hq=6, Hkv=2, D=128, T_max=192, Gk=16, Gv=128, R=48, k4=8, k16=0))
     assert _step(H, gc, ocs, rng, True) <= 3
     assert gc.decode_path() == M.PATH_VECTOR
+
+
+@pytest.mark.parametrize("R,Gk", [(128, 128), (256, 128)])
+def test_accumulators_of_all_packed_sequences_are_cleared_in_one_launch(H, R, Gk):
+    """Six of eight full windows leave in one step (records of one block each: one pack launch; of two records: scored and
+    packed per run of neighbours in equal state), their accumulators are cleared with one launch, then attention."""
+    rng = np.random.default_rng(7700 + R)
+    lens = (R, R, 70, 2 * R, R, R, 100, R)
+    gc, ocs = _filled(H, rng, lens, dict(Hq=6, Hkv=2, D=128, T_max=4 * R, Gk=Gk, Gv=128, R=R, k4=8, k16=0,
+                                         qacc_reset_on_flush=1))
+    _step_q = rng.standard_normal((len(lens), 6, 128)).astype(np.float16)
+    gc.decode_attention(H.dev(_step_q), accumulate_q=True)      # something to clear
+    for b, oc in enumerate(ocs):
+        oc.decode_attention(_step_q[b:b + 1], accumulate_q=True)
+    runs = 4                                                     # (R, R) (2 R) (R, R) (R)
+    assert _step(H, gc, ocs, rng, True) <= (1 if R == 128 else 2 * runs) + 2
+    assert _step(H, gc, ocs, rng, True) == 1
