@@ -82,8 +82,9 @@ typedef struct {
   uint64_t blocks;     /* [B*Hkv][T_max/Rr] block records (Rr tokens each, see R above), see mixkvq_block_layout */
   uint64_t res_k;      /* [B*Hkv][sink + R][D] fp16 keys: per pair the sink rows, then the residual window */
   uint64_t res_v;      /* [B*Hkv][sink + R][D] fp16 values likewise */
-  uint64_t qacc;       /* [B*Hkv][D] u64 sums of |q| in units of 2^-24, then [B*Hkv] u64 counts (a running launch counts
-                        * its workgroups in the top 16 bits of a count and leaves them 0) */
+  uint64_t qacc;       /* [B*Hkv][D] u64 sums of |q| in units of 2^-24, then [B*Hkv] u64 counts; from the next multiple
+                        * of 256 bytes on [B*Hkv] u64 words in which a running attention or selection call counts its
+                        * workgroups (0 between calls) */
   uint64_t workspace;  /* split-K partials and selection scratch */
 } mixkvq_sizes;
 
@@ -150,7 +151,8 @@ int mixkvq_cache_state_seq(const mixkvq_cache* c, int32_t b, int64_t* n_quantize
 /* Resuming from a snapshot.  Everything a cache holds is in its five device buffers plus these token counts, so a
  * snapshot is a copy of the buffers and of what mixkvq_cache_state(_seq) reports; to resume, copy the buffers back
  * (into the same or another cache of the same configuration, with the same block table if one is in use) and set the
- * counts here.  Host-only.  EINVAL for counts that no sequence of appends produces (n_quantized a multiple of R up to
+ * counts here.  (A copy of the qacc buffer that was taken while an attention or selection call was running: set the words
+ * behind the counts to 0 after copying it back, see mixkvq_sizes.)  Host-only.  EINVAL for counts that no sequence of appends produces (n_quantized a multiple of R up to
  * T_max; n_residual 1..R with the deferred flush once anything was flushed, 0..R-1 with the eager one; the window
  * empty until the sink is full).  Appendix D.1 describes the cache as exactly this state. */
 int mixkvq_cache_set_state(mixkvq_cache* c, int64_t n_quantized, int32_t n_residual, int32_t n_sink);

@@ -179,6 +179,8 @@ class Cache:
         bufs, states = snap
         for dst, src in zip((self.blocks, self.res_k, self.res_v, self.qacc, self.workspace), bufs):
             dst.copy_(src)
+        # (the words by which a running call counts its workgroups: a call may have been running when the copy was taken)
+        self.qacc[self.cfg.B * self.cfg.Hkv * (self.cfg.D + 1) * 8:].zero_()
         if all(st == states[0] for st in states):
             _check(self.lib.mixkvq_cache_set_state(self.handle, *states[0]))
         else:

@@ -105,6 +105,7 @@ struct mixkvq_cache {
   SeqState* seq;     // [B]: every sequence has its own counts (they are equal while the batch runs in lock-step)
   hipEvent_t ev_start = nullptr, ev_stop = nullptr;   // optional timing of the split kernel
   int last_path = MIXKVQ_PATH_NONE;                   // kernel of the last attention launch
+  bool tickets_clear = false;                         // the ticket words were set to 0 once
 };
 
 namespace mixkvq {
@@ -121,6 +122,7 @@ static CacheView sub_view(const mixkvq_cache* c, int b0, int nb) {
   v.res_v += p0 * v.RW * kD;
   v.qacc += p0 * kD;
   v.qcnt += p0;
+  v.tickets += p0;
   return v;
 }
 
@@ -139,6 +141,18 @@ static AppendPlan plan_append(const mixkvq_config& cfg, int R, const SeqState& s
   if (pl.F < 0) pl.F = 0;
   pl.n_rest = (int)(total - pl.F * R);
   return pl;
+}
+
+// The ticket words start at 0: the reset sees to it, or for a cache that was never reset its first call that draws
+// tickets.  Later resets leave them alone (a call may be running on another stream).  In a captured graph the fill runs with
+// every replay and says nothing about now.
+static hipError_t clear_tickets(mixkvq_cache* c, hipStream_t s) {
+  if (c->tickets_clear) return hipSuccess;
+  if (hipError_t e = launch_zero_tickets(c->v, s); e != hipSuccess) return e;
+  hipStreamCaptureStatus status = hipStreamCaptureStatusActive;
+  if (hipStreamIsCapturing(s, &status) != hipSuccess) (void)hipGetLastError();
+  c->tickets_clear = status == hipStreamCaptureStatusNone;
+  return hipSuccess;
 }
 
 // Appends n_new tokens to sequences [b0, b0 + nb), which share one state.  k_new, v_new point at batch entry b0.
@@ -174,6 +188,7 @@ static int append_range(mixkvq_cache* c, int b0, int nb, const __half* k_new, co
         const int nA = p0 < r0 ? (int)((p1 < r0 ? p1 : r0) - p0) : 0;      // tokens taken from the window
         const __half* kA = v.res_k + (size_t)(S + p0) * kD;
         const __half* kB = kw + (p0 + nA - r0) * kvs.t;
+        MIXKVQ_TRY_HIP(clear_tickets(c, s));
         MIXKVQ_TRY_HIP(launch_select2(v, kA, nA, ws, kB, R - nA, kvs, sel_blk, s));
         // (stream origin shifted so that record 0 of this launch is record u * per of the call; r0 - u R <= 0 for u >= 1)
         MIXKVQ_TRY_HIP(launch_flush(v, kw + (u ? (u * R - r0) * kvs.t : 0), vw + (u ? (u * R - r0) * kvs.t : 0), kvs,
@@ -247,6 +262,7 @@ static int flush_full_windows(mixkvq_cache* c, bool equal, hipStream_t s) {
       if (c->seq[b0].n_res == R) {
         const CacheView v = sub_view(c, b0, b1 - b0);
         uint8_t* const sel = scored_apart ? select_scratch(v) : nullptr;
+        if (sel) MIXKVQ_TRY_HIP(clear_tickets(c, s));
         if (sel) MIXKVQ_TRY_HIP(launch_select2(v, v.res_k + (size_t)cfg.sink * kD, R, ws, nullptr, 0, ws, sel, s));
         MIXKVQ_TRY_HIP(launch_flush(v, v.res_k, v.res_v, ws, R, (int)(c->seq[b0].n_quant / Rr), per, sel, 0, s));
       }
@@ -284,7 +300,7 @@ int mixkvq_cache_sizes(const mixkvq_config* cfg, mixkvq_sizes* out) {
   out->blocks = al256(P * (uint64_t)(cfg->T_max / rec_tokens(*cfg)) * (uint64_t)l.rec_bytes);
   out->res_k = al256(P * (uint64_t)(cfg->R + cfg->sink) * cfg->D * 2);
   out->res_v = out->res_k;
-  out->qacc = al256(P * (uint64_t)(cfg->D + 1) * 8);
+  out->qacc = al256(P * (uint64_t)(cfg->D + 1) * 8) + al256(P * 8);
   uint64_t a = decode_workspace_bytes(*cfg), b = select_workspace_bytes(*cfg);
   out->workspace = al256(a > b ? a : b);
   return MIXKVQ_OK;
@@ -320,6 +336,7 @@ int mixkvq_cache_create(const mixkvq_config* cfg, const mixkvq_buffers* bufs, mi
   c->v.res_v = (__half*)bufs->res_v;
   c->v.qacc = (unsigned long long*)bufs->qacc;
   c->v.qcnt = c->v.qacc + (size_t)c->v.P * cfg->D;
+  c->v.tickets = (unsigned long long*)((uint8_t*)bufs->qacc + al256((uint64_t)c->v.P * (cfg->D + 1) * 8));
   c->v.ws = (uint8_t*)bufs->workspace;
   const uint64_t wd = decode_workspace_bytes(*cfg), wsel = select_workspace_bytes(*cfg);
   c->v.ws_bytes = (int64_t)(wd > wsel ? wd : wsel);
@@ -337,6 +354,7 @@ void mixkvq_cache_destroy(mixkvq_cache* c) {
 int mixkvq_cache_reset(mixkvq_cache* c, void* stream) {
   if (!c) return MIXKVQ_EINVAL;
   MIXKVQ_TRY_HIP(launch_zero_qacc(c->v, (hipStream_t)stream));
+  MIXKVQ_TRY_HIP(clear_tickets(c, (hipStream_t)stream));
   for (int b = 0; b < c->v.cfg.B; ++b) c->seq[b] = SeqState{0, 0, 0};
   return MIXKVQ_OK;
 }
@@ -398,6 +416,7 @@ int mixkvq_select_channels(mixkvq_cache* c, const void* q, int32_t Lq, const int
   hipStream_t s = (hipStream_t)stream;
   const Strides3 qs = Lq > 0 ? Strides3{q_strides[0], q_strides[1], q_strides[2]} : Strides3{0, 0, 0};
   Strides3 ks{k_strides[0], k_strides[1], k_strides[2]};
+  MIXKVQ_TRY_HIP(clear_tickets(c, s));
   MIXKVQ_TRY_HIP(launch_select(c->v, (const __half*)q, Lq, qs, (const __half*)k, L, ks, sel, s));
   return MIXKVQ_OK;
 }
@@ -411,6 +430,7 @@ int mixkvq_select_channels_seq(mixkvq_cache* c, int32_t b, const void* q, int32_
   const CacheView v = sub_view(c, b, 1);
   const Strides3 qs = Lq > 0 ? Strides3{0, q_strides[0], q_strides[1]} : Strides3{0, 0, 0};
   Strides3 ks{0, k_strides[0], k_strides[1]};
+  MIXKVQ_TRY_HIP(clear_tickets(c, s));
   MIXKVQ_TRY_HIP(launch_select(v, (const __half*)q, Lq, qs, (const __half*)k, L, ks, sel, s));
   return MIXKVQ_OK;
 }
@@ -476,6 +496,7 @@ int mixkvq_prefill(mixkvq_cache* c, const void* q, int32_t Lq, const int64_t q_s
   hipStream_t s = (hipStream_t)stream;
   const Strides3 qs = Lq > 0 ? Strides3{q_strides[0], q_strides[1], q_strides[2]} : Strides3{0, 0, 0};
   Strides3 ks{kv_strides[0], kv_strides[1], kv_strides[2]};
+  MIXKVQ_TRY_HIP(clear_tickets(c, s));
   MIXKVQ_TRY_HIP(launch_select(c->v, (const __half*)q, Lq, qs, (const __half*)k, L, ks, sel, s));
   return mixkvq_quantize_append(c, k, v, L, kv_strides, sel, stream);
 }
@@ -504,6 +525,7 @@ int mixkvq_decode_attention(mixkvq_cache* c, const void* q, void* out, float* ls
   if (!decode_counts(c, &n_blocks, &n_fp16, &sc)) return MIXKVQ_EINVAL;
   if (n_blocks == 0 && n_fp16 == 0) return MIXKVQ_EEMPTY;
   hipStream_t s = (hipStream_t)stream;
+  MIXKVQ_TRY_HIP(clear_tickets(c, s));
   if (!(scale > 0.f)) scale = 1.0f / sqrtf((float)cfg.D);
   MIXKVQ_TRY_HIP(launch_decode(c->v, (const __half*)q, (__half*)out, lse, scale, n_blocks, n_fp16, accumulate_q,
                                NewToken{nullptr, nullptr, {0, 0, 0}}, sc.enabled ? &sc : nullptr, s, c->ev_start,
@@ -557,6 +579,7 @@ int mixkvq_decode_step(mixkvq_cache* c, const void* k_new, const void* v_new, co
   // (Appending sequence by sequence costs one 2.5 us launch per run of equal states: 24 sequences of 60 to 12 003
   // tokens took 101 us per step that way, 31 us now.)
   hipStream_t s = (hipStream_t)stream;
+  MIXKVQ_TRY_HIP(clear_tickets(c, s));
   SeqState* before = new (std::nothrow) SeqState[cfg.B];
   if (!before) return MIXKVQ_ENOMEM;
   memcpy(before, c->seq, sizeof(SeqState) * cfg.B);

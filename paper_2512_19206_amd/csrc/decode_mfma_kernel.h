@@ -206,7 +206,7 @@ struct HalfSplit {
 // A thread owns four channels of one head, so g x 32 threads merge a pair without exchanging anything, and every load
 // of sixteen partials is in flight before the first wait.
 //
-// The last workgroup of a pair to finish merges it (see kTicket).  The partials, the ticket and the
+// The last workgroup of a pair to finish merges it (see CacheView::tickets).  The partials, the ticket and the
 // loads are agent-scope accesses, which go past the chip's eight L2 caches; no cache is flushed for them.  A launch of
 // its own for the merge costs what any dependent launch costs, whatever it does: 28.6 us per step instead of 24.1 at
 // 32 pairs of 32 805 tokens (16 partials each), 12.9 instead of 10.1 for one pair of 1 027 tokens (32 partials).
@@ -711,7 +711,7 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
         for (int h = 0; h < g; ++h) acc += fix24_abs(sQraw[h * kD + d]);
         cv.qacc[(size_t)p * kD + d] = acc;
       }
-      // (an atomic: the pair's other workgroups may be drawing tickets from the same word)
+      // (an atomic: no old value to wait for)
       if (lane == 0) __hip_atomic_fetch_add(cv.qcnt + p, (u64_t)g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
@@ -1279,11 +1279,11 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
     // every store of this workgroup has reached the coherence point before its ticket is drawn
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (tid == 0) *sTicket = (int)(__hip_atomic_fetch_add(tickets + p, kTicket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) / kTicket);
+    if (tid == 0) *sTicket = (int)__hip_atomic_fetch_add(tickets + p, (u64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     if (*sTicket == n_splits - 1) {     // all partials of the pair are there; the ticket goes back to 0 for the next launch
       if (eh < g) merge_pair<true>(pair, n_splits, g, eh, c4, out, lse, bh, cv.cfg.in_dtype);
-      if (tid == 0) __hip_atomic_fetch_sub(tickets + p, (u64_t)n_splits * kTicket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (tid == 0) __hip_atomic_fetch_sub(tickets + p, (u64_t)n_splits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
   MIXKVQ_PHASE(15)
@@ -1320,7 +1320,7 @@ static hipError_t launch_one(const CacheView& v, const __half* q, float scale, i
   }
   const dim3 grid = sc.n_units ? dim3(v.cfg.Hkv, sc.n_units) : dim3(v.P, n_splits);
   // the partials in the cache's workspace come with tickets for the merge; any other buffer takes the merge launch
-  u64_t* tickets = part == reinterpret_cast<float*>(v.ws) ? v.qcnt : nullptr;
+  u64_t* tickets = part == reinterpret_cast<float*>(v.ws) ? v.tickets : nullptr;
   if (ev_start && ev_stop) {
     // profiling aid: the two events take the start and the end time of this kernel itself (not of the launch call)
     hipExtLaunchKernelGGL(kern, grid, dim3(kMfmaThreads), (uint32_t)lds, s, ev_start, ev_stop, 0u, v, q,

@@ -48,10 +48,6 @@ struct FlushList {
   int32_t first_rec[kMaxRaggedB];     // first record of the block of that sequence
 };
 
-// The last workgroup of a (batch, KV head) pair to finish is found by a ticket that the pair's workgroups draw from the
-// top 16 bits of its |q| count (a count of tokens never gets there; a launch gives a pair at most 65 535 workgroups).
-constexpr unsigned long long kTicket = 1ull << 48;
-
 // Device-visible view of a cache: plain data passed by value to kernels.
 struct CacheView {
   mixkvq_config cfg;
@@ -66,7 +62,11 @@ struct CacheView {
   __half* res_k;         // [P][RW][D]
   __half* res_v;
   unsigned long long* qacc;  // [P][D]
-  unsigned long long* qcnt;  // [P]; the top 16 bits are the ticket of a running launch (kTicket), 0 between launches
+  unsigned long long* qcnt;  // [P]
+  // [P] from the next multiple of 256 bytes behind the counts on: the pair's workgroups of a running launch draw their numbers from it, and the one that draws the
+  // last knows that the others are done; 0 between launches.  (Words of their own: a call that only reads the accumulator
+  // must not change it while it runs, and the workspace may serve several caches in turn, so nothing in it outlives a call.)
+  unsigned long long* tickets;
   uint8_t* ws;
   int64_t ws_bytes;      // bytes of the workspace (of the whole cache, also in a view of some sequences)
 };
@@ -86,6 +86,7 @@ int max_splits_for(int P);                                 // split-K ceiling us
 
 // ---- kernel launchers (each returns a hipError_t from the launch) ----
 hipError_t launch_zero_qacc(const CacheView& v, hipStream_t s);
+hipError_t launch_zero_tickets(const CacheView& v, hipStream_t s);
 hipError_t launch_zero_qacc_listed(const CacheView& v, const FlushList& list, hipStream_t s);     // of the listed sequences
 // adds |q| of Lq tokens (0: none) to the accumulator, then scores and selects over the L tokens of k
 hipError_t launch_select(const CacheView& v, const __half* q, int Lq, Strides3 qs, const __half* k, int L, Strides3 ks,

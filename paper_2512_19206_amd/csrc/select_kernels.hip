@@ -31,6 +31,11 @@ __global__ void __launch_bounds__(kD) zero_listed_kernel(CacheView cv, FlushList
   if (threadIdx.x == 0) cv.qcnt[p] = 0ull;
 }
 
+hipError_t launch_zero_tickets(const CacheView& v, hipStream_t s) {
+  zero_u64_kernel<<<dim3((unsigned)((v.P + 255) / 256)), dim3(256), 0, s>>>(v.tickets, (size_t)v.P, nullptr, 0);
+  return hipGetLastError();
+}
+
 hipError_t launch_zero_qacc_listed(const CacheView& v, const FlushList& list, hipStream_t s) {
   zero_listed_kernel<<<dim3(list.n * v.cfg.Hkv), dim3(kD), 0, s>>>(v, list);
   return hipGetLastError();
@@ -45,9 +50,8 @@ hipError_t launch_zero_qacc_listed(const CacheView& v, const FlushList& list, hi
 //           (integers: any order is exact).
 //   range   running minima and maxima of packed 16-bit keys that order like the fp16 values; a workgroup leaves its
 //           result (128 channels, 512 bytes) in the workspace, so nothing has to be initialised.
-//   select  the workgroups of a pair draw tickets from the top bits of its |q| count, which the |q| workgroups advance
-//           with the same atomic.  Sums, partial ranges and tickets are agent-scope accesses (they pass the chip's eight
-//           L2 caches by), and a workgroup's own have been acknowledged before its ticket is drawn.
+//   select  the workgroups of a pair draw tickets.  Sums, partial ranges and tickets are agent-scope accesses (they pass
+//           the chip's eight L2 caches by), and a workgroup's own have been acknowledged before its ticket is drawn.
 // As launches of their own (|q|, initial ranges, ranges, selection) the four took 7.5 + 1.4 + 6.3 + 9.5 us and the gaps
 // between them on 8 pairs of 1 000 tokens, of which the work itself is a fraction.
 // ---------------------------------------------------------------------------
@@ -137,12 +141,17 @@ __device__ __forceinline__ T load_agent(const T* p) { return __hip_atomic_load(p
 template <bool BF, bool AL>      // BF: the caller's tensors hold bfloat16 (converted to binary16 on entry); AL: 16-byte aligned rows
 __global__ void __launch_bounds__(kStreamThreads) select_kernel(CacheView cv, SelectArgs a) {
   __shared__ __align__(16) unsigned char smem[16 * kD * 8];
+  __shared__ int sTicket;
   __shared__ unsigned long long sCount;
   const int Hkv = cv.cfg.Hkv, g = cv.g;
   const int p = blockIdx.x, b = p / Hkv, j = p % Hkv, tid = threadIdx.x, y = blockIdx.y;
   const int c = tid & 15, r = tid >> 4;
   const int nk = a.nA + a.nB;
-  int tokens = 0;      // |q| workgroups: what the pair's count grows by
+  // The pair's token count, which its last workgroup advances; only thresholds look at it (read ahead then: behind the ticket
+  // that cost 0.7 us of 8; added by every |q| workgroup beside its ticket, 2 of 12).
+  const unsigned long long added = (unsigned long long)a.Lq * (unsigned long long)g;
+  unsigned long long count = 0ull;
+  if (tid == 0 && cv.cfg.policy == 1) count = cv.qcnt[p] + added;
   if (y < a.nq) {
     auto sAcc = reinterpret_cast<unsigned long long (*)[kD]>(smem);      // [16][kD]
     const int hh = y % g, t0 = (y / g) * a.rows_q, t1 = min(a.Lq, t0 + a.rows_q);
@@ -160,7 +169,6 @@ __global__ void __launch_bounds__(kStreamThreads) select_kernel(CacheView cv, Se
       for (int rr = 0; rr < 16; ++rr) sum += sAcc[rr][tid];
       __hip_atomic_fetch_add(cv.qacc + (size_t)p * kD + tid, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    tokens = t1 - t0;
   } else {
     auto sLo = reinterpret_cast<unsigned (*)[kD / 2]>(smem);      // [16][kD / 2]
     auto sHi = sLo + 16;
@@ -203,15 +211,17 @@ __global__ void __launch_bounds__(kStreamThreads) select_kernel(CacheView cv, Se
   // every store and atomic of this workgroup has reached the coherence point before its ticket is drawn
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (tid == 0)
-    sCount = __hip_atomic_fetch_add(cv.qcnt + p, kTicket + (unsigned long long)tokens, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (tid == 0) {
+    sTicket = (int)__hip_atomic_fetch_add(cv.tickets + p, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    sCount = count;
+  }
   __syncthreads();
-  const int n_wgs = a.nq + nk;
-  const unsigned long long before = sCount;
-  if ((int)(before / kTicket) != n_wgs - 1) return;
+  if (sTicket != a.nq + nk - 1) return;
   // ---- the pair's last workgroup: all sums and partial ranges are there; the ticket goes back to 0 ----
-  if (tid == 0) __hip_atomic_fetch_sub(cv.qcnt + p, (unsigned long long)n_wgs * kTicket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  const unsigned long long count = before % kTicket + (unsigned long long)tokens;
+  if (tid == 0) {
+    __hip_atomic_fetch_sub(cv.tickets + p, (unsigned long long)(a.nq + nk), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (added) __hip_atomic_fetch_add(cv.qcnt + p, added, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
   unsigned long long sum = 0ull;
   if (tid < kD) sum = load_agent(cv.qacc + (size_t)p * kD + tid);
   {
@@ -252,7 +262,7 @@ __global__ void __launch_bounds__(kStreamThreads) select_kernel(CacheView cv, Se
     sA[tid] = cv.cfg.score_mode ? (double)rng : (double)sum * (double)rng;
   }
   __syncthreads();
-  const int tier = rank_channels(cv.cfg, count, sA, sPart);      // (threads 0..127: of their channel)
+  const int tier = rank_channels(cv.cfg, sCount, sA, sPart);      // (threads 0..127: of their channel)
   // positions inside the tiers: ballots over the two wavefronts that hold the channels
   const unsigned long long m1 = __ballot(tier == 1), m2 = __ballot(tier == 2);
   unsigned long long* sMask = reinterpret_cast<unsigned long long*>(smem);      // the first wavefront's two ballots
@@ -292,7 +302,7 @@ static hipError_t launch_select_kernel(const CacheView& v, SelectArgs a, hipStre
   while ((int64_t)v.g * pieces(a.Lq, a.rows_q) > 32768 && a.rows_q < kMaxExactRows) a.rows_q *= 2;
   a.nq = v.g * pieces(a.Lq, a.rows_q);
   a.part = reinterpret_cast<unsigned*>(v.ws + (size_t)v.P * kD);
-  // as many partial ranges as the workspace has room for (at least four per pair), and as a ticket can count
+  // as many partial ranges as the workspace has room for (at least four per pair), and as the grid takes
   int64_t room = (v.ws_bytes - (int64_t)v.P * kD) / ((int64_t)v.P * kRangePartBytes);
   room = room < 16384 ? room : 16384;
   int64_t rows = rows_per_workgroup(v.P, a.LA + a.LB);
