@@ -805,11 +805,7 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
                                      value_channel<NVG>(xp, qq, n);
           a[e] = (unsigned)cp[0] | ((unsigned)cp[kVStride / 2] << 16);
         }
-        f32x4 t = mfma(a, Bp, f32x4{0.f, 0.f, 0.f, 0.f});
-        if (role) {      // a value that is infinite must not meet a remainder of the other sign, or 0: the head alone decides
-#pragma unroll
-          for (int i = 0; i < 4; ++i) t[i] = fminf(fmaxf(t[i], -3e38f), 3e38f);
-        }
+        const f32x4 t = mfma(a, Bp, f32x4{0.f, 0.f, 0.f, 0.f});
         // the block loop accumulates sum p' c 4^sc 2^-24 = 2^(kPBoost-24) sum p c and is scaled back at the end
         O[xp][qq] = t * (5.9604644775390625e-8f * (float)(1 << kPBoost) / (float)(1 << kWBoost));
       }
