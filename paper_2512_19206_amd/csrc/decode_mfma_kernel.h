@@ -233,8 +233,13 @@ __device__ __forceinline__ void store_output4(__half* out, float* lse, size_t bh
     const float x = l > 0.f ? o[i] / l : 0.f;      // l == 0: a sequence without tokens
     r[i] = bf16 ? f32_to_bf16_bits(x) : __half_as_ushort(__float2half_rn(x));
   }
-  *reinterpret_cast<uint2*>(reinterpret_cast<unsigned short*>(out) + bh * kD + 4 * c4) =
-      make_uint2(r[0] | ((unsigned)r[1] << 16), r[2] | ((unsigned)r[3] << 16));
+  unsigned short* dst = reinterpret_cast<unsigned short*>(out) + bh * kD + 4 * c4;
+  if ((reinterpret_cast<uintptr_t>(out) & 7u) == 0) {
+    *reinterpret_cast<uint2*>(dst) = make_uint2(r[0] | ((unsigned)r[1] << 16), r[2] | ((unsigned)r[3] << 16));
+  } else {      // (the caller's tensor may start at any element)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) dst[i] = r[i];
+  }
   // (sum first: nothing for the compiler to contract, so that both forms of the merge give the same bits; l >= 1/2)
   if (lse && c4 == 0) lse[bh] = l > 0.f ? (m + __builtin_amdgcn_logf(l)) * 0.6931471805599453f : -INFINITY;
 }
