@@ -15,7 +15,8 @@ namespace mixkvq {
 
 constexpr int kFlushThreads = 256;
 constexpr int64_t kWideBlocks = 128;       // up to this many records of 128 tokens per launch the workgroups have 512 threads
-constexpr int64_t kSplitBlocks = 2048;     // up to this many blocks per launch the keys and the values of a block are two workgroups
+// up to this many blocks per launch the keys and the values of a block are two workgroups
+constexpr int64_t split_blocks(int R) { return R == kMaxR ? 2048 : 1408; }
 constexpr int kRowPad = 8;                 // halfs of padding per LDS row (keeps 16-byte alignment)
 constexpr int kRowStride = kD + kRowPad;   // 136 halfs = 272 bytes
 
@@ -383,7 +384,10 @@ __device__ __forceinline__ uint4 load_chunk(const __half* res_p, const __half* f
 // nothing, and where the grid does not fill the chip the time is one workgroup's chain of phases.  Once it is full several
 // times over the fused form is the better one: it overlaps the keys' arithmetic with the values' loads.  Fused / split at
 // R = G = 128 and 12 fp16 channels: 32 to 256 blocks 13.1-13.9 / 8.8-9.2 us, 512: 16.9 / 16.8, 1 024: 31.3 / 28.1, 2 048:
-// 49.5 / 47.7, 3 072: 66.8 / 67.5, 4 096: 93.0 / 96.7.
+// 49.5 / 47.7, 3 072: 66.8 / 67.5, 4 096: 93.0 / 96.7.  Smaller records have less arithmetic to overlap and the line lies
+// lower.  1 280, 1 408, 1 536 and 2 048 blocks of 96 tokens 29.1 / 28.6, 31.3 / 30.8, 32.2 / 32.8, 41.0 / 41.8; of 64 tokens
+// 24.1 / 24.0, 25.6 / 25.8, 26.1 / 27.2, 33.6 / 34.8, scored under thresholds 32.2 / 31.8, 35.8 / 34.5, 36.2 / 37.1, 46.6 / 47.4;
+// of 32 tokens 19.1 / 19.0, 20.0 / 20.2, 20.4 / 21.6, 27.0 / 28.5; of 16 tokens 17.4 / 17.5, 17.7 / 18.6, 18.3 / 20.0, 24.4 / 25.6.
 // NT: 512 threads halve the serial work of a phase, but one such workgroup fills a compute unit (registers, LDS), so only
 // where the grid is at most one per unit: 256 / 512 threads at 128-token records with 16 4-bit channels 8.0 / 7.7 us at 32
 // blocks, 8.8 / 8.2 at 128, 8.7 / 10.6 at 160; scored under thresholds, groups of 32: 13.0 / 12.2, 13.3 / 12.4, 13.5 / 12.7
@@ -854,7 +858,7 @@ static void launch_blocks(const CacheView& v, const __half* k_new, const __half*
   else if (v.cfg.R == kMaxR && (int64_t)n_pairs * nf <= kWideBlocks)
     flush_block_fast_kernel<true, 512><<<dim3(n_pairs, nf + wc.wgs, 2), dim3(512), 0, s>>>(v, k_new, v_new, kvs, r0, first_block,
                                                                                           sel, list, wc);
-  else if ((int64_t)n_pairs * nf <= kSplitBlocks)
+  else if ((int64_t)n_pairs * nf <= split_blocks(v.cfg.R))
     flush_block_fast_kernel<true, 256><<<dim3(n_pairs, nf + wc.wgs, 2), dim3(kFlushThreads), 0, s>>>(v, k_new, v_new, kvs, r0,
                                                                                                first_block, sel, list, wc);
   else

@@ -62,6 +62,33 @@ def test_both_forms_give_the_same_records(H, blocks):
         assert torch.equal(a[:, :5], b[:, :5])
 
 
+@pytest.mark.parametrize("R,blocks", [(64, 1406), (64, 1408), (64, 1410), (16, 1410), (32, 1600), (128, 2050)])
+@pytest.mark.parametrize("first", [0, 7, -1])      # tokens that wait in the window before the call (-1: a full window)
+def test_large_launches_behind_a_window(R, blocks, first):
+    """On either side of the line, and above it with the window read (and then overwritten) by the first block: records,
+    window rows and the selection against the same tokens in pieces far below the line."""
+    import torch
+    import paper_2512_19206_amd as M
+    first = R if first < 0 else first
+    kw = dict(B=1, Hq=2, Hkv=2, D=128, T_max=(blocks // 2 + 2) * R, Gk=min(R, 32), Gv=64, R=R, k4=8, k16=0)
+    gen = torch.Generator(device="cuda").manual_seed(blocks + first)
+    n = first + (blocks // 2) * R + R // 2
+    k = (torch.randn((1, 2, n, 128), generator=gen, device="cuda") * 3).half()
+    v = torch.randn((1, 2, n, 128), generator=gen, device="cuda").half()
+    caches = [M.Cache(M.make_config(**kw)) for _ in range(2)]
+    sel = caches[0].select_channels(k[:, :, :300], k)
+    for c, piece in zip(caches, (n, 5 * R + 3)):
+        cuts = ([0, first] if first else [0]) + list(range(first + piece, n, piece)) + [n]
+        for a, b in zip(cuts, cuts[1:]):
+            c.quantize_append(k[:, :, a:b], v[:, :, a:b], sel=sel)
+    assert caches[0].state() == caches[1].state()
+    nq, r = caches[0].state()
+    assert nq // R >= blocks // 2 and r > 0
+    assert torch.equal(caches[0].block_records()[:, :nq // R], caches[1].block_records()[:, :nq // R])
+    for x, y in zip(caches[0].residual(), caches[1].residual()):
+        assert torch.equal(x[:, :r], y[:, :r])
+
+
 @pytest.mark.parametrize("per_pair", [15, 16, 17])      # 120, 128 and 136 records in a launch of 8 pairs
 @pytest.mark.parametrize("kw", [
     dict(Gk=128, Gv=128, R=128, k4=16, k16=0),
