@@ -585,6 +585,9 @@ int mixkvq_decode_step(mixkvq_cache* c, const void* k_new, const void* v_new, co
   memcpy(before, c->seq, sizeof(SeqState) * cfg.B);
   rc = n_flush > 0 ? flush_full_windows(c, equal, s) : MIXKVQ_OK;
   if (rc == MIXKVQ_OK) {
+    // blocks that have left their windows stay packed if the attention launch fails (packed again, they would be scored with
+    // accumulators that may have been cleared); only the token is not in then
+    if (n_flush > 0) memcpy(before, c->seq, sizeof(SeqState) * cfg.B);
     for (int b = 0; b < cfg.B; ++b) {
       SeqState& st = c->seq[b];
       (st.n_sink < cfg.sink ? st.n_sink : st.n_res) += 1;

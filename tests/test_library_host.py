@@ -164,3 +164,16 @@ def test_host_state_machine_under_address_and_undefined_behaviour_sanitizers(M, 
     assert r.returncode == 0, r.stdout + r.stderr
     assert "host shim driver: ok" in r.stdout
     assert "runtime error" not in r.stderr and "AddressSanitizer" not in r.stderr, r.stderr
+
+
+def test_what_a_decode_step_keeps_when_its_launches_fail(M, tmp_path):
+    """csrc/api.hip against launchers that fail on demand (tests/host_launch_stub.cpp)."""
+    import subprocess
+    from paper_2512_19206_amd import build as B
+    exe = str(tmp_path / "host_launch_stub")
+    cmd = [B.hipcc_path(), "-O1", "-std=c++17", "--offload-arch=gfx950", "-I", os.path.join(ROOT, "include"), "-I", B.CSRC,
+           "-x", "hip", os.path.join(B.CSRC, "api.hip"), os.path.join(ROOT, "tests", "host_launch_stub.cpp"), "-o", exe]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout + r.stderr
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and "host launch stub: ok" in r.stdout, r.stdout + r.stderr
