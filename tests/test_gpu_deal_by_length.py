@@ -62,6 +62,47 @@ def test_a_batch_equals_its_sequences(Hkv, g, lens, paged, over):
                 assert torch.equal(x[b * Hkv:(b + 1) * Hkv, :n], y[:, :n]), (step, b)
 
 
+@pytest.mark.parametrize("Hkv,g,lens,paged,over", [
+    (2, 2, (4500, 40, 700, 1250, 129), False, dict(R=32, Gk=32, Gv=32, k4=16, k16=0)),
+    (4, 7, (2900, 130, 64, 1500, 257), True, dict(R=128, Gk=128, Gv=128, k4=16, k16=0)),
+    (2, 5, (2000, 5, 400), False, dict(R=128, Gk=32, Gv=32, k4=16, k16=8, sink=128)),
+    (1, 3, (5000, 255, 513), False, dict(R=256, Gk=128, Gv=128, k4=0, k16=12, sink=96)),
+])
+def test_a_batch_against_the_oracle(Hkv, g, lens, paged, over):
+    """The same kind of batch at the plain bar: every sequence against an oracle cache of its own."""
+    import gpu_common as H
+    import paper_2512_19206_amd as M
+    from oracle import mixkvq_oracle as O
+    rng = np.random.default_rng(8000 + Hkv * 10 + g)
+    B, R = len(lens), over["R"]
+    kw = dict(Hq=Hkv * g, Hkv=Hkv, D=128, T_max=-(-(max(lens) + 3) // R) * R, **over)
+    gc = M.Cache(M.make_config(B=B, **kw))
+    if paged:
+        slots = B * (gc.cfg.T_max // gc.rec_tokens)
+        gc.set_block_table(H.dev(rng.permutation(slots).astype(np.int32)).view(B, -1).contiguous())
+    scale, ocs = rng.uniform(0.3, 4.0, 128), []
+    draw = lambda *s: rng.standard_normal(s).astype(np.float16)
+    for b, n in enumerate(lens):
+        K, V, Q = (draw(1, Hkv, n, 128) * scale).astype(np.float16), draw(1, Hkv, n, 128), draw(1, Hkv * g, 16, 128)
+        ocs.append(O.OracleCache(O.OracleConfig(B=1, **kw)))
+        ref = ocs[-1].select_channels(Q, K)
+        sel = gc.select_channels_seq(b, H.dev(Q[0]), H.dev(K[0]))
+        assert np.array_equal(sel.cpu().numpy(), ref[0])
+        gc.quantize_append_seq(b, H.dev(K[0]), H.dev(V[0]), sel=sel)
+        ocs[-1].append(K, V, ref)
+    for _ in range(2):
+        k, v, q = (draw(B, Hkv, 1, 128) * scale).astype(np.float16), draw(B, Hkv, 1, 128), draw(B, Hkv * g, 128)
+        out, lse = gc.decode_step(H.dev(k), H.dev(v), H.dev(q), accumulate_q=True)
+        torch.cuda.synchronize()
+        assert gc.decode_path() == M.PATH_MATRIX
+        out, lse = out.float().cpu().numpy(), lse.cpu().numpy()
+        for b, oc in enumerate(ocs):
+            oc.append(k[b:b + 1], v[b:b + 1])
+            ro, rl = oc.decode_attention(q[b:b + 1], accumulate_q=True)
+            assert np.all(np.abs(out[b] - ro[0]) <= H.ATOL + H.RTOL * np.abs(ro[0])), b
+            assert np.all(np.abs(lse[b] - rl[0]) <= H.LSE_ATOL + 1e-4 * np.abs(rl[0])), b
+
+
 def test_an_empty_sequence_among_long_ones():
     import paper_2512_19206_amd as M
     gen = torch.Generator(device="cuda").manual_seed(5)

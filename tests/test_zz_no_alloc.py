@@ -64,6 +64,42 @@ def test_vector_alu_kernel_and_window_only():
     _compare(gc2, q)
 
 
+@pytest.mark.parametrize("k4,k16,thresholds", [(16, 0, False), (0, 12, False), (16, 8, True)])
+def test_sequences_of_different_lengths(k4, k16, thresholds):
+    """The workgroups of such a batch are dealt equally here and by length with the workspace, so the orders of the sums
+    differ: within twice the bar of each other, and each sequence as in a cache of its own (one of them empty)."""
+    rng = np.random.default_rng(31 + k16)
+    lens, Hkv, g = (3000, 70, 0, 1500, 129, 640), 2, 7
+    kw = dict(Hq=Hkv * g, Hkv=Hkv, D=128, T_max=3072, Gk=128, Gv=128, R=128, k4=k4, k16=k16)
+    if thresholds:
+        kw.update(policy=1, tau16=5.0, tau4=2.0)
+    gc = M.Cache(M.make_config(B=len(lens), **kw))
+    alone = [M.Cache(M.make_config(B=1, **kw)) for _ in lens]
+    for b, n in enumerate(lens):
+        if n:
+            K = dev((rng.standard_normal((Hkv, n, 128)) * rng.uniform(0.3, 6, 128)).astype(np.float16))
+            V = dev(rng.standard_normal((Hkv, n, 128)).astype(np.float16))
+            Q = dev(rng.standard_normal((Hkv * g, 16, 128)).astype(np.float16))
+            for c, i in ((gc, b), (alone[b], 0)):
+                sel = c.select_channels_seq(i, Q, K)
+                c.quantize_append_seq(i, K, V, sel=None if thresholds else sel)
+    q = dev(rng.standard_normal((len(lens), Hkv * g, 128)).astype(np.float16))
+    near = lambda a, r: bool(((a.float() - r.float()).abs() <= 2 * (ATOL + RTOL * r.float().abs())).all())
+    near_lse = lambda a, r: bool(((a - r).abs() <= 2 * (LSE_ATOL + 1e-4 * r.abs())).all())
+    for _ in range(2):
+        ref, ref_lse = M.mixkvq_decode_attention(gc, q)
+        out, lse = torch.full_like(ref, float("nan")), torch.full_like(ref_lse, float("nan"))
+        M.mixkvq_decode_attention_noalloc(gc, q, out, lse)
+        torch.cuda.synchronize()
+        full = [b for b, n in enumerate(lens) if n]
+        assert near(out[full], ref[full]) and near_lse(lse[full], ref_lse[full])
+        assert bool((out[2] == 0).all()) and bool((lse[2] == -np.inf).all())
+        for b in full:
+            o1, l1 = M.mixkvq_decode_attention(alone[b], q[b:b + 1])
+            assert near(out[b:b + 1], o1) and near_lse(lse[b:b + 1], l1)
+    assert gc.decode_path() == M.PATH_MATRIX
+
+
 def test_too_large_a_launch_is_refused_and_an_empty_cache_reported():
     lib = M.load_library()
     # 4096 pairs of 8 query heads each: 4096 x 1 split x 8 x 130 floats = 17 MB of partials
