@@ -33,6 +33,8 @@ bool try_launch_decode_mfma(const CacheView& v, const __half* q, float scale, in
   // their binary16 remainder; rounded to binary16 alone the outputs were 1.1e-4 apart).
   const int rh = c.R == 32 && c.Gk == 32;
   if ((c.R % 64 != 0 && !rh) || (c.Gk % 64 != 0 && c.Gk != 32) || (c.Gv % 64 != 0 && c.Gv != 32)) return false;
+  // (queries that do not start on 8 bytes, which this kernel reads at a time, stay with the vector-ALU path there)
+  if (n_blocks < 1 && (reinterpret_cast<uintptr_t>(q) & 7u)) return false;
   if (v.lay.off_v > kKPartMax || v.lay.rec_bytes - v.lay.off_v_s > kVMetaMax) return false;
   const int nvg = v.lay.NVG;
   const int nkl = (v.lay.off_v / 16 + 63) / 64;
