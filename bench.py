@@ -251,10 +251,10 @@ def bench_prefill(args, w, cfg_id):
     in_b, out_b = prefill_bytes(w, Lq)
     in_noq = in_b - w.B * w.Hq * Lq * w.D * 2
     value = in_b / el / 1e9
-    # measured HBM bytes of the step's three streaming kernels (the full-size workload only: that is what was profiled)
+    # measured HBM bytes of the step's two streaming kernels (the full-size workload only: that is what was profiled)
     traffic = None
     if w == S.WORKLOADS[cfg_id]:
-        parts = [measured_traffic(w.name, k) for k in ("qabs_accumulate_kernel", "key_range_kernel", "flush_block_fast_kernel")]
+        parts = [measured_traffic(w.name, k) for k in ("select_kernel", "flush_block_fast_kernel")]
         if all(x is not None for x in parts):
             traffic = round(sum(parts), 1)
     result = {
@@ -270,7 +270,7 @@ def bench_prefill(args, w, cfg_id):
         "per_block_selection": {"ms_per_step": round(el_pb * 1e3, 4), "value": round(in_b / el_pb / 1e9, 2), "unit": "GB/s",
                                 "note": "same calls, but every block is scored on its own tokens inside the pack kernel "
                                         "(sel = NULL) instead of using the selection made over the whole prompt"},
-        "roofline": {"bound": "hbm", "kernel": "whole step (qabs_accumulate, key_range, flush_block: streaming kernels)",
+        "roofline": {"bound": "hbm", "kernel": "whole step (select, flush_block: streaming kernels)",
                      "achieved": round((in_b + out_b) / el / 1e9, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round((in_b + out_b) / el / 1e9 / HBM_PEAK_GBS, 4), "traffic": traffic},
     }

@@ -209,7 +209,7 @@ int mixkvq_quantize_append_seq(mixkvq_cache* c, int32_t b, const void* k_new, co
 
 /* One query token per sequence (Section 3.1, Eq. 1, over keys/values dequantized by Eq. 3).
  *   q    DEVICE fp16 [B][Hq][D] contiguous;  out DEVICE fp16 [B][Hq][D];  lse DEVICE fp32 [B][Hq] or NULL
- *        (natural-log sum of exp of the scaled logits).
+ *        (natural-log sum of exp of the scaled logits).  out may start at any element.
  *   scale <= 0 means 1/sqrt(D).  accumulate_q != 0 also adds |q| to the accumulator (Appendix D.2).
  * EEMPTY if the cache holds no token.  When the sequences differ in length each attends over its own tokens (at most
  * 256 sequences then, else EINVAL); a sequence without tokens gets out = 0 and lse = -inf and its |q| is not accumulated. */
@@ -230,16 +230,18 @@ int mixkvq_decode_attention_noalloc(mixkvq_cache* c, const void* q, void* out, f
 /* One decode step in the fewest launches: the same result and cache state as
  * mixkvq_quantize_append(c, k_new, v_new, 1, kv_strides, NULL, stream) followed by
  * mixkvq_decode_attention(c, q, out, lse, scale, accumulate_q, stream), with the same argument rules and
- * errors (Appendix D.1: the new key/value enter the residual buffer; Eq. 1 over the cache).  When the append
- * flushes no block, the attention launch moves the new rows into the window itself. */
+ * errors (Appendix D.1: the new key/value enter the residual buffer; Eq. 1 over the cache).  Unless an eager flush packs
+ * the new token itself, the attention launch moves the new rows into the sink or the window, behind the launches that pack
+ * the windows a deferred flush empties (one launch for all sequences where a block is one record).  If the attention launch
+ * fails after those (EHIP), the packed blocks stay packed and the new token is not appended. */
 int mixkvq_decode_step(mixkvq_cache* c, const void* k_new, const void* v_new, const int64_t kv_strides[3],
                        const void* q, void* out, float* lse, float scale, int32_t accumulate_q, void* stream);
 
 /* Profiling aid.  With a pair of hipEvent_t handles (HOST, created by the caller with timing enabled), every
  * following mixkvq_decode_attention / mixkvq_decode_step on this cache makes start_event and stop_event take the start
- * and the end time of its split-K attention kernel (the kernel's own time stamps, as a profiler reports them; with the
- * vector-ALU fallback kernel the events are recorded in the stream just before and after it).  Pass NULL, NULL to
- * switch it off. */
+ * and the end time of its split-K attention kernel, which also merges the splits (the kernel's own time stamps, as a
+ * profiler reports them; with the vector-ALU fallback kernel, whose merge is a launch of its own, the events are recorded
+ * in the stream just before and after it).  Pass NULL, NULL to switch it off. */
 int mixkvq_set_timing_events(mixkvq_cache* c, void* start_event, void* stop_event);
 
 /* Profiling aid: which kernel the last mixkvq_decode_attention / mixkvq_decode_step on this cache launched.

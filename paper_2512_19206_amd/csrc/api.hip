@@ -577,7 +577,7 @@ int mixkvq_decode_step(mixkvq_cache* c, const void* k_new, const void* v_new, co
   // Deferred: the full windows leave first; the new token of every sequence then goes to its next fp16 row (of the
   // sink or of the window), which the attention launch does itself, whether the sequences have equal lengths or not.
   // (Appending sequence by sequence costs one 2.5 us launch per run of equal states: 24 sequences of 60 to 12 003
-  // tokens took 101 us per step that way, 31 us now.)
+  // tokens took 101 us per step that way, 21 now.)
   hipStream_t s = (hipStream_t)stream;
   MIXKVQ_TRY_HIP(clear_tickets(c, s));
   SeqState* before = new (std::nothrow) SeqState[cfg.B];

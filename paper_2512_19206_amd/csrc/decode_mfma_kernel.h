@@ -209,7 +209,8 @@ struct HalfSplit {
 // The last workgroup of a pair to finish merges it (see CacheView::tickets).  The partials, the ticket and the
 // loads are agent-scope accesses, which go past the chip's eight L2 caches; no cache is flushed for them.  A launch of
 // its own for the merge costs what any dependent launch costs, whatever it does: 28.6 us per step instead of 24.1 at
-// 32 pairs of 32 805 tokens (16 partials each), 12.9 instead of 10.1 for one pair of 1 027 tokens (32 partials).
+// 32 pairs of 32 805 tokens (16 partials each), 12.9 instead of 10.1 for one pair of 1 027 tokens (32 partials then; at
+// most 9 since no workgroup goes without a record).
 // The loads of a separate merge launch (SHARED = false: callers without ticket memory) are plain ones; the arithmetic
 // is the same.
 // ---------------------------------------------------------------------------
@@ -368,8 +369,9 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
   int my_sub = gw - first_sub_gw;
   if (my_sub < 0) my_sub += n_gw;
   if (my_sub >= n_sub) my_sub = -1;
-  // one wavefront per pair (the next in the deal, never one with a sub-unit unless the pair has a single
-  // workgroup) stores this step's new token and adds |q| to the accumulator
+  // one wavefront per pair (the next in the deal: one without a sub-unit unless every wavefront of the pair has one) stores
+  // this step's new token and adds |q| to the accumulator; the sub-unit of that token reads it from the caller's tensors, so
+  // neither waits for the other
   const bool bookkeeper =
       (first_sub_gw + n_sub >= n_gw ? first_sub_gw + n_sub - n_gw : first_sub_gw + n_sub) == gw && !skip_pair;
 

@@ -392,6 +392,8 @@ __device__ __forceinline__ uint4 load_chunk(const __half* res_p, const __half* f
 // where the grid is at most one per unit: 256 / 512 threads at 128-token records with 16 4-bit channels 8.0 / 7.7 us at 32
 // blocks, 8.8 / 8.2 at 128, 8.7 / 10.6 at 160; scored under thresholds, groups of 32: 13.0 / 12.2, 13.3 / 12.4, 13.5 / 12.7
 // and 13.5 / 15.2 at 192.  Records of 64 or 32 tokens gain nothing (6.8 / 6.7, 6.6 / 6.9 at 64 blocks).
+// (9 chunks of 1 000 tokens, 8 pairs, scored under thresholds: 241 us with 256 threads, 226 with 512; that what decides the
+// tiers is asked for ahead of the tile changes nothing by itself: 241.6.)
 // Rows blockIdx.y >= gridDim.y - wc.wgs copy the tokens that stay behind in the window (WindowCopy).
 template <bool SPLIT, int NT>
 __global__ void __launch_bounds__(NT, NT == 256 ? 3 : 2)   // 256: three workgroups per CU (LDS) = three wavefronts per SIMD; 512: one

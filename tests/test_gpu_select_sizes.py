@@ -1,7 +1,6 @@
 """Scoring and selection run as one launch whose workgroups take pieces of the queries and of the keys: lengths around
 its passes of 16 rows, batches of eight loads and pieces of 256 rows, rows of any alignment, one sequence of a batch, and
-the count that a pair's workgroups draw tickets from (exact again after every call).  Everything is compared with the
-oracle as whole numbers."""
+the |q| counts (exact after every call).  Everything is compared with the oracle as whole numbers."""
 import numpy as np
 import pytest
 import torch
