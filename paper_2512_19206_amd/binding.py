@@ -177,10 +177,13 @@ class Cache:
     def restore(self, snap):
         """Takes a snapshot of a cache of the same configuration back in."""
         bufs, states = snap
-        for dst, src in zip((self.blocks, self.res_k, self.res_v, self.qacc, self.workspace), bufs):
+        # the accumulator ends with the words by which a running call counts its workgroups: a call may have been running when
+        # the copy was taken, and a snapshot written before there were such words ends ahead of them
+        used = self.cfg.B * self.cfg.Hkv * (self.cfg.D + 1) * 8
+        qacc = self.qacc[:-(-used // 256) * 256] if bufs[3].numel() == -(-used // 256) * 256 else self.qacc
+        for dst, src in zip((self.blocks, self.res_k, self.res_v, qacc, self.workspace), bufs):
             dst.copy_(src)
-        # (the words by which a running call counts its workgroups: a call may have been running when the copy was taken)
-        self.qacc[self.cfg.B * self.cfg.Hkv * (self.cfg.D + 1) * 8:].zero_()
+        self.qacc[used:].zero_()
         if all(st == states[0] for st in states):
             _check(self.lib.mixkvq_cache_set_state(self.handle, *states[0]))
         else:

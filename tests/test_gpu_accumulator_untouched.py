@@ -75,8 +75,10 @@ def test_a_handle_that_was_never_reset(H):
         H.check_attention(oc, gc, q)
 
 
-def test_snapshot_taken_while_a_call_runs(H):
-    """Such a copy of the qacc buffer holds a number of workgroups behind the counts."""
+@pytest.mark.parametrize("older", [0, 1])
+def test_snapshot_taken_while_a_call_runs(H, older):
+    """Such a copy of the qacc buffer holds a number of workgroups behind the counts.  older: a snapshot that ends ahead of
+    those words."""
     rng = np.random.default_rng(7820)
     oc, gc = H.make_pair(**KW)
     K, V, q = _tensors(rng, 128 * 9 + 50)
@@ -84,8 +86,10 @@ def test_snapshot_taken_while_a_call_runs(H):
     oc.append(K, V)
     H.check_attention(oc, gc, q)
     bufs, states = gc.snapshot()
-    bufs[3][3 * 2 * 129 * 8:].fill_(1)
-    gc.restore((bufs, states))
+    used = 3 * 2 * 129 * 8
+    bufs[3][used:].fill_(1)
+    gc.qacc.fill_(0x55)
+    gc.restore((bufs[:3] + [bufs[3][:-(-used // 256) * 256]] + bufs[4:] if older else bufs, states))
     for _ in range(2):
         H.check_attention(oc, gc, q)
     H.check_state(oc, gc)
