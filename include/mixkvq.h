@@ -152,9 +152,10 @@ int mixkvq_cache_state_seq(const mixkvq_cache* c, int32_t b, int64_t* n_quantize
  * snapshot is a copy of the buffers and of what mixkvq_cache_state(_seq) reports; to resume, copy the buffers back
  * (into the same or another cache of the same configuration, with the same block table if one is in use) and set the
  * counts here.  (A copy of the qacc buffer that was taken while an attention or selection call was running: set the words
- * behind the counts to 0 after copying it back, see mixkvq_sizes.)  Host-only.  EINVAL for counts that no sequence of appends produces (n_quantized a multiple of R up to
- * T_max; n_residual 1..R with the deferred flush once anything was flushed, 0..R-1 with the eager one; the window
- * empty until the sink is full).  Appendix D.1 describes the cache as exactly this state. */
+ * behind the counts to 0 after copying it back, see mixkvq_sizes.)  Host-only.  EINVAL for counts that no sequence of
+ * appends produces (n_quantized a multiple of R up to T_max; n_residual 1..R with the deferred flush once anything was
+ * flushed, 0..R-1 with the eager one; the window empty until the sink is full).  Appendix D.1 describes the cache as
+ * exactly this state. */
 int mixkvq_cache_set_state(mixkvq_cache* c, int64_t n_quantized, int32_t n_residual, int32_t n_sink);
 int mixkvq_cache_set_state_seq(mixkvq_cache* c, int32_t b, int64_t n_quantized, int32_t n_residual, int32_t n_sink);
 

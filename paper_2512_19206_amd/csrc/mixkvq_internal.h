@@ -63,9 +63,10 @@ struct CacheView {
   __half* res_v;
   unsigned long long* qacc;  // [P][D]
   unsigned long long* qcnt;  // [P]
-  // [P] from the next multiple of 256 bytes behind the counts on: the pair's workgroups of a running launch draw their numbers from it, and the one that draws the
-  // last knows that the others are done; 0 between launches.  (Words of their own: a call that only reads the accumulator
-  // must not change it while it runs, and the workspace may serve several caches in turn, so nothing in it outlives a call.)
+  // [P] from the next multiple of 256 bytes behind the counts on: the pair's workgroups of a running launch draw their numbers
+  // from it, and the one that draws the last knows that the others are done; 0 between launches.  (Words of their own: a call
+  // that only reads the accumulator must not change it while it runs, and the workspace may serve several caches in turn, so
+  // nothing in it outlives a call.  On the counts' cache line they cost a selection of 1 531 tokens 0.5 us of 10.)
   unsigned long long* tickets;
   uint8_t* ws;
   int64_t ws_bytes;      // bytes of the workspace (of the whole cache, also in a view of some sequences)
