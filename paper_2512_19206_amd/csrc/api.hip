@@ -231,7 +231,8 @@ static bool decode_counts(const mixkvq_cache* c, int* n_blocks, int* n_fp16, Seq
     for (int b = 0; b < cfg.B; ++b) {
       const SeqState& st = c->seq[b];
       sc->n_blocks[b] = (int)(st.n_quant / cfg.R);
-      sc->n_fp16[b] = (uint16_t)(st.n_sink + st.n_res);
+      const uint32_t nf = (uint32_t)(st.n_sink + st.n_res);
+      sc->n_fp16[b >> 1] = (b & 1) ? (sc->n_fp16[b >> 1] & 0xffffu) | (nf << 16) : nf;
     }
   }
   return true;

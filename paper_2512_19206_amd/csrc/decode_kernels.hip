@@ -42,7 +42,7 @@ decode_split_kernel(CacheView cv, const __half* __restrict__ q, float scale, int
   const int b = p / cfg.Hkv, j = p % cfg.Hkv;
   if (sc.enabled) {      // sequences of different lengths: this pair's own counts
     n_blocks = sc.n_blocks[b];
-    n_fp16 = sc.n_fp16[b];
+    n_fp16 = fp16_rows_of(sc, b);
   }
   const int lane_lo = tid & (kD - 1), half = tid >> 7;   // role index and head half
   const int h0 = half * 4;                               // heads h0 .. h0+3 (< g)
@@ -214,7 +214,7 @@ __global__ void __launch_bounds__(kD) token_books_kernel(CacheView cv, const __h
   const bool bf16 = cv.cfg.in_dtype != 0;
   if (sc.enabled) {
     n_blocks = sc.n_blocks[b];
-    n_fp16 = sc.n_fp16[b];
+    n_fp16 = fp16_rows_of(sc, b);
   }
   if (nt.k && tid < 32) {      // 16 threads for the key row, 16 for the value row
     const int64_t src = (int64_t)b * nt.st.b + (int64_t)j * nt.st.h + (tid & 15) * 8;
@@ -301,7 +301,7 @@ static void deal_by_length(const CacheView& v, int n_splits, SeqCounts* sc) {
   if (budget > B * max_splits_for(v.P)) budget = B * max_splits_for(v.P);
   if (budget > kMaxUnits) return;
   auto units_of = [&](int b, int chain) {
-    const int subs = (sc->n_fp16[b] + 31) / 32, least = (subs + 3) / 4;
+    const int subs = (fp16_rows_of(*sc, b) + 31) / 32, least = (subs + 3) / 4;
     int n = (sc->n_blocks[b] + subs + 4 * chain - 1) / (4 * chain);
     if (n > kMaxSplits) n = kMaxSplits;
     if (n < least) n = least;
@@ -314,7 +314,7 @@ static void deal_by_length(const CacheView& v, int n_splits, SeqCounts* sc) {
   };
   int most = 1;
   for (int b = 0; b < B; ++b) {
-    const int n = sc->n_blocks[b] + (sc->n_fp16[b] + 31) / 32;
+    const int n = sc->n_blocks[b] + (fp16_rows_of(*sc, b) + 31) / 32;
     most = n > most ? n : most;
   }
   int lo = 1, hi = (most + 4 * n_splits - 1) / (4 * n_splits);      // (the equal deal's chain always fits)

@@ -34,6 +34,7 @@ namespace mixkvq {
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kMfmaThreads = 256;
 constexpr int kComputeUnits = 256;              // MI355X
@@ -42,7 +43,7 @@ constexpr int kKPartMax = 12288;                // bytes of a record before the 
 constexpr int kVMetaMax = 2048;                 // value scales + zero-points of one block
 constexpr int kQsStride = 168;                  // halfs per head row of the slot-ordered q table (160 slots + padding)
 constexpr int kQsBytes = 8 * kQsStride * 2;
-constexpr int kWaveLds = kKPartMax + kVMetaMax + 256 + kQsBytes;   // + a spare 256 bytes + slot-ordered q
+constexpr int kWaveLds = kKPartMax + kVMetaMax + 256 + kQsBytes;   // + tier marks of the channels + slot-ordered q
 constexpr int kHdrLds = 2048 + 256 + 2048;      // q as given [8][128], exponents and wave maxima, normalised q transposed [128][8]
 constexpr int kPartStrideM = kD + 2;
 constexpr int kPBoost = 8;                      // softmax weights go to the matrix cores as p * 2^kPBoost (see mfma_part)
@@ -100,6 +101,17 @@ __device__ __forceinline__ float xkg_sum(float v) {
   auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
+// max over 32 neighbouring lanes, without a trip through LDS
+__device__ __forceinline__ float half_wave_max(float v) {
+#define MIXKVQ_DPP_FMAX(CTRL) v = fmaxf(v, __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), CTRL, 0xF, 0xF, true)))
+  MIXKVQ_DPP_FMAX(0xB1);       // quad_perm [1,0,3,2]
+  MIXKVQ_DPP_FMAX(0x4E);       // quad_perm [2,3,0,1]
+  MIXKVQ_DPP_FMAX(0x141);      // row_half_mirror
+  MIXKVQ_DPP_FMAX(0x140);      // row_mirror
+#undef MIXKVQ_DPP_FMAX
+  auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+}
 // value of lane+8 inside each row of 16 lanes (0 for lanes 8..15)
 __device__ __forceinline__ unsigned row_shl8u(unsigned v) { return __builtin_amdgcn_update_dpp(0u, v, 0x108, 0xF, 0xF, true); }
 // value of lane (i+8)%16 inside each row of 16 lanes
@@ -147,6 +159,24 @@ __device__ __forceinline__ void wave_lds_handoff() {
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
+
+// A record as a buffer: base and size in scalar registers, so that a lane only adds a byte offset that stays the same for
+// the whole kernel, and what lies past the end of the record (or of a record that does not exist: size 0) reads as 0
+// without going to memory.  The loads of a record therefore stand in straight-line code, which lets the compiler wait for
+// exactly those it is about to use; behind a branch it waits for all that are under way (see the record loop).
+typedef __amdgpu_buffer_rsrc_t record_t;
+__device__ __forceinline__ record_t record_at(const unsigned char* base, int bytes) {
+  const unsigned long long a = reinterpret_cast<unsigned long long>(base);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)a);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(a >> 32));
+  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(((unsigned long long)hi << 32) | lo), 0,
+                                           __builtin_amdgcn_readfirstlane(bytes), 0x00020000);      // raw, unstructured
+}
+constexpr int kKeep = 0, kStream = 2;      // cache policy of a load: as usual, or read once (nt)
+template <int POLICY>
+__device__ __forceinline__ u32x4 load16(record_t r, unsigned off) { return __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, POLICY); }
+template <int POLICY>
+__device__ __forceinline__ u32x2 load8(record_t r, unsigned off) { return __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, POLICY); }
 
 // Channel of A-row `row` of the value product (xp, qq), i.e. which value code word a lane holds in element qq of
 // vreg[.][xp].  All 16 rows of one product must share a value group (the small operand carries the group's
@@ -312,24 +342,32 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
             off_v_s = cv.lay.off_v_s;
   const unsigned char* const blocks = cv.blocks;
   const int tid = threadIdx.x;
+  // The arguments the start of the kernel needs are read together: read where each is first used they are four dependent
+  // trips through the scalar cache.
+  asm("" : "+s"(n_splits) : "s"(sc.enabled), "s"(sc.n_units), "s"(n_blocks), "s"(Hq), "s"(Hkv), "s"(cv.cfg.in_dtype),
+               "s"(rec_bytes), "s"(off_idx), "s"(off_v), "s"(off_v_s), "s"(g), "s"(NB), "s"(cv.RW), "s"(blocks), "s"(cv.table),
+               "s"(cv.res_k), "s"(cv.res_v), "s"(cv.qacc), "s"(cv.qcnt), "s"(q), "s"(accumulate_q), "s"(nt.k), "s"(nt.v),
+               "s"(nt.st.b), "s"(nt.st.h));
   int p = blockIdx.x, split = blockIdx.y, part0 = p * n_splits;     // part0: first partial of the pair
   int b = p / Hkv;
-  if (sc.n_units) {      // grid (KV heads, units): the sequences have workgroups by their lengths
-    const int u = blockIdx.y;
-    b = (int)(sc.owner[u >> 2] >> (8 * (u & 3)) & 0xffu);
-    const unsigned span = sc.span[b];
-    n_splits = (int)(span >> 16);
-    split = u - (int)(span & 0xffffu);
-    part0 = (int)(span & 0xffffu) * Hkv + p * n_splits;
-    p += b * Hkv;
-  }
-  const int jkv = p - b * Hkv;
   bool skip_pair = false;
   if (sc.enabled) {      // sequences of different lengths: this pair's own counts; a sequence without tokens is skipped
+    if (sc.n_units) {      // grid (KV heads, units): the sequences have workgroups by their lengths
+      const int u = blockIdx.y;
+      b = (int)(sc.owner[u >> 2] >> (8 * (u & 3)) & 0xffu);
+    }
+    const unsigned span = sc.span[b];
     n_blocks = sc.n_blocks[b];
-    n_res = sc.n_fp16[b];
+    n_res = fp16_rows_of(sc, b);
     skip_pair = n_blocks == 0 && n_res == 0;
+    if (sc.n_units) {
+      n_splits = (int)(span >> 16);
+      split = blockIdx.y - (int)(span & 0xffffu);
+      part0 = (int)(span & 0xffffu) * Hkv + p * n_splits;
+      p += b * Hkv;
+    }
   }
+  const int jkv = p - b * Hkv;
   const int nt_dst = n_res - 1;      // fp16 row of this step's new token (if there is one): the last row in use
   // (the wavefront index is the same in all lanes: as a scalar it keeps record indices and addresses off the vector ALU)
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 15, kg = lane >> 4;
@@ -351,6 +389,7 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
   unsigned char* wbase = smem + kHdrLds + wave * kWaveLds;           // this wave's private region
   unsigned char* sK = wbase;                                        // record bytes [0, NKL KiB)
   unsigned char* sVm = wbase + kKPartMax;                           // v_s, v_z planes
+  unsigned char* sMark = wbase + kKPartMax + kVMetaMax;              // [128] tier marks of a record's channels
   unsigned short* sQs = reinterpret_cast<unsigned short*>(wbase + kKPartMax + kVMetaMax + 256);   // [8][kQsStride]
 
   // Work units of the pair: its block records, then the residual window in sub-units of 32 tokens, dealt
@@ -380,7 +419,6 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
   const int tokbase = (G32 ? 8 : 16) * (n >> 2) + 2 * (n & 3);
   const bool no_tokens = RH && kg >= 2;     // this lane's token group lies past the end of a 32-token record
   const int kgv = no_tokens ? 0 : kg;       // the token group whose value words and scales it reads
-  const int rec_chunks = rec_bytes >> 4;
   const int nvm = (rec_bytes - off_v_s) >> 4;     // 16-byte chunks of the value scale/zero planes
   // LDS byte offsets of this lane's words in token `tokbase` (clamped to existing words)
   // With 8 two-bit words per token a token's row is 32 bytes, and the 16 tokens a lane group reads in one
@@ -388,7 +426,7 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
   // plane (SWZ) is staged with its 16-byte pieces permuted inside every aligned run of four: piece J goes to
   // J ^ ((J >> 5) & 3), i.e. bits 4..5 of the token index are XORed into the two address bits that are the same for
   // all lanes of an instruction; the 64 lanes then cover all banks.
-  constexpr bool SWZ = T::Wlo == 8 && NKL <= 8;     // (variants that stage more pieces have no registers to spare for the permuted piece indices)
+  constexpr bool SWZ = T::Wlo == 8 && NKL <= 8 && !(NVG == 4 && PG == 2 && !G32);     // (variants that stage more pieces have no registers to spare for the permuted piece indices)
   constexpr int kOffx[4] = {0, 1, G32 ? 32 : 8, G32 ? 33 : 9};      // token offsets of the four tiles of a 64-token span
   int lo_word_off[NU][SWZ ? 4 : 1];     // [round][tile] (one entry per round without the permutation)
 #pragma unroll
@@ -425,7 +463,7 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
   // down to 2^-25 of the wavefront's largest weight (2^-17 without).
   // (the variants with the highest register pressure, both side tiers and four value groups, do not keep these eight
   //  constants across the loop, where they would be spilled: they form them where they are used, two instructions each)
-  constexpr bool kLeanConstants = NVG == 4 && K4 > 0 && K16 > 0;
+  constexpr bool kLeanConstants = NVG == 4 && ((K4 > 0 && K16 > 0) || (PG == 2 && !G32 && !RH));
   float sc2f[4];        // 2 sc - kPBoost: exponent offset of p' for pair i
   unsigned w4sc[4];     // fp16 pair (4^sc 2^-kPBoost, same): turns p' back into p for the sum l
 #pragma unroll
@@ -450,6 +488,8 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
   // fp16-tier pairs, zero beyond the tier, as two small operands: q16a is zero in columns 8..15 and q16b in columns
   // 0..7.  A product of tile 0 (1) with q16a and one of tile 2 (3) with q16b into the SAME accumulator leave in
   // every lane the tile its half keeps (lanes 0..7 of a row keep tiles 0 and 1, lanes 8..15 tiles 2 and 3).
+  // (kLeanTier16: without registers to spare one copy is kept and masked where it is used)
+  constexpr bool kLeanTier16 = NVG == 4 && K4 > 0 && K16 > 0 && PG == 2 && !G32 && !RH;
   unsigned q16a[4], q16b[4];
   constexpr int kSelWords = K4 + K16 > 0 ? (K4 + K16 + 3) / 4 : 1;
   unsigned sel_prev[kSelWords];     // wave-uniform: the selection q was last laid out for
@@ -479,104 +519,95 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
 #define MIXKVQ_REC(IDX) (blocks + (size_t)(IDX) * rec_bytes)     // (fewer than 2^31 records: the host checks)
   int slot_cur = 0, slot_nx = 0;
 
-  // Loads of one block.  A record's address is a scalar; every lane adds a 32-bit byte offset that is fixed for
-  // the whole kernel (so the loop spends no vector instruction on addresses).  Chunk indices are clamped to the
-  // record so that every lane loads and stores unconditionally (a clamped lane repeats the record's last chunk).
+  // Loads of one record (REC: a record_t).  Offsets of this lane's pieces: 16-byte piece c * 64 + lane of the key part (an
+  // instruction's own offset reaches four pieces), of the value scale / zero-point planes, and the value words of token group
+  // kgv: channels value_channel(0, 0..3, n).
   // Variants that stage more than 8 KiB of key part, or have four value groups, or both side tiers with key groups of 32
-  // tokens, have no registers to spare for one offset per piece (kept, they are
-  // spilled and reloaded inside the loop, and a reload waits for every record load in flight before it): those form each
-  // offset where it is used, with an add and a minimum, from a copy of the lane's first offset that the compiler
-  // cannot see through (else it would hoist the ten to twelve results out of the loop again).
+  // tokens, have no registers to spare for these (kept, they are spilled): those form all but the lane's first offset where
+  // they are used, from a copy of it that the compiler cannot see through.
   constexpr bool kKeepOffsets = NKL <= 8 && NVG != 4 && !(G32 && K4 > 0 && K16 > 0);
-  unsigned koff[kKeepOffsets ? NKL : 1], vmoff[NVM];
-#pragma unroll
-  for (int c = 0; c < (kKeepOffsets ? NKL : 1); ++c)
-    koff[c] = 16u * (unsigned)(c * 64 + lane < rec_chunks ? c * 64 + lane : rec_chunks - 1);
-  const unsigned koff_last = 16u * (unsigned)(rec_chunks - 1);
-#pragma unroll
-  for (int c = 0; c < NVM; ++c) vmoff[c] = (unsigned)off_v_s + 16u * (unsigned)(c * 64 + lane < nvm ? c * 64 + lane : nvm - 1);
-  // byte offset of this lane's value words in token group 0 of a record: channels value_channel(0, 0..3, n) of row kgv
+  const unsigned lane16 = 16u * (unsigned)lane;
   const unsigned voff = (unsigned)off_v + 4u * (unsigned)(kgv * kD) + (NVG == 4 ? 8u : 16u) * (unsigned)n;
-  /* RG variants split a record's key part in the pieces its first 64 tokens need (EARLY, with the value */       \
-  /* metadata) and the rest (LATE); elsewhere everything is EARLY */
+  // (records of fewer than 128 tokens have no second half: past the end of the record, nothing is read)
+  const unsigned second_half = (RG || R > 64) ? 2048u : (unsigned)rec_bytes;
+  // RG variants split a record's key part in the pieces its first 64 tokens need (EARLY, with the value metadata) and the
+  // rest (LATE); elsewhere everything is EARLY
   using HS = HalfSplit<K4, K16, THR>;
 #define MIXKVQ_IS_EARLY(C) (!RG || HS::early(C))
-#define MIXKVQ_KOFF(C) (kKeepOffsets ? koff[kKeepOffsets ? (C) : 0] : min(lane16_ + 1024u * (unsigned)(C), koff_last))
-#define MIXKVQ_ISSUE_K_EARLY(REC)                                                                           \
+  // Cache policy.  A step reads every record once; what it leaves behind in the last-level cache (256 MB) is of use to the next
+  // step over the same cache only where nothing else comes between, and beyond that size it only pushes other lines out.  The
+  // value words are therefore read with the non-temporal policy.  us per step, without / with: 512 pairs of 32 790 tokens
+  // (1.6 GB) 277 / 262, 32 pairs of 32 805 (82 MB) 22.5 / 22.9 over two caches in turn and 26.2 / 25.8 over seven; 24 steps of 24
+  // sequences of 60 to 12 003 tokens 468 / 468.
+  constexpr int kPolicyK = kKeep, kPolicyV = kStream;
+#define MIXKVQ_ISSUE_K_EARLY(REC)                                                                     \
   {                                                                                                          \
-    const unsigned char* rec_ = MIXKVQ_REC(REC);                                                             \
-    unsigned lane16_ = koff[0];                                                                              \
-    if (!kKeepOffsets) asm volatile("" : "+v"(lane16_));                                                     \
+    unsigned at_ = lane16;                                                                                   \
+    if (!kKeepOffsets) asm volatile("" : "+v"(at_));                                                         \
     _Pragma("unroll") for (int c = 0; c < NKL; ++c)                                                         \
-        if (MIXKVQ_IS_EARLY(c)) kreg[c] = *reinterpret_cast<const u32x4*>(rec_ + MIXKVQ_KOFF(c));            \
-    _Pragma("unroll") for (int c = 0; c < NVM; ++c)                                                         \
-        vmreg[c] = *reinterpret_cast<const u32x4*>(rec_ + vmoff[c]);                                         \
+        if (MIXKVQ_IS_EARLY(c)) kreg[c] = load16<kPolicyK>(REC, at_ + 4096u * (unsigned)(c / 4) + 1024u * (unsigned)(c % 4)); \
+    at_ += (unsigned)off_v_s;                                                                                \
+    _Pragma("unroll") for (int c = 0; c < NVM; ++c) vmreg[c] = load16<kPolicyK>(REC, at_ + 1024u * (unsigned)c);      \
   }
-#define MIXKVQ_ISSUE_K_LATE(REC)                                                                            \
+#define MIXKVQ_ISSUE_K_LATE(REC)                                                                      \
   {                                                                                                          \
-    const unsigned char* rec_ = MIXKVQ_REC(REC);                                                             \
-    unsigned lane16_ = koff[0];                                                                              \
-    if (!kKeepOffsets) asm volatile("" : "+v"(lane16_));                                                     \
     _Pragma("unroll") for (int c = 0; c < NKL; ++c)                                                         \
-        if (!MIXKVQ_IS_EARLY(c)) kreg[c] = *reinterpret_cast<const u32x4*>(rec_ + MIXKVQ_KOFF(c));           \
+        if (!MIXKVQ_IS_EARLY(c)) kreg[c] = load16<kPolicyK>(REC, lane16 + 4096u * (unsigned)(c / 4) + 1024u * (unsigned)(c % 4)); \
   }
-  /* the four value words of vreg[.][X]: channels value_channel(X, 0..3, n) of the token group row at byte ROWB_ */
-#define MIXKVQ_LOAD_VWORDS(DST, ROWB_, X)                                                                    \
+  // The value words of one half (64 tokens) of a record, vreg[H][X] = channels value_channel(X, 0..3, n): asked for as soon as
+  // the previous record's matrix products have consumed the registers they land in, so that each half has most of a
+  // record's time to arrive.
+#define MIXKVQ_ISSUE_V_HALF(REC, H)                                                                    \
   {                                                                                                          \
-    if (NVG == 4) {                                                                                          \
-      const uint2 lo_ = *reinterpret_cast<const uint2*>((ROWB_) + 256 * (X));                                \
-      const uint2 hi_ = *reinterpret_cast<const uint2*>((ROWB_) + 256 * (X) + 128);                          \
-      DST = u32x4{lo_.x, lo_.y, hi_.x, hi_.y};                                                               \
-    } else {                                                                                                 \
-      DST = *reinterpret_cast<const u32x4*>((ROWB_) + 256 * (X));                                            \
+    _Pragma("unroll") for (int x = 0; x < 2; ++x) {                                                         \
+      const unsigned at_ = ((H) ? voff + second_half : voff) + 256u * (unsigned)x;                          \
+      if (NVG == 4) {                                                                                        \
+        const u32x2 lo_ = load8<kPolicyV>(REC, at_), hi_ = load8<kPolicyV>(REC, at_ + 128u);                                    \
+        vreg[H][x] = u32x4{lo_[0], lo_[1], hi_[0], hi_[1]};                                                 \
+      } else {                                                                                               \
+        vreg[H][x] = load16<kPolicyV>(REC, at_);                                                                      \
+      }                                                                                                      \
     }                                                                                                        \
   }
-#define MIXKVQ_ISSUE_V_LOADS(REC)                                                                           \
-  {                                                                                                          \
-    const unsigned char* rec_ = MIXKVQ_REC(REC);                                                             \
-    _Pragma("unroll") for (int h = 0; h < 2; ++h) _Pragma("unroll") for (int x = 0; x < 2; ++x)             \
-        MIXKVQ_LOAD_VWORDS(vreg[h][x], rec_ + 2048 * (h * 64 < R ? h : 0) + voff, x)                        \
-  }
 
-  // The value words of one half (64 tokens) of a record: asked for as soon as the previous record's matrix
-  // products have consumed the registers they land in, so that each half has most of a record's time to arrive.
-#define MIXKVQ_ISSUE_V_HALF(REC, H)                                                                          \
-  {                                                                                                          \
-    const unsigned char* rec_ = MIXKVQ_REC(REC);                                                             \
-    _Pragma("unroll") for (int x = 0; x < 2; ++x)                                                           \
-        MIXKVQ_LOAD_VWORDS(vreg[H][x], rec_ + 2048 * (H) + voff, x)                                         \
-  }
-
-  // q in slot order from the selection words SELW (wave-uniform): a table [head][slot] in LDS, slots 0..127 for the
-  // block's 2-bit channels in ascending order (zero past the last one), slots 128.. for the fp16 tier and then the
-  // 4-bit tier.  Bitmaps of the two tiers are built with scalar arithmetic; every lane then knows the slots of its
-  // two channels (lane, lane + 64) from population counts, reads their 8 heads from the transposed q (one 16-byte
-  // read each) and scatters them into the table: no list of channels goes through memory.  Places no channel
-  // claims are zeroed (FIRST_: the ones that never change; threshold policy: also the ones that depend on the block).
-  // Every lane finally reads the 8 entries of each of its contraction steps with one 16-byte read.
+  // q in slot order: a table [head][slot] in LDS, slots 0..127 for the block's 2-bit channels in ascending order (zero
+  // past the last one), slots 128.. for the fp16 tier and then the 4-bit tier.  QUERY_SLOTS: lane i holds entry i of the
+  // record's channel list (CH; >= 128: an unused entry) and marks its channel in a byte array; ballots over the marks are the
+  // tiers' bitmaps, and every lane knows the slots of its two channels (lane, lane + 64) from population counts.  (Bitmaps from
+  // the list in scalar registers took 180 scalar instructions.)  LAYOUT_Q: a lane reads its channels' 8 heads from the
+  // transposed q (one 16-byte read each) and scatters them into the table.  Places no channel claims are zeroed (FIRST_: the
+  // ones that never change; threshold policy: also the ones that depend on the block).  Every lane finally reads the 8
+  // entries of each of its contraction steps with one 16-byte read.
 #define MIXKVQ_BELOW(MASK_) \
   ((int)__builtin_amdgcn_mbcnt_hi((unsigned)((MASK_) >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)(MASK_), 0u)))
-#define MIXKVQ_REBUILD_Q(SELW, FIRST_)                                                                         \
-  {                                                                                                            \
-    unsigned long long a0_ = 0, a1_ = 0, b0_ = 0, b1_ = 0;   /* fp16 tier / 4-bit tier, channels 0..63 / 64..127 */ \
-    _Pragma("unroll") for (int i = 0; i < K4 + K16; ++i) {                                                     \
-      const unsigned ch = (SELW[i >> 2] >> (8 * (i & 3))) & 0xffu;   /* >= 128: an unused entry */             \
-      const unsigned long long lo_ = ch < 64u ? 1ull << (ch & 63u) : 0ull;                                     \
-      const unsigned long long hi_ = (ch >= 64u && ch < 128u) ? 1ull << (ch & 63u) : 0ull;                     \
-      if (i < K16) { a0_ |= lo_; a1_ |= hi_; } else { b0_ |= lo_; b1_ |= hi_; }                                \
-    }                                                                                                          \
+#define MIXKVQ_QUERY_SLOTS(CH)                                                                                 \
+  if (K4 + K16 > 0) {                                                                                          \
+    reinterpret_cast<unsigned short*>(sMark)[lane] = 0;                                                        \
+    wave_lds_handoff();                                                                                        \
+    unsigned ch_ = (CH);                                                                                       \
+    asm("" : "+v"(ch_));     /* (nothing of it before this point, where it may still be on its way) */         \
+    if (lane < K4 + K16 && ch_ < (unsigned)kD) sMark[ch_] = lane < K16 ? 2 : 1;                                \
+    wave_lds_handoff();                                                                                        \
+    const int t0_ = sMark[lane], t1_ = sMark[lane + 64];                                                       \
+    const unsigned long long a0_ = K16 > 0 ? __ballot(t0_ == 2) : 0ull, a1_ = K16 > 0 ? __ballot(t1_ == 2) : 0ull; \
+    const unsigned long long b0_ = K4 > 0 ? __ballot(t0_ == 1) : 0ull, b1_ = K4 > 0 ? __ballot(t1_ == 1) : 0ull;   \
     const unsigned long long m0_ = a0_ | b0_, m1_ = a1_ | b1_;                                                 \
-    const int n16_ = __popcll(a0_) + __popcll(a1_), n4_ = __popcll(b0_) + __popcll(b1_);                       \
-    const int n_lo_ = kD - n16_ - n4_;                                                                         \
-    int slot0_ = lane - MIXKVQ_BELOW(m0_), slot1_ = 64 + lane - __popcll(m0_) - MIXKVQ_BELOW(m1_);             \
+    n16_ = __popcll(a0_) + __popcll(a1_);                                                                      \
+    n4_ = __popcll(b0_) + __popcll(b1_);                                                                       \
+    slot0_ = lane - MIXKVQ_BELOW(m0_);                                                                         \
+    slot1_ = 64 + lane - __popcll(m0_) - MIXKVQ_BELOW(m1_);                                                    \
     if (K16 > 0) {                                                                                             \
-      if ((a0_ >> lane) & 1) slot0_ = 128 + MIXKVQ_BELOW(a0_);                                                 \
-      if ((a1_ >> lane) & 1) slot1_ = 128 + __popcll(a0_) + MIXKVQ_BELOW(a1_);                                 \
+      if (t0_ == 2) slot0_ = 128 + MIXKVQ_BELOW(a0_);                                                          \
+      if (t1_ == 2) slot1_ = 128 + __popcll(a0_) + MIXKVQ_BELOW(a1_);                                          \
     }                                                                                                          \
     if (K4 > 0) {                                                                                              \
-      if ((b0_ >> lane) & 1) slot0_ = 128 + K16 + MIXKVQ_BELOW(b0_);                                           \
-      if ((b1_ >> lane) & 1) slot1_ = 128 + K16 + __popcll(b0_) + MIXKVQ_BELOW(b1_);                           \
+      if (t0_ == 1) slot0_ = 128 + K16 + MIXKVQ_BELOW(b0_);                                                    \
+      if (t1_ == 1) slot1_ = 128 + K16 + __popcll(b0_) + MIXKVQ_BELOW(b1_);                                    \
     }                                                                                                          \
+  }
+#define MIXKVQ_LAYOUT_Q(FIRST_)                                                                                \
+  {                                                                                                            \
+    const int n_lo_ = kD - n16_ - n4_;                                                                         \
     {                                                                                                          \
       const u32x4 h0_ = *reinterpret_cast<const u32x4*>(sQt + lane * 8);                                       \
       const u32x4 h1_ = *reinterpret_cast<const u32x4*>(sQt + (lane + 64) * 8);                                \
@@ -610,7 +641,7 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
       const u32x4 t_ = *reinterpret_cast<const u32x4*>(qrow + 128 + (8 * kg < K16 ? 8 * kg : 0));              \
       _Pragma("unroll") for (int e = 0; e < 4; ++e) {                                                          \
         const unsigned v_ = 8 * kg + 2 * e < K16 ? t_[e] : 0u;   /* (the table goes on with the 4-bit tier) */ \
-        q16a[e] = role ? 0u : v_;                                                                              \
+        q16a[e] = kLeanTier16 || !role ? v_ : 0u;                                                                              \
         q16b[e] = role ? v_ : 0u;                                                                              \
       }                                                                                                        \
     }                                                                                                          \
@@ -634,24 +665,14 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
       nt_row = *reinterpret_cast<const uint4*>((lane < 16 ? nt.k : nt.v) + src);
     }
   }
-  uint2 qraw = make_uint2(0u, 0u);
-  {
-    const int h = tid >> 5, l32 = tid & 31;
-    if (h < g) qraw = *reinterpret_cast<const uint2*>(q + ((size_t)b * Hq + jkv * g + h) * kD + l32 * 4);
-  }
-  unsigned sel_first[kSelWords];
-#pragma unroll
-  for (int i = 0; i < kSelWords; ++i) sel_first[i] = 0u;
+  const bool has_rec = blk < blk_hi;
   if (tab) {
-    if (blk < blk_hi) slot_cur = tab[blk];
+    if (has_rec) slot_cur = tab[blk];
     if (blk + blk_step < blk_hi) slot_nx = tab[blk + blk_step];
   }
-  const unsigned rec_first = MIXKVQ_REC_INDEX(blk, slot_cur);
-  if (K4 + K16 > 0 && blk < blk_hi) {
-    const unsigned* recw = reinterpret_cast<const unsigned*>(MIXKVQ_REC(rec_first) + off_idx);
-#pragma unroll
-    for (int i = 0; i < kSelWords; ++i) sel_first[i] = recw[i];
-  }
+  const record_t rec_first = record_at(MIXKVQ_REC(MIXKVQ_REC_INDEX(blk, slot_cur)), has_rec ? rec_bytes : 0);
+  unsigned list_first = 255u;      // entry `lane` of the first record's channel list
+  if (K4 + K16 > 0) list_first = (unsigned char)__builtin_amdgcn_raw_buffer_load_b8(rec_first, off_idx + lane, 0, 0);
   // Residual sub-unit of this wavefront: 2 key tiles x 4 contraction steps, 32 value rows.  This step's new
   // token is read from the caller's tensors.
   const int sub_t0 = 32 * (my_sub > 0 ? my_sub : 0);
@@ -675,7 +696,17 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
       vr[it] = *reinterpret_cast<const u32x4*>(src + 8 * (ci & 15));
     }
   }
-  if (blk < blk_hi) MIXKVQ_ISSUE_K_EARLY(rec_first)
+  // q (a head that does not exist reads the last one), then the first record's early pieces: not behind a branch, so that
+  // what follows waits for q alone (1.1 us less than waiting for everything asked for so far).
+  uint2 qraw;
+  {
+    const int h = tid >> 5, l32 = tid & 31;
+    qraw = *reinterpret_cast<const uint2*>(q + ((size_t)b * Hq + jkv * g + (h < g ? h : g - 1)) * kD + l32 * 4);
+  }
+  MIXKVQ_ISSUE_K_EARLY(rec_first)
+  // what the layout of q needs of the first record's selection, while q is on its way
+  int slot0_ = lane, slot1_ = 64 + lane, n16_ = 0, n4_ = 0;
+  MIXKVQ_QUERY_SLOTS(list_first)
 
   // ---- normalise q per head: qn = q * 2^-Eq with max|qn| in [1/2, 1) ----
   {
@@ -684,10 +715,11 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
       qraw.x = bf16x2_to_f16x2(qraw.x);
       qraw.y = bf16x2_to_f16x2(qraw.y);
     }
+    if (h >= g) qraw = make_uint2(0u, 0u);
     const h2 q01 = __builtin_bit_cast(h2, qraw.x), q23 = __builtin_bit_cast(h2, qraw.y);
     const float v[4] = {(float)q01[0], (float)q01[1], (float)q23[0], (float)q23[1]};
     float mx = fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3])));
-    for (int o = 16; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 32));
+    mx = half_wave_max(mx);
     int ef = (int)((__float_as_uint(mx) >> 23) & 0xff) - 127 + 15;   // fp16 exponent field of the maximum
     if (ef < 1) ef = 1;
     const int eq = ef - 14;
@@ -715,7 +747,8 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
       for (int hc = 0; hc < 2; ++hc) {
         const int d = lane + 64 * hc;
         unsigned long long acc = qacc_old[hc];
-        for (int h = 0; h < g; ++h) acc += fix24_abs(sQraw[h * kD + d]);
+#pragma unroll
+        for (int h = 0; h < 8; ++h) acc += fix24_abs(sQraw[h * kD + d]);      // (the rows past the last head are 0)
         cv.qacc[(size_t)p * kD + d] = acc;
       }
       // (an atomic: no old value to wait for)
@@ -724,18 +757,11 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
   }
   // q in the slot order of the first record, while that record is still on its way (its value words are
   // asked for only now: the first answers come the sooner the less every wavefront asks for at once)
-  if (blk < blk_hi) {
-    if (RG) {      // in the order of use: first half of the values, rest of the keys, second half of the values
-      MIXKVQ_ISSUE_V_HALF(rec_first, 0)
-      MIXKVQ_ISSUE_K_LATE(rec_first)
-      MIXKVQ_ISSUE_V_HALF(rec_first, 1)
-    } else {
-      MIXKVQ_ISSUE_V_LOADS(rec_first)
-    }
-#pragma unroll
-    for (int i = 0; i < kSelWords; ++i) sel_prev[i] = __builtin_amdgcn_readfirstlane(sel_first[i]);
-    MIXKVQ_REBUILD_Q(sel_prev, true)
-  }
+  // (in the order of use: first half of the values, rest of the keys, second half of the values)
+  MIXKVQ_ISSUE_V_HALF(rec_first, 0)
+  MIXKVQ_ISSUE_K_LATE(rec_first)
+  MIXKVQ_ISSUE_V_HALF(rec_first, 1)
+  if (has_rec) MIXKVQ_LAYOUT_Q(true)
 
   // ---- residual window (fp16 keys/values): 32 tokens per wavefront, before its block records ----
   if (my_sub >= 0) {
@@ -917,7 +943,15 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
       for (int x = (X0); x < (X1); ++x) S[x] = mfma(unpack4(wh4[x]), Bh4, S[x]);                         \
     }                                                                                                    \
     if (K16 > 0) {                                                                                       \
-      const u32x4 bqa = {q16a[0], q16a[1], q16a[2], q16a[3]}, bqb = {q16b[0], q16b[1], q16b[2], q16b[3]};   \
+      u32x4 bqa = {q16a[0], q16a[1], q16a[2], q16a[3]}, bqb = {q16b[0], q16b[1], q16b[2], q16b[3]};         \
+      if (kLeanTier16) {                                                                                 \
+        int role_ = role;                                                                                \
+        asm volatile("" : "+v"(role_));                                                                  \
+        _Pragma("unroll") for (int e = 0; e < 4; ++e) {                                                  \
+          bqb[e] = role_ ? q16a[e] : 0u;                                                                 \
+          bqa[e] = role_ ? 0u : q16a[e];                                                                 \
+        }                                                                                                \
+      }                                                                                                  \
     _Pragma("unroll")                                                                                    \
       for (int x = (X0); x < (X1); ++x) {                                                                \
         const unsigned char* src = sK + k16_off + 2 * (64 * hsg + offx[x]) * K16;                        \
@@ -947,10 +981,11 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
     for (int c = 0; c < NKL; ++c)
       if (MIXKVQ_IS_EARLY(c)) reinterpret_cast<u32x4*>(sK)[SWZ ? kst[c] : c * 64 + lane] = kreg[c];
 #pragma unroll
-    for (int c = 0; c < NVM; ++c) reinterpret_cast<u32x4*>(sVm)[c * 64 + lane < nvm ? c * 64 + lane : nvm - 1] = vmreg[c];
+    for (int c = 0; c < NVM; ++c) reinterpret_cast<u32x4*>(sVm)[c * 64 + lane] = vmreg[c];
     wave_lds_handoff();
-    const unsigned rec_nx = MIXKVQ_REC_INDEX(blk + blk_step, slot_nx);     // the next record of this wavefront
-    if (blk + blk_step < blk_hi) MIXKVQ_ISSUE_K_EARLY(rec_nx)
+    // the next record of this wavefront (size 0: there is none)
+    const record_t rec_nx = record_at(MIXKVQ_REC(MIXKVQ_REC_INDEX(blk + blk_step, slot_nx)), blk + blk_step < blk_hi ? rec_bytes : 0);
+    MIXKVQ_ISSUE_K_EARLY(rec_nx)
     int slot_nn = 0;      // requested behind the record loads; needed only after they have arrived
     if (tab && blk + 2 * blk_step < blk_hi) slot_nn = tab[blk + 2 * blk_step];
     // Value scales above 255 (a group of values that spans more than 765) would overflow p' * s in fp16.  Such a
@@ -986,7 +1021,12 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
         rebuild |= selw[i] != sel_prev[i];
         sel_prev[i] = selw[i];
       }
-      if (rebuild) MIXKVQ_REBUILD_Q(selw, false)
+      if (rebuild && blk != blk_lo) {      // (for the first record q is in place)
+        int slot0_ = lane, slot1_ = 64 + lane, n16_ = 0, n4_ = 0;
+        const unsigned list_ = sK[off_idx + lane];      // (past the list: not used)
+        MIXKVQ_QUERY_SLOTS(list_)
+        MIXKVQ_LAYOUT_Q(false)
+      }
     }
 
     // operands that live across the super-groups of one key group
@@ -999,7 +1039,7 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
         for (int c = 0; c < NKL; ++c)
           if (!MIXKVQ_IS_EARLY(c)) reinterpret_cast<u32x4*>(sK)[SWZ ? kst[c] : c * 64 + lane] = kreg[c];
         wave_lds_handoff();
-        if (blk + blk_step < blk_hi) MIXKVQ_ISSUE_K_LATE(rec_nx)
+        MIXKVQ_ISSUE_K_LATE(rec_nx)
       }
       if (64 * hsg < R) {
         if (younger) {      // 5 of 8 half-records (measured: 4 of 8 nearly as good, 3 of 8 and 6 of 8 and more worse)
@@ -1164,8 +1204,8 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
             O[xp][qq] = mfma(a1, Bp[a][1], O[xp][qq]);
           }
         }
-        if (blk + blk_step < blk_hi) MIXKVQ_ISSUE_V_HALF(rec_nx, hsg)
       }
+      MIXKVQ_ISSUE_V_HALF(rec_nx, hsg)
     }
     if (big_s) {
 #pragma unroll
@@ -1180,14 +1220,12 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
   MIXKVQ_PHASE(14)
 #undef MIXKVQ_ISSUE_K_EARLY
 #undef MIXKVQ_ISSUE_K_LATE
-#undef MIXKVQ_KOFF
 #undef MIXKVQ_IS_EARLY
 #undef MIXKVQ_REC
 #undef MIXKVQ_REC_INDEX
-#undef MIXKVQ_ISSUE_V_LOADS
 #undef MIXKVQ_ISSUE_V_HALF
-#undef MIXKVQ_LOAD_VWORDS
-#undef MIXKVQ_REBUILD_Q
+#undef MIXKVQ_QUERY_SLOTS
+#undef MIXKVQ_LAYOUT_Q
 #undef MIXKVQ_BELOW
 #undef MIXKVQ_GROUP_OPERANDS
 #undef MIXKVQ_KEY_TILES

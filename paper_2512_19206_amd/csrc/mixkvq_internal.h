@@ -32,13 +32,18 @@ constexpr int kMaxUnits = 512;
 struct SeqCounts {
   int32_t enabled;
   int32_t n_blocks[kMaxRaggedB];      // quantized blocks of sequence b
-  uint16_t n_fp16[kMaxRaggedB];       // its fp16 rows in use (sink + residual window)
+  uint32_t n_fp16[kMaxRaggedB / 2];   // its fp16 rows in use (sink + residual window): half b % 2 of word b / 2, so that a
+                                      // kernel reads it through the scalar cache
   // How the matrix-core kernel's workgroups are dealt to the sequences (n_units == 0: every sequence takes the launch's
   // n_splits).  A unit is one workgroup per KV head; the units of a sequence are consecutive.
   int32_t n_units;
   uint32_t span[kMaxRaggedB];         // first unit of the sequence | its units << 16
   uint32_t owner[kMaxUnits / 4];      // sequence of unit u: byte u % 4 of word u / 4
 };
+
+__host__ __device__ __forceinline__ int fp16_rows_of(const SeqCounts& sc, int b) {
+  return (int)(sc.n_fp16[b >> 1] >> (16 * (b & 1)) & 0xffffu);
+}
 
 // Sequences whose full window one launch of the pack kernel quantizes, passed by value (n == 0: every sequence of the
 // view, all starting at the same record).
