@@ -9,6 +9,8 @@
 namespace mixkvq {
 
 constexpr int kDecThreads = 256;
+// Two launches that read this much each fill the last-level cache (256 MB).
+constexpr int64_t kStreamBytes = 128ll << 20;
 constexpr int kMaxG = 8;
 constexpr int kPartStride = kD + 2;   // floats per (split, head): O[D], m, l
 
@@ -259,15 +261,21 @@ __global__ void __launch_bounds__(kD) decode_merge_kernel(const float* __restric
   if (lse && d == 0) lse[bh] = l > 0.f ? m + __logf(l) : -INFINITY;
 }
 
-bool try_launch_decode_mfma(const CacheView& v, const __half* q, float scale, int n_blocks, int n_res, int n_splits,
+bool try_launch_decode_mfma(const CacheView& v, const __half* q, float scale, int n_blocks, int n_res, DecodeGrid dg,
                             float* part, __half* out, float* lse, int accumulate_q, NewToken nt, const SeqCounts& sc,
                             hipStream_t s, hipEvent_t ev_start, hipEvent_t ev_stop, hipError_t* err);
 
 // Split count of a decode launch (one rule for every caller): enough workgroups to fill the chip (tunable through
-// MIXKVQ_DECODE_WGS for experiments), never above the ceiling the workspace was sized for.  *n_splits_mc is the count
-// the matrix-core kernel takes: its fp16 rows are cut into sub-units of 32 tokens and a wavefront takes at most one of
-// them, so a pair needs at least as many wavefronts (4 per workgroup) as it has sub-units.
-static void choose_splits(const CacheView& v, int n_blocks, int n_fp16, int* n_splits_out, int* n_splits_mc_out) {
+// MIXKVQ_DECODE_WGS for experiments), never above the ceiling the workspace was sized for.  *mc is the grid the matrix-core
+// kernel takes: its fp16 rows are cut into sub-units of 32 tokens and a wavefront takes at most one of
+// them, so a pair needs at least as many wavefronts as it has sub-units.
+// Where a pair has several workgroups of four wavefronts, half as many workgroups of eight (`wide`) leave half as many
+// partials to the pair's last workgroup, which pulls them past the caches with the bandwidth of one compute unit, and draw half
+// as many tickets.  They are taken unless rounding lengthens the chain of records a wavefront works through, or the workgroups of
+// four have a compute unit each.  us per step, four / eight: 24 pairs of 9 001 tokens (18 / 9 partials) 19.4 / 17.9, 32 pairs of
+// 32 805 (16 / 8) 23.1 / 22.6, records of 32 tokens, 32 pairs of 4 100, 48 steps 718 / 705, 24 sequences of 60 to 12 003, 24 steps
+// 487 / 468; one pair of 1 027 tokens, which keeps its nine workgroups of four, 9.8 / 10.7.
+static void choose_splits(const CacheView& v, int n_blocks, int n_fp16, bool wide, int* n_splits_out, DecodeGrid* mc) {
   static const int target_wgs = [] {
     const char* e = getenv("MIXKVQ_DECODE_WGS");
     int t = e ? atoi(e) : 0;
@@ -285,7 +293,15 @@ static void choose_splits(const CacheView& v, int n_blocks, int n_fp16, int* n_s
   const int max_useful = (n_blocks + subs + 3) / 4;
   if (n_splits_mc > max_useful && max_useful > 0) n_splits_mc = max_useful;
   *n_splits_out = n_splits;
-  *n_splits_mc_out = n_splits_mc;
+  *mc = DecodeGrid{n_splits_mc, 4, 0};
+  if (!wide || n_splits_mc < 2) return;
+  const int units = n_blocks + subs;
+  int n8 = target_wgs / 2 / v.P;
+  if (n8 > (units + 7) / 8) n8 = (units + 7) / 8;
+  if (n8 < (subs + 7) / 8) n8 = (subs + 7) / 8;
+  if (n8 < 1) n8 = 1;
+  const int chain8 = (units + 8 * n8 - 1) / (8 * n8), chain4 = (units + 4 * n_splits_mc - 1) / (4 * n_splits_mc);
+  if (chain8 < chain4 || (chain8 == chain4 && v.P * n_splits_mc > target_wgs / 2)) *mc = DecodeGrid{n8, 8, 0};
 }
 
 // Deals the matrix-core kernel's workgroups to sequences of different lengths: with the same number for every sequence the
@@ -294,38 +310,48 @@ static void choose_splits(const CacheView& v, int n_blocks, int n_fp16, int* n_s
 // at once (two per compute unit; never fewer than the equal deal has), with the fp16 rows' minimum for every sequence and
 // at most the partials the workspace has room for.  Host work: a few divisions per sequence.  24 steps of 24 sequences of
 // 60 to 12 003 tokens, 4 KV heads: 617 us with five workgroups for every pair, 509 this way.
-static void deal_by_length(const CacheView& v, int n_splits, SeqCounts* sc) {
+// Workgroups of eight wavefronts are dealt (see choose_splits) unless those of four give a shorter chain.
+static void deal_by_length(const CacheView& v, int n_splits, SeqCounts* sc, DecodeGrid* dg) {
   const int B = v.cfg.B;
-  int budget = kDecodeTargetWGs / v.cfg.Hkv;
-  if (budget < B * n_splits) budget = B * n_splits;
-  if (budget > B * max_splits_for(v.P)) budget = B * max_splits_for(v.P);
-  if (budget > kMaxUnits) return;
-  auto units_of = [&](int b, int chain) {
-    const int subs = (fp16_rows_of(*sc, b) + 31) / 32, least = (subs + 3) / 4;
-    int n = (sc->n_blocks[b] + subs + 4 * chain - 1) / (4 * chain);
-    if (n > kMaxSplits) n = kMaxSplits;
-    if (n < least) n = least;
-    return n < 1 ? 1 : n;
-  };
-  auto fits = [&](int chain) {
-    int total = 0;
-    for (int b = 0; b < B; ++b) total += units_of(b, chain);
-    return total <= budget;
-  };
   int most = 1;
   for (int b = 0; b < B; ++b) {
     const int n = sc->n_blocks[b] + (fp16_rows_of(*sc, b) + 31) / 32;
     most = n > most ? n : most;
   }
-  int lo = 1, hi = (most + 4 * n_splits - 1) / (4 * n_splits);      // (the equal deal's chain always fits)
-  while (lo < hi) {
-    const int mid = (lo + hi) / 2;
-    if (fits(mid)) hi = mid;
-    else lo = mid + 1;
+  auto units_of = [&](int b, int chain, int waves) {
+    const int subs = (fp16_rows_of(*sc, b) + 31) / 32, least = (subs + waves - 1) / waves;
+    int n = (sc->n_blocks[b] + subs + waves * chain - 1) / (waves * chain);
+    if (n > kMaxSplits) n = kMaxSplits;
+    if (n < least) n = least;
+    return n < 1 ? 1 : n;
+  };
+  // shortest chain that fits for workgroups of this many wavefronts (none up to `hi`: hi + 1)
+  auto shortest = [&](int waves, int budget, int hi) {
+    auto fits = [&](int chain) {
+      int total = 0;
+      for (int b = 0; b < B; ++b) total += units_of(b, chain, waves);
+      return total <= budget;
+    };
+    int lo = 1, end = hi + 1;
+    while (lo < end) {
+      const int mid = (lo + end) / 2;
+      if (fits(mid)) end = mid;
+      else lo = mid + 1;
+    }
+    return lo;
+  };
+  int budget = kDecodeTargetWGs / v.cfg.Hkv;
+  if (budget < B * n_splits) budget = B * n_splits;
+  if (budget > B * max_splits_for(v.P)) budget = B * max_splits_for(v.P);
+  if (budget > kMaxUnits) return;
+  int waves = 4, chain = shortest(4, budget, (most + 4 * n_splits - 1) / (4 * n_splits) - 1);      // (the equal deal's always fits)
+  if (const int c8 = shortest(8, kDecodeTargetWGs / 2 / v.cfg.Hkv, chain); c8 <= chain) {
+    waves = 8;
+    chain = c8;
   }
   int first = 0;
   for (int b = 0; b < B; ++b) {
-    const int n = units_of(b, lo);
+    const int n = units_of(b, chain, waves);
     sc->span[b] = (uint32_t)first | ((uint32_t)n << 16);
     for (int u = first; u < first + n; ++u) {
       if ((u & 3) == 0) sc->owner[u >> 2] = 0u;
@@ -334,12 +360,14 @@ static void deal_by_length(const CacheView& v, int n_splits, SeqCounts* sc) {
     first += n;
   }
   sc->n_units = first;
+  *dg = DecodeGrid{n_splits, waves, 0};
 }
 
 size_t decode_launch_partials_bytes(const CacheView& v, int n_blocks, int n_fp16) {
-  int n_splits, n_splits_mc;
-  choose_splits(v, n_blocks, n_fp16, &n_splits, &n_splits_mc);
-  const int n = n_splits_mc > n_splits ? n_splits_mc : n_splits;
+  int n_splits;
+  DecodeGrid mc;
+  choose_splits(v, n_blocks, n_fp16, false, &n_splits, &mc);      // (workgroups of eight wavefronts write half of that)
+  const int n = mc.n_splits > n_splits ? mc.n_splits : n_splits;
   return (size_t)v.P * n * v.g * kPartStride * sizeof(float);
 }
 
@@ -375,14 +403,21 @@ hipError_t launch_decode(const CacheView& v, const __half* q, __half* out, float
                          hipEvent_t ev_start, hipEvent_t ev_stop, int* path, float* part) {
   static const SeqCounts kLockStep = [] { SeqCounts z; memset(&z, 0, sizeof(z)); return z; }();
   const SeqCounts& sc = sc_in ? *sc_in : kLockStep;
-  int n_splits, n_splits_mc;
-  choose_splits(v, n_blocks, n_fp16, &n_splits, &n_splits_mc);
+  int n_splits;
+  DecodeGrid mc;
   // (a given buffer of partials comes without tickets: its merge launch reads the same number for every sequence)
-  if (!part && sc_in && n_splits_mc <= max_splits_for(v.P)) deal_by_length(v, n_splits_mc, sc_in);
+  choose_splits(v, n_blocks, n_fp16, !sc_in, &n_splits, &mc);
+  if (!part && sc_in && mc.n_splits <= max_splits_for(v.P)) deal_by_length(v, mc.n_splits, sc_in, &mc);
+  int64_t records = (int64_t)v.P * n_blocks;
+  if (sc_in) {
+    records = 0;
+    for (int b = 0; b < v.cfg.B; ++b) records += (int64_t)sc.n_blocks[b] * v.cfg.Hkv;
+  }
+  mc.streamed = records * v.lay.rec_bytes >= kStreamBytes;
   if (!part) part = reinterpret_cast<float*>(v.ws);
   hipError_t e = hipSuccess;
-  if (n_splits_mc <= max_splits_for(v.P) &&
-      try_launch_decode_mfma(v, q, scale, n_blocks, n_fp16, n_splits_mc, part, out, lse, accumulate_q, nt, sc, s,
+  if (mc.n_splits <= max_splits_for(v.P) &&
+      try_launch_decode_mfma(v, q, scale, n_blocks, n_fp16, mc, part, out, lse, accumulate_q, nt, sc, s,
                              ev_start, ev_stop, &e)) {
     *path = MIXKVQ_PATH_MATRIX;
     return e;

@@ -5,23 +5,23 @@
 
 namespace mixkvq {
 
-// The merge as a launch of its own, one workgroup per pair (see merge_pair).
-__global__ void __launch_bounds__(256)
-decode_merge_pair_kernel(CacheView cv, const float* __restrict__ part, int n_parts, __half* __restrict__ out,
+// The merge as a launch of its own, one workgroup per pair, in the order of sums of the attention launch's own (see merge_pair).
+__global__ void __launch_bounds__(512)
+decode_merge_pair_kernel(CacheView cv, const float* __restrict__ part, int n_parts, int n_half, __half* __restrict__ out,
                          float* __restrict__ lse) {
-  const int p = blockIdx.x, h = threadIdx.x >> 5, c4 = threadIdx.x & 31, g = cv.g;
-  if (h >= g) return;
+  __shared__ __align__(16) unsigned char lds[6144];
+  const int p = blockIdx.x, tid = threadIdx.x, h = tid >> 5 & 7, g = cv.g;
   const size_t bh = (size_t)(p / cv.cfg.Hkv) * cv.cfg.Hq + (size_t)(p % cv.cfg.Hkv) * g + h;
-  merge_pair<false>(part + (size_t)p * n_parts * g * kPartStrideM, n_parts, g, h, c4, out, lse, bh, cv.cfg.in_dtype);
+  merge_pair<false>(part + (size_t)p * n_parts * g * kPartStrideM, n_parts, n_half, tid, g, lds, out, lse, bh, cv.cfg.in_dtype);
 }
 
-hipError_t launch_merge_pair(const CacheView& v, const float* part, int n_splits, __half* out, float* lse, hipStream_t s) {
-  decode_merge_pair_kernel<<<dim3(v.P), dim3(256), 0, s>>>(v, part, n_splits, out, lse);
+hipError_t launch_merge_pair(const CacheView& v, const float* part, DecodeGrid dg, __half* out, float* lse, hipStream_t s) {
+  decode_merge_pair_kernel<<<dim3(v.P), dim3(64 * dg.n_waves), 0, s>>>(v, part, dg.n_splits, dg.n_waves >> 2, out, lse);
   return hipGetLastError();
 }
 
 // Returns true and launches when the configuration is one the matrix-core kernel covers.
-bool try_launch_decode_mfma(const CacheView& v, const __half* q, float scale, int n_blocks, int n_res, int n_splits,
+bool try_launch_decode_mfma(const CacheView& v, const __half* q, float scale, int n_blocks, int n_res, DecodeGrid dg,
                             float* part, __half* out, float* lse, int accumulate_q, NewToken nt, const SeqCounts& sc,
                             hipStream_t s, hipEvent_t ev_start, hipEvent_t ev_stop, hipError_t* err) {
   const mixkvq_config& c = v.cfg;
@@ -44,13 +44,16 @@ bool try_launch_decode_mfma(const CacheView& v, const __half* q, float scale, in
   bool ok = true;
 #define MIXKVQ_CASE(K4_, K16_, NVG_, NKL_, RG_, THR_, G32_, PG_, RH_)                                               \
   if (c.k4 == K4_ && c.k16 == K16_ && nvg == NVG_ && nkl <= NKL_ && c.policy == THR_ && g32 == G32_ && paged == PG_ && \
-      rh == RH_ && (RG_ == 0 || (c.R == 128 && c.Gk == 128 && HalfSplit<K4_, K16_, THR_>::off_klo == v.lay.off_klo &&  \
+      rh == RH_ && (RG_ != 2 || dg.streamed) && (RG_ == 0 || (c.R == 128 && c.Gk == 128 && HalfSplit<K4_, K16_, THR_>::off_klo == v.lay.off_klo &&  \
                                  HalfSplit<K4_, K16_, THR_>::off_k4 == v.lay.off_k4 &&                              \
                                  HalfSplit<K4_, K16_, THR_>::off_k16 == v.lay.off_k16 &&                            \
                                  HalfSplit<K4_, K16_, THR_>::off_v == v.lay.off_v)))                                \
-    e = launch_one<K4_, K16_, NVG_, NKL_, RG_, THR_, G32_, PG_, RH_>(v, q, scale, n_blocks, n_res, n_splits, part, out, lse,  \
+    e = launch_one<K4_, K16_, NVG_, NKL_, RG_, THR_, G32_, PG_, RH_>(v, q, scale, n_blocks, n_res, dg, part, out, lse,  \
                                                            accumulate_q, nt, sc, s, ev_start, ev_stop);             \
   else
+  MIXKVQ_CASE(16, 0, 1, 6, 2, 0, 0, 0, 0)
+  MIXKVQ_CASE(0, 12, 1, 8, 2, 0, 0, 0, 0)
+  MIXKVQ_CASE(8, 0, 1, 6, 2, 0, 0, 0, 0)
   MIXKVQ_CASE(16, 0, 1, 6, 1, 0, 0, 0, 0)
   MIXKVQ_CASE(0, 12, 1, 8, 1, 0, 0, 0, 0)
   MIXKVQ_CASE(8, 0, 1, 6, 1, 0, 0, 0, 0)
@@ -113,7 +116,7 @@ bool try_launch_decode_mfma(const CacheView& v, const __half* q, float scale, in
   ok = false;
 #undef MIXKVQ_CASE
   if (!ok) {     // not one of the variants above: the wider tables (they take either layout)
-    const GenericArgs a{v, q, scale, n_blocks, n_res, n_splits, part, out, lse, accumulate_q, nt, sc, s, ev_start, ev_stop,
+    const GenericArgs a{v, q, scale, n_blocks, n_res, dg, part, out, lse, accumulate_q, nt, sc, s, ev_start, ev_stop,
                         nkl, g32, rh};
     return rh ? try_launch_generic_rh(a, err) : (g32 ? try_launch_generic_g32(a, err) : try_launch_generic_plain(a, err));
   }

@@ -25,7 +25,8 @@ struct GenericArgs {
   const CacheView& v;
   const __half* q;
   float scale;
-  int n_blocks, n_res, n_splits;
+  int n_blocks, n_res;
+  DecodeGrid dg;
   float* part;
   __half* out;
   float* lse;
@@ -45,7 +46,7 @@ static bool try_generic(const GenericArgs& a, hipError_t* err) {
   if constexpr (NKL * 1024 <= kKPartMax) {
     const mixkvq_config& c = a.v.cfg;
     if (c.k4 == K4 && c.k16 == K16 && a.v.lay.NVG == NVG && c.policy == THR && a.g32 == G32 && a.rh == RH && a.nkl <= NKL) {
-      *err = launch_one<K4, K16, NVG, NKL, 0, THR, G32, 2, RH>(a.v, a.q, a.scale, a.n_blocks, a.n_res, a.n_splits, a.part,
+      *err = launch_one<K4, K16, NVG, NKL, 0, THR, G32, 2, RH>(a.v, a.q, a.scale, a.n_blocks, a.n_res, a.dg, a.part,
                                                               a.out, a.lse, a.accumulate_q, a.nt, a.sc, a.s, a.ev_start,
                                                               a.ev_stop);
       return true;

@@ -36,15 +36,14 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int kMfmaThreads = 256;
 constexpr int kComputeUnits = 256;              // MI355X
-constexpr int kWaves = kMfmaThreads / 64;
+constexpr int kMaxWaves = 8;                    // a workgroup has four or eight wavefronts (see choose_splits)
 constexpr int kKPartMax = 12288;                // bytes of a record before the value plane (staged in LDS)
 constexpr int kVMetaMax = 2048;                 // value scales + zero-points of one block
 constexpr int kQsStride = 168;                  // halfs per head row of the slot-ordered q table (160 slots + padding)
 constexpr int kQsBytes = 8 * kQsStride * 2;
 constexpr int kWaveLds = kKPartMax + kVMetaMax + 256 + kQsBytes;   // + tier marks of the channels + slot-ordered q
-constexpr int kHdrLds = 2048 + 256 + 2048;      // q as given [8][128], exponents and wave maxima, normalised q transposed [128][8]
+constexpr int kHdrLds = 2048 + 512 + 2048;      // q as given [8][128], exponents and wave maxima, normalised q transposed [128][8]
 constexpr int kPartStrideM = kD + 2;
 constexpr int kPBoost = 8;                      // softmax weights go to the matrix cores as p * 2^kPBoost (see mfma_part)
 constexpr unsigned kBigScale = 0x5BF8u;         // fp16 255: the largest value scale for which p' * s cannot overflow
@@ -54,11 +53,11 @@ constexpr unsigned kBigScale = 0x5BF8u;         // fp16 255: the largest value s
 __device__ unsigned long long g_phase_clock[4096 * 16];
 #define MIXKVQ_PHASE(K_)                                                                              \
   if (lane == 0)                                                                                      \
-    g_phase_clock[((blockIdx.y * gridDim.x + blockIdx.x) * kWaves + wave) % 4096 * 16 + (K_)] = wall_clock64();
+    g_phase_clock[((blockIdx.y * gridDim.x + blockIdx.x) * n_waves + wave) % 4096 * 16 + (K_)] = wall_clock64();
 // slots 12 and 13: the shader clock at the first and the last phase
 #define MIXKVQ_PHASE_CYCLES(K_)                                                                       \
   if (lane == 0)                                                                                      \
-    g_phase_clock[((blockIdx.y * gridDim.x + blockIdx.x) * kWaves + wave) % 4096 * 16 + (K_)] = clock64();
+    g_phase_clock[((blockIdx.y * gridDim.x + blockIdx.x) * n_waves + wave) % 4096 * 16 + (K_)] = clock64();
 #else
 #define MIXKVQ_PHASE(K_)
 #define MIXKVQ_PHASE_CYCLES(K_)
@@ -233,8 +232,8 @@ struct HalfSplit {
 // ---------------------------------------------------------------------------
 // Split-K partials and their log-sum-exp merge: m* = max m_i, l* = sum l_i 2^(m_i - m*),
 // O = sum O_i 2^(m_i - m*) / l* (log2 domain).  The partial of one workgroup is O [g][128], then (m, l) [g], binary32.
-// A thread owns four channels of one head, so g x 32 threads merge a pair without exchanging anything, and every load
-// of sixteen partials is in flight before the first wait.
+// A thread owns four channels of one head and sixteen partials are in flight per thread before the first wait; with eight
+// wavefronts the two halves of the workgroup take alternate partials and join their results through LDS.
 //
 // The last workgroup of a pair to finish merges it (see CacheView::tickets).  The partials, the ticket and the
 // loads are agent-scope accesses, which go past the chip's eight L2 caches; no cache is flushed for them.  A launch of
@@ -274,57 +273,85 @@ __device__ __forceinline__ void store_output4(__half* out, float* lse, size_t bh
   // (sum first: nothing for the compiler to contract, so that both forms of the merge give the same bits; l >= 1/2)
   if (lse && c4 == 0) lse[bh] = l > 0.f ? (m + __builtin_amdgcn_logf(l)) * 0.6931471805599453f : -INFINITY;
 }
-// Partials `pair` [n_parts][g * kPartStrideM] of one pair; thread (h, c4) with h < g.
+// Every step-th of the partials `pair` [n_parts][g * kPartStrideM] of one pair from `first` on (scalars); thread (h, c4), h < g.
+struct Merged { f32x4 o; float l, m; };
 template <bool SHARED>
-__device__ __forceinline__ void merge_pair(const float* __restrict__ pair, int n_parts, int g, int h, int c4, __half* out,
-                                           float* lse, size_t bh, int bf16) {
+__device__ __forceinline__ Merged merge_parts(const float* __restrict__ pair, int first, int step, int n_parts, int g, int h, int c4) {
   const int stride = g * kPartStrideM;
   constexpr int kFly = 16;
-  float m_run = -INFINITY, l_run = 0.f;
-  f32x4 o_run = {0.f, 0.f, 0.f, 0.f};
-  for (int s0 = 0; s0 < n_parts; s0 += kFly) {
+  Merged r{{0.f, 0.f, 0.f, 0.f}, 0.f, -INFINITY};
+  for (int s0 = first; s0 < n_parts; s0 += kFly * step) {
     float2 ml[kFly], oa[kFly], ob[kFly];
 #pragma unroll
     for (int i = 0; i < kFly; ++i) {
-      const float* p = pair + (s0 + i < n_parts ? s0 + i : n_parts - 1) * stride;     // (a repeated part gets weight 0)
-      ml[i] = load_part2<SHARED>(p + g * kD + 2 * h);
-      oa[i] = load_part2<SHARED>(p + h * kD + 4 * c4);
-      ob[i] = load_part2<SHARED>(p + h * kD + 4 * c4 + 2);
+      ml[i] = make_float2(-INFINITY, 0.f);
+      oa[i] = ob[i] = make_float2(0.f, 0.f);
+      if (s0 + i * step < n_parts) {
+        const float* p = pair + (s0 + i * step) * stride;
+        ml[i] = load_part2<SHARED>(p + g * kD + 2 * h);
+        oa[i] = load_part2<SHARED>(p + h * kD + 4 * c4);
+        ob[i] = load_part2<SHARED>(p + h * kD + 4 * c4 + 2);
+      }
     }
-    float m_new = m_run;
+    float m_new = r.m;
 #pragma unroll
-    for (int i = 0; i < kFly; ++i) {
-      if (s0 + i >= n_parts) ml[i] = make_float2(-INFINITY, 0.f);
-      m_new = fmaxf(m_new, ml[i].x);
-    }
-    const float alpha = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
-    l_run *= alpha;
-    o_run *= alpha;
-    m_run = m_new;
+    for (int i = 0; i < kFly; ++i) m_new = fmaxf(m_new, ml[i].x);
+    const float alpha = r.m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(r.m - m_new);
+    r.l *= alpha;
+    r.o *= alpha;
+    r.m = m_new;
 #pragma unroll
     for (int i = 0; i < kFly; ++i) {
       const float w = ml[i].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[i].x - m_new);
-      l_run = fmaf(ml[i].y, w, l_run);
-      o_run[0] = fmaf(oa[i].x, w, o_run[0]);
-      o_run[1] = fmaf(oa[i].y, w, o_run[1]);
-      o_run[2] = fmaf(ob[i].x, w, o_run[2]);
-      o_run[3] = fmaf(ob[i].y, w, o_run[3]);
+      r.l = fmaf(ml[i].y, w, r.l);
+      r.o[0] = fmaf(oa[i].x, w, r.o[0]);
+      r.o[1] = fmaf(oa[i].y, w, r.o[1]);
+      r.o[2] = fmaf(ob[i].x, w, r.o[2]);
+      r.o[3] = fmaf(ob[i].y, w, r.o[3]);
     }
   }
-  store_output4(out, lse, bh, c4, o_run, l_run, m_run, bf16);
+  return r;
+}
+// The merge of one pair by all threads of a workgroup of 4 * n_half wavefronts; `lds`: 6 KiB of its own.
+template <bool SHARED>
+__device__ __forceinline__ void merge_pair(const float* __restrict__ pair, int n_parts, int n_half, int tid, int g, unsigned char* lds,
+                                           __half* out, float* lse, size_t bh, int bf16) {
+  const int h = tid >> 5 & 7, c4 = tid & 31, half = __builtin_amdgcn_readfirstlane(tid >> 8);
+  Merged r = merge_parts<SHARED>(pair, half, n_half, n_parts, g, h < g ? h : 0, c4);
+  if (n_half > 1) {
+    f32x4* const sO = reinterpret_cast<f32x4*>(lds);            // [256] o, then [256] (l, m)
+    float2* const sLM = reinterpret_cast<float2*>(lds + 4096);
+    if (half) {
+      sO[tid & 255] = r.o;
+      sLM[tid & 255] = make_float2(r.l, r.m);
+    }
+    __syncthreads();
+    if (!half) {
+      const f32x4 o1 = sO[tid];
+      const float2 lm1 = sLM[tid];
+      const float m = fmaxf(r.m, lm1.y);
+      const float w0 = r.m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(r.m - m);
+      const float w1 = lm1.y == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(lm1.y - m);
+      r.l = fmaf(lm1.x, w1, r.l * w0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) r.o[i] = fmaf(o1[i], w1, r.o[i] * w0);
+      r.m = m;
+    }
+  }
+  if (h < g && half == 0) store_output4(out, lse, bh, c4, r.o, r.l, r.m, bf16);
 }
 
-hipError_t launch_merge_pair(const CacheView& v, const float* part, int n_splits, __half* out, float* lse, hipStream_t s);
+hipError_t launch_merge_pair(const CacheView& v, const float* part, DecodeGrid dg, __half* out, float* lse, hipStream_t s);
 
 template <int K4, int K16, int NVG, int NKL, int RG, int THR, int G32, int PG, int RH>
 __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __restrict__ q, float scale_log2e,
-                                          int n_blocks, int n_res, int n_splits, float* __restrict__ part,
+                                          int n_blocks, int n_res, int n_splits, int n_waves, float* __restrict__ part,
                                           int accumulate_q, const NewToken& nt, const SeqCounts& sc, unsigned char* smem,
                                           u64_t* __restrict__ tickets, __half* __restrict__ out, float* __restrict__ lse) {
   using T = Tiers<K4, K16, THR>;
   constexpr int NU = T::NU;
   // scalars of the by-value view (kept in SGPRs; no references into the kernel argument)
-  // RG = 1: R = Gk = 128 known at compile time (one straight-line body per block record)
+  // RG >= 1: R = Gk = 128 known at compile time (one straight-line body per block record); 2: see kPolicyK
   // G32 = 1: key groups of 32 tokens.  A tile of 16 tokens must lie in ONE key group (its small operand carries
   // that group's scales), so tiles 0, 1 take the first 32 tokens of a 64-token span and tiles 2, 3 the second 32,
   // each lane group owning 8 tokens of either half; the value words of such a cache are interleaved to match
@@ -344,7 +371,7 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
   const int tid = threadIdx.x;
   // The arguments the start of the kernel needs are read together: read where each is first used they are four dependent
   // trips through the scalar cache.
-  asm("" : "+s"(n_splits) : "s"(sc.enabled), "s"(sc.n_units), "s"(n_blocks), "s"(Hq), "s"(Hkv), "s"(cv.cfg.in_dtype),
+  asm("" : "+s"(n_splits) : "s"(sc.enabled), "s"(sc.n_units), "s"(n_blocks), "s"(n_waves), "s"(Hq), "s"(Hkv), "s"(cv.cfg.in_dtype),
                "s"(rec_bytes), "s"(off_idx), "s"(off_v), "s"(off_v_s), "s"(g), "s"(NB), "s"(cv.RW), "s"(blocks), "s"(cv.table),
                "s"(cv.res_k), "s"(cv.res_v), "s"(cv.qacc), "s"(cv.qcnt), "s"(q), "s"(accumulate_q), "s"(nt.k), "s"(nt.v),
                "s"(nt.st.b), "s"(nt.st.h));
@@ -371,21 +398,22 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
   const int nt_dst = n_res - 1;      // fp16 row of this step's new token (if there is one): the last row in use
   // (the wavefront index is the same in all lanes: as a scalar it keeps record indices and addresses off the vector ALU)
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 15, kg = lane >> 4;
-  // Two workgroups share a compute unit, and among wavefronts of equal priority a SIMD issues from the OLDER one
-  // first.  With one round of workgroups (at most two per compute unit, all resident from the start) the workgroups
-  // of the second half of the grid are the younger ones everywhere: measured, their wavefronts finished 30 % later
+  // Two wavefronts share a SIMD, and among wavefronts of equal priority it issues from the OLDER one first.  The younger ones
+  // are the second four of a workgroup of eight; with workgroups of four and one round of them (at most two per compute unit,
+  // all resident from the start) the second half of the grid: measured, their wavefronts finished 30 % later
   // than their neighbours, which then left the SIMDs to a single wavefront each for the last quarter of the kernel.
   // The younger wavefronts therefore raise their priority during five of every eight half-records (s_setprio only
   // reorders instruction issue): each of the two then wins about half of the time and both finish nearly together.
   const int n_wgs = gridDim.x * gridDim.y;
-  const bool younger = n_wgs > kComputeUnits && n_wgs <= 2 * kComputeUnits &&
-                       (int)(blockIdx.y * gridDim.x + blockIdx.x) >= kComputeUnits;
+  const bool younger = n_waves > 4 ? wave >= 4
+                                   : n_wgs > kComputeUnits && n_wgs <= 2 * kComputeUnits &&
+                                         (int)(blockIdx.y * gridDim.x + blockIdx.x) >= kComputeUnits;
   const int head = n & 7, role = n >> 3;     // role 0: head of q*s, role 1: tail
   const bool live = head < g;
 
   unsigned short* sQraw = reinterpret_cast<unsigned short*>(smem);   // [8][128] q as given, in binary16
   int* sEq = reinterpret_cast<int*>(smem + 2048);                   // [8] exponents
-  __half* sQt = reinterpret_cast<__half*>(smem + 2048 + 256);       // normalised q [128][8]: the 8 heads of a channel in 16 bytes
+  __half* sQt = reinterpret_cast<__half*>(smem + 2048 + 512);       // normalised q [128][8]: the 8 heads of a channel in 16 bytes
   unsigned char* wbase = smem + kHdrLds + wave * kWaveLds;           // this wave's private region
   unsigned char* sK = wbase;                                        // record bytes [0, NKL KiB)
   unsigned char* sVm = wbase + kKPartMax;                           // v_s, v_z planes
@@ -394,9 +422,9 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
 
   // Work units of the pair: its block records, then the residual window in sub-units of 32 tokens, dealt
   // round-robin over all wavefronts of the pair's workgroups.
-  const int gw = split * kWaves + wave, n_gw = n_splits * kWaves;
+  const int gw = split * n_waves + wave, n_gw = n_splits * n_waves;
   // The wavefronts of a workgroup take neighbouring records at the same time (wavefront w of workgroup s
-  // takes units s*4 + w, then + 4*n_splits, ...): the chip streams a few long contiguous ranges.
+  // takes units s*n_waves + w, then + n_waves*n_splits, ...): the chip streams a few long contiguous ranges.
   const int blk_lo = gw;
   const int blk_hi = n_blocks;
   const int blk_step = n_gw;
@@ -536,10 +564,11 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
 #define MIXKVQ_IS_EARLY(C) (!RG || HS::early(C))
   // Cache policy.  A step reads every record once; what it leaves behind in the last-level cache (256 MB) is of use to the next
   // step over the same cache only where nothing else comes between, and beyond that size it only pushes other lines out.  The
-  // value words are therefore read with the non-temporal policy.  us per step, without / with: 512 pairs of 32 790 tokens
-  // (1.6 GB) 277 / 262, 32 pairs of 32 805 (82 MB) 22.5 / 22.9 over two caches in turn and 26.2 / 25.8 over seven; 24 steps of 24
-  // sequences of 60 to 12 003 tokens 468 / 468.
-  constexpr int kPolicyK = kKeep, kPolicyV = kStream;
+  // value words are therefore read with the non-temporal policy, and the keys too in launches that read more than half of that
+  // cache (RG = 2).  us per step, neither / values / both: 512 pairs of 32 790 tokens (1.6 GB) 277 / 262 / 260, 32 pairs of
+  // 131 091 (320 MB) 66.1 / 65.5 / 64.5; 32 pairs of 32 805 (82 MB) 22.5 / 22.9 / 23.3 over two caches in turn, 26.2 / 25.8 / 25.3
+  // over seven; 24 steps of 24 sequences of 60 to 12 003 tokens 468 / 468 / 481.
+  constexpr int kPolicyK = RG == 2 ? kStream : kKeep, kPolicyV = kStream;
 #define MIXKVQ_ISSUE_K_EARLY(REC)                                                                     \
   {                                                                                                          \
     unsigned at_ = lane16;                                                                                   \
@@ -641,7 +670,7 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
       const u32x4 t_ = *reinterpret_cast<const u32x4*>(qrow + 128 + (8 * kg < K16 ? 8 * kg : 0));              \
       _Pragma("unroll") for (int e = 0; e < 4; ++e) {                                                          \
         const unsigned v_ = 8 * kg + 2 * e < K16 ? t_[e] : 0u;   /* (the table goes on with the 4-bit tier) */ \
-        q16a[e] = kLeanTier16 || !role ? v_ : 0u;                                                                              \
+        q16a[e] = kLeanTier16 || !role ? v_ : 0u;                                                              \
         q16b[e] = role ? v_ : 0u;                                                                              \
       }                                                                                                        \
     }                                                                                                          \
@@ -700,7 +729,7 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
   // what follows waits for q alone (1.1 us less than waiting for everything asked for so far).
   uint2 qraw;
   {
-    const int h = tid >> 5, l32 = tid & 31;
+    const int h = tid >> 5 & 7, l32 = tid & 31;
     qraw = *reinterpret_cast<const uint2*>(q + ((size_t)b * Hq + jkv * g + (h < g ? h : g - 1)) * kD + l32 * 4);
   }
   MIXKVQ_ISSUE_K_EARLY(rec_first)
@@ -710,7 +739,7 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
 
   // ---- normalise q per head: qn = q * 2^-Eq with max|qn| in [1/2, 1) ----
   {
-    const int h = tid >> 5, l32 = tid & 31;
+    const int h = tid >> 5 & 7, l32 = tid & 31;      // (of eight wavefronts two write the same)
     if (cv.cfg.in_dtype) {      // bfloat16 queries enter as binary16
       qraw.x = bf16x2_to_f16x2(qraw.x);
       qraw.y = bf16x2_to_f16x2(qraw.y);
@@ -1262,7 +1291,7 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
   const int kg_e = (tid_e & 63) >> 4;
   float* wO = reinterpret_cast<float*>(wbase);        // [8][128] O, then [8] l
   float* sM = reinterpret_cast<float*>(smem + 2048 + 64);          // [waves][8]
-  int* sTicket = reinterpret_cast<int*>(smem + 2048 + 64 + 128);
+  int* sTicket = reinterpret_cast<int*>(smem + 2048 + 64 + 32 * kMaxWaves);
   if (role == 0 && live) {
 #pragma unroll
     for (int xp = 0; xp < 2; ++xp)
@@ -1285,27 +1314,31 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
     }
   }
   __syncthreads();
-  // one thread per (head, four channels)
-  const int eh = tid_e >> 5, c4 = tid_e & 31;
+  // one thread per (head, four channels); of eight wavefronts the first four
+  const int eh = tid_e >> 5 & 7, c4 = tid_e & 31, half = __builtin_amdgcn_readfirstlane(tid_e >> 8);
   const size_t bh = (size_t)b * Hq + (size_t)jkv * g + eh;
   if constexpr (kLeanEnd) part0 = sc.n_units ? (int)(sc.span[b] & 0xffffu) * Hkv + jkv * n_splits : p * n_splits;
   float* const pair = part + (size_t)part0 * g * kPartStrideM;
-  if (eh < g) {
+  if (eh < g && half == 0) {
     const float* r0 = reinterpret_cast<const float*>(smem + kHdrLds);
     constexpr int kWaveF = kWaveLds / 4;
-    float mw[kWaves], m_wg = -INFINITY;
+    float mw[kMaxWaves], m_wg = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-      mw[w] = sM[w * 8 + eh];
+    for (int w = 0; w < kMaxWaves; ++w) {
+      mw[w] = w < 4 || n_waves > 4 ? sM[w * 8 + eh] : -INFINITY;
       m_wg = fmaxf(m_wg, mw[w]);
     }
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     float lw = 0.f;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-      const float f = mw[w] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw[w] - m_wg);
-      acc += *reinterpret_cast<const f32x4*>(r0 + w * kWaveF + eh * kD + 4 * c4) * f;
-      lw = fmaf(r0[w * kWaveF + 8 * kD + eh], f, lw);
+    for (int w4 = 0; w4 < kMaxWaves; w4 += 4) {
+      if (w4 >= n_waves) break;
+#pragma unroll
+      for (int w = w4; w < w4 + 4; ++w) {
+        const float f = mw[w] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw[w] - m_wg);
+        acc += *reinterpret_cast<const f32x4*>(r0 + w * kWaveF + eh * kD + 4 * c4) * f;
+        lw = fmaf(r0[w * kWaveF + 8 * kD + eh], f, lw);
+      }
     }
     if (n_splits == 1) {     // the pair's only workgroup: the result is final
       store_output4(out, lse, bh, c4, acc, lw, m_wg, cv.cfg.in_dtype);
@@ -1323,7 +1356,8 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
     if (tid == 0) *sTicket = (int)__hip_atomic_fetch_add(tickets + p, (u64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     if (*sTicket == n_splits - 1) {     // all partials of the pair are there; the ticket goes back to 0 for the next launch
-      if (eh < g) merge_pair<true>(pair, n_splits, g, eh, c4, out, lse, bh, cv.cfg.in_dtype);
+      // (the wavefronts' regions are free: every thread is past the barriers above)
+      merge_pair<true>(pair, n_splits, n_waves >> 2, tid_e, g, smem + kHdrLds, out, lse, bh, cv.cfg.in_dtype);
       if (tid == 0) __hip_atomic_fetch_sub(tickets + p, (u64_t)n_splits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
@@ -1334,28 +1368,30 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
 // One launch per decode step: the workgroups (pair, split) share the pair's block records and its
 // residual window.
 template <int K4, int K16, int NVG, int NKL, int RG, int THR, int G32, int PG, int RH>
-__global__ void __launch_bounds__(kMfmaThreads, 2)
+__global__ void __launch_bounds__(64 * kMaxWaves, 2)
 decode_fused_kernel(CacheView cv, const __half* __restrict__ q, float scale, int n_blocks, int n_res, int n_splits,
-                    float* __restrict__ part, int accumulate_q, NewToken nt, SeqCounts sc, u64_t* __restrict__ tickets,
+                    int n_waves, float* __restrict__ part, int accumulate_q, NewToken nt, SeqCounts sc, u64_t* __restrict__ tickets,
                     __half* __restrict__ out, float* __restrict__ lse) {
   extern __shared__ __align__(16) unsigned char smem[];
-  mfma_part<K4, K16, NVG, NKL, RG, THR, G32, PG, RH>(cv, q, scale * 1.4426950408889634f, n_blocks, n_res, n_splits, part,
+  mfma_part<K4, K16, NVG, NKL, RG, THR, G32, PG, RH>(cv, q, scale * 1.4426950408889634f, n_blocks, n_res, n_splits, n_waves, part,
                                              accumulate_q, nt, sc, smem, tickets, out, lse);
 }
 
 template <int K4, int K16, int NVG, int NKL, int RG, int THR, int G32, int PG, int RH>
-static hipError_t launch_one(const CacheView& v, const __half* q, float scale, int n_blocks, int n_res, int n_splits,
+static hipError_t launch_one(const CacheView& v, const __half* q, float scale, int n_blocks, int n_res, DecodeGrid dg,
                              float* part, __half* out, float* lse, int accumulate_q, NewToken nt, const SeqCounts& sc,
                              hipStream_t s, hipEvent_t ev_start, hipEvent_t ev_stop) {
   auto kern = decode_fused_kernel<K4, K16, NVG, NKL, RG, THR, G32, PG, RH>;
-  const size_t lds = kHdrLds + (size_t)kWaves * kWaveLds;
+  const int n_splits = dg.n_splits;
+  const size_t lds = kHdrLds + (size_t)dg.n_waves * kWaveLds;
   // the kernel's LDS limit is raised once per device (a repeated call from another thread does no harm)
   static std::atomic<uint64_t> attr_set{0};
   int device = 0;
   if (hipError_t e = hipGetDevice(&device); e != hipSuccess) return e;
   const uint64_t bit = 1ull << (device & 63);
   if (!(attr_set.load(std::memory_order_acquire) & bit)) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       kHdrLds + kMaxWaves * kWaveLds);
     if (e != hipSuccess) return e;
     attr_set.fetch_or(bit, std::memory_order_release);
   }
@@ -1364,15 +1400,15 @@ static hipError_t launch_one(const CacheView& v, const __half* q, float scale, i
   u64_t* tickets = part == reinterpret_cast<float*>(v.ws) ? v.tickets : nullptr;
   if (ev_start && ev_stop) {
     // profiling aid: the two events take the start and the end time of this kernel itself (not of the launch call)
-    hipExtLaunchKernelGGL(kern, grid, dim3(kMfmaThreads), (uint32_t)lds, s, ev_start, ev_stop, 0u, v, q,
-                          scale, n_blocks, n_res, n_splits, part, accumulate_q, nt, sc, tickets, out, lse);
+    hipExtLaunchKernelGGL(kern, grid, dim3(64 * dg.n_waves), (uint32_t)lds, s, ev_start, ev_stop, 0u, v, q,
+                          scale, n_blocks, n_res, n_splits, dg.n_waves, part, accumulate_q, nt, sc, tickets, out, lse);
   } else {
-    kern<<<grid, dim3(kMfmaThreads), lds, s>>>(v, q, scale, n_blocks, n_res, n_splits, part, accumulate_q, nt, sc,
-                                                             tickets, out, lse);
+    kern<<<grid, dim3(64 * dg.n_waves), lds, s>>>(v, q, scale, n_blocks, n_res, n_splits, dg.n_waves, part, accumulate_q, nt,
+                                                  sc, tickets, out, lse);
   }
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   if (n_splits == 1 || tickets) return hipSuccess;
-  return launch_merge_pair(v, part, n_splits, out, lse, s);
+  return launch_merge_pair(v, part, dg, out, lse, s);
 }
 
 }  // namespace mixkvq

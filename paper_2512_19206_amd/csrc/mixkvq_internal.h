@@ -45,6 +45,10 @@ __host__ __device__ __forceinline__ int fp16_rows_of(const SeqCounts& sc, int b)
   return (int)(sc.n_fp16[b >> 1] >> (16 * (b & 1)) & 0xffffu);
 }
 
+// Grid of the matrix-core decode kernel: workgroups per pair, wavefronts per workgroup (4 or 8); streamed: the
+// launch reads more than the last-level cache keeps for the next one.
+struct DecodeGrid { int n_splits, n_waves, streamed; };
+
 // Sequences whose full window one launch of the pack kernel quantizes, passed by value (n == 0: every sequence of the
 // view, all starting at the same record).
 struct FlushList {
