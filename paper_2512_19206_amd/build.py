@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmixkvq.so")
-SOURCES = ["api.hip", "select_kernels.hip", "quantize_kernels.hip", "decode_kernels.hip", "decode_mfma.hip",
+SOURCES = ["api.hip", "select_kernels.hip", "quantize_kernels.hip", "decode_kernels.hip", "decode_mfma.hip", "decode_mfma_any_lengths.hip",
            "decode_mfma_generic_plain.hip", "decode_mfma_generic_g32.hip", "decode_mfma_generic_rh.hip"]
 OBJ_DIR = os.path.join(HERE, "_build")      # object files (git-ignored)
 

@@ -46,7 +46,7 @@ static bool try_generic(const GenericArgs& a, hipError_t* err) {
   if constexpr (NKL * 1024 <= kKPartMax) {
     const mixkvq_config& c = a.v.cfg;
     if (c.k4 == K4 && c.k16 == K16 && a.v.lay.NVG == NVG && c.policy == THR && a.g32 == G32 && a.rh == RH && a.nkl <= NKL) {
-      *err = launch_one<K4, K16, NVG, NKL, 0, THR, G32, 2, RH>(a.v, a.q, a.scale, a.n_blocks, a.n_res, a.dg, a.part,
+      *err = launch_one<K4, K16, NVG, NKL, 0, THR, G32, 2, RH, SeqCounts>(a.v, a.q, a.scale, a.n_blocks, a.n_res, a.dg, a.part,
                                                               a.out, a.lse, a.accumulate_q, a.nt, a.sc, a.s, a.ev_start,
                                                               a.ev_stop);
       return true;
@@ -55,6 +55,7 @@ static bool try_generic(const GenericArgs& a, hipError_t* err) {
   return false;
 }
 
+bool try_main_table_any_lengths(const GenericArgs& a, hipError_t* err);    // the table of decode_mfma_table.h with SeqCounts
 bool try_launch_generic_plain(const GenericArgs& a, hipError_t* err);      // key groups of 64 or 128 tokens
 bool try_launch_generic_g32(const GenericArgs& a, hipError_t* err);        // key groups of 32 tokens
 bool try_launch_generic_rh(const GenericArgs& a, hipError_t* err);         // records of 32 tokens

@@ -26,6 +26,7 @@
 #pragma once
 #include <hip/hip_ext.h>
 #include <atomic>
+#include <type_traits>
 #include "mixkvq_internal.h"
 
 namespace mixkvq {
@@ -343,10 +344,15 @@ __device__ __forceinline__ void merge_pair(const float* __restrict__ pair, int n
 
 hipError_t launch_merge_pair(const CacheView& v, const float* part, DecodeGrid dg, __half* out, float* lse, hipStream_t s);
 
-template <int K4, int K16, int NVG, int NKL, int RG, int THR, int G32, int PG, int RH>
+// What a launch over sequences of equal lengths passes in the place of SeqCounts: 3 KB of arguments less to write per launch,
+// and nothing to ask about lengths (a step's C call 5.3 -> 4.8 us; 24 pairs of 9 001 tokens 17.9 -> 17.6 us per step, 32 pairs of
+// 32 805 23.0 -> 22.8, 48 steps with records of 32 tokens 706 -> 701).
+struct NoCounts {};
+
+template <int K4, int K16, int NVG, int NKL, int RG, int THR, int G32, int PG, int RH, class Counts>
 __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __restrict__ q, float scale_log2e,
                                           int n_blocks, int n_res, int n_splits, int n_waves, float* __restrict__ part,
-                                          int accumulate_q, const NewToken& nt, const SeqCounts& sc, unsigned char* smem,
+                                          int accumulate_q, const NewToken& nt, const Counts& sc, unsigned char* smem,
                                           u64_t* __restrict__ tickets, __half* __restrict__ out, float* __restrict__ lse) {
   using T = Tiers<K4, K16, THR>;
   constexpr int NU = T::NU;
@@ -371,27 +377,31 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
   const int tid = threadIdx.x;
   // The arguments the start of the kernel needs are read together: read where each is first used they are four dependent
   // trips through the scalar cache.
-  asm("" : "+s"(n_splits) : "s"(sc.enabled), "s"(sc.n_units), "s"(n_blocks), "s"(n_waves), "s"(Hq), "s"(Hkv), "s"(cv.cfg.in_dtype),
+  constexpr bool kCounts = !std::is_same<Counts, NoCounts>::value;
+  if constexpr (kCounts) asm("" : "+s"(n_splits) : "s"(sc.enabled), "s"(sc.n_units));
+  asm("" : "+s"(n_splits) : "s"(n_blocks), "s"(n_waves), "s"(Hq), "s"(Hkv), "s"(cv.cfg.in_dtype),
                "s"(rec_bytes), "s"(off_idx), "s"(off_v), "s"(off_v_s), "s"(g), "s"(NB), "s"(cv.RW), "s"(blocks), "s"(cv.table),
                "s"(cv.res_k), "s"(cv.res_v), "s"(cv.qacc), "s"(cv.qcnt), "s"(q), "s"(accumulate_q), "s"(nt.k), "s"(nt.v),
                "s"(nt.st.b), "s"(nt.st.h));
   int p = blockIdx.x, split = blockIdx.y, part0 = p * n_splits;     // part0: first partial of the pair
   int b = p / Hkv;
   bool skip_pair = false;
-  if (sc.enabled) {      // sequences of different lengths: this pair's own counts; a sequence without tokens is skipped
-    if (sc.n_units) {      // grid (KV heads, units): the sequences have workgroups by their lengths
-      const int u = blockIdx.y;
-      b = (int)(sc.owner[u >> 2] >> (8 * (u & 3)) & 0xffu);
-    }
-    const unsigned span = sc.span[b];
-    n_blocks = sc.n_blocks[b];
-    n_res = fp16_rows_of(sc, b);
-    skip_pair = n_blocks == 0 && n_res == 0;
-    if (sc.n_units) {
-      n_splits = (int)(span >> 16);
-      split = blockIdx.y - (int)(span & 0xffffu);
-      part0 = (int)(span & 0xffffu) * Hkv + p * n_splits;
-      p += b * Hkv;
+  if constexpr (kCounts) {
+    if (sc.enabled) {      // sequences of different lengths: this pair's own counts; a sequence without tokens is skipped
+      if (sc.n_units) {      // grid (KV heads, units): the sequences have workgroups by their lengths
+        const int u = blockIdx.y;
+        b = (int)(sc.owner[u >> 2] >> (8 * (u & 3)) & 0xffu);
+      }
+      const unsigned span = sc.span[b];
+      n_blocks = sc.n_blocks[b];
+      n_res = fp16_rows_of(sc, b);
+      skip_pair = n_blocks == 0 && n_res == 0;
+      if (sc.n_units) {
+        n_splits = (int)(span >> 16);
+        split = blockIdx.y - (int)(span & 0xffffu);
+        part0 = (int)(span & 0xffffu) * Hkv + p * n_splits;
+        p += b * Hkv;
+      }
     }
   }
   const int jkv = p - b * Hkv;
@@ -1317,7 +1327,8 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
   // one thread per (head, four channels); of eight wavefronts the first four
   const int eh = tid_e >> 5 & 7, c4 = tid_e & 31, half = __builtin_amdgcn_readfirstlane(tid_e >> 8);
   const size_t bh = (size_t)b * Hq + (size_t)jkv * g + eh;
-  if constexpr (kLeanEnd) part0 = sc.n_units ? (int)(sc.span[b] & 0xffffu) * Hkv + jkv * n_splits : p * n_splits;
+  if constexpr (kLeanEnd && kCounts) part0 = sc.n_units ? (int)(sc.span[b] & 0xffffu) * Hkv + jkv * n_splits : p * n_splits;
+  else if constexpr (kLeanEnd) part0 = p * n_splits;
   float* const pair = part + (size_t)part0 * g * kPartStrideM;
   if (eh < g && half == 0) {
     const float* r0 = reinterpret_cast<const float*>(smem + kHdrLds);
@@ -1366,22 +1377,28 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
 }
 
 // One launch per decode step: the workgroups (pair, split) share the pair's block records and its
-// residual window.
-template <int K4, int K16, int NVG, int NKL, int RG, int THR, int G32, int PG, int RH>
-__global__ void __launch_bounds__(64 * kMaxWaves, 2)
-decode_fused_kernel(CacheView cv, const __half* __restrict__ q, float scale, int n_blocks, int n_res, int n_splits,
-                    int n_waves, float* __restrict__ part, int accumulate_q, NewToken nt, SeqCounts sc, u64_t* __restrict__ tickets,
-                    __half* __restrict__ out, float* __restrict__ lse) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  mfma_part<K4, K16, NVG, NKL, RG, THR, G32, PG, RH>(cv, q, scale * 1.4426950408889634f, n_blocks, n_res, n_splits, n_waves, part,
-                                             accumulate_q, nt, sc, smem, tickets, out, lse);
-}
+// residual window.  One kernel for sequences of any lengths, one for equal lengths.
+#define MIXKVQ_DECODE_KERNEL(COUNTS_)                                                                                      \
+  template <int K4, int K16, int NVG, int NKL, int RG, int THR, int G32, int PG, int RH>                                   \
+  __global__ void __launch_bounds__(64 * kMaxWaves, 2)                                                                     \
+  decode_fused_kernel(CacheView cv, const __half* __restrict__ q, float scale, int n_blocks, int n_res, int n_splits,      \
+                      int n_waves, float* __restrict__ part, int accumulate_q, NewToken nt, u64_t* __restrict__ tickets,   \
+                      __half* __restrict__ out, float* __restrict__ lse, COUNTS_ sc) {                                     \
+    extern __shared__ __align__(16) unsigned char smem[];                                                                  \
+    mfma_part<K4, K16, NVG, NKL, RG, THR, G32, PG, RH>(cv, q, scale * 1.4426950408889634f, n_blocks, n_res, n_splits,      \
+                                                       n_waves, part, accumulate_q, nt, sc, smem, tickets, out, lse);      \
+  }
+MIXKVQ_DECODE_KERNEL(SeqCounts)
+MIXKVQ_DECODE_KERNEL(NoCounts)
+#undef MIXKVQ_DECODE_KERNEL
 
-template <int K4, int K16, int NVG, int NKL, int RG, int THR, int G32, int PG, int RH>
+template <int K4, int K16, int NVG, int NKL, int RG, int THR, int G32, int PG, int RH, class Counts>
 static hipError_t launch_one(const CacheView& v, const __half* q, float scale, int n_blocks, int n_res, DecodeGrid dg,
                              float* part, __half* out, float* lse, int accumulate_q, NewToken nt, const SeqCounts& sc,
                              hipStream_t s, hipEvent_t ev_start, hipEvent_t ev_stop) {
-  auto kern = decode_fused_kernel<K4, K16, NVG, NKL, RG, THR, G32, PG, RH>;
+  void (*const kern)(CacheView, const __half*, float, int, int, int, int, float*, int, NewToken, u64_t*, __half*, float*, Counts) =
+      decode_fused_kernel<K4, K16, NVG, NKL, RG, THR, G32, PG, RH>;
+  constexpr bool kCounts = !std::is_same<Counts, NoCounts>::value;
   const int n_splits = dg.n_splits;
   const size_t lds = kHdrLds + (size_t)dg.n_waves * kWaveLds;
   // the kernel's LDS limit is raised once per device (a repeated call from another thread does no harm)
@@ -1395,16 +1412,21 @@ static hipError_t launch_one(const CacheView& v, const __half* q, float scale, i
     if (e != hipSuccess) return e;
     attr_set.fetch_or(bit, std::memory_order_release);
   }
-  const dim3 grid = sc.n_units ? dim3(v.cfg.Hkv, sc.n_units) : dim3(v.P, n_splits);
+  const dim3 grid = kCounts && sc.n_units ? dim3(v.cfg.Hkv, sc.n_units) : dim3(v.P, n_splits);
+  const Counts& counts = [&]() -> const Counts& {
+    static const NoCounts none{};
+    if constexpr (kCounts) return sc;
+    else return none;
+  }();
   // the partials in the cache's workspace come with tickets for the merge; any other buffer takes the merge launch
   u64_t* tickets = part == reinterpret_cast<float*>(v.ws) ? v.tickets : nullptr;
   if (ev_start && ev_stop) {
     // profiling aid: the two events take the start and the end time of this kernel itself (not of the launch call)
     hipExtLaunchKernelGGL(kern, grid, dim3(64 * dg.n_waves), (uint32_t)lds, s, ev_start, ev_stop, 0u, v, q,
-                          scale, n_blocks, n_res, n_splits, dg.n_waves, part, accumulate_q, nt, sc, tickets, out, lse);
+                          scale, n_blocks, n_res, n_splits, dg.n_waves, part, accumulate_q, nt, tickets, out, lse, counts);
   } else {
     kern<<<grid, dim3(64 * dg.n_waves), lds, s>>>(v, q, scale, n_blocks, n_res, n_splits, dg.n_waves, part, accumulate_q, nt,
-                                                  sc, tickets, out, lse);
+                                                  tickets, out, lse, counts);
   }
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   if (n_splits == 1 || tickets) return hipSuccess;
