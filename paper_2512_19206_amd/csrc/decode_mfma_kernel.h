@@ -172,7 +172,8 @@ __device__ __forceinline__ record_t record_at(const unsigned char* base, int byt
   return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(((unsigned long long)hi << 32) | lo), 0,
                                            __builtin_amdgcn_readfirstlane(bytes), 0x00020000);      // raw, unstructured
 }
-constexpr int kKeep = 0, kStream = 2;      // cache policy of a load: as usual, or read once (nt)
+// cache policy of a load: as usual, read once (nt), or past the L2 caches to what other workgroups have stored (sc1)
+constexpr int kKeep = 0, kStream = 2, kAgent = 16;
 template <int POLICY>
 __device__ __forceinline__ u32x4 load16(record_t r, unsigned off) { return __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, POLICY); }
 template <int POLICY>
@@ -233,8 +234,11 @@ struct HalfSplit {
 // ---------------------------------------------------------------------------
 // Split-K partials and their log-sum-exp merge: m* = max m_i, l* = sum l_i 2^(m_i - m*),
 // O = sum O_i 2^(m_i - m*) / l* (log2 domain).  The partial of one workgroup is O [g][128], then (m, l) [g], binary32.
-// A thread owns four channels of one head and sixteen partials are in flight per thread before the first wait; with eight
-// wavefronts the two halves of the workgroup take alternate partials and join their results through LDS.
+// A thread owns four channels of one head and ten partials are in flight per thread before the first wait; with eight
+// wavefronts the two halves of the workgroup take alternate partials and join their results through LDS.  One workgroup per pair
+// runs this code, its first time on that compute unit as a rule, so its size counts: offsets into a buffer and no special case
+// for an empty partial took 48 steps with records of 32 tokens (8 partials) from 701 to 680 us, ten partials in flight instead
+// of sixteen to 677 (eight: 675, four: 672), one pair of 1 027 tokens (9 partials) from 9.0 to 8.7 and 8.5 (8.9, 9.1).
 //
 // The last workgroup of a pair to finish merges it (see CacheView::tickets).  The partials, the ticket and the
 // loads are agent-scope accesses, which go past the chip's eight L2 caches; no cache is flushed for them.  A launch of
@@ -245,13 +249,6 @@ struct HalfSplit {
 // is the same.
 // ---------------------------------------------------------------------------
 typedef unsigned long long u64_t;
-template <bool SHARED>
-__device__ __forceinline__ float2 load_part2(const float* p) {
-  if constexpr (SHARED)
-    return __builtin_bit_cast(float2, __hip_atomic_load(reinterpret_cast<const u64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-  else
-    return *reinterpret_cast<const float2*>(p);
-}
 __device__ __forceinline__ void store_part2(float* p, float x, float y) {
   __hip_atomic_store(reinterpret_cast<u64_t*>(p), __builtin_bit_cast(u64_t, make_float2(x, y)), __ATOMIC_RELAXED,
                      __HIP_MEMORY_SCOPE_AGENT);
@@ -278,37 +275,42 @@ __device__ __forceinline__ void store_output4(__half* out, float* lse, size_t bh
 struct Merged { f32x4 o; float l, m; };
 template <bool SHARED>
 __device__ __forceinline__ Merged merge_parts(const float* __restrict__ pair, int first, int step, int n_parts, int g, int h, int c4) {
-  const int stride = g * kPartStrideM;
-  constexpr int kFly = 16;
+  constexpr int kFly = 10, kPolicy = SHARED ? kAgent : kKeep;
+  const unsigned stride = 4u * (unsigned)(g * kPartStrideM);
+  const record_t all = record_at(reinterpret_cast<const unsigned char*>(pair), (int)(n_parts * stride));
+  unsigned at_o = first * stride + 4u * (unsigned)(h * kD + 4 * c4), at_ml = first * stride + 4u * (unsigned)(g * kD + 2 * h);
   Merged r{{0.f, 0.f, 0.f, 0.f}, 0.f, -INFINITY};
   for (int s0 = first; s0 < n_parts; s0 += kFly * step) {
-    float2 ml[kFly], oa[kFly], ob[kFly];
+    f32x4 o[kFly];
+    float m[kFly], l[kFly];
 #pragma unroll
     for (int i = 0; i < kFly; ++i) {
-      ml[i] = make_float2(-INFINITY, 0.f);
-      oa[i] = ob[i] = make_float2(0.f, 0.f);
+      o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      m[i] = -INFINITY;
+      l[i] = 0.f;
       if (s0 + i * step < n_parts) {
-        const float* p = pair + (s0 + i * step) * stride;
-        ml[i] = load_part2<SHARED>(p + g * kD + 2 * h);
-        oa[i] = load_part2<SHARED>(p + h * kD + 4 * c4);
-        ob[i] = load_part2<SHARED>(p + h * kD + 4 * c4 + 2);
+        const u32x2 ml = load8<kPolicy>(all, at_ml);
+        o[i] = __builtin_bit_cast(f32x4, load16<kPolicy>(all, at_o));
+        m[i] = __uint_as_float(ml[0]);
+        l[i] = __uint_as_float(ml[1]);
+        at_ml += step * stride;
+        at_o += step * stride;
       }
     }
     float m_new = r.m;
 #pragma unroll
-    for (int i = 0; i < kFly; ++i) m_new = fmaxf(m_new, ml[i].x);
-    const float alpha = r.m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(r.m - m_new);
+    for (int i = 0; i < kFly; ++i) m_new = fmaxf(m_new, m[i]);
+    const float m_ref = m_new == -INFINITY ? 0.f : m_new;      // (exp2(-inf) = 0 is the weight of a partial without tokens)
+    const float alpha = __builtin_amdgcn_exp2f(r.m - m_ref);
     r.l *= alpha;
     r.o *= alpha;
     r.m = m_new;
 #pragma unroll
     for (int i = 0; i < kFly; ++i) {
-      const float w = ml[i].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[i].x - m_new);
-      r.l = fmaf(ml[i].y, w, r.l);
-      r.o[0] = fmaf(oa[i].x, w, r.o[0]);
-      r.o[1] = fmaf(oa[i].y, w, r.o[1]);
-      r.o[2] = fmaf(ob[i].x, w, r.o[2]);
-      r.o[3] = fmaf(ob[i].y, w, r.o[3]);
+      const float w = __builtin_amdgcn_exp2f(m[i] - m_ref);
+      r.l = fmaf(l[i], w, r.l);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) r.o[c] = fmaf(o[i][c], w, r.o[c]);
     }
   }
   return r;
