@@ -9,8 +9,8 @@
 namespace mixkvq {
 
 constexpr int kDecThreads = 256;
-// Two launches that read this much each fill the last-level cache (256 MB).
-constexpr int64_t kStreamBytes = 128ll << 20;
+// Launches that read more than this, the size of the last-level cache, ask for their keys with the non-temporal policy too.
+constexpr int64_t kStreamBytes = 256ll << 20;
 constexpr int kMaxG = 8;
 constexpr int kPartStride = kD + 2;   // floats per (split, head): O[D], m, l
 
@@ -265,16 +265,24 @@ bool try_launch_decode_mfma(const CacheView& v, const __half* q, float scale, in
                             float* part, __half* out, float* lse, int accumulate_q, NewToken nt, const SeqCounts& sc,
                             hipStream_t s, hipEvent_t ev_start, hipEvent_t ev_stop, hipError_t* err);
 
+// Workgroups of eight wavefronts instead of twice as many of four?  They leave half as many partials to the pair's last
+// workgroup, which pulls them past the caches with the bandwidth of one compute unit, and draw half as many tickets; but their
+// wavefronts share a compute unit, and start and end together.  So: for a shorter chain of records per wavefront (rounding);
+// with the same chain, where those of four would share compute units (more than 256 of them) and a pair has more than twelve, a
+// merge of more than one round, or would have no partials left at all; with a compute unit each only from 25 on.
+// us per step, four / eight: 24 pairs of 9 001 tokens (18 / 9 workgroups a pair) 19.4 / 17.9, 32 of 32 805 (16 / 8) 23.1 / 22.6, 188 of
+// 990 (2 / 1) 15.0 / 13.2, 3 of 15 354 (60 / 30) 15.7 / 12.7, 48 steps of 32 pairs with records of 32 tokens (16 / 8) 718 / 705; on
+// the other side of the lines 14 pairs of 7 218 (15 / 8), 43 steps, 500 / 520, 8 of 6 071 (13 / 7), 33 steps, 413 / 466, 112 of 3 453
+// (4 / 2) 16.4 / 17.8, one of 1 027 (9 / 5) 9.8 / 10.7.
+static bool eight_wavefronts(int chain4, int chain8, int n4, int n8, int wgs4) {
+  if (chain8 != chain4) return chain8 < chain4;
+  return wgs4 > kDecodeTargetWGs / 2 ? n4 > 12 || n8 == 1 : n4 > 24;
+}
+
 // Split count of a decode launch (one rule for every caller): enough workgroups to fill the chip (tunable through
 // MIXKVQ_DECODE_WGS for experiments), never above the ceiling the workspace was sized for.  *mc is the grid the matrix-core
 // kernel takes: its fp16 rows are cut into sub-units of 32 tokens and a wavefront takes at most one of
 // them, so a pair needs at least as many wavefronts as it has sub-units.
-// Where a pair has several workgroups of four wavefronts, half as many workgroups of eight (`wide`) leave half as many
-// partials to the pair's last workgroup, which pulls them past the caches with the bandwidth of one compute unit, and draw half
-// as many tickets.  They are taken unless rounding lengthens the chain of records a wavefront works through, or the workgroups of
-// four have a compute unit each.  us per step, four / eight: 24 pairs of 9 001 tokens (18 / 9 partials) 19.4 / 17.9, 32 pairs of
-// 32 805 (16 / 8) 23.1 / 22.6, records of 32 tokens, 32 pairs of 4 100, 48 steps 718 / 705, 24 sequences of 60 to 12 003, 24 steps
-// 487 / 468; one pair of 1 027 tokens, which keeps its nine workgroups of four, 9.8 / 10.7.
 static void choose_splits(const CacheView& v, int n_blocks, int n_fp16, bool wide, int* n_splits_out, DecodeGrid* mc) {
   static const int target_wgs = [] {
     const char* e = getenv("MIXKVQ_DECODE_WGS");
@@ -301,7 +309,7 @@ static void choose_splits(const CacheView& v, int n_blocks, int n_fp16, bool wid
   if (n8 < (subs + 7) / 8) n8 = (subs + 7) / 8;
   if (n8 < 1) n8 = 1;
   const int chain8 = (units + 8 * n8 - 1) / (8 * n8), chain4 = (units + 4 * n_splits_mc - 1) / (4 * n_splits_mc);
-  if (chain8 < chain4 || (chain8 == chain4 && v.P * n_splits_mc > target_wgs / 2)) *mc = DecodeGrid{n8, 8, 0};
+  if (eight_wavefronts(chain4, chain8, n_splits_mc, n8, v.P * n_splits_mc)) *mc = DecodeGrid{n8, 8, 0};
 }
 
 // Deals the matrix-core kernel's workgroups to sequences of different lengths: with the same number for every sequence the
@@ -310,7 +318,7 @@ static void choose_splits(const CacheView& v, int n_blocks, int n_fp16, bool wid
 // at once (two per compute unit; never fewer than the equal deal has), with the fp16 rows' minimum for every sequence and
 // at most the partials the workspace has room for.  Host work: a few divisions per sequence.  24 steps of 24 sequences of
 // 60 to 12 003 tokens, 4 KV heads: 617 us with five workgroups for every pair, 509 this way.
-// Workgroups of eight wavefronts are dealt (see choose_splits) unless those of four give a shorter chain.
+// (Workgroups of four or eight wavefronts: see eight_wavefronts, with the longest sequence's numbers.)
 static void deal_by_length(const CacheView& v, int n_splits, SeqCounts* sc, DecodeGrid* dg) {
   const int B = v.cfg.B;
   int most = 1;
@@ -346,8 +354,17 @@ static void deal_by_length(const CacheView& v, int n_splits, SeqCounts* sc, Deco
   if (budget > kMaxUnits) return;
   int waves = 4, chain = shortest(4, budget, (most + 4 * n_splits - 1) / (4 * n_splits) - 1);      // (the equal deal's always fits)
   if (const int c8 = shortest(8, kDecodeTargetWGs / 2 / v.cfg.Hkv, chain); c8 <= chain) {
-    waves = 8;
-    chain = c8;
+    int wgs4 = 0, n4 = 0, n8 = 0;
+    for (int b = 0; b < B; ++b) {
+      const int u = units_of(b, chain, 4), w = units_of(b, c8, 8);
+      wgs4 += u * v.cfg.Hkv;
+      n4 = u > n4 ? u : n4;
+      n8 = w > n8 ? w : n8;
+    }
+    if (eight_wavefronts(chain, c8, n4, n8, wgs4)) {
+      waves = 8;
+      chain = c8;
+    }
   }
   int first = 0;
   for (int b = 0; b < B; ++b) {

@@ -20,6 +20,12 @@ hipError_t launch_merge_pair(const CacheView& v, const float* part, DecodeGrid d
   return hipGetLastError();
 }
 
+template <class Counts>
+static hipError_t launch_rows_only(const GenericArgs& a) {
+  return launch_one<0, 0, 1, 1, 3, 0, 0, 0, 0, Counts>(a.v, a.q, a.scale, a.n_blocks, a.n_res, a.dg, a.part, a.out, a.lse,
+                                                       a.accumulate_q, a.nt, a.sc, a.s, a.ev_start, a.ev_stop);
+}
+
 // Returns true and launches when the configuration is one the matrix-core kernel covers.
 bool try_launch_decode_mfma(const CacheView& v, const __half* q, float scale, int n_blocks, int n_res, DecodeGrid dg,
                             float* part, __half* out, float* lse, int accumulate_q, NewToken nt, const SeqCounts& sc,
@@ -40,6 +46,10 @@ bool try_launch_decode_mfma(const CacheView& v, const __half* q, float scale, in
   const int g32 = c.Gk == 32 && !rh;
   const GenericArgs a{v, q, scale, n_blocks, n_res, dg, part, out, lse, accumulate_q, nt, sc, s, ev_start, ev_stop,
                       nkl, g32, rh};
+  if (n_blocks < 1) {      // fp16 rows only: one variant for every configuration
+    *err = sc.enabled ? launch_rows_only<SeqCounts>(a) : launch_rows_only<NoCounts>(a);
+    return true;
+  }
   if (sc.enabled ? try_main_table_any_lengths(a, err) : try_main_table<NoCounts>(a, err)) return true;
   // not one of the variants above: the wider tables (they take either layout and any lengths)
   return rh ? try_launch_generic_rh(a, err) : (g32 ? try_launch_generic_g32(a, err) : try_launch_generic_plain(a, err));

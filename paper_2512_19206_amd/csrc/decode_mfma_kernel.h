@@ -38,7 +38,7 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kComputeUnits = 256;              // MI355X
-constexpr int kMaxWaves = 8;                    // a workgroup has four or eight wavefronts (see choose_splits)
+constexpr int kMaxWaves = 8;                    // a workgroup has four or eight wavefronts (see eight_wavefronts)
 constexpr int kKPartMax = 12288;                // bytes of a record before the value plane (staged in LDS)
 constexpr int kVMetaMax = 2048;                 // value scales + zero-points of one block
 constexpr int kQsStride = 168;                  // halfs per head row of the slot-ordered q table (160 slots + padding)
@@ -234,11 +234,11 @@ struct HalfSplit {
 // ---------------------------------------------------------------------------
 // Split-K partials and their log-sum-exp merge: m* = max m_i, l* = sum l_i 2^(m_i - m*),
 // O = sum O_i 2^(m_i - m*) / l* (log2 domain).  The partial of one workgroup is O [g][128], then (m, l) [g], binary32.
-// A thread owns four channels of one head and ten partials are in flight per thread before the first wait; with eight
+// A thread owns four channels of one head and twelve partials are in flight per thread before the first wait; with eight
 // wavefronts the two halves of the workgroup take alternate partials and join their results through LDS.  One workgroup per pair
 // runs this code, its first time on that compute unit as a rule, so its size counts: offsets into a buffer and no special case
-// for an empty partial took 48 steps with records of 32 tokens (8 partials) from 701 to 680 us, ten partials in flight instead
-// of sixteen to 677 (eight: 675, four: 672), one pair of 1 027 tokens (9 partials) from 9.0 to 8.7 and 8.5 (8.9, 9.1).
+// for an empty partial took 48 steps with records of 32 tokens (8 partials) from 701 to 680 us, twelve partials in flight instead
+// of sixteen to 676 (eight: 675, four: 672), one pair of 1 027 tokens (9 partials) from 9.0 to 8.7 and 8.6 (8.9, 9.1).
 //
 // The last workgroup of a pair to finish merges it (see CacheView::tickets).  The partials, the ticket and the
 // loads are agent-scope accesses, which go past the chip's eight L2 caches; no cache is flushed for them.  A launch of
@@ -275,7 +275,7 @@ __device__ __forceinline__ void store_output4(__half* out, float* lse, size_t bh
 struct Merged { f32x4 o; float l, m; };
 template <bool SHARED>
 __device__ __forceinline__ Merged merge_parts(const float* __restrict__ pair, int first, int step, int n_parts, int g, int h, int c4) {
-  constexpr int kFly = 10, kPolicy = SHARED ? kAgent : kKeep;
+  constexpr int kFly = 12, kPolicy = SHARED ? kAgent : kKeep;
   const unsigned stride = 4u * (unsigned)(g * kPartStrideM);
   const record_t all = record_at(reinterpret_cast<const unsigned char*>(pair), (int)(n_parts * stride));
   unsigned at_o = first * stride + 4u * (unsigned)(h * kD + 4 * c4), at_ml = first * stride + 4u * (unsigned)(g * kD + 2 * h);
@@ -360,6 +360,8 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
   constexpr int NU = T::NU;
   // scalars of the by-value view (kept in SGPRs; no references into the kernel argument)
   // RG >= 1: R = Gk = 128 known at compile time (one straight-line body per block record); 2: see kPolicyK
+  // RG = 3: no block records at all, fp16 rows only (the other parameters do not matter then; 6.8 -> 6.5 us per
+  // step of one sequence of 90 tokens, mostly loads that were asked for in vain)
   // G32 = 1: key groups of 32 tokens.  A tile of 16 tokens must lie in ONE key group (its small operand carries
   // that group's scales), so tiles 0, 1 take the first 32 tokens of a 64-token span and tiles 2, 3 the second 32,
   // each lane group owning 8 tokens of either half; the value words of such a cache are interleaved to match
@@ -369,6 +371,7 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
   // group 0 instead (finite numbers that meet weights of exactly zero).
   static_assert(!(G32 && RG), "RG fixes Gk = 128");
   static_assert(!(RH && (G32 || RG)), "RH is the plain tile order on a record of 32 tokens");
+  constexpr bool kRecords = RG != 3;
   const int R = RG ? 128 : cv.cfg.R, Gk = RG ? 128 : (G32 ? 32 : cv.cfg.Gk);
   const int g = cv.g, Hq = cv.cfg.Hq, Hkv = cv.cfg.Hkv, NB = cv.NB;
   const int rec_bytes = cv.lay.rec_bytes, off_idx = cv.lay.off_idx, off_klo_s = cv.lay.off_klo_s,
@@ -438,7 +441,7 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
   // The wavefronts of a workgroup take neighbouring records at the same time (wavefront w of workgroup s
   // takes units s*n_waves + w, then + n_waves*n_splits, ...): the chip streams a few long contiguous ranges.
   const int blk_lo = gw;
-  const int blk_hi = n_blocks;
+  const int blk_hi = kRecords ? n_blocks : 0;
   const int blk_step = n_gw;
   // fp16 rows (sink tokens, then the residual window; n_res counts both): sub-units of 32 tokens follow the
   // records in the same round-robin deal
@@ -576,8 +579,8 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
 #define MIXKVQ_IS_EARLY(C) (!RG || HS::early(C))
   // Cache policy.  A step reads every record once; what it leaves behind in the last-level cache (256 MB) is of use to the next
   // step over the same cache only where nothing else comes between, and beyond that size it only pushes other lines out.  The
-  // value words are therefore read with the non-temporal policy, and the keys too in launches that read more than half of that
-  // cache (RG = 2).  us per step, neither / values / both: 512 pairs of 32 790 tokens (1.6 GB) 277 / 262 / 260, 32 pairs of
+  // value words are therefore read with the non-temporal policy, and the keys too in launches that read more than it
+  // holds (RG = 2).  us per step, neither / values / both: 512 pairs of 32 790 tokens (1.6 GB) 277 / 262 / 260, 32 pairs of
   // 131 091 (320 MB) 66.1 / 65.5 / 64.5; 32 pairs of 32 805 (82 MB) 22.5 / 22.9 / 23.3 over two caches in turn, 26.2 / 25.8 / 25.3
   // over seven; 24 steps of 24 sequences of 60 to 12 003 tokens 468 / 468 / 481.
   constexpr int kPolicyK = RG == 2 ? kStream : kKeep, kPolicyV = kStream;
@@ -706,14 +709,14 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
       nt_row = *reinterpret_cast<const uint4*>((lane < 16 ? nt.k : nt.v) + src);
     }
   }
-  const bool has_rec = blk < blk_hi;
+  const bool has_rec = kRecords && blk < blk_hi;
   if (tab) {
     if (has_rec) slot_cur = tab[blk];
     if (blk + blk_step < blk_hi) slot_nx = tab[blk + blk_step];
   }
   const record_t rec_first = record_at(MIXKVQ_REC(MIXKVQ_REC_INDEX(blk, slot_cur)), has_rec ? rec_bytes : 0);
   unsigned list_first = 255u;      // entry `lane` of the first record's channel list
-  if (K4 + K16 > 0) list_first = (unsigned char)__builtin_amdgcn_raw_buffer_load_b8(rec_first, off_idx + lane, 0, 0);
+  if (kRecords && K4 + K16 > 0) list_first = (unsigned char)__builtin_amdgcn_raw_buffer_load_b8(rec_first, off_idx + lane, 0, 0);
   // Residual sub-unit of this wavefront: 2 key tiles x 4 contraction steps, 32 value rows.  This step's new
   // token is read from the caller's tensors.
   const int sub_t0 = 32 * (my_sub > 0 ? my_sub : 0);
@@ -744,10 +747,10 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
     const int h = tid >> 5 & 7, l32 = tid & 31;
     qraw = *reinterpret_cast<const uint2*>(q + ((size_t)b * Hq + jkv * g + (h < g ? h : g - 1)) * kD + l32 * 4);
   }
-  MIXKVQ_ISSUE_K_EARLY(rec_first)
+  if (kRecords) MIXKVQ_ISSUE_K_EARLY(rec_first)
   // what the layout of q needs of the first record's selection, while q is on its way
   int slot0_ = lane, slot1_ = 64 + lane, n16_ = 0, n4_ = 0;
-  MIXKVQ_QUERY_SLOTS(list_first)
+  if (kRecords) MIXKVQ_QUERY_SLOTS(list_first)
 
   // ---- normalise q per head: qn = q * 2^-Eq with max|qn| in [1/2, 1) ----
   {
@@ -799,9 +802,11 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
   // q in the slot order of the first record, while that record is still on its way (its value words are
   // asked for only now: the first answers come the sooner the less every wavefront asks for at once)
   // (in the order of use: first half of the values, rest of the keys, second half of the values)
-  MIXKVQ_ISSUE_V_HALF(rec_first, 0)
-  MIXKVQ_ISSUE_K_LATE(rec_first)
-  MIXKVQ_ISSUE_V_HALF(rec_first, 1)
+  if (kRecords) {
+    MIXKVQ_ISSUE_V_HALF(rec_first, 0)
+    MIXKVQ_ISSUE_K_LATE(rec_first)
+    MIXKVQ_ISSUE_V_HALF(rec_first, 1)
+  }
   if (has_rec) MIXKVQ_LAYOUT_Q(true)
 
   // ---- residual window (fp16 keys/values): 32 tokens per wavefront, before its block records ----
@@ -1016,7 +1021,7 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
   MIXKVQ_PHASE(2)
   [[maybe_unused]] int phase_i = 3;
   [[maybe_unused]] int prio_iter = 0;
-  for (; blk < blk_hi; blk += blk_step, ++prio_iter) {
+  for (; kRecords && blk < blk_hi; blk += blk_step, ++prio_iter) {
     // ---- stage the key part and value metadata in LDS (wave-private: no barrier needed) ----
 #pragma unroll
     for (int c = 0; c < NKL; ++c)
