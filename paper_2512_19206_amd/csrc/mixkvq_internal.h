@@ -204,39 +204,65 @@ __device__ __forceinline__ void tier_sizes(const mixkvq_config& cfg, int c16, in
   }
 }
 
-// Tier (2: fp16, 1: 4 bit, 0: 2 bit) of channel tid in threads 0..127 of a workgroup of 256 or more (0 in the others), from the
-// 128 scores sA (16-byte aligned) and the pair's token count: the rank of a channel is the number of channels that beat it
-// (higher score, or equal score and lower index).  The two halves of the workgroup compare against 64 channels each, with
-// the loop unrolled so that the LDS reads run ahead of the compares (as a plain loop with the threshold counts in it, one
-// LDS latency per channel, this took 6.6 us of the 19 us of a pack workgroup).  sPart: 256 words.
-__device__ __forceinline__ int rank_channels(const mixkvq_config& cfg, unsigned long long count, const double* sA,
+// Tier (2: fp16, 1: 4 bit, 0: 2 bit) of channel tid in threads 0..127 of a workgroup of NT (0 in the others), from the 128
+// scores sA, the upper halves of their bit patterns sHi (both 16-byte aligned, written by the caller ahead of a barrier) and the
+// pair's token count.  The rank of a channel is the number of channels that beat it (higher score, or equal score and lower
+// index).  Scores are not negative, so their bit patterns order like them, and the upper halves decide all but ties among
+// those: a thread counts the upper halves of 128 * 128 / NT channels that are above its own (a compare and an add with carry
+// each, where two binary64 compares and the index took eight instructions), its wavefront counts the equal ones, and only
+// where there are more of them than the channels themselves the lower halves and the indices are looked at.
+// sPart: NT words.  (9 chunks of 1 000 tokens, selected and then packed by their own scores under thresholds: 226 -> 217 us.)
+template <int NT>
+__device__ __forceinline__ int rank_channels(const mixkvq_config& cfg, unsigned long long count, const double* sA, const unsigned* sHi,
                                              unsigned* sPart) {
-  const int tid = threadIdx.x, d = tid & (kD - 1), e0 = (tid >> 7 & 1) * (kD / 2);
-  const double Ad = sA[d];
-  int rank = 0;
-  const double2* row = reinterpret_cast<const double2*>(sA + e0);
-#pragma unroll 16
-  for (int i = 0; i < kD / 4; ++i) {
-    const double2 o = row[i];
-    const int e = e0 + 2 * i;
-    rank += (o.x > Ad) || (o.x == Ad && e < d);
-    rank += (o.y > Ad) || (o.y == Ad && e + 1 < d);
+  constexpr int NE = kD * kD / NT;
+  const int tid = threadIdx.x, d = tid & (kD - 1), part = tid >> 7, e0 = part * NE;
+  const unsigned mine = sHi[d];
+  const uint4* row = reinterpret_cast<const uint4*>(sHi + e0);
+  int rank = 0, equal = 0;
+#pragma unroll
+  for (int i = 0; i < NE / 4; ++i) {
+    const uint4 o = row[i];
+    const unsigned w[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      rank += w[k] > mine;
+      equal += __popcll(__ballot(w[k] == mine));
+    }
   }
+  // a wavefront's channels are 64 (tid >> 6 & 1) and up: each equals itself where they are among the NE
+  const int first = 64 * (tid >> 6 & 1), self = e0 < first + 64 && first < e0 + NE ? (NE < 64 ? NE : 64) : 0;
   int c16 = 0, c_any = 0;      // channels above the thresholds among the 64 of this wavefront
-  if (cfg.policy == 1) {
+  if (cfg.policy == 1 && part == 0) {
+    const double Ad = sA[d];
     const double thr16 = score_threshold(cfg.tau16, count, cfg.score_mode);
     const double thr4 = score_threshold(cfg.tau4, count, cfg.score_mode);
     c16 = __popcll(__ballot(Ad > thr16));
     c_any = __popcll(__ballot(Ad > thr16 || Ad > thr4));
   }
-  if (tid < 2 * kD) sPart[tid] = (unsigned)rank | ((unsigned)c16 << 8) | ((unsigned)c_any << 16);     // rank, c16, c_any <= 64 each
+  sPart[tid] = (unsigned)rank | ((unsigned)c16 << 8) | ((unsigned)c_any << 16) | (equal != self ? 0x80000000u : 0u);     // rank, c16, c_any <= 64 each
   __syncthreads();
   if (tid >= kD) return 0;
-  const unsigned mine = sPart[tid], other = sPart[tid ^ 64];                       // the two wavefronts with the channels
+  const unsigned here = sPart[tid], other = sPart[tid ^ 64];                       // the two wavefronts with the channels
   int n16, n4;
-  tier_sizes(cfg, (int)((mine >> 8) & 0xffu) + (int)((other >> 8) & 0xffu), (int)((mine >> 16) & 0xffu) + (int)((other >> 16) & 0xffu),
+  tier_sizes(cfg, (int)((here >> 8) & 0xffu) + (int)((other >> 8) & 0xffu), (int)((here >> 16) & 0x7fu) + (int)((other >> 16) & 0x7fu),
              &n16, &n4);
-  rank = (int)(mine & 0xffu) + (int)(sPart[tid + kD] & 0xffu);
+  unsigned ties = 0u;
+  rank = 0;
+#pragma unroll
+  for (int k = 0; k < NT / kD; ++k) {
+    rank += (int)(sPart[tid + k * kD] & 0xffu);
+    ties |= sPart[tid + k * kD];
+  }
+  if (ties >> 31) {
+    const double Ad = sA[d];
+    rank = 0;
+#pragma unroll 8
+    for (int e = 0; e < kD; ++e) {
+      const double o = sA[e];
+      rank += (o > Ad) || (o == Ad && e < d);
+    }
+  }
   return rank < n16 ? 2 : (rank < n16 + n4 ? 1 : 0);
 }
 
