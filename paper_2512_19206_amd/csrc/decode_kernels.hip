@@ -9,8 +9,6 @@
 namespace mixkvq {
 
 constexpr int kDecThreads = 256;
-// Launches that read more than this, the size of the last-level cache, ask for their keys with the non-temporal policy too.
-constexpr int64_t kStreamBytes = 256ll << 20;
 constexpr int kMaxG = 8;
 constexpr int kPartStride = kD + 2;   // floats per (split, head): O[D], m, l
 
@@ -430,7 +428,7 @@ hipError_t launch_decode(const CacheView& v, const __half* q, __half* out, float
     records = 0;
     for (int b = 0; b < v.cfg.B; ++b) records += (int64_t)sc.n_blocks[b] * v.cfg.Hkv;
   }
-  mc.streamed = records * v.lay.rec_bytes >= kStreamBytes;
+  mc.streamed = records * v.lay.rec_bytes > kLastLevelCache;      // then the keys are read with the non-temporal policy too
   if (!part) part = reinterpret_cast<float*>(v.ws);
   hipError_t e = hipSuccess;
   if (mc.n_splits <= max_splits_for(v.P) &&

@@ -15,6 +15,7 @@ constexpr int kMaxWindow = 256;     // the one residual length above kMaxR: its 
 constexpr int kMaxSplits = 64;      // split-K ceiling per (batch, KV head) pair
 constexpr int kSplitTargetWGs = 1024;   // sizes the workspace: split ceiling = kSplitTargetWGs / pairs
 constexpr int kDecodeTargetWGs = 512;   // workgroups the decode launch aims for
+constexpr int64_t kLastLevelCache = 256ll << 20;   // bytes
 constexpr int kMaxRec = 24576;      // largest supported block record in bytes (it is staged whole in LDS)
 
 struct Layout : mixkvq_block_layout_t {};
