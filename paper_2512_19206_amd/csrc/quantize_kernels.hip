@@ -14,7 +14,8 @@
 namespace mixkvq {
 
 constexpr int kFlushThreads = 256;
-constexpr int64_t kWideBlocks = 128;       // up to this many records of 128 tokens per launch the workgroups have 512 threads
+constexpr int kWideThreads = 1024;
+constexpr int64_t kWideBlocks = 128;       // up to this many records of 128 tokens per launch the workgroups have kWideThreads
 // up to this many blocks per launch the keys and the values of a block are two workgroups
 constexpr int64_t split_blocks(int R) { return R == kMaxR ? 2048 : 1408; }
 constexpr int kRowPad = 8;                 // halfs of padding per LDS row (keeps 16-byte alignment)
@@ -388,15 +389,15 @@ __device__ __forceinline__ uint4 load_chunk(const __half* res_p, const __half* f
 // lower.  1 280, 1 408, 1 536 and 2 048 blocks of 96 tokens 29.1 / 28.6, 31.3 / 30.8, 32.2 / 32.8, 41.0 / 41.8; of 64 tokens
 // 24.1 / 24.0, 25.6 / 25.8, 26.1 / 27.2, 33.6 / 34.8, scored under thresholds 32.2 / 31.8, 35.8 / 34.5, 36.2 / 37.1, 46.6 / 47.4;
 // of 32 tokens 19.1 / 19.0, 20.0 / 20.2, 20.4 / 21.6, 27.0 / 28.5; of 16 tokens 17.4 / 17.5, 17.7 / 18.6, 18.3 / 20.0, 24.4 / 25.6.
-// NT: 512 threads halve the serial work of a phase, but one such workgroup fills a compute unit (registers, LDS), so only
-// where the grid is at most one per unit: 256 / 512 threads at 128-token records with 16 4-bit channels 8.0 / 7.7 us at 32
+// NT: 1 024 threads quarter the serial work of a phase, but one such workgroup fills a compute unit (registers, LDS), so only
+// where the grid is at most one per unit.  256 / 512 threads at 128-token records with 16 4-bit channels 8.0 / 7.7 us at 32
 // blocks, 8.8 / 8.2 at 128, 8.7 / 10.6 at 160; scored under thresholds, groups of 32: 13.0 / 12.2, 13.3 / 12.4, 13.5 / 12.7
-// and 13.5 / 15.2 at 192.  Records of 64 or 32 tokens gain nothing (6.8 / 6.7, 6.6 / 6.9 at 64 blocks).
-// (9 chunks of 1 000 tokens, 8 pairs, scored under thresholds: 241 us with 256 threads, 226 with 512; that what decides the
-// tiers is asked for ahead of the tile changes nothing by itself: 241.6.)
+// and 13.5 / 15.2 at 192.  Records of 64 or 32 tokens gain nothing (6.8 / 6.7, 6.6 / 6.9 at 64 blocks).  512 / 1 024 threads: 9
+// chunks of 1 000 tokens, 8 pairs, scored under thresholds, with their selections 210 / 201 us; 24 decode steps of 24 sequences
+// that pack a block now and then 450 / 446; 44 blocks with a given selection the same.
 // Rows blockIdx.y >= gridDim.y - wc.wgs copy the tokens that stay behind in the window (WindowCopy).
 template <bool SPLIT, int NT>
-__global__ void __launch_bounds__(NT, NT == 256 ? 3 : 2)   // 256: three workgroups per CU (LDS) = three wavefronts per SIMD; 512: one
+__global__ void __launch_bounds__(NT, NT == 256 ? 3 : NT / 256)   // 256: three workgroups per CU (LDS) = three wavefronts per SIMD; more: one
 flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __half* __restrict__ v_new, Strides3 st,
                         int r0, int first_block, const uint8_t* __restrict__ sel_in, FlushList list, WindowCopy wc) {
   const bool do_k = !SPLIT || blockIdx.z == 0, do_v = !SPLIT || blockIdx.z == 1;
@@ -636,11 +637,13 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
     // ---- 2-bit key words [token][Wlo]: thread = (word column, token lane); the 16 channels of the column
     //      and their parameters stay in registers ---------------------------------------------------------
     {
-      // with 512 threads the two halves of the workgroup take alternate groups, or alternate runs of 32 tokens of the only one
-      const int wd = tid & 7, half = NT == 512 ? tid >> 8 : 0;
-      const bool by_group = NT == 512 && NG > 1;
-      const int tl = (tid >> 3 & 31) + (NT == 512 && !by_group ? 32 * half : 0);
-      const int t_step = NT == 512 && !by_group ? 64 : 32;
+      // the runs of 256 threads take alternate groups, and alternate runs of 32 tokens of a group where there are fewer groups
+      // than runs of threads
+      constexpr int Q = NT / 256;
+      const int wd = tid & 7, run = tid >> 8;
+      const int gq = NG < Q ? NG : Q;      // (NG is 1, 2, 4 or 8 where Q is not 1)
+      const int tl = (tid >> 3 & 31) + 32 * (Q > 1 ? run / gq : 0);
+      const int t_step = Q > 1 ? 32 * (Q / gq) : 32;
       if (wd < Wlo) {
         int doff[16];
 #pragma unroll
@@ -648,7 +651,7 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
           const int jj = 16 * wd + i;
           doff[i] = jj < n_lo ? (int)sLoList[jj] : -1;
         }
-        for (int grp = by_group ? half : 0; grp < NG; grp += by_group ? 2 : 1) {
+        for (int grp = Q > 1 ? run % gq : 0; grp < NG; grp += gq) {
           float rc[16], nz[16];
 #pragma unroll
           for (int i = 0; i < 16; ++i) {
@@ -663,7 +666,7 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
           for (int i = 0; i < 16; ++i) col[i] = sT + (grp * Gk + tl) * kFastStride + (doff[i] < 0 ? 0 : doff[i]);
           const int n_it = tl < Gk ? (Gk - tl + t_step - 1) / t_step : 0;      // tokens tl, tl + t_step, ... below Gk (Gk <= 128)
 #pragma unroll
-          for (int k = 0; k < (NT == 512 ? 2 : kMaxR / 32); ++k) {
+          for (int k = 0; k < kMaxR / 32 / Q; ++k) {
             if (k >= n_it) break;
             const int t = grp * Gk + tl + t_step * k;
             float hw[2] = {0.f, 0.f};
@@ -694,11 +697,23 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
       }
     }
     MIXKVQ_FPHASE(5)
-    // ---- 4-bit key words: [token][k4/8] -------------------------------------
-    // (a thread keeps its token; the runs of 128 threads alternate over the words: no divisions by run-time values)
-    for (int wd = tid >> 7; wd < W4; wd += NT / 128) {
+    // ---- 4-bit key words [token][k4/8]; in the wide form also the fp16 tier [token][k16], four of its channels at a time ------
+    // (a thread keeps its token; the runs of 128 threads alternate over the words, then the fours: no divisions by run-time
+    // values, and with 1 024 threads the two tiers are encoded side by side)
+    constexpr bool kSideBySide = NT > 256;
+    for (int wd = tid >> 7; wd < W4 + (kSideBySide ? k16 / 4 : 0); wd += NT / 128) {
       const int t = tid & 127;
       if (t >= R) break;
+      if (kSideBySide && wd >= W4) {
+        const int i0 = 4 * (wd - W4);
+        unsigned short x[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = i0 + i < n_16 ? h2bits(sT[t * kFastStride + sHiList[i0 + i]]) : (unsigned short)0;
+        // (records and planes start on 16 bytes: the four are 8-byte aligned)
+        *reinterpret_cast<uint2*>(rec + off_k16 + 2 * (t * k16 + i0)) =
+            make_uint2(x[0] | ((unsigned)x[1] << 16), x[2] | ((unsigned)x[3] << 16));
+        continue;
+      }
       const int grp = t / Gk, it = t * W4 + wd;
       float hw[2] = {0.f, 0.f};
       float dev[2] = {0.f, 0.f};
@@ -728,7 +743,7 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
       reinterpret_cast<unsigned*>(rec + off_k4)[it] = w;
     }
     // ---- fp16 tier: [token][k16] ------------------------------------------
-    for (int i = tid >> 7; i < k16; i += NT / 128) {
+    for (int i = tid >> 7; !kSideBySide && i < k16; i += NT / 128) {
       const int t = tid & 127;
       if (t < R) reinterpret_cast<__half*>(rec + off_k16)[t * k16 + i] = i < n_16 ? sT[t * kFastStride + sHiList[i]] : __ushort_as_half(0);
     }
@@ -859,8 +874,8 @@ static void launch_blocks(const CacheView& v, const __half* k_new, const __half*
   if (!fast)
     flush_block_kernel<<<dim3(n_pairs, nf), dim3(kFlushThreads), 0, s>>>(v, k_new, v_new, kvs, r0, first_block, sel, list);
   else if (v.cfg.R == kMaxR && (int64_t)n_pairs * nf <= kWideBlocks)
-    flush_block_fast_kernel<true, 512><<<dim3(n_pairs, nf + wc.wgs, 2), dim3(512), 0, s>>>(v, k_new, v_new, kvs, r0, first_block,
-                                                                                          sel, list, wc);
+    flush_block_fast_kernel<true, kWideThreads><<<dim3(n_pairs, nf + wc.wgs, 2), dim3(kWideThreads), 0, s>>>(
+        v, k_new, v_new, kvs, r0, first_block, sel, list, wc);
   else if ((int64_t)n_pairs * nf <= split_blocks(v.cfg.R))
     flush_block_fast_kernel<true, 256><<<dim3(n_pairs, nf + wc.wgs, 2), dim3(kFlushThreads), 0, s>>>(v, k_new, v_new, kvs, r0,
                                                                                                first_block, sel, list, wc);
