@@ -209,9 +209,10 @@ __device__ __forceinline__ void tier_sizes(const mixkvq_config& cfg, int c16, in
 // scores sA, the upper halves of their bit patterns sHi (both 16-byte aligned, written by the caller ahead of a barrier) and the
 // pair's token count.  The rank of a channel is the number of channels that beat it (higher score, or equal score and lower
 // index).  Scores are not negative, so their bit patterns order like them, and the upper halves decide all but ties among
-// those: a thread counts the upper halves of 128 * 128 / NT channels that are above its own (a compare and an add with carry
-// each, where two binary64 compares and the index took eight instructions), its wavefront counts the equal ones, and only
-// where there are more of them than the channels themselves the lower halves and the indices are looked at.
+// those: a thread counts the upper halves of 128 * 128 / NT channels that are above and those that equal its own (a compare and
+// an add with carry each, where two binary64 compares and the index took eight instructions and counting the equal ones
+// with ballots waited for the scalar unit each time), and only where more equal it than itself the whole scores and the
+// indices are looked at.
 // sPart: NT words.  (9 chunks of 1 000 tokens, selected and then packed by their own scores under thresholds: 226 -> 217 us.)
 template <int NT>
 __device__ __forceinline__ int rank_channels(const mixkvq_config& cfg, unsigned long long count, const double* sA, const unsigned* sHi,
@@ -228,11 +229,10 @@ __device__ __forceinline__ int rank_channels(const mixkvq_config& cfg, unsigned 
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       rank += w[k] > mine;
-      equal += __popcll(__ballot(w[k] == mine));
+      equal += w[k] == mine;
     }
   }
-  // a wavefront's channels are 64 (tid >> 6 & 1) and up: each equals itself where they are among the NE
-  const int first = 64 * (tid >> 6 & 1), self = e0 < first + 64 && first < e0 + NE ? (NE < 64 ? NE : 64) : 0;
+  const int self = d >= e0 && d < e0 + NE;
   int c16 = 0, c_any = 0;      // channels above the thresholds among the 64 of this wavefront
   if (cfg.policy == 1 && part == 0) {
     const double Ad = sA[d];
