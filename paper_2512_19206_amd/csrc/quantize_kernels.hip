@@ -395,9 +395,16 @@ __device__ __forceinline__ uint4 load_chunk(const __half* res_p, const __half* f
 // and 13.5 / 15.2 at 192.  Records of 64 or 32 tokens gain nothing (6.8 / 6.7, 6.6 / 6.9 at 64 blocks).  512 / 1 024 threads: 9
 // chunks of 1 000 tokens, 8 pairs, scored under thresholds, with their selections 210 / 201 us; 24 decode steps of 24 sequences
 // that pack a block now and then 450 / 446; 44 blocks with a given selection the same.
+// NGM: 1 where a record has one key group and one value group, else 8.  The kernel is bound by vector-ALU issue between
+// barriers, so what counts is how many workgroups share a compute unit: with room for one group's parameters instead of eight the
+// LDS of four fits (40 520 bytes each), and their 128 registers a thread do when the value tile is asked for behind the 2-bit
+// keys (asked for ahead of them, 26 registers are spilled and the whole is slower than with three: 1 728 us instead of 1 645 for
+// 16 prompts of 32 768 tokens with their selection, 1 571 this way).  R = G = 128, 16 4-bit channels, three / four workgroups: 512
+// blocks 17.2 / 14.5 us, 1 024 28.7 / 26.1, 2 048 50.5 / 44.0, 4 096 92.7 / 82.1; the line between split and fused stays:
+// 2 048 blocks 44.4 / 44.0, 2 560 52.7 / 52.6, 4 096 81.8 / 84.5.
 // Rows blockIdx.y >= gridDim.y - wc.wgs copy the tokens that stay behind in the window (WindowCopy).
-template <bool SPLIT, int NT>
-__global__ void __launch_bounds__(NT, NT == 256 ? 3 : NT / 256)   // 256: three workgroups per CU (LDS) = three wavefronts per SIMD; more: one
+template <bool SPLIT, int NT, int NGM>
+__global__ void __launch_bounds__(NT, NT > 256 ? NT / 256 : (NGM == 1 ? 4 : 3))   // 256: wavefronts per SIMD = workgroups per CU; more: one
 flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __half* __restrict__ v_new, Strides3 st,
                         int r0, int first_block, const uint8_t* __restrict__ sel_in, FlushList list, WindowCopy wc) {
   const bool do_k = !SPLIT || blockIdx.z == 0, do_v = !SPLIT || blockIdx.z == 1;
@@ -413,10 +420,10 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
   __shared__ unsigned char sHiList[kD];    // fp16 tier then 4-bit tier
   // parameters of the groups, keys: [group][channel], values: [token][value group]: the pair (r, nz) of the fast
   // codes, and scale | zero-point << 16 (binary16 bits) for the codes that are redone with the division
-  __shared__ __align__(16) float sRN[2 * 8 * kD];
-  float* const sR = sRN;               // r
-  float* const sNZ = sRN + 8 * kD;     // nz
-  __shared__ unsigned sSZ[8 * kD];
+  __shared__ __align__(16) float sRN[3 * NGM * kD];
+  float* const sR = sRN;                 // r
+  float* const sNZ = sRN + NGM * kD;     // nz
+  unsigned* const sSZ = reinterpret_cast<unsigned*>(sRN + 2 * NGM * kD);
   __shared__ unsigned sKmax[9];            // [8]: largest value scale
   __shared__ unsigned sChunk[2][kMaxR / 16][kD / 2];   // (min, max) keys per 16-token chunk and channel pair
   unsigned (*sCLo)[kD / 2] = sChunk[0];
@@ -438,8 +445,8 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
   const int n_ch = R / 16;                 // chunks of 16 tokens
 
   MIXKVQ_FPHASE(0)
-  // ---- the key tile first; the value tile is requested once the keys are staged in LDS, so that the wait for the
-  //      keys is a wait for 32 KiB and the values arrive while the keys are encoded ------------------------------
+  // ---- the key tile first; the value tile is requested once the keys are staged in LDS (or later: see NGM), so that the
+  //      wait for the keys is a wait for 32 KiB and the values arrive while the keys are encoded ------------------
   constexpr int kPieces = kMaxR * 16 / NT, kRows = NT / 16;     // 16-byte pieces a thread stages, rows between them
   uint4 vreg[kPieces];
   const int64_t pair_off = (int64_t)(p / Hkv) * st.b + (int64_t)(p % Hkv) * st.h;
@@ -497,7 +504,8 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
       }
     }
   }
-  if (do_v) {
+  constexpr bool kLateValues = NGM == 1;
+  auto load_values = [&] {
     if (one_place) {
       const __half* vp = (from_res ? res_vp : v_new + pair_off) + first * row_stride + (tid & 15) * 8;
 #pragma unroll
@@ -513,7 +521,8 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
         if (idx < n_chunks16) vreg[i] = load_chunk(res_vp, v_new + pair_off, st.t, r0, pos0, idx, bf16);
       }
     }
-  }
+  };
+  if (do_v && !kLateValues) load_values();
   __syncthreads();
   if (do_k) {
 
@@ -696,6 +705,7 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
         }
       }
     }
+    if (kLateValues && !SPLIT) load_values();
     MIXKVQ_FPHASE(5)
     // ---- 4-bit key words [token][k4/8]; in the wide form also the fp16 tier [token][k16], four of its channels at a time ------
     // (a thread keeps its token; the runs of 128 threads alternate over the words, then the fours: no divisions by run-time
@@ -751,6 +761,7 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
   if (!SPLIT) __syncthreads();     // the key tile makes room for the values
 
   if (do_v) {
+    if (kLateValues && SPLIT) load_values();
     MIXKVQ_FPHASE(6)
     // ---- values ---------------------------------------------------------------------------------
     // The tile goes to LDS; on the way every thread reduces its 16-byte pieces (still in registers) to the minimum
@@ -874,14 +885,15 @@ static void launch_blocks(const CacheView& v, const __half* k_new, const __half*
   if (!fast)
     flush_block_kernel<<<dim3(n_pairs, nf), dim3(kFlushThreads), 0, s>>>(v, k_new, v_new, kvs, r0, first_block, sel, list);
   else if (v.cfg.R == kMaxR && (int64_t)n_pairs * nf <= kWideBlocks)
-    flush_block_fast_kernel<true, kWideThreads><<<dim3(n_pairs, nf + wc.wgs, 2), dim3(kWideThreads), 0, s>>>(
+    flush_block_fast_kernel<true, kWideThreads, 8><<<dim3(n_pairs, nf + wc.wgs, 2), dim3(kWideThreads), 0, s>>>(
         v, k_new, v_new, kvs, r0, first_block, sel, list, wc);
-  else if ((int64_t)n_pairs * nf <= split_blocks(v.cfg.R))
-    flush_block_fast_kernel<true, 256><<<dim3(n_pairs, nf + wc.wgs, 2), dim3(kFlushThreads), 0, s>>>(v, k_new, v_new, kvs, r0,
-                                                                                               first_block, sel, list, wc);
-  else
-    flush_block_fast_kernel<false, 256><<<dim3(n_pairs, nf + wc.wgs), dim3(kFlushThreads), 0, s>>>(v, k_new, v_new, kvs, r0,
-                                                                                             first_block, sel, list, wc);
+  else {
+    const bool split = (int64_t)n_pairs * nf <= split_blocks(v.cfg.R), one = v.lay.NG == 1 && v.lay.NVG == 1;
+    const dim3 grid(n_pairs, nf + wc.wgs, split ? 2 : 1), block(kFlushThreads);
+    auto kern = split ? (one ? flush_block_fast_kernel<true, 256, 1> : flush_block_fast_kernel<true, 256, 8>)
+                      : (one ? flush_block_fast_kernel<false, 256, 1> : flush_block_fast_kernel<false, 256, 8>);
+    kern<<<grid, block, 0, s>>>(v, k_new, v_new, kvs, r0, first_block, sel, list, wc);
+  }
 }
 
 hipError_t launch_flush(const CacheView& v, const __half* k_new, const __half* v_new, Strides3 kvs, int r0,
