@@ -14,8 +14,7 @@
 namespace mixkvq {
 
 constexpr int kFlushThreads = 256;
-constexpr int kWideThreads = 1024;
-constexpr int64_t kWideBlocks = 128;       // up to this many records of 128 tokens per launch the workgroups have kWideThreads
+constexpr int64_t kWideBlocks = 128;       // up to this many records of 128 tokens per launch the workgroups have 512 or 1 024 threads
 // up to this many blocks per launch the keys and the values of a block are two workgroups
 constexpr int64_t split_blocks(int R) { return R == kMaxR ? 2048 : 1408; }
 constexpr int kRowPad = 8;                 // halfs of padding per LDS row (keeps 16-byte alignment)
@@ -389,12 +388,13 @@ __device__ __forceinline__ uint4 load_chunk(const __half* res_p, const __half* f
 // lower.  1 280, 1 408, 1 536 and 2 048 blocks of 96 tokens 29.1 / 28.6, 31.3 / 30.8, 32.2 / 32.8, 41.0 / 41.8; of 64 tokens
 // 24.1 / 24.0, 25.6 / 25.8, 26.1 / 27.2, 33.6 / 34.8, scored under thresholds 32.2 / 31.8, 35.8 / 34.5, 36.2 / 37.1, 46.6 / 47.4;
 // of 32 tokens 19.1 / 19.0, 20.0 / 20.2, 20.4 / 21.6, 27.0 / 28.5; of 16 tokens 17.4 / 17.5, 17.7 / 18.6, 18.3 / 20.0, 24.4 / 25.6.
-// NT: 1 024 threads quarter the serial work of a phase, but one such workgroup fills a compute unit (registers, LDS), so only
+// NT: 512 or 1 024 threads share the serial work of a phase, but one such workgroup fills a compute unit (registers, LDS), so only
 // where the grid is at most one per unit.  256 / 512 threads at 128-token records with 16 4-bit channels 8.0 / 7.7 us at 32
 // blocks, 8.8 / 8.2 at 128, 8.7 / 10.6 at 160; scored under thresholds, groups of 32: 13.0 / 12.2, 13.3 / 12.4, 13.5 / 12.7
 // and 13.5 / 15.2 at 192.  Records of 64 or 32 tokens gain nothing (6.8 / 6.7, 6.6 / 6.9 at 64 blocks).  512 / 1 024 threads: 9
 // chunks of 1 000 tokens, 8 pairs, scored under thresholds, with their selections 210 / 201 us; 24 decode steps of 24 sequences
-// that pack a block now and then 450 / 446; 44 blocks with a given selection the same.
+// that pack a block now and then 450 / 446; groups of 32, 12 fp16 channels given, 32 blocks 9.1 / 8.5, 128 blocks 9.5 / 9.0.  With one
+// key group there is nothing more to share out (16 4-bit channels given, 32 blocks 8.5 / 8.8, 128 blocks 8.7 / 9.5): 512 there.
 // NGM: 1 where a record has one key group and one value group, else 8.  The kernel is bound by vector-ALU issue between
 // barriers, so what counts is how many workgroups share a compute unit: with room for one group's parameters instead of eight the
 // LDS of four fits (40 520 bytes each), and their 128 registers a thread do when the value tile is asked for behind the 2-bit
@@ -709,7 +709,7 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
     MIXKVQ_FPHASE(5)
     // ---- 4-bit key words [token][k4/8]; in the wide form also the fp16 tier [token][k16], four of its channels at a time ------
     // (a thread keeps its token; the runs of 128 threads alternate over the words, then the fours: no divisions by run-time
-    // values, and with 1 024 threads the two tiers are encoded side by side)
+    // values, and with more than 256 threads the two tiers are encoded side by side)
     constexpr bool kSideBySide = NT > 256;
     for (int wd = tid >> 7; wd < W4 + (kSideBySide ? k16 / 4 : 0); wd += NT / 128) {
       const int t = tid & 127;
@@ -884,9 +884,11 @@ static void launch_blocks(const CacheView& v, const __half* k_new, const __half*
                           hipStream_t s) {
   if (!fast)
     flush_block_kernel<<<dim3(n_pairs, nf), dim3(kFlushThreads), 0, s>>>(v, k_new, v_new, kvs, r0, first_block, sel, list);
-  else if (v.cfg.R == kMaxR && (int64_t)n_pairs * nf <= kWideBlocks)
-    flush_block_fast_kernel<true, kWideThreads, 8><<<dim3(n_pairs, nf + wc.wgs, 2), dim3(kWideThreads), 0, s>>>(
-        v, k_new, v_new, kvs, r0, first_block, sel, list, wc);
+  else if (v.cfg.R == kMaxR && (int64_t)n_pairs * nf <= kWideBlocks) {
+    const int threads = v.lay.NG > 1 ? 1024 : 512;
+    auto kern = v.lay.NG > 1 ? flush_block_fast_kernel<true, 1024, 8> : flush_block_fast_kernel<true, 512, 8>;
+    kern<<<dim3(n_pairs, nf + wc.wgs, 2), dim3(threads), 0, s>>>(v, k_new, v_new, kvs, r0, first_block, sel, list, wc);
+  }
   else {
     const bool split = (int64_t)n_pairs * nf <= split_blocks(v.cfg.R), one = v.lay.NG == 1 && v.lay.NVG == 1;
     const dim3 grid(n_pairs, nf + wc.wgs, split ? 2 : 1), block(kFlushThreads);
