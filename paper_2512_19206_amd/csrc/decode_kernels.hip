@@ -264,14 +264,15 @@ bool try_launch_decode_mfma(const CacheView& v, const __half* q, float scale, in
                             hipStream_t s, hipEvent_t ev_start, hipEvent_t ev_stop, hipError_t* err);
 
 // Workgroups of eight wavefronts instead of twice as many of four?  They leave half as many partials to the pair's last
-// workgroup, which pulls them past the caches with the bandwidth of one compute unit, and draw half as many tickets; but their
-// wavefronts share a compute unit, and start and end together.  So: for a shorter chain of records per wavefront (rounding);
+// workgroup, which pulls them past the caches with the bandwidth of one compute unit, and draw half as many tickets (at the ceiling
+// of 64 workgroups a pair there are as many of either, and those of eight have half the chain); but their wavefronts share a
+// compute unit, and start and end together.  So: for a shorter chain of records per wavefront (rounding, the ceiling);
 // with the same chain, where those of four would share compute units (more than 256 of them) and a pair has more than twelve, a
 // merge of more than one round, or would have no partials left at all; with a compute unit each only from 25 on.
 // us per step, four / eight: 24 pairs of 9 001 tokens (18 / 9 workgroups a pair) 19.4 / 17.9, 32 of 32 805 (16 / 8) 23.1 / 22.6, 188 of
-// 990 (2 / 1) 15.0 / 13.2, 3 of 15 354 (60 / 30) 15.7 / 12.7, 48 steps of 32 pairs with records of 32 tokens (16 / 8) 718 / 705; on
-// the other side of the lines 14 pairs of 7 218 (15 / 8), 43 steps, 500 / 520, 8 of 6 071 (13 / 7), 33 steps, 413 / 466, 112 of 3 453
-// (4 / 2) 16.4 / 17.8, one of 1 027 (9 / 5) 9.8 / 10.7.
+// 990 (2 / 1) 15.0 / 13.2, 3 of 15 354 (60 / 30) 15.7 / 12.7, 48 steps of 32 pairs with records of 32 tokens (16 / 8) 718 / 705, one
+// pair of 131 172 (64 / 64) 22.5 / 19.7; on the other side of the lines 14 pairs of 7 218 (15 / 8), 43 steps, 500 / 520, 8 of 6 071
+// (13 / 7), 33 steps, 413 / 466, 112 of 3 453 (4 / 2) 16.4 / 17.8, one of 1 027 (9 / 5) 9.8 / 10.7.
 static bool eight_wavefronts(int chain4, int chain8, int n4, int n8, int wgs4) {
   if (chain8 != chain4) return chain8 < chain4;
   return wgs4 > kDecodeTargetWGs / 2 ? n4 > 12 || n8 == 1 : n4 > 24;
@@ -301,11 +302,13 @@ static void choose_splits(const CacheView& v, int n_blocks, int n_fp16, bool wid
   *n_splits_out = n_splits;
   *mc = DecodeGrid{n_splits_mc, 4, 0};
   if (!wide || n_splits_mc < 2) return;
-  const int units = n_blocks + subs;
+  const int units = n_blocks + subs, ceiling = max_splits_for(v.P);
   int n8 = target_wgs / 2 / v.P;
+  if (n8 > ceiling) n8 = ceiling;      // (binds for one to three pairs)
   if (n8 > (units + 7) / 8) n8 = (units + 7) / 8;
   if (n8 < (subs + 7) / 8) n8 = (subs + 7) / 8;
   if (n8 < 1) n8 = 1;
+  if (n8 > ceiling) return;
   const int chain8 = (units + 8 * n8 - 1) / (8 * n8), chain4 = (units + 4 * n_splits_mc - 1) / (4 * n_splits_mc);
   if (eight_wavefronts(chain4, chain8, n_splits_mc, n8, v.P * n_splits_mc)) *mc = DecodeGrid{n8, 8, 0};
 }
@@ -381,7 +384,7 @@ static void deal_by_length(const CacheView& v, int n_splits, SeqCounts* sc, Deco
 size_t decode_launch_partials_bytes(const CacheView& v, int n_blocks, int n_fp16) {
   int n_splits;
   DecodeGrid mc;
-  choose_splits(v, n_blocks, n_fp16, false, &n_splits, &mc);      // (workgroups of eight wavefronts write half of that)
+  choose_splits(v, n_blocks, n_fp16, false, &n_splits, &mc);      // (there are never more workgroups of eight than of four)
   const int n = mc.n_splits > n_splits ? mc.n_splits : n_splits;
   return (size_t)v.P * n * v.g * kPartStride * sizeof(float);
 }

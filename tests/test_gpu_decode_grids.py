@@ -19,6 +19,10 @@ pytestmark = pytest.mark.gpu
     (2, 2, 3, 30, dict(R=256, sink=128)),      # twelve sub-units of fp16 rows
     (5, 4, 6, 0, dict(sink=64)),     # fp16 rows only
     (70, 4, 3, 0, dict(R=256)),
+    # up to three pairs of more than 512 records: the ceiling of 64 workgroups a pair, eight wavefronts each
+    (1, 1, 5, 1100, dict(R=32, Gk=32, Gv=32)),
+    (2, 1, 7, 520, dict(R=32, Gk=32, Gv=32)),
+    (1, 3, 1, 640, dict(R=64, Gk=64)),
 ])
 def test_against_the_oracle(B, Hkv, g, blocks, over):
     import gpu_common as H
@@ -55,6 +59,10 @@ def test_against_the_oracle(B, Hkv, g, blocks, over):
         assert torch.equal(out, out[:1].expand_as(out)) and torch.equal(lse, lse[:1].expand_as(lse))
         acc, cnt = gc.query_accumulator()
         assert np.array_equal(acc[-Hkv:].cpu().numpy().astype(np.uint64), oc.qacc) and int(cnt[-1]) == int(oc.qcnt.ravel()[-1])
+    # through the entry point with partials of its own: the same grid, the merge a launch of its own
+    again, lse2 = gc.decode_attention_noalloc(rep(q), torch.empty_like(out), torch.empty_like(lse))
+    torch.cuda.synchronize()
+    assert gc.decode_path() == M.PATH_MATRIX and torch.equal(again, out) and torch.equal(lse2, lse)
 
 
 @pytest.mark.parametrize("k4,k16", [(16, 0), (0, 12), (8, 0)])

@@ -177,3 +177,21 @@ def test_what_a_decode_step_keeps_when_its_launches_fail(M, tmp_path):
     assert r.returncode == 0, r.stdout + r.stderr
     r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and "host launch stub: ok" in r.stdout, r.stdout + r.stderr
+
+
+def test_grids_of_decode_launches(M, tmp_path):
+    """The rules of csrc/decode_kernels.hip that choose a decode launch's grid (tests/host_grid_rule.cpp): never above the
+    ceiling that decides between the matrix-core and the vector-ALU kernel, enough wavefronts for the fp16 rows, partials that
+    fit, and the grids that were measured."""
+    import subprocess
+    from paper_2512_19206_amd import build as B
+    objs = [os.path.join(B.OBJ_DIR, os.path.splitext(s)[0] + ".o") for s in B.SOURCES if s != "decode_kernels.hip"]
+    if not all(os.path.exists(o) for o in objs):
+        B.build_library()
+    obj, exe = str(tmp_path / "host_grid_rule.o"), str(tmp_path / "host_grid_rule")
+    env = {k: v for k, v in os.environ.items() if k != "MIXKVQ_DECODE_WGS"}
+    for cmd in ([B.hipcc_path()] + B._flags() + ["-O1", "-x", "hip", "-c", os.path.join(ROOT, "tests", "host_grid_rule.cpp"), "-o", obj],
+                [B.hipcc_path(), "--offload-arch=gfx950", obj] + objs + ["-o", exe], [exe]):
+        r = subprocess.run(cmd, capture_output=True, text=True, env=env, timeout=120)
+        assert r.returncode == 0, r.stdout + r.stderr
+    assert "decode grids: ok" in r.stdout
