@@ -206,64 +206,60 @@ __device__ __forceinline__ void tier_sizes(const mixkvq_config& cfg, int c16, in
 }
 
 // Tier (2: fp16, 1: 4 bit, 0: 2 bit) of channel tid in threads 0..127 of a workgroup of NT (0 in the others), from the 128
-// scores sA, the upper halves of their bit patterns sHi (both 16-byte aligned, written by the caller ahead of a barrier) and the
-// pair's token count.  The rank of a channel is the number of channels that beat it (higher score, or equal score and lower
-// index).  Scores are not negative, so their bit patterns order like them, and the upper halves decide all but ties among
-// those: a thread counts the upper halves of 128 * 128 / NT channels that are above and those that equal its own (a compare and
-// an add with carry each, where two binary64 compares and the index took eight instructions and counting the equal ones
-// with ballots waited for the scalar unit each time), and only where more equal it than itself the whole scores and the
-// indices are looked at.
-// sPart: NT words.  (9 chunks of 1 000 tokens, selected and then packed by their own scores under thresholds: 226 -> 217 us.)
+// scores sA (not negative, 16-byte aligned, written by the caller ahead of a barrier) and the pair's token count.  The rank of a
+// channel is the number of channels that beat it (higher score, or equal score and lower index).  A thread compares channel d
+// with 128 * 128 / NT others, d ^ i: whether d ^ i is the lower index depends on the highest bit of i alone, so a whole run of
+// them is compared with one threshold, the score itself or the next number below it, and a comparison is one instruction and
+// an add with carry, ties included.  (Deciding by the upper halves of the bit patterns, with the whole scores only where those
+// tie, is no shorter, and one workgroup in forty then takes a serial path that everything waits for.  us with two compares
+// and the index for every pair of scores / by upper halves / this way: selection of 96 pairs of 568 tokens 10.9 / 12.4 / 9.4, of
+// 120 of 400 22.1 / 23.4 / 21.0; blocks packed by their own scores under thresholds, 128 of 128 tokens 12.4 / 13.5 / 10.4, 320
+// 13.8 / 15.0 / 12.9, 512 of 64 tokens 13.8 / 14.2 / 11.3.)
+// sPart: NT words.
 template <int NT>
-__device__ __forceinline__ int rank_channels(const mixkvq_config& cfg, unsigned long long count, const double* sA, const unsigned* sHi,
-                                             unsigned* sPart) {
+__device__ __forceinline__ int rank_channels(const mixkvq_config& cfg, unsigned long long count, const double* sA, unsigned* sPart) {
   constexpr int NE = kD * kD / NT;
-  const int tid = threadIdx.x, d = tid & (kD - 1), part = tid >> 7, e0 = part * NE;
-  const unsigned mine = sHi[d];
-  const uint4* row = reinterpret_cast<const uint4*>(sHi + e0);
-  int rank = 0, equal = 0;
+  const int tid = threadIdx.x, d = tid & (kD - 1), part = __builtin_amdgcn_readfirstlane(tid >> 7);
+  const double Ad = sA[d], below = Ad > 0.0 ? __longlong_as_double(__double_as_longlong(Ad) - 1) : -1.0;
+  const double2* row = reinterpret_cast<const double2*>(sA);      // scores 2 j and 2 j + 1
+  int rank = 0;
+  if (part == 0) {      // i = 1 .. NE - 1
+    const double2 o = row[d >> 1];
+    rank = (d & 1) ? o.x > below : o.y > Ad;
 #pragma unroll
-  for (int i = 0; i < NE / 4; ++i) {
-    const uint4 o = row[i];
-    const unsigned w[4] = {o.x, o.y, o.z, o.w};
+    for (int j = 1; j < NE / 2; ++j) {
+      const int top = 2 << (31 - __builtin_clz(j));      // highest bit of i = 2 j and 2 j + 1
+      const double limit = (d & top) ? below : Ad;
+      const double2 o = row[(d >> 1) ^ j];
+      rank += o.x > limit;
+      rank += o.y > limit;
+    }
+  } else {      // i = part * NE .. part * NE + NE - 1
+    const int top = 1 << (31 - __builtin_clz(part * NE));
+    const double limit = (d & top) ? below : Ad;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      rank += w[k] > mine;
-      equal += w[k] == mine;
+    for (int j = 0; j < NE / 2; ++j) {
+      const double2 o = row[(d >> 1) ^ (part * (NE / 2) + j)];
+      rank += o.x > limit;
+      rank += o.y > limit;
     }
   }
-  const int self = d >= e0 && d < e0 + NE;
   int c16 = 0, c_any = 0;      // channels above the thresholds among the 64 of this wavefront
   if (cfg.policy == 1 && part == 0) {
-    const double Ad = sA[d];
     const double thr16 = score_threshold(cfg.tau16, count, cfg.score_mode);
     const double thr4 = score_threshold(cfg.tau4, count, cfg.score_mode);
     c16 = __popcll(__ballot(Ad > thr16));
     c_any = __popcll(__ballot(Ad > thr16 || Ad > thr4));
   }
-  sPart[tid] = (unsigned)rank | ((unsigned)c16 << 8) | ((unsigned)c_any << 16) | (equal != self ? 0x80000000u : 0u);     // rank, c16, c_any <= 64 each
+  sPart[tid] = (unsigned)rank | ((unsigned)c16 << 8) | ((unsigned)c_any << 16);     // rank, c16, c_any <= 64 each
   __syncthreads();
   if (tid >= kD) return 0;
   const unsigned here = sPart[tid], other = sPart[tid ^ 64];                       // the two wavefronts with the channels
   int n16, n4;
-  tier_sizes(cfg, (int)((here >> 8) & 0xffu) + (int)((other >> 8) & 0xffu), (int)((here >> 16) & 0x7fu) + (int)((other >> 16) & 0x7fu),
-             &n16, &n4);
-  unsigned ties = 0u;
+  tier_sizes(cfg, (int)((here >> 8) & 0xffu) + (int)((other >> 8) & 0xffu), (int)(here >> 16) + (int)(other >> 16), &n16, &n4);
   rank = 0;
 #pragma unroll
-  for (int k = 0; k < NT / kD; ++k) {
-    rank += (int)(sPart[tid + k * kD] & 0xffu);
-    ties |= sPart[tid + k * kD];
-  }
-  if (ties >> 31) {
-    const double Ad = sA[d];
-    rank = 0;
-#pragma unroll 8
-    for (int e = 0; e < kD; ++e) {
-      const double o = sA[e];
-      rank += (o > Ad) || (o == Ad && e < d);
-    }
-  }
+  for (int k = 0; k < NT / kD; ++k) rank += (int)(sPart[tid + k * kD] & 0xffu);
   return rank < n16 ? 2 : (rank < n16 + n4 ? 1 : 0);
 }
 

@@ -549,7 +549,6 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
     // ---- channel tiers ------------------------------------------------------------------------
     if (scored) {
       unsigned* const sPart = reinterpret_cast<unsigned*>(sRN);      // (sRN is not yet in use)
-      unsigned* const sHi = sPart + NT;
       if (tid < kD) {
         const _Float16* cl = reinterpret_cast<const _Float16*>(&sCLo[0][0]);
         const _Float16* chh = reinterpret_cast<const _Float16*>(&sCHi[0][0]);
@@ -560,12 +559,10 @@ flush_block_fast_kernel(CacheView cv, const __half* __restrict__ k_new, const __
           hi = b2 > hi ? b2 : hi;
         }
         const long long rng = fix24(h_bits(hi)) - fix24(h_bits(lo));
-        const double A = score_mode ? (double)rng : (double)qsum * (double)rng;
-        sA[tid] = A;
-        sHi[tid] = (unsigned)__double2hiint(A);
+        sA[tid] = score_mode ? (double)rng : (double)qsum * (double)rng;
       }
       __syncthreads();
-      const int tier = rank_channels<NT>(cv.cfg, qcount, sA, sHi, sPart);
+      const int tier = rank_channels<NT>(cv.cfg, qcount, sA, sPart);
       if (tid < kD) sTier[tid] = (unsigned char)tier;
     } else {
       if (tid < kD) sTier[tid] = 0;

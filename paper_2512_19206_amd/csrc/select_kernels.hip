@@ -255,7 +255,6 @@ __global__ void __launch_bounds__(kStreamThreads) select_kernel(CacheView cv, Se
   __syncthreads();
   double* sA = reinterpret_cast<double*>(smem + 2048);
   unsigned* sPart = reinterpret_cast<unsigned*>(smem + 2048 + 1024);
-  unsigned* sHi = reinterpret_cast<unsigned*>(smem + 4096);
   if (tid < kD) {
     const unsigned short* m = reinterpret_cast<const unsigned short*>(smem);      // [4][2][128] fp16 bits
     long long lo = fix24(m[tid]), hi = fix24(m[kD + tid]);
@@ -266,12 +265,10 @@ __global__ void __launch_bounds__(kStreamThreads) select_kernel(CacheView cv, Se
       hi = h > hi ? h : hi;
     }
     const long long rng = hi - lo;
-    const double A = cv.cfg.score_mode ? (double)rng : (double)sum * (double)rng;
-    sA[tid] = A;
-    sHi[tid] = (unsigned)__double2hiint(A);
+    sA[tid] = cv.cfg.score_mode ? (double)rng : (double)sum * (double)rng;
   }
   __syncthreads();
-  const int tier = rank_channels<kStreamThreads>(cv.cfg, sCount, sA, sHi, sPart);      // (threads 0..127: of their channel)
+  const int tier = rank_channels<kStreamThreads>(cv.cfg, sCount, sA, sPart);      // (threads 0..127: of their channel)
   // positions inside the tiers: ballots over the two wavefronts that hold the channels
   const unsigned long long m1 = __ballot(tier == 1), m2 = __ballot(tier == 2);
   unsigned long long* sMask = reinterpret_cast<unsigned long long*>(smem);      // the first wavefront's two ballots

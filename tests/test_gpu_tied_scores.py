@@ -9,7 +9,8 @@ pytestmark = pytest.mark.gpu
 
 def _tensors(kind, T, seed):
     """Keys of range 2 in every channel; queries whose |q| sums are 1024 + n_d 2^-14 with n_d a permutation ('lower': runs of
-    16 share the upper half), all equal ('equal'), or equal in every second channel ('mixed')."""
+    16 share the upper half), all equal ('equal'), or equal in every second channel ('mixed').  'ranges': keys of a few
+    ranges, n_d as in 'lower'."""
     rng = np.random.default_rng(seed)
     K = rng.uniform(-1, 1, (1, 2, T, 128)).astype(np.float16)
     K[:, :, 0::128], K[:, :, 1::128] = 1.0, -1.0      # (in every block of 128 or 32 tokens that starts there)
@@ -22,14 +23,17 @@ def _tensors(kind, T, seed):
         n[:] = 5
     elif kind == "mixed":
         n[::2] = 5
+    elif kind == "ranges":
+        K *= rng.choice([0.25, 0.5, 1.0, 2.0], 128).astype(np.float16)
     Q[:, :, 0] = 1024.0
     Q[:, :, 1] = (n * 2.0 ** -14).astype(np.float16)
     return K, rng.standard_normal((1, 2, T, 128)).astype(np.float16), Q
 
 
-@pytest.mark.parametrize("policy", [dict(k4=16, k16=0), dict(k4=16, k16=8, policy=1, tau16=1000.0, tau4=10.0)])
+@pytest.mark.parametrize("policy", [dict(k4=16, k16=0), dict(k4=16, k16=8, policy=1, tau16=1000.0, tau4=10.0),
+                                    dict(k4=24, k16=12, score_mode=1)])
 @pytest.mark.parametrize("R,G,blocks", [(128, 128, 1), (128, 32, 2), (128, 128, 70), (128, 64, 70), (32, 32, 3)])
-@pytest.mark.parametrize("kind", ["equal", "lower", "mixed"])
+@pytest.mark.parametrize("kind", ["equal", "lower", "mixed", "ranges"])
 def test_ties(kind, R, G, blocks, policy):
     import gpu_common as H
     T = R * blocks + 1
