@@ -15,6 +15,8 @@ namespace mixkvq {
 
 constexpr int kFlushThreads = 256;
 constexpr int64_t kWideBlocks = 128;       // up to this many records of 128 tokens per launch the workgroups have 512 or 1 024 threads
+// more LDS than a fourth workgroup of flush_block_fast_kernel<., 256, 1> on a compute unit would find, and not too much for three
+constexpr unsigned kThreePerUnit = 1024;
 // up to this many blocks per launch the keys and the values of a block are two workgroups
 constexpr int64_t split_blocks(int R) { return R == kMaxR ? 2048 : 1408; }
 constexpr int kRowPad = 8;                 // halfs of padding per LDS row (keeps 16-byte alignment)
@@ -401,7 +403,9 @@ __device__ __forceinline__ uint4 load_chunk(const __half* res_p, const __half* f
 // keys (asked for ahead of them, 26 registers are spilled and the whole is slower than with three: 1 728 us instead of 1 645 for
 // 16 prompts of 32 768 tokens with their selection, 1 571 this way).  R = G = 128, 16 4-bit channels, three / four workgroups: 512
 // blocks 17.2 / 14.5 us, 1 024 28.7 / 26.1, 2 048 50.5 / 44.0, 4 096 92.7 / 82.1; the line between split and fused stays:
-// 2 048 blocks 44.4 / 44.0, 2 560 52.7 / 52.6, 4 096 81.8 / 84.5.
+// 2 048 blocks 44.4 / 44.0, 2 560 52.7 / 52.6, 4 096 81.8 / 84.5.  Grids that fit three to a compute unit are held at three
+// (kThreePerUnit): with room for four they are not spread evenly.  Without / with: 376 blocks 12.3 / 11.1 us, 384 12.1 / 11.2, of
+// 64 tokens 8.9 / 8.6, 384 of 96 prompts 13.4 / 12.5; 136 to 368 blocks the same either way.
 // Rows blockIdx.y >= gridDim.y - wc.wgs copy the tokens that stay behind in the window (WindowCopy).
 template <bool SPLIT, int NT, int NGM>
 __global__ void __launch_bounds__(NT, NT > 256 ? NT / 256 : (NGM == 1 ? 4 : 3))   // 256: wavefronts per SIMD = workgroups per CU; more: one
@@ -891,7 +895,8 @@ static void launch_blocks(const CacheView& v, const __half* k_new, const __half*
     const dim3 grid(n_pairs, nf + wc.wgs, split ? 2 : 1), block(kFlushThreads);
     auto kern = split ? (one ? flush_block_fast_kernel<true, 256, 1> : flush_block_fast_kernel<true, 256, 8>)
                       : (one ? flush_block_fast_kernel<false, 256, 1> : flush_block_fast_kernel<false, 256, 8>);
-    kern<<<grid, block, 0, s>>>(v, k_new, v_new, kvs, r0, first_block, sel, list, wc);
+    const bool three = one && split && 2 * (int64_t)n_pairs * nf <= 3 * 256;
+    kern<<<grid, block, three ? kThreePerUnit : 0, s>>>(v, k_new, v_new, kvs, r0, first_block, sel, list, wc);
   }
 }
 

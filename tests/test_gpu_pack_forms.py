@@ -1,4 +1,4 @@
-"""The forms of the pack kernel (1 024 threads; keys and values apart; both together; room for one group's parameters or
+"""The forms of the pack kernel (512 or 1 024 threads; keys and values apart; both together; room for one group's parameters or
 for eight) give the same records: a batch large enough for one form against its sequences one by one, which take another,
 and the first of those against the oracle."""
 import numpy as np
@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("B,blocks,G,over", [
     (16, 33, 128, dict(k4=16, k16=0)),                 # 2 112 blocks together / 132 apart per sequence
     (16, 33, 32, dict(k4=16, k16=8)),
-    (4, 12, 128, dict(k4=0, k16=12)),                  # 192 blocks apart / 48 with 1 024 threads
+    (8, 14, 128, dict(k4=16, k16=0)),                  # 448 blocks apart, up to four workgroups per compute unit / 56 with 512 threads
+    (4, 12, 128, dict(k4=0, k16=12)),                  # 192 blocks apart, three per compute unit / 48 with 512 threads
     (4, 12, 64, dict(k4=8, k16=4)),
     (4, 12, 16, dict(k4=16, k16=0)),                   # eight key groups, eight value groups
     (4, 12, 32, dict(k4=32, k16=12, policy=1, tau16=4.0, tau4=1.0)),
