@@ -234,11 +234,14 @@ struct HalfSplit {
 // ---------------------------------------------------------------------------
 // Split-K partials and their log-sum-exp merge: m* = max m_i, l* = sum l_i 2^(m_i - m*),
 // O = sum O_i 2^(m_i - m*) / l* (log2 domain).  The partial of one workgroup is O [g][128], then (m, l) [g], binary32.
-// A thread owns four channels of one head and twelve partials are in flight per thread before the first wait; with eight
-// wavefronts the two halves of the workgroup take alternate partials and join their results through LDS.  One workgroup per pair
-// runs this code, its first time on that compute unit as a rule, so its size counts: offsets into a buffer and no special case
-// for an empty partial took 48 steps with records of 32 tokens (8 partials) from 701 to 680 us, twelve partials in flight instead
-// of sixteen to 676 (eight: 675, four: 672), one pair of 1 027 tokens (9 partials) from 9.0 to 8.7 and 8.6 (8.9, 9.1).
+// A thread owns four channels of one head and twelve or sixteen partials are in flight per thread before the first wait; with
+// eight wavefronts the two halves of the workgroup take alternate partials and join their results through LDS.  One workgroup per
+// pair runs this code, its first time on that compute unit as a rule, so its size counts: offsets into a buffer and no special
+// case for an empty partial took 48 steps with records of 32 tokens (8 partials) from 701 to 680 us, twelve partials in flight
+// instead of sixteen to 676 (eight: 675, four: 672), one pair of 1 027 tokens (9 partials) from 9.0 to 8.7 and 8.6 (8.9, 9.1).
+// Sixteen are taken where that saves a round; and the threads of heads that do not exist load nothing, as all of these go past
+// the caches.  us, twelve and a repeated head / this way: 8 pairs of one head, 14 partials, 11.6 / 10.5; 8 of seven heads, 13
+// partials, 11.1 / 10.7; 12 of two, 14 partials, 12.5 / 11.5; 4 of one, 2 x 32 partials, 17.6 / 15.1; one pair of 1 027 tokens 8.7 / 8.5.
 //
 // The last workgroup of a pair to finish merges it (see CacheView::tickets).  The partials, the ticket and the
 // loads are agent-scope accesses, which go past the chip's eight L2 caches; no cache is flushed for them.  A launch of
@@ -273,9 +276,9 @@ __device__ __forceinline__ void store_output4(__half* out, float* lse, size_t bh
 }
 // Every step-th of the partials `pair` [n_parts][g * kPartStrideM] of one pair from `first` on (scalars); thread (h, c4), h < g.
 struct Merged { f32x4 o; float l, m; };
-template <bool SHARED>
+template <bool SHARED, int kFly>
 __device__ __forceinline__ Merged merge_parts(const float* __restrict__ pair, int first, int step, int n_parts, int g, int h, int c4) {
-  constexpr int kFly = 12, kPolicy = SHARED ? kAgent : kKeep;
+  constexpr int kPolicy = SHARED ? kAgent : kKeep;
   const unsigned stride = 4u * (unsigned)(g * kPartStrideM);
   const record_t all = record_at(reinterpret_cast<const unsigned char*>(pair), (int)(n_parts * stride));
   unsigned at_o = first * stride + 4u * (unsigned)(h * kD + 4 * c4), at_ml = first * stride + 4u * (unsigned)(g * kD + 2 * h);
@@ -320,7 +323,13 @@ template <bool SHARED>
 __device__ __forceinline__ void merge_pair(const float* __restrict__ pair, int n_parts, int n_half, int tid, int g, unsigned char* lds,
                                            __half* out, float* lse, size_t bh, int bf16) {
   const int h = tid >> 5 & 7, c4 = tid & 31, half = __builtin_amdgcn_readfirstlane(tid >> 8);
-  Merged r = merge_parts<SHARED>(pair, half, n_half, n_parts, g, h < g ? h : 0, c4);
+  Merged r{{0.f, 0.f, 0.f, 0.f}, 0.f, -INFINITY};
+  const int n = n_half > 1 ? (n_parts + 1) >> 1 : n_parts;      // partials of a half (the other may have one less)
+  const bool wide = (n > 12 && n <= 16) || (n > 24 && n <= 32) || n > 36;      // one round less with 16 in flight
+  if (h < g) {      // (no loads for heads that do not exist)
+    if (wide) r = merge_parts<SHARED, 16>(pair, half, n_half, n_parts, g, h, c4);
+    else r = merge_parts<SHARED, 12>(pair, half, n_half, n_parts, g, h, c4);
+  }
   if (n_half > 1) {
     f32x4* const sO = reinterpret_cast<f32x4*>(lds);            // [256] o, then [256] (l, m)
     float2* const sLM = reinterpret_cast<float2*>(lds + 4096);

@@ -10,7 +10,9 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("B,Hkv,g,blocks,over", [
     (1, 1, 1, 40, {}),               # eleven workgroups of four
-    (1, 3, 1, 240, {}),              # sixty: eight wavefronts, a merge of several rounds
+    (2, 4, 1, 52, {}),               # fourteen of four: sixteen partials in flight
+    (1, 2, 3, 110, {}),              # twenty-nine
+    (1, 3, 1, 240, {}),              # sixty-one of four: thirty-one of eight
     (16, 2, 5, 62, {}),              # sixteen of four, more than 256 of them: eight of eight
     (20, 2, 7, 62, {}),              # twelve of four
     (24, 8, 1, 7, {}),               # two of four: one of eight, nothing to merge
