@@ -239,9 +239,11 @@ struct HalfSplit {
 // pair runs this code, its first time on that compute unit as a rule, so its size counts: offsets into a buffer and no special
 // case for an empty partial took 48 steps with records of 32 tokens (8 partials) from 701 to 680 us, twelve partials in flight
 // instead of sixteen to 676 (eight: 675, four: 672), one pair of 1 027 tokens (9 partials) from 9.0 to 8.7 and 8.6 (8.9, 9.1).
-// Sixteen are taken where that saves a round; and the threads of heads that do not exist load nothing, as all of these go past
-// the caches.  us, twelve and a repeated head / this way: 8 pairs of one head, 14 partials, 11.6 / 10.5; 8 of seven heads, 13
-// partials, 11.1 / 10.7; 12 of two, 14 partials, 12.5 / 11.5; 4 of one, 2 x 32 partials, 17.6 / 15.1; one pair of 1 027 tokens 8.7 / 8.5.
+// Four more are taken where that saves a round (as a second form of the loop they cost 0.1 us, two forms to the end of the
+// kernel 0.2: code that is jumped over is code to fetch); and the threads of heads that do not exist load nothing, as all of
+// these go past the caches.  us, twelve and a repeated head / this way: 8 pairs of one head, 14 partials, 11.6 / 10.4; 8 of seven
+// heads, 13 partials, 11.1 / 10.7; 12 of two, 14 partials, 12.3 / 11.4; 4 of one, 2 x 32 partials, 17.6 / 15.1; one pair of 1 027 tokens
+// 8.6 / 8.4.
 //
 // The last workgroup of a pair to finish merges it (see CacheView::tickets).  The partials, the ticket and the
 // loads are agent-scope accesses, which go past the chip's eight L2 caches; no cache is flushed for them.  A launch of
@@ -276,18 +278,19 @@ __device__ __forceinline__ void store_output4(__half* out, float* lse, size_t bh
 }
 // Every step-th of the partials `pair` [n_parts][g * kPartStrideM] of one pair from `first` on (scalars); thread (h, c4), h < g.
 struct Merged { f32x4 o; float l, m; };
-template <bool SHARED, int kFly>
+template <bool SHARED>
 __device__ __forceinline__ Merged merge_parts(const float* __restrict__ pair, int first, int step, int n_parts, int g, int h, int c4) {
-  constexpr int kPolicy = SHARED ? kAgent : kKeep;
+  constexpr int kFly = 12, kMore = 4, kPolicy = SHARED ? kAgent : kKeep;
+  const int n = step > 1 ? (n_parts + 1) >> 1 : n_parts;      // (the second half may have one less)
+  const bool more = (n > 12 && n <= 16) || (n > 24 && n <= 32) || n > 36;      // sixteen in flight: a round less
   const unsigned stride = 4u * (unsigned)(g * kPartStrideM);
   const record_t all = record_at(reinterpret_cast<const unsigned char*>(pair), (int)(n_parts * stride));
   unsigned at_o = first * stride + 4u * (unsigned)(h * kD + 4 * c4), at_ml = first * stride + 4u * (unsigned)(g * kD + 2 * h);
   Merged r{{0.f, 0.f, 0.f, 0.f}, 0.f, -INFINITY};
-  for (int s0 = first; s0 < n_parts; s0 += kFly * step) {
-    f32x4 o[kFly];
-    float m[kFly], l[kFly];
-#pragma unroll
-    for (int i = 0; i < kFly; ++i) {
+  for (int s0 = first; s0 < n_parts; s0 += (more ? kFly + kMore : kFly) * step) {
+    f32x4 o[kFly + kMore];
+    float m[kFly + kMore], l[kFly + kMore];
+    auto load = [&](int i) {
       o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
       m[i] = -INFINITY;
       l[i] = 0.f;
@@ -299,21 +302,36 @@ __device__ __forceinline__ Merged merge_parts(const float* __restrict__ pair, in
         at_ml += step * stride;
         at_o += step * stride;
       }
+    };
+#pragma unroll
+    for (int i = 0; i < kFly; ++i) load(i);
+    if (more) {
+#pragma unroll
+      for (int i = kFly; i < kFly + kMore; ++i) load(i);
     }
     float m_new = r.m;
 #pragma unroll
     for (int i = 0; i < kFly; ++i) m_new = fmaxf(m_new, m[i]);
+    if (more) {
+#pragma unroll
+      for (int i = kFly; i < kFly + kMore; ++i) m_new = fmaxf(m_new, m[i]);
+    }
     const float m_ref = m_new == -INFINITY ? 0.f : m_new;      // (exp2(-inf) = 0 is the weight of a partial without tokens)
     const float alpha = __builtin_amdgcn_exp2f(r.m - m_ref);
     r.l *= alpha;
     r.o *= alpha;
     r.m = m_new;
-#pragma unroll
-    for (int i = 0; i < kFly; ++i) {
+    auto add = [&](int i) {
       const float w = __builtin_amdgcn_exp2f(m[i] - m_ref);
       r.l = fmaf(l[i], w, r.l);
 #pragma unroll
       for (int c = 0; c < 4; ++c) r.o[c] = fmaf(o[i][c], w, r.o[c]);
+    };
+#pragma unroll
+    for (int i = 0; i < kFly; ++i) add(i);
+    if (more) {
+#pragma unroll
+      for (int i = kFly; i < kFly + kMore; ++i) add(i);
     }
   }
   return r;
@@ -324,12 +342,7 @@ __device__ __forceinline__ void merge_pair(const float* __restrict__ pair, int n
                                            __half* out, float* lse, size_t bh, int bf16) {
   const int h = tid >> 5 & 7, c4 = tid & 31, half = __builtin_amdgcn_readfirstlane(tid >> 8);
   Merged r{{0.f, 0.f, 0.f, 0.f}, 0.f, -INFINITY};
-  const int n = n_half > 1 ? (n_parts + 1) >> 1 : n_parts;      // partials of a half (the other may have one less)
-  const bool wide = (n > 12 && n <= 16) || (n > 24 && n <= 32) || n > 36;      // one round less with 16 in flight
-  if (h < g) {      // (no loads for heads that do not exist)
-    if (wide) r = merge_parts<SHARED, 16>(pair, half, n_half, n_parts, g, h, c4);
-    else r = merge_parts<SHARED, 12>(pair, half, n_half, n_parts, g, h, c4);
-  }
+  if (h < g) r = merge_parts<SHARED>(pair, half, n_half, n_parts, g, h, c4);      // (no loads for heads that do not exist)
   if (n_half > 1) {
     f32x4* const sO = reinterpret_cast<f32x4*>(lds);            // [256] o, then [256] (l, m)
     float2* const sLM = reinterpret_cast<float2*>(lds + 4096);
