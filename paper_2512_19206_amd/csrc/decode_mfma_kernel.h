@@ -395,7 +395,8 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
   static_assert(!(RH && (G32 || RG)), "RH is the plain tile order on a record of 32 tokens");
   constexpr bool kRecords = RG != 3;
   const int R = RG ? 128 : cv.cfg.R, Gk = RG ? 128 : (G32 ? 32 : cv.cfg.Gk);
-  const int g = cv.g, Hq = cv.cfg.Hq, Hkv = cv.cfg.Hkv, NB = cv.NB;
+  const int g = cv.g, Hq = cv.cfg.Hq, NB = cv.NB;
+  int Hkv = cv.cfg.Hkv;
   const int rec_bytes = cv.lay.rec_bytes, off_idx = cv.lay.off_idx, off_klo_s = cv.lay.off_klo_s,
             off_klo_z = cv.lay.off_klo_z, off_k4_s = cv.lay.off_k4_s, off_k4_z = cv.lay.off_k4_z,
             off_kmax = cv.lay.off_kmax, off_klo = cv.lay.off_klo, off_k4 = cv.lay.off_k4, off_k16 = cv.lay.off_k16, off_v = cv.lay.off_v,
@@ -403,10 +404,11 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
   const unsigned char* const blocks = cv.blocks;
   const int tid = threadIdx.x;
   // The arguments the start of the kernel needs are read together: read where each is first used they are four dependent
-  // trips through the scalar cache.
+  // trips through the scalar cache.  (The division by Hkv, which comes first, takes its operand from here: else the
+  // compiler puts it, and a wait, between two batches of the loads.  The grid's size is one of the arguments.)
   constexpr bool kCounts = !std::is_same<Counts, NoCounts>::value;
   if constexpr (kCounts) asm("" : "+s"(n_splits) : "s"(sc.enabled), "s"(sc.n_units));
-  asm("" : "+s"(n_splits) : "s"(n_blocks), "s"(n_waves), "s"(Hq), "s"(Hkv), "s"(cv.cfg.in_dtype),
+  asm("" : "+s"(n_splits), "+s"(Hkv) : "s"(n_blocks), "s"(n_waves), "s"(Hq), "s"(gridDim.x), "s"(gridDim.y), "s"(cv.cfg.in_dtype),
                "s"(rec_bytes), "s"(off_idx), "s"(off_v), "s"(off_v_s), "s"(g), "s"(NB), "s"(cv.RW), "s"(blocks), "s"(cv.table),
                "s"(cv.res_k), "s"(cv.res_v), "s"(cv.qacc), "s"(cv.qcnt), "s"(q), "s"(accumulate_q), "s"(nt.k), "s"(nt.v),
                "s"(nt.st.b), "s"(nt.st.h));
