@@ -266,16 +266,24 @@ bool try_launch_decode_mfma(const CacheView& v, const __half* q, float scale, in
 // Workgroups of eight wavefronts instead of twice as many of four?  They leave half as many partials to the pair's last
 // workgroup, which pulls them past the caches with the bandwidth of one compute unit, and draw half as many tickets (at the ceiling
 // of 64 workgroups a pair there are as many of either, and those of eight have half the chain); but their wavefronts share a
-// compute unit, and start and end together.  So: for a shorter chain of records per wavefront (rounding, the ceiling);
-// with the same chain, where those of four would share compute units (more than 256 of them) and a pair has more than twelve, a
-// merge of more than one round, or would have no partials left at all; with a compute unit each only from 25 on.
-// us per step, four / eight: 24 pairs of 9 001 tokens (18 / 9 workgroups a pair) 19.4 / 17.9, 32 of 32 805 (16 / 8) 23.1 / 22.6, 188 of
-// 990 (2 / 1) 15.0 / 13.2, 3 of 15 354 (60 / 30) 15.7 / 12.7, 48 steps of 32 pairs with records of 32 tokens (16 / 8) 718 / 705, one
-// pair of 131 172 (64 / 64) 22.5 / 19.7; on the other side of the lines 14 pairs of 7 218 (15 / 8), 43 steps, 500 / 520, 8 of 6 071
-// (13 / 7), 33 steps, 413 / 466, 112 of 3 453 (4 / 2) 16.4 / 17.8, one of 1 027 (9 / 5) 9.8 / 10.7.
-static bool eight_wavefronts(int chain4, int chain8, int n4, int n8, int wgs4) {
+// compute unit, and start and end together, where those of four overlap one another's start and end.  So:
+//  - not where they do not all fit at once, one to a unit, unless they nearly fill a second round and leave no partials.  us per
+//    attention, four / eight: 280 pairs of 994 tokens 23.9 / 28.5, 336 of 7 589 69.7 / 81.5, 528 of 899 34.1 / 41.4, 146 of 25 885 (438
+//    workgroups / 292) 91 / 116; 408 of 243 19.4 / 17.7, 440 of 21 240 212 / 202, 496 of 19 098 194 / 187;
+//  - for a shorter chain of records per wavefront (rounding, the ceiling);
+//  - with the same chain, where those of four would share units (more than 256 of them) and a pair has more than fifteen, twelve
+//    if it has seven or eight heads, whose partials are longer, or would have none left at all.  By workgroups of four a pair: 12
+//    (40 pairs of seven heads) of 7 973 tokens 14.4 / 15.1, of 32 805 26.9 / 28.4; 16 (32) of 7 973 13.8 / 12.8, of 32 805 24.1 / 23.3, in
+//    records of 32 tokens of 4 101 14.9 / 14.2; 18 (28) of 16 421 17.0 / 15.7; 2 / 1 (188) of 990 15.0 / 13.2.  Over all configurations 13 to
+//    16 workgroups of four are 2 % faster with six heads and fewer and those of eight 1 % with seven and eight;
+//  - with the same chain and a unit for each of four, where a pair has more than 32, 24 if it has seven or eight heads.  Over
+//    all configurations, four / eight: 17 to 24 workgroups 0.94 (0.95 with seven and eight heads), 25 to 32 0.97 (1.01), 33 to 48 1.02
+//    (1.05), 49 to 64 1.12 (1.12).
+static bool eight_wavefronts(int chain4, int chain8, int n4, int n8, int wgs4, int wgs8, int g) {
+  constexpr int kUnits = kDecodeTargetWGs / 2;
+  if (wgs8 > kUnits && !(n8 == 1 && wgs8 > kUnits + kUnits / 2 && wgs8 <= 2 * kUnits)) return false;
   if (chain8 != chain4) return chain8 < chain4;
-  return wgs4 > kDecodeTargetWGs / 2 ? n4 > 12 || n8 == 1 : n4 > 24;
+  return wgs4 > kUnits ? n4 > (g > 6 ? 12 : 15) || n8 == 1 : n4 > (g > 6 ? 24 : 32);
 }
 
 // Split count of a decode launch (one rule for every caller): enough workgroups to fill the chip (tunable through
@@ -310,7 +318,9 @@ static void choose_splits(const CacheView& v, int n_blocks, int n_fp16, bool wid
   if (n8 < 1) n8 = 1;
   if (n8 > ceiling) return;
   const int chain8 = (units + 8 * n8 - 1) / (8 * n8), chain4 = (units + 4 * n_splits_mc - 1) / (4 * n_splits_mc);
-  if (eight_wavefronts(chain4, chain8, n_splits_mc, n8, v.P * n_splits_mc)) *mc = DecodeGrid{n8, 8, 0};
+  // (above the ceiling those of four are no choice: the launch would go to the vector-ALU kernel)
+  if (n_splits_mc > ceiling || eight_wavefronts(chain4, chain8, n_splits_mc, n8, v.P * n_splits_mc, v.P * n8, v.g))
+    *mc = DecodeGrid{n8, 8, 0};
 }
 
 // Deals the matrix-core kernel's workgroups to sequences of different lengths: with the same number for every sequence the
@@ -355,14 +365,15 @@ static void deal_by_length(const CacheView& v, int n_splits, SeqCounts* sc, Deco
   if (budget > kMaxUnits) return;
   int waves = 4, chain = shortest(4, budget, (most + 4 * n_splits - 1) / (4 * n_splits) - 1);      // (the equal deal's always fits)
   if (const int c8 = shortest(8, kDecodeTargetWGs / 2 / v.cfg.Hkv, chain); c8 <= chain) {
-    int wgs4 = 0, n4 = 0, n8 = 0;
+    int wgs4 = 0, wgs8 = 0, n4 = 0, n8 = 0;
     for (int b = 0; b < B; ++b) {
       const int u = units_of(b, chain, 4), w = units_of(b, c8, 8);
       wgs4 += u * v.cfg.Hkv;
+      wgs8 += w * v.cfg.Hkv;
       n4 = u > n4 ? u : n4;
       n8 = w > n8 ? w : n8;
     }
-    if (eight_wavefronts(chain, c8, n4, n8, wgs4)) {
+    if (eight_wavefronts(chain, c8, n4, n8, wgs4, wgs8, v.g)) {
       waves = 8;
       chain = c8;
     }

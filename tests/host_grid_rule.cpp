@@ -26,14 +26,14 @@ static CacheView view_of(int B, int Hkv, int g) {
 
 static int chain_of(int units, const DecodeGrid& d) { return (units + d.n_waves * d.n_splits - 1) / (d.n_waves * d.n_splits); }
 
-static void equal_lengths(int P, int n_blocks, int n_fp16) {
-  const CacheView v = view_of(P, 1, 8);
+static void equal_lengths(int P, int g, int n_blocks, int n_fp16) {
+  const CacheView v = view_of(P, 1, g);
   const int subs = (n_fp16 + 31) / 32, units = n_blocks + subs, cap = max_splits_for(P);
   int ns4, ns8;
   DecodeGrid four, got;
   choose_splits(v, n_blocks, n_fp16, false, &ns4, &four);
   choose_splits(v, n_blocks, n_fp16, true, &ns8, &got);
-#define AT "P %d, %d records, %d fp16 rows: %d workgroups of %d (%d of four, ceiling %d)", P, n_blocks, n_fp16, got.n_splits, got.n_waves, four.n_splits, cap
+#define AT "P %d, %d heads, %d records, %d fp16 rows: %d workgroups of %d (%d of four, ceiling %d)", P, g, n_blocks, n_fp16, got.n_splits, got.n_waves, four.n_splits, cap
   CHECK(ns4 == ns8 && ns4 >= 1 && ns4 <= cap, AT);
   CHECK(four.n_waves == 4 && (got.n_waves == 4 || got.n_waves == 8), AT);
   CHECK(got.n_waves == 8 ? got.n_splits <= four.n_splits : got.n_splits == four.n_splits, AT);
@@ -41,19 +41,28 @@ static void equal_lengths(int P, int n_blocks, int n_fp16) {
   CHECK(got.n_splits >= 1 && (got.n_splits <= cap || four.n_splits > cap), AT);
   CHECK(got.n_splits * got.n_waves >= subs, AT);                                            // a sub-unit per wavefront at most
   CHECK(got.n_splits == 1 || (got.n_splits - 1) * got.n_waves < units, AT);                 // every workgroup has a unit
-  CHECK(chain_of(units, got) <= chain_of(units, four), AT);
+  CHECK(chain_of(units, got) <= chain_of(units, four) || four.n_splits > cap, AT);
+  // workgroups of eight in one round, or one a pair
+  CHECK(got.n_waves == 4 || P * got.n_splits <= 256 || got.n_splits == 1 || four.n_splits > cap, AT);
   if (got.n_splits <= cap)      // the partials it writes are those the size was given for
     CHECK((size_t)P * got.n_splits * v.g * kPartStride * sizeof(float) <= decode_launch_partials_bytes(v, n_blocks, n_fp16), AT);
 #undef AT
 }
 
-// pairs, records, fp16 rows: the grid that the timings beside eight_wavefronts speak for
-static const struct { int P, n_blocks, n_fp16, n_splits, n_waves; } kLines[] = {
-    {24, 70, 41, 9, 8},    {32, 256, 37, 8, 8},  {188, 7, 94, 1, 8},     {3, 239, 59, 31, 8},  {32, 128, 4, 8, 8},
-    {14, 56, 50, 15, 4},   {8, 47, 55, 13, 4},   {112, 26, 125, 4, 4},   {1, 32, 3, 9, 4},      {512, 256, 22, 1, 4},
-    {1, 40, 125, 11, 4},   {80, 62, 125, 6, 4},  {192, 7, 125, 1, 8},    {264, 3, 125, 1, 4},   {20, 0, 189, 2, 4},
+// pairs, heads of a pair, records, fp16 rows: the grid that the timings beside eight_wavefronts speak for
+static const struct { int P, g, n_blocks, n_fp16, n_splits, n_waves; } kLines[] = {
+    {24, 7, 70, 41, 9, 8},    {32, 7, 256, 37, 8, 8},   {32, 1, 62, 37, 8, 8},    {28, 7, 128, 37, 9, 8},  {188, 4, 7, 94, 1, 8},
+    {36, 6, 128, 37, 14, 4},  {36, 7, 128, 37, 7, 8},   {34, 1, 500, 37, 15, 4},  {34, 8, 328, 37, 7, 8},  {40, 8, 62, 37, 12, 4},
+    {40, 7, 256, 37, 12, 4},  {112, 1, 26, 125, 4, 4},  {3, 2, 239, 59, 31, 8},   {1, 6, 126, 32, 32, 4},  {1, 7, 126, 32, 16, 8},
+    {1, 7, 94, 32, 24, 4},    {1, 7, 98, 32, 13, 8},    {1, 1, 130, 32, 17, 8},   {14, 7, 56, 50, 15, 4},  {1, 1, 32, 3, 9, 4},
+    // more than one round of workgroups of eight
+    {146, 7, 200, 285, 3, 4}, {336, 5, 58, 160, 2, 4},  {384, 1, 30, 160, 2, 4},  {385, 1, 30, 160, 1, 8}, {512, 8, 30, 160, 1, 8},
+    {513, 8, 30, 160, 2, 4},  {592, 1, 16, 133, 2, 4},  {592, 1, 16, 97, 1, 4},   {912, 2, 50, 128, 1, 4}, {512, 5, 256, 22, 1, 4},
+    // above the ceiling of one workgroup a pair those of four are no choice
+    {1025, 1, 40, 160, 1, 8}, {1200, 8, 0, 256, 1, 8},
+    {1, 1, 40, 125, 11, 4},   {80, 7, 62, 125, 6, 4},   {192, 1, 7, 125, 1, 8},   {264, 8, 3, 125, 1, 4},  {20, 6, 0, 189, 2, 4},
     // the ceiling of 64 workgroups a pair
-    {1, 508, 128, 64, 8},  {1, 1024, 128, 64, 8}, {2, 4096, 1, 64, 8},   {3, 600, 20, 64, 8},   {4, 1024, 128, 64, 8},
+    {1, 7, 508, 128, 64, 8},  {1, 1, 1024, 128, 64, 8}, {2, 7, 4096, 1, 64, 8},   {3, 1, 600, 20, 64, 8},  {4, 8, 1024, 128, 64, 8},
 };
 
 static void different_lengths(std::mt19937& rng) {
@@ -81,6 +90,7 @@ static void different_lengths(std::mt19937& rng) {
     return;
   }
   CHECK(sc.n_units <= kMaxUnits && sc.n_units <= B * max_splits_for(v.P), AT);      // (the units' partials fit the workspace)
+  CHECK(dg.n_waves == 4 || sc.n_units * Hkv <= 256, AT);      // workgroups of eight in one round
   int at = 0;
   for (int b = 0; b < B; ++b) {
     const int first = (int)(sc.span[b] & 0xffffu), n = (int)(sc.span[b] >> 16);
@@ -96,16 +106,17 @@ int main() {
   for (int P = 1; P <= 512; P += P < 40 ? 1 : 1 + P / 16)
     for (int n_blocks = 0; n_blocks <= 4096; n_blocks += n_blocks < 700 ? 1 : 37)
       for (int n_fp16 : {0, 1, 32, 33, 100, 128, 160, 225, 256, 384})
-        if (n_blocks + n_fp16 > 0) equal_lengths(P, n_blocks, n_fp16);
+        if (n_blocks + n_fp16 > 0)
+          for (int g : {1, 8}) equal_lengths(P, g, n_blocks, n_fp16);
   for (int P : {513, 700, 1023, 1024, 1025, 4096})
     for (int n_blocks = 0; n_blocks <= 300; ++n_blocks)
-      for (int n_fp16 : {1, 33, 128, 160, 256, 384}) equal_lengths(P, n_blocks, n_fp16);
+      for (int n_fp16 : {1, 33, 128, 160, 256, 384}) equal_lengths(P, 8, n_blocks, n_fp16);
   for (const auto& l : kLines) {
     int ns;
     DecodeGrid got;
-    choose_splits(view_of(l.P, 1, 8), l.n_blocks, l.n_fp16, true, &ns, &got);
-    CHECK(got.n_splits == l.n_splits && got.n_waves == l.n_waves, "P %d, %d records, %d fp16 rows: %d workgroups of %d instead of %d of %d",
-          l.P, l.n_blocks, l.n_fp16, got.n_splits, got.n_waves, l.n_splits, l.n_waves);
+    choose_splits(view_of(l.P, 1, l.g), l.n_blocks, l.n_fp16, true, &ns, &got);
+    CHECK(got.n_splits == l.n_splits && got.n_waves == l.n_waves, "P %d, %d heads, %d records, %d fp16 rows: %d workgroups of %d instead of %d of %d",
+          l.P, l.g, l.n_blocks, l.n_fp16, got.n_splits, got.n_waves, l.n_splits, l.n_waves);
   }
   std::mt19937 rng(1);
   for (int i = 0; i < 20000; ++i) different_lengths(rng);

@@ -17,6 +17,7 @@ pytestmark = pytest.mark.gpu
     (20, 2, 7, 62, {}),              # twelve of four
     (24, 8, 1, 7, {}),               # two of four: one of eight, nothing to merge
     (33, 8, 8, 3, {}),               # one of four
+    (38, 8, 1, 2, dict(R=256)),      # two of four, no room for all of eight at once
     (3, 8, 2, 20, dict(R=32, Gk=32, Gv=32)),
     (2, 2, 3, 30, dict(R=256, sink=128)),      # twelve sub-units of fp16 rows
     (5, 4, 6, 0, dict(sink=64)),     # fp16 rows only
