@@ -62,19 +62,15 @@ def test_both_forms_give_the_same_records(H, blocks):
         assert torch.equal(a[:, :5], b[:, :5])
 
 
-@pytest.mark.parametrize("R,blocks", [(64, 1406), (64, 1408), (64, 1410), (16, 1410), (32, 1600), (128, 2050)])
-@pytest.mark.parametrize("first", [0, 7, -1])      # tokens that wait in the window before the call (-1: a full window)
-def test_large_launches_behind_a_window(R, blocks, first):
-    """On either side of the line, and above it with the window read (and then overwritten) by the first block: records,
-    window rows and the selection against the same tokens in pieces far below the line."""
+def _behind_a_window(R, blocks, first, Gk, Gv, dtype="float16"):
     import torch
     import paper_2512_19206_amd as M
     first = R if first < 0 else first
-    kw = dict(B=1, Hq=2, Hkv=2, D=128, T_max=(blocks // 2 + 2) * R, Gk=min(R, 32), Gv=64, R=R, k4=8, k16=0)
+    kw = dict(B=1, Hq=2, Hkv=2, D=128, T_max=(blocks // 2 + 2) * R, Gk=Gk, Gv=Gv, R=R, k4=8, k16=0, in_dtype=int(dtype == "bfloat16"))
     gen = torch.Generator(device="cuda").manual_seed(blocks + first)
     n = first + (blocks // 2) * R + R // 2
-    k = (torch.randn((1, 2, n, 128), generator=gen, device="cuda") * 3).half()
-    v = torch.randn((1, 2, n, 128), generator=gen, device="cuda").half()
+    k = (torch.randn((1, 2, n, 128), generator=gen, device="cuda") * 3).to(getattr(torch, dtype))
+    v = torch.randn((1, 2, n, 128), generator=gen, device="cuda").to(getattr(torch, dtype))
     caches = [M.Cache(M.make_config(**kw)) for _ in range(2)]
     sel = caches[0].select_channels(k[:, :, :300], k)
     for c, piece in zip(caches, (n, 5 * R + 3)):
@@ -89,6 +85,22 @@ def test_large_launches_behind_a_window(R, blocks, first):
         assert torch.equal(x[:, :r], y[:, :r])
 
 
+@pytest.mark.parametrize("R,blocks", [(64, 1406), (64, 1408), (64, 1410), (16, 1410), (32, 1600), (128, 2050)])
+@pytest.mark.parametrize("first", [0, 7, -1])      # tokens that wait in the window before the call (-1: a full window)
+def test_large_launches_behind_a_window(R, blocks, first):
+    """On either side of the line, and above it with the window read (and then overwritten) by the first block: records,
+    window rows and the selection against the same tokens in pieces far below the line."""
+    _behind_a_window(R, blocks, first, min(R, 32), 64)
+
+
+@pytest.mark.parametrize("R,blocks,dtype", [(128, 2050, "float16"), (128, 2050, "bfloat16"), (64, 1410, "bfloat16"), (128, 380, "float16"), (128, 800, "bfloat16")])
+@pytest.mark.parametrize("first", [0, 7, -1])
+def test_one_group_launches_behind_a_window(R, blocks, dtype, first):
+    """The same with one key and one value group, where the values are asked for behind the 2-bit keys: above the line (the
+    first block's values come from the window it overwrites), three and four workgroups to a compute unit below it."""
+    _behind_a_window(R, blocks, first, R, 128, dtype)
+
+
 @pytest.mark.parametrize("per_pair", [15, 16, 17])      # 120, 128 and 136 records in a launch of 8 pairs
 @pytest.mark.parametrize("kw", [
     dict(Gk=128, Gv=128, R=128, k4=16, k16=0),
@@ -97,7 +109,7 @@ def test_large_launches_behind_a_window(R, blocks, first):
     dict(Gk=32, Gv=32, R=128, k4=16, k16=8, policy=1, tau16=1.5, tau4=0.3),
 ])
 def test_both_widths_give_the_same_records(H, kw, per_pair):
-    """Records of one launch around the line between workgroups of 512 and of 256 threads against the oracle's."""
+    """Records of one launch around the line between workgroups of 512 or 1 024 and of 256 threads against the oracle's."""
     kw = dict(B=2, Hq=8, Hkv=4, D=128, T_max=(per_pair + 1) * 128, **kw)
     oc, gc = H.make_pair(**kw)
     rng = np.random.default_rng(per_pair)
