@@ -90,3 +90,16 @@ def test_more_than_the_last_level_cache(k4, k16):
     # (the one sequence's sums run in another order: twice the distance of either from binary64)
     assert torch.all((out[:1].float() - ref.float()).abs() <= 2e-3 + 1e-2 * ref.float().abs())
     assert torch.all((lse[:1] - ref_lse).abs() <= 2e-3 + 1e-4 * ref_lse.abs())
+    # one sequence a block shorter: the launch over different lengths reads as much, the others' outputs stay what they were
+    n_quant, n_res, n_sink = one.state_seq(0)
+    M.load_library().mixkvq_cache_set_state_seq(gc.handle, 5, n_quant - 128, n_res, n_sink)
+    assert (B * blocks - 1) * Hkv * gc.layout.rec_bytes > 256 << 20
+    ragged, ragged_lse = gc.decode_attention(q.expand(B, -1, -1).contiguous())
+    M.load_library().mixkvq_cache_set_state(one.handle, n_quant - 128, n_res, n_sink)
+    short, short_lse = one.decode_attention(q)
+    torch.cuda.synchronize()
+    assert gc.decode_path() == M.PATH_MATRIX
+    want = torch.cat([ref.expand(5, -1, -1), short, ref.expand(B - 6, -1, -1)]).float()
+    want_lse = torch.cat([ref_lse.expand(5, -1), short_lse, ref_lse.expand(B - 6, -1)])
+    assert torch.all((ragged.float() - want).abs() <= 2e-3 + 1e-2 * want.abs())
+    assert torch.all((ragged_lse - want_lse).abs() <= 2e-3 + 1e-4 * want_lse.abs())
