@@ -1312,8 +1312,8 @@ __device__ __forceinline__ void mfma_part(const CacheView& cv, const __half* __r
     z = xkg_sum(z);
     zsum[a] = z + row_ror8(z);
   }
-  // each wavefront leaves its result in its own LDS region; after one barrier all threads merge the four
-  // in a fixed order
+  // each wavefront leaves its result in its own LDS region; after one barrier the first four wavefronts merge those of all
+  // (four or eight) in a fixed order
   // columns 8..15 of the value products hold the part that came from the remainders of P*s
   f32x4 Ot[2][4];
 #pragma unroll
